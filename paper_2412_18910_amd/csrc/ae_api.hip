@@ -69,10 +69,10 @@ Mat make_mat(const void *p, int N, int K) {
   return m;
 }
 
-// generic path: Y[r][n] (+)= X[r][:] . W[n][:] + bias[n]
-void gemm(ae_ctx *c, const Mat &W, const float *X, int ldx, int rows, const float *bias, float *Y, int ldy,
-          int accumulate) {
-  launch_gemm_generic(W.rowmajor, c->cfg.dtype, W.N, W.K, X, ldx, rows, bias, Y, ldy, accumulate, c->stream, c->gate);
+// one GEMM of the decode step (1..16 rows) in the model's precision
+void gemm(ae_ctx *c, const GemmLaunch &L) {
+  if (c->fast) launch_gemm_mfma(L, c->stream);
+  else launch_gemm_f32(L, c->stream);
 }
 
 bool tileable(const Mat &m) { return m.N % 16 == 0 && m.K % 256 == 0; }
@@ -100,65 +100,50 @@ int retile_fused(ae_ctx *c, Mat &dst, const Mat *const *src, int nsrc, bool inte
 void *kv_layer_ptr(ae_ctx *c, int li) { return (char *)c->kv + (size_t)li * c->kv_layer_stride; }
 
 // One pre-norm decoder layer over `rows` slots starting at pos0; x is updated in place.
-// next_gain (fast path): RMSNorm gain applied to this layer's output for its consumer (the
-// next layer, the final norm, or nullptr when the consumer takes the raw output).
+// next_gain: RMSNorm gain applied to this layer's output for its consumer (the next layer, the
+// final norm, or nullptr when the consumer takes the raw output).
+// Activations go between kernels in the form the next GEMM reads (bf16: packed MFMA B operands;
+// float32: rows).  RMSNorm is split between producer (x*gain, partial sums of x^2) and consumer
+// (1/rms on accumulators); SwiGLU and both residual adds are GEMM epilogues.
 void run_layer(ae_ctx *c, int li, float *x, int rows, int pos0, const float *next_gain) {
   const ae_config &g = c->cfg;
   const LayerW &w = c->layers[li];
   const int d = g.d_model, dq = g.n_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn;
   hipStream_t s = c->stream;
-  if (c->fast) {
-    // Activations stay in packed (MFMA B-operand) form between kernels.  RMSNorm is split
-    // between producer (x*gain, partial sums of x^2) and consumer (1/rms on accumulators);
-    // SwiGLU and both residual adds are GEMM epilogues.
-    const int Pd = d / 16;
-    GemmLaunch qkv;
-    qkv.W = &w.f_qkv; qkv.Xp = c->xp_a; qkv.rows = rows; qkv.ssq_in = c->ssq_a; qkv.P_in = c->Pa; qkv.eps = g.rms_eps;
-    qkv.epi = EPI_QKV; qkv.nseg = 3;   // rotary embedding + KV append happen in the epilogue
-    qkv.Y[0] = c->q; qkv.ldy[0] = dq;
-    qkv.seg_N[0] = dq; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
-    qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
-    qkv.pos0 = pos0; qkv.n_ctx = kv_capacity(g); qkv.hd = g.head_dim;
-    qkv.gate = c->gate;
-    launch_gemm_mfma(qkv, s);
-    launch_attention_mfma(c->q, rows, pos0, g, kv_layer_ptr(c, li), c->kv_v_offset, c->attn_part, c->xp_att, s, c->gate);
-    GemmLaunch o;
-    o.W = &w.wo; o.Xp = c->xp_att; o.rows = rows; o.epi = EPI_RESID; o.Y[0] = x; o.ldy[0] = d; o.seg_N[0] = d;
-    o.Xp_out = c->xp_f; o.gain_out = w.ffn_norm; o.ssq_out = c->ssq_f;
-    o.gate = c->gate;
-    launch_gemm_mfma(o, s);
-    GemmLaunch gu;
-    gu.W = &w.f_gu; gu.Xp = c->xp_f; gu.rows = rows; gu.ssq_in = c->ssq_f; gu.P_in = Pd; gu.eps = g.rms_eps;
-    gu.epi = EPI_SWIGLU; gu.Xp_out = c->xp_h; gu.seg_N[0] = 2 * f;
-    gu.gate = c->gate;
-    const bool timed = c->ktime && c->kt_used + 2 <= (int)c->kt_ev.size();
-    if (timed) hipEventRecord(c->kt_ev[c->kt_used], s);
-    launch_gemm_mfma(gu, s);
-    if (timed) { hipEventRecord(c->kt_ev[c->kt_used + 1], s); c->kt_used += 2; }
-    GemmLaunch dn;
-    dn.W = &w.w_down; dn.Xp = c->xp_h; dn.rows = rows; dn.epi = EPI_RESID; dn.Y[0] = x; dn.ldy[0] = d; dn.seg_N[0] = d;
-    // the draft layer's raw output is the first half of the next chained token's input [feature ;
-    // embedding] and the LM head's operand: it goes straight into that packed buffer
-    const bool draft_layer = li == g.n_layers;
-    dn.Xp_out = draft_layer ? c->xp_cat : c->xp_a; dn.gain_out = next_gain; dn.ssq_out = c->ssq_a;
-    dn.gate = c->gate;
-    launch_gemm_mfma(dn, s);
-    c->Pa = Pd;
-    return;
-  }
-  launch_rmsnorm(x, w.attn_norm, rows, d, g.rms_eps, c->xn, s, c->gate);
-  gemm(c, w.wq, c->xn, d, rows, nullptr, c->q, dq, 0);
-  gemm(c, w.wk, c->xn, d, rows, nullptr, c->kbuf, dkv, 0);
-  gemm(c, w.wv, c->xn, d, rows, nullptr, c->vbuf, dkv, 0);
-  launch_rope_append(c->q, c->kbuf, c->vbuf, rows, pos0, g, c->rope_tab, kv_layer_ptr(c, li), c->kv_v_offset, false, s,
-                     c->gate);
-  launch_attention(c->q, rows, pos0, g, kv_layer_ptr(c, li), c->kv_v_offset, c->attn_part, c->att, s, c->gate);
-  gemm(c, w.wo, c->att, dq, rows, nullptr, x, d, 1);
-  launch_rmsnorm(x, w.ffn_norm, rows, d, g.rms_eps, c->xn, s, c->gate);
-  gemm(c, w.w_gate, c->xn, d, rows, nullptr, c->gate_proj, f, 0);
-  gemm(c, w.w_up, c->xn, d, rows, nullptr, c->up, f, 0);
-  launch_silu_mul(c->gate_proj, c->up, rows, f, c->hmid, s, c->gate);
-  gemm(c, w.w_down, c->hmid, f, rows, nullptr, x, d, 1);
+  const int Pd = (d + 15) / 16;
+  GemmLaunch qkv;
+  qkv.W = &w.f_qkv; qkv.Xp = c->xp_a; qkv.ldx = d; qkv.rows = rows; qkv.ssq_in = c->ssq_a; qkv.P_in = c->Pa; qkv.eps = g.rms_eps;
+  qkv.epi = EPI_QKV; qkv.nseg = 3;   // rotary embedding + KV append happen in the epilogue
+  qkv.Y[0] = c->q; qkv.ldy[0] = dq;
+  qkv.seg_N[0] = dq; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
+  qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
+  qkv.pos0 = pos0; qkv.n_ctx = kv_capacity(g); qkv.hd = g.head_dim;
+  qkv.gate = c->gate;
+  gemm(c, qkv);
+  if (c->fast) launch_attention_mfma(c->q, rows, pos0, g, kv_layer_ptr(c, li), c->kv_v_offset, c->attn_part, c->xp_att, s, c->gate);
+  else launch_attention_f32(c->q, rows, pos0, g, kv_layer_ptr(c, li), c->kv_v_offset, c->attn_part, (float *)c->xp_att, s, c->gate);
+  GemmLaunch o;
+  o.W = &w.wo; o.Xp = c->xp_att; o.ldx = dq; o.rows = rows; o.epi = EPI_RESID; o.Y[0] = x; o.ldy[0] = d; o.seg_N[0] = d;
+  o.Xp_out = c->xp_f; o.ldxo = d; o.gain_out = w.ffn_norm; o.ssq_out = c->ssq_f;
+  o.gate = c->gate;
+  gemm(c, o);
+  GemmLaunch gu;
+  gu.W = &w.f_gu; gu.Xp = c->xp_f; gu.ldx = d; gu.rows = rows; gu.ssq_in = c->ssq_f; gu.P_in = Pd; gu.eps = g.rms_eps;
+  gu.epi = EPI_SWIGLU; gu.Xp_out = c->xp_h; gu.ldxo = f; gu.seg_N[0] = 2 * f;
+  gu.gate = c->gate;
+  const bool timed = c->fast && c->ktime && c->kt_used + 2 <= (int)c->kt_ev.size();
+  if (timed) hipEventRecord(c->kt_ev[c->kt_used], s);
+  gemm(c, gu);
+  if (timed) { hipEventRecord(c->kt_ev[c->kt_used + 1], s); c->kt_used += 2; }
+  GemmLaunch dn;
+  dn.W = &w.w_down; dn.Xp = c->xp_h; dn.ldx = f; dn.rows = rows; dn.epi = EPI_RESID; dn.Y[0] = x; dn.ldy[0] = d; dn.seg_N[0] = d;
+  // the draft layer's raw output is the first half of the next chained token's input [feature ;
+  // embedding] and the LM head's operand: it goes straight into that buffer
+  const bool draft_layer = li == g.n_layers;
+  dn.Xp_out = draft_layer ? c->xp_cat : c->xp_a; dn.ldxo = draft_layer ? 2 * d : d; dn.gain_out = next_gain; dn.ssq_out = c->ssq_a;
+  dn.gate = c->gate;
+  gemm(c, dn);
+  c->Pa = Pd;
 }
 
 // Target forward of `rows` tokens (device ids) at slots pos0..; features -> F rows 0..rows-1;
@@ -167,57 +152,44 @@ void target_forward(ae_ctx *c, const int32_t *ids_dev, int rows, int pos0, int l
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
   const int nr = rows - logit_from;
-  if (c->fast) {
-    launch_embed_packed(c->tok_emb, ids_dev, rows, g.d_model, c->layers[0].attn_norm, c->x, c->xp_a, c->ssq_a, s);
-    c->Pa = 1;
-    for (int l = 0; l < g.n_layers; ++l)
-      run_layer(c, l, c->x, rows, pos0, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : c->final_norm);
-    launch_rmsnorm(c->x, c->final_norm, rows, g.d_model, g.rms_eps, c->F, s);   // feature rows (LDLP, draft head)
-    if (nr > 0) {
-      GemmLaunch lm;   // final RMSNorm folded into the LM head
-      lm.W = &c->lm_head; lm.Xp = c->xp_a; lm.rows = nr; lm.row0 = logit_from; lm.ssq_in = c->ssq_a; lm.P_in = c->Pa;
-      lm.eps = g.rms_eps; lm.epi = EPI_STORE; lm.Y[0] = c->logits; lm.ldy[0] = g.vocab; lm.seg_N[0] = g.vocab;
-      lm.amax_val = c->amax_val; lm.amax_idx = c->amax_idx;   // per-row argmax rides on the epilogue
-      launch_gemm_mfma(lm, s);
-      launch_argmax_finish(c->amax_val, c->amax_idx, g.vocab / 16, nr, c->st, -1, s);
-    }
-    return;
-  }
-  launch_embed(c->tok_emb, g.dtype, ids_dev, rows, g.d_model, c->x, s);
-  for (int l = 0; l < g.n_layers; ++l) run_layer(c, l, c->x, rows, pos0, nullptr);
-  launch_rmsnorm(c->x, c->final_norm, rows, g.d_model, g.rms_eps, c->F, s);
+  if (c->fast) launch_embed_packed(c->tok_emb, ids_dev, rows, g.d_model, c->layers[0].attn_norm, c->x, c->xp_a, c->ssq_a, s);
+  else launch_embed_f32(c->tok_emb, ids_dev, rows, g.d_model, c->layers[0].attn_norm, c->x, c->xp_a, c->ssq_a, s);
+  c->Pa = 1;
+  for (int l = 0; l < g.n_layers; ++l)
+    run_layer(c, l, c->x, rows, pos0, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : c->final_norm);
+  launch_rmsnorm(c->x, c->final_norm, rows, g.d_model, g.rms_eps, c->F, s);   // feature rows (LDLP, draft head)
   if (nr > 0) {
-    gemm(c, c->lm_head, c->F + (size_t)logit_from * g.d_model, g.d_model, nr, nullptr, c->logits, g.vocab, 0);
-    launch_argmax(c->logits, nr, g.vocab, c->st->argmax, s);
+    GemmLaunch lm;   // final RMSNorm folded into the LM head
+    lm.W = &c->lm_head; lm.Xp = c->xp_a; lm.ldx = g.d_model; lm.rows = nr; lm.row0 = logit_from; lm.ssq_in = c->ssq_a; lm.P_in = c->Pa;
+    lm.eps = g.rms_eps; lm.epi = EPI_STORE; lm.Y[0] = c->logits; lm.ldy[0] = g.vocab; lm.seg_N[0] = g.vocab;
+    lm.amax_val = c->amax_val; lm.amax_idx = c->amax_idx;   // per-row argmax rides on the epilogue
+    gemm(c, lm);
+    launch_argmax_finish(c->amax_val, c->amax_idx, (g.vocab + 15) / 16, nr, c->st, -1, s);
   }
 }
 
 // Draft head over `rows` slots from slot0: slot input = fc([feature ; emb(next token)]).
-// Leaves the head's outputs in x rows 0..rows-1 (bf16 path: also packed in xp_cat, first half).
-// chained_row >= 0 (bf16 path, one row): the input is already in row chained_row of xp_cat, the
+// Leaves the head's outputs in x rows 0..rows-1 and in the first halves of xp_cat's rows.
+// chained_row >= 0 (one row): the input is already in row chained_row of xp_cat, the
 // head's previous output (left there by its down projection) and the embedding of the token
 // picked from it (left there by the kernel that picked it).
 void draft_rows(ae_ctx *c, const float *feat, int feat_ld, const int32_t *next_ids_dev, int rows, int slot0,
                 int chained_row = -1) {
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
-  const LayerW &dl = c->layers[g.n_layers];
-  if (c->fast) {
-    if (chained_row < 0)
-      launch_draft_cat_packed(feat, feat_ld, c->tok_emb, next_ids_dev, rows, g.d_model, c->xp_cat, s, c->gate);
-    GemmLaunch fc;
-    fc.W = &c->draft_fc; fc.Xp = c->xp_cat; fc.rows = rows; fc.epi = EPI_STORE; fc.bias = c->draft_fc_b;
-    fc.row0 = chained_row < 0 ? 0 : chained_row;
-    fc.Y[0] = c->x; fc.ldy[0] = g.d_model; fc.seg_N[0] = g.d_model;
-    fc.Xp_out = c->xp_a; fc.gain_out = dl.attn_norm; fc.ssq_out = c->ssq_a;
-    fc.gate = c->gate;
-    launch_gemm_mfma(fc, s);
-    c->Pa = g.d_model / 16;
-    run_layer(c, g.n_layers, c->x, rows, slot0, nullptr);   // leaves packed(raw output) in xp_a
-    return;
+  const int d = g.d_model;
+  if (chained_row < 0) {
+    if (c->fast) launch_draft_cat_packed(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate);
+    else launch_draft_cat_f32(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate);
   }
-  launch_draft_cat(feat, feat_ld, c->tok_emb, g.dtype, next_ids_dev, rows, g.d_model, c->cat, s, c->gate);
-  gemm(c, c->draft_fc, c->cat, 2 * g.d_model, rows, c->draft_fc_b, c->x, g.d_model, 0);
+  GemmLaunch fc;
+  fc.W = &c->draft_fc; fc.Xp = c->xp_cat; fc.ldx = 2 * d; fc.rows = rows; fc.epi = EPI_STORE; fc.bias = c->draft_fc_b;
+  fc.row0 = chained_row < 0 ? 0 : chained_row;
+  fc.Y[0] = c->x; fc.ldy[0] = d; fc.seg_N[0] = d;
+  fc.Xp_out = c->xp_a; fc.ldxo = d; fc.gain_out = c->layers[g.n_layers].attn_norm; fc.ssq_out = c->ssq_a;
+  fc.gate = c->gate;
+  gemm(c, fc);
+  c->Pa = (d + 15) / 16;
   run_layer(c, g.n_layers, c->x, rows, slot0, nullptr);
 }
 
@@ -229,34 +201,27 @@ void draft_lm_head(ae_ctx *c, int row, int i, int k) {
   hipStream_t s = c->stream;
   float *dl = c->dlogits + (size_t)i * g.vocab;
   const bool greedy = !(g.temperature > 0.f);
-  if (c->fast) {
-    GemmLaunch lm;
-    lm.W = &c->lm_head; lm.Xp = c->xp_cat; lm.rows = 1; lm.row0 = row; lm.epi = EPI_STORE;
-    lm.Y[0] = dl; lm.ldy[0] = g.vocab; lm.seg_N[0] = g.vocab;
-    DddFinish ddd;   // the DDD rule's statistic rides on the LM-head epilogue and on the kernel that fixes the token
-    if (g.ddd_enabled) {
-      ddd.val = c->amax_val; ddd.lse_sum = c->lse_sum; ddd.logits = dl; ddd.NB = g.vocab / 16; ddd.k = k;
-      ddd.inv_t = greedy ? 1.f : 1.f / g.temperature; ddd.theta = g.ddd_threshold;
-      lm.lse_sum = c->lse_sum; lm.lse_inv_t = ddd.inv_t;
-    }
-    if (greedy || g.ddd_enabled) { lm.amax_val = c->amax_val; lm.amax_idx = c->amax_idx; }
-    lm.gate = c->gate;
-    launch_gemm_mfma(lm, s);
-    DraftCat cat;   // the picked token's embedding joins the head's output in its packed input row
-    cat.emb = c->tok_emb; cat.Xp = c->xp_cat; cat.d = g.d_model; cat.row = row;
-    if (greedy) {
-      launch_argmax_finish(c->amax_val, c->amax_idx, g.vocab / 16, 1, c->st, i, s, c->gate, cat, ddd);   // argmax + override
-    } else {
-      launch_sample_draft(dl, g.vocab, g.temperature, c->st, i, c->prob, s, c->gate);
-      launch_pick_draft_packed(c->st, i, s, c->gate, cat, ddd);
-    }
-    return;
+  const int NB = (g.vocab + 15) / 16;
+  GemmLaunch lm;
+  lm.W = &c->lm_head; lm.Xp = c->xp_cat; lm.ldx = 2 * g.d_model; lm.rows = 1; lm.row0 = row; lm.epi = EPI_STORE;
+  lm.Y[0] = dl; lm.ldy[0] = g.vocab; lm.seg_N[0] = g.vocab;
+  DddFinish ddd;   // the DDD rule's statistic rides on the LM-head epilogue and on the kernel that fixes the token
+  if (g.ddd_enabled) {
+    ddd.val = c->amax_val; ddd.lse_sum = c->lse_sum; ddd.logits = dl; ddd.NB = NB; ddd.k = k;
+    ddd.inv_t = greedy ? 1.f : 1.f / g.temperature; ddd.theta = g.ddd_threshold;
+    lm.lse_sum = c->lse_sum; lm.lse_inv_t = ddd.inv_t;
   }
-  gemm(c, c->lm_head, c->x + (size_t)row * g.d_model, g.d_model, 1, nullptr, dl, g.vocab, 0);
-  if (greedy) launch_argmax(dl, 1, g.vocab, c->st->argmax, s, c->gate);
-  else launch_sample_draft(dl, g.vocab, g.temperature, c->st, i, c->prob, s, c->gate);
-  launch_pick_draft(c->st, i, s, c->gate);
-  if (g.ddd_enabled) launch_draft_logprob(dl, g.vocab, g.temperature, c->st, i, k, g.ddd_threshold, s, c->gate);
+  if (greedy || g.ddd_enabled) { lm.amax_val = c->amax_val; lm.amax_idx = c->amax_idx; }
+  lm.gate = c->gate;
+  gemm(c, lm);
+  DraftCat cat;   // the picked token's embedding joins the head's output in its input row
+  cat.emb = c->tok_emb; cat.Xp = c->xp_cat; cat.d = g.d_model; cat.row = row; cat.f32 = !c->fast;
+  if (greedy) {
+    launch_argmax_finish(c->amax_val, c->amax_idx, NB, 1, c->st, i, s, c->gate, cat, ddd);   // argmax + override
+  } else {
+    launch_sample_draft(dl, g.vocab, g.temperature, c->st, i, c->prob, s, c->gate);
+    launch_pick_draft_packed(c->st, i, s, c->gate, cat, ddd);
+  }
 }
 
 void enqueue_ldlp(ae_ctx *c, int slot, int f_row, bool relative_to_accept) {
@@ -292,15 +257,15 @@ int read_state(ae_ctx *c, bool published = false) {
 }
 
 // ---- dense prompt pass --------------------------------------------------------------
-// the dense GEMM's workgroup tile spans 256 output rows
+// the bf16 dense GEMM's workgroup tile spans 256 output rows
 bool dense_ok(const ae_ctx *c) {
   const ae_config &g = c->cfg;
   return c->fast && g.d_model >= 256 && 2 * g.d_ffn >= 256 && (g.n_heads + 2 * g.n_kv_heads) * g.head_dim >= 256;
 }
 
 // Chunk buffers for `cap` rows (a multiple of 128): float residual stream and queries, the
-// packed inputs of the five GEMMs, RMSNorm partial sums and 1/rms.  Zero-filled so that the
-// padding rows of a chunk are finite.
+// inputs of the five GEMMs; bf16: RMSNorm partial sums and 1/rms, zero-filled so that the
+// padding rows of a packed chunk are finite.
 int ensure_dense(ae_ctx *c, int n) {
   const ae_config &g = c->cfg;
   const int want = ((n < c->dense_chunk ? n : c->dense_chunk) + 127) / 128 * 128;
@@ -310,7 +275,11 @@ int ensure_dense(ae_ctx *c, int n) {
   c->dense_owned.clear();
   c->dense_cap = 0;
   const size_t cap = want, d = g.d_model, dq = (size_t)g.n_heads * g.head_dim, f = g.d_ffn;
-  struct { void **p; size_t bytes; } bufs[] = {
+  const size_t dmax = dq > d ? dq : d;
+  struct Buf { void **p; size_t bytes; };
+  const std::vector<Buf> bufs = !c->fast ? std::vector<Buf>{
+      {(void **)&c->px, cap * d * 4}, {(void **)&c->pq, cap * dq * 4}, {&c->pxa, cap * d * 4}, {&c->pxatt, cap * dmax * 4},
+      {&c->pxh, cap * f * 4}, {&c->pxcat, cap * 2 * d * 4}} : std::vector<Buf>{
       {(void **)&c->px, cap * d * 4},      {(void **)&c->pq, cap * dq * 4},   {(void **)&c->prinv, cap * 4},
       {(void **)&c->pssq_a, cap * d * 4 / 16 * 1 + cap * 4}, {(void **)&c->pssq_f, cap * d * 4 / 16 + cap * 4},
       {&c->pxa, cap * d * 4},              {&c->pxf, cap * d * 4},            {&c->pxatt, cap * dq * 4},
@@ -319,10 +288,13 @@ int ensure_dense(ae_ctx *c, int n) {
     void *q = nullptr;
     const size_t bytes = (b.bytes + 255) / 256 * 256;
     hipError_t e = hipMalloc(&q, bytes);
-    if (e != hipSuccess) return fail(c, AE_ENOMEM, std::string("dense prefill buffers: ") + hipGetErrorString(e));
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(c, AE_ENOMEM, std::string("dense prefill buffers: ") + hipGetErrorString(e));
+    }
     c->dense_owned.push_back(q);
     *b.p = q;
-    launch_fill_zero(q, bytes, c->stream);
+    if (c->fast) launch_fill_zero(q, bytes, c->stream);
   }
   c->dense_cap = want;
   return AE_OK;
@@ -381,6 +353,51 @@ void dense_chunk(ae_ctx *c, int p0, int rows, int drows) {
   }
 }
 
+// The same in float32: wide GEMMs over rows, RMSNorm in kernels of its own.
+void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
+  const ae_config &g = c->cfg;
+  hipStream_t s = c->stream;
+  const int d = g.d_model, dq = g.n_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn;
+  float *xn = (float *)c->pxa, *att = (float *)c->pxatt;
+  launch_embed_f32(c->tok_emb, c->hist + p0, rows, d, nullptr, c->px, nullptr, nullptr, s);
+  auto qkv_pass = [&](int li, const float *x, int nrows, bool with_q) {   // RMSNorm, projections, rotary, append
+    const LayerW &w = c->layers[li];
+    launch_rmsnorm(x, w.attn_norm, nrows, d, g.rms_eps, xn, s);
+    GemmLaunch qkv;
+    qkv.W = &w.f_qkv; qkv.Xp = xn; qkv.ldx = d; qkv.rows = nrows; qkv.epi = EPI_QKV;
+    qkv.Y[0] = c->pq; qkv.ldy[0] = dq;
+    qkv.seg_N[0] = with_q ? dq : 0; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
+    qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
+    qkv.pos0 = p0; qkv.n_ctx = kv_capacity(g); qkv.hd = g.head_dim;
+    launch_gemm_f32_dense(qkv, s);
+  };
+  for (int l = 0; l < g.n_layers; ++l) {
+    const LayerW &w = c->layers[l];
+    qkv_pass(l, c->px, rows, true);
+    launch_attention_prefill_f32(c->pq, rows, p0, g, kv_layer_ptr(c, l), c->kv_v_offset, att, s);
+    GemmLaunch o;
+    o.W = &w.wo; o.Xp = att; o.ldx = dq; o.rows = rows; o.epi = EPI_RESID; o.Y[0] = c->px; o.ldy[0] = d;
+    launch_gemm_f32_dense(o, s);
+    launch_rmsnorm(c->px, w.ffn_norm, rows, d, g.rms_eps, xn, s);
+    GemmLaunch gu;
+    gu.W = &w.f_gu; gu.Xp = xn; gu.ldx = d; gu.rows = rows; gu.epi = EPI_SWIGLU; gu.Xp_out = c->pxh; gu.ldxo = f;
+    launch_gemm_f32_dense(gu, s);
+    GemmLaunch dn;
+    dn.W = &w.w_down; dn.Xp = c->pxh; dn.ldx = f; dn.rows = rows; dn.epi = EPI_RESID; dn.Y[0] = c->px; dn.ldy[0] = d;
+    launch_gemm_f32_dense(dn, s);
+  }
+  if (drows > 0) {
+    // Eq. 2 catch-up of prompt slots: only the head's K/V rows are ever read again
+    launch_rmsnorm(c->px, c->final_norm, drows, d, g.rms_eps, xn, s);
+    launch_draft_cat_f32(xn, d, c->tok_emb, c->hist + p0 + 1, drows, d, c->pxcat, s);
+    GemmLaunch fc;
+    fc.W = &c->draft_fc; fc.Xp = c->pxcat; fc.ldx = 2 * d; fc.rows = drows; fc.epi = EPI_STORE; fc.bias = c->draft_fc_b;
+    fc.Y[0] = att; fc.ldy[0] = d;
+    launch_gemm_f32_dense(fc, s);
+    qkv_pass(g.n_layers, att, drows, false);
+  }
+}
+
 // Whole prompt through the dense pass; leaves the last position's feature in F row
 // (n-1) % 16 (where the 16-row path leaves it) and its logits / argmax in row 0.
 int prefill_dense(ae_ctx *c, int n) {
@@ -392,19 +409,20 @@ int prefill_dense(ae_ctx *c, int n) {
   for (int p0 = 0; p0 < n; p0 += c->dense_cap) {
     const int rows = n - p0 < c->dense_cap ? n - p0 : c->dense_cap;
     const bool last = p0 + rows == n;
-    dense_chunk(c, p0, rows, last ? rows - 1 : rows);
+    if (c->fast) dense_chunk(c, p0, rows, last ? rows - 1 : rows);
+    else dense_chunk_f32(c, p0, rows, last ? rows - 1 : rows);
     last_rows = rows;
   }
   const int frow = (n - 1) % kMaxRows;
   float *F = c->F + (size_t)frow * g.d_model;
   launch_rmsnorm(c->px + (size_t)(last_rows - 1) * g.d_model, c->final_norm, 1, g.d_model, g.rms_eps, F, s);
-  launch_pack_rows(F, g.d_model, 1, g.d_model, nullptr, c->xp_a, s);
+  if (c->fast) launch_pack_rows(F, g.d_model, 1, g.d_model, nullptr, c->xp_a, s);
   GemmLaunch lm;
-  lm.W = &c->lm_head; lm.Xp = c->xp_a; lm.rows = 1; lm.epi = EPI_STORE;
+  lm.W = &c->lm_head; lm.Xp = c->fast ? c->xp_a : F; lm.ldx = g.d_model; lm.rows = 1; lm.epi = EPI_STORE;
   lm.Y[0] = c->logits; lm.ldy[0] = g.vocab; lm.seg_N[0] = g.vocab;
   lm.amax_val = c->amax_val; lm.amax_idx = c->amax_idx;
-  launch_gemm_mfma(lm, s);
-  launch_argmax_finish(c->amax_val, c->amax_idx, g.vocab / 16, 1, c->st, -1, s);
+  gemm(c, lm);
+  launch_argmax_finish(c->amax_val, c->amax_idx, (g.vocab + 15) / 16, 1, c->st, -1, s);
   c->nF = frow + 1;
   return AE_OK;
 }
@@ -513,8 +531,16 @@ int ae_init(const ae_config *cfg, const ae_weights *w, void *hip_stream, ae_ctx 
   c->ldlp_b_in = w->ldlp_b_in; c->ldlp_w_res = w->ldlp_w_res; c->ldlp_b_res = w->ldlp_b_res;
   c->ldlp_w_out = w->ldlp_w_out; c->ldlp_b_out = w->ldlp_b_out;
 
-  // bf16: re-tile every streamed matrix into the MFMA operand layout (see kernels_mfma.hip)
+  // bf16: re-tile every streamed matrix into the MFMA operand layout (see kernels_mfma.hip); float32
+  // matrices are read where they are
   c->fast = g.dtype == AE_BF16;
+  if (!c->fast)
+    for (auto &l : c->layers) {
+      l.f_qkv.N = dq + 2 * dkv; l.f_gu.N = 2 * f;
+      l.f_qkv.K = l.f_gu.K = d;
+      l.f_qkv.part[0] = l.wq.rowmajor; l.f_qkv.part[1] = l.wk.rowmajor; l.f_qkv.part[2] = l.wv.rowmajor;
+      l.f_gu.part[0] = l.w_gate.rowmajor; l.f_gu.part[1] = l.w_up.rowmajor;
+    }
   if (c->fast) {
     attention_mfma_setup();
     int cus = 0;
@@ -548,15 +574,17 @@ int ae_init(const ae_config *cfg, const ae_weights *w, void *hip_stream, ae_ctx 
       if ((rc = retile_fused(c, t, one, 1, false))) return bail(rc);
       l.w_down.tiled = t.tiled;
     }
-    // packed activation buffers: K * 64 bytes each (hi + lo, 16 row slots)
-    const size_t dqq = (size_t)g.n_heads * g.head_dim;
+  }
+  {
+    // GEMM inputs, K * 64 bytes each: bf16 hi + lo or float32, 16 row slots; RMSNorm partial sums per 16 columns
+    const size_t dqq = (size_t)g.n_heads * g.head_dim, ssq = ((size_t)g.d_model + 15) / 16 * 16, nv = ((size_t)V + 15) / 16 * 16;
     char *pa = nullptr, *pf = nullptr, *pt = nullptr, *ph = nullptr, *pc = nullptr;
     if ((rc = dev_alloc(c, &pa, (size_t)g.d_model * 64)) || (rc = dev_alloc(c, &pf, (size_t)g.d_model * 64)) ||
         (rc = dev_alloc(c, &pt, dqq * 64)) || (rc = dev_alloc(c, &ph, (size_t)g.d_ffn * 64)) ||
         (rc = dev_alloc(c, &pc, (size_t)2 * g.d_model * 64)) ||
-        (rc = dev_alloc(c, &c->ssq_a, (size_t)g.d_model)) || (rc = dev_alloc(c, &c->ssq_f, (size_t)g.d_model)) ||
-        (rc = dev_alloc(c, &c->amax_val, (size_t)g.vocab)) || (rc = dev_alloc(c, &c->amax_idx, (size_t)g.vocab)) ||
-        (rc = dev_alloc(c, &c->lse_sum, (size_t)g.vocab)))
+        (rc = dev_alloc(c, &c->ssq_a, ssq)) || (rc = dev_alloc(c, &c->ssq_f, ssq)) ||
+        (rc = dev_alloc(c, &c->amax_val, nv)) || (rc = dev_alloc(c, &c->amax_idx, nv)) ||
+        (rc = dev_alloc(c, &c->lse_sum, nv)))
       return bail(rc);
     c->xp_a = pa; c->xp_f = pf; c->xp_att = pt; c->xp_h = ph; c->xp_cat = pc;
     launch_fill_zero(pa, (size_t)g.d_model * 64, c->stream);
@@ -564,8 +592,8 @@ int ae_init(const ae_config *cfg, const ae_weights *w, void *hip_stream, ae_ctx 
     launch_fill_zero(pt, dqq * 64, c->stream);
     launch_fill_zero(ph, (size_t)g.d_ffn * 64, c->stream);
     launch_fill_zero(pc, (size_t)2 * g.d_model * 64, c->stream);
-    launch_fill_zero(c->ssq_a, (size_t)g.d_model * 4, c->stream);
-    launch_fill_zero(c->ssq_f, (size_t)g.d_model * 4, c->stream);
+    launch_fill_zero(c->ssq_a, ssq * 4, c->stream);
+    launch_fill_zero(c->ssq_f, ssq * 4, c->stream);
   }
 
   // KV cache for n_layers target layers + the draft layer, zero-filled so that slots that
@@ -579,14 +607,9 @@ int ae_init(const ae_config *cfg, const ae_weights *w, void *hip_stream, ae_ctx 
   launch_fill_zero(c->kv, (kv_bytes + 15) / 16 * 16, c->stream);
 
   const size_t R = kMaxRows;
-  const int dmax = dq > d ? dq : d;
   if ((rc = dev_alloc(c, &c->rope_tab, (size_t)g.n_ctx_max * (g.head_dim / 2))) ||
-      (rc = dev_alloc(c, &c->x, R * d)) || (rc = dev_alloc(c, &c->xn, R * d)) ||
-      (rc = dev_alloc(c, &c->q, R * dq)) || (rc = dev_alloc(c, &c->kbuf, R * dkv)) ||
-      (rc = dev_alloc(c, &c->vbuf, R * dkv)) || (rc = dev_alloc(c, &c->att, R * dmax)) ||
-      (rc = dev_alloc(c, &c->gate_proj, R * f)) || (rc = dev_alloc(c, &c->up, R * f)) ||
-      (rc = dev_alloc(c, &c->hmid, R * f)) || (rc = dev_alloc(c, &c->F, R * d)) ||
-      (rc = dev_alloc(c, &c->cat, R * 2 * d)) || (rc = dev_alloc(c, &c->logits, (size_t)(g.k_max + 1) * V)) ||
+      (rc = dev_alloc(c, &c->x, R * d)) || (rc = dev_alloc(c, &c->q, R * dq)) ||
+      (rc = dev_alloc(c, &c->F, R * d)) || (rc = dev_alloc(c, &c->logits, (size_t)(g.k_max + 1) * V)) ||
       (rc = dev_alloc(c, &c->dlogits, (size_t)(g.k_max > 0 ? g.k_max : 1) * V)) ||
       (rc = dev_alloc(c, &c->attn_part, attn_part_floats(g))) ||
       (rc = dev_alloc(c, &c->ldlp_z, (size_t)kMaxLdlpHidden)) ||
@@ -639,7 +662,10 @@ int ae_prefill(ae_ctx *c, const int32_t *ids, int n) {
   memcpy(c->h_hist.data(), ids, sizeof(int32_t) * n);
   c->kv_len = 0; c->dlen = 0; c->nF = 0;
   c->have_pending = c->have_draft = c->have_verify = c->k_next_valid = false;
-  const bool dense = c->prefill_mode == AE_PREFILL_DENSE || (c->prefill_mode == AE_PREFILL_AUTO && dense_ok(c) && n >= kDenseMinPrompt);
+  bool dense = c->prefill_mode == AE_PREFILL_DENSE ||
+               (c->prefill_mode == AE_PREFILL_AUTO && (dense_ok(c) || !c->fast) && n >= kDenseMinPrompt);
+  // float32 prompts always had the 16-row pass: no room for the chunk buffers is no reason to refuse one
+  if (dense && !c->fast && ensure_dense(c, n) == AE_ENOMEM) dense = false;
   if (dense) {
     int rc = prefill_dense(c, n);
     if (rc) return rc;
@@ -786,7 +812,6 @@ int ae_draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draf
   // catch-up over the slots validated by the last accept: true feature + following token
   draft_rows(c, c->F + (size_t)(c->nF - catch_rows) * g.d_model, g.d_model, c->hist + c->dlen + 1, catch_rows, c->dlen);
   c->dlen = n;
-  const float *fh = c->x + (size_t)(catch_rows - 1) * g.d_model;
   int fh_row = catch_rows - 1;
   // AdaEAGLE-DDD (Sec. 3.4, 4.2): past the predicted length the head exits unless the
   // log-probability of the tokens drafted so far is still at least the threshold.  Host mode
@@ -813,8 +838,7 @@ int ae_draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draf
       }
     }
     if (i > 0) {  // chain: the head's previous output replaces the feature
-      draft_rows(c, fh, g.d_model, c->st->draft_ids + (i - 1), 1, n - 1 + i, c->fast ? fh_row : -1);
-      fh = c->x;
+      draft_rows(c, nullptr, 0, nullptr, 1, n - 1 + i, fh_row);
       fh_row = 0;
     }
     draft_lm_head(c, fh_row, i, k);

@@ -53,13 +53,14 @@ static_assert(offsetof(DevState, u_draft) % 8 == 0, "doubles must stay aligned")
 struct Mat {
   const void *rowmajor = nullptr;  // caller's [N,K]
   void *tiled = nullptr;           // ctx-owned MFMA-tile layout, bf16 only
+  const void *part[3] = {nullptr, nullptr, nullptr};   // float32: row-major sources of a fused matrix
   int N = 0, K = 0;
 };
 
 struct LayerW {
   const float *attn_norm = nullptr, *ffn_norm = nullptr;
   Mat wq, wk, wv, wo, w_gate, w_up, w_down;
-  Mat f_qkv, f_gu;   // bf16 fast path: fused tiled [q;k;v] and row-block-interleaved [gate,up]
+  Mat f_qkv, f_gu;   // fused [q;k;v] and [gate,up]: bf16 tiled (gate and up row-blocks interleaved), float32 by parts
 };
 
 }  // namespace ae
@@ -68,7 +69,7 @@ struct ae_ctx {
   ae_config cfg{};
   hipStream_t stream = nullptr;
   int device = 0;
-  bool fast = false;            // bf16 MFMA path (else generic kernels)
+  bool fast = false;            // bf16 weights and cache (else float32)
   std::string err;
 
   // weights
@@ -89,15 +90,13 @@ struct ae_ctx {
   float *kv_stage = nullptr;       // this device's address of the library's static staging array
 
   // activations (float, kMaxRows rows each)
-  float *x = nullptr, *xn = nullptr, *q = nullptr, *kbuf = nullptr, *vbuf = nullptr, *att = nullptr;
-  float *gate_proj = nullptr, *up = nullptr, *hmid = nullptr;
+  float *x = nullptr, *q = nullptr;
   float *F = nullptr;              // feature rows (post final norm)
-  float *cat = nullptr;            // [rows][2d] draft fc input
   float *logits = nullptr;         // [k_max+1][V]
   float *dlogits = nullptr;        // [k_max][V]
   float *attn_part = nullptr;      // split-KV partials
   float *ldlp_z = nullptr;         // LDLP hidden vector
-  // bf16 fast path: packed activations (GEMM B operands) and RMSNorm partial sums
+  // GEMM inputs (bf16: packed B operands; float32: 16 rows, row-major) and RMSNorm partial sums
   void *xp_a = nullptr, *xp_f = nullptr, *xp_att = nullptr, *xp_h = nullptr, *xp_cat = nullptr;
   float *ssq_a = nullptr, *ssq_f = nullptr;
   float *amax_val = nullptr;       // LM-head argmax partials [16][vocab/16]
@@ -110,7 +109,8 @@ struct ae_ctx {
   ae::DevState *h_st = nullptr;    // pinned host mirror of *st, written by the device (publish_state)
   ae::DevState *h_st_dev = nullptr;   // the device's address of that mirror
 
-  // dense prompt pass (bf16 only): chunk buffers, allocated at the first long prompt
+  // dense prompt pass: chunk buffers, allocated at the first long prompt (float32: pxa normalised rows, pxh FFN
+  // rows, pxcat draft head input, pxatt attention output; pxf and the partial sums are bf16 only)
   int prefill_mode = 0;            // AE_PREFILL_AUTO / _BLOCKS / _DENSE
   int dense_chunk = 2048;          // rows per dense pass (multiple of 128)
   int dense_cap = 0;               // rows the buffers below hold
@@ -146,25 +146,9 @@ struct ae_ctx {
 
 namespace ae {
 
-// ---- generic kernels (kernels_generic.hip); all launches are asynchronous on `s` ----
-void launch_embed(const void *emb, int dtype, const int32_t *ids_dev, int rows, int d, float *out, hipStream_t s);
+// ---- dtype-independent kernels (kernels_generic.hip); all launches are asynchronous on `s` ----
 void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s,
                     const int32_t *gate = nullptr);
-// Y[r][n] (+)= sum_k X[r][k] W[n][k] + bias[n];  accumulate != 0 adds into Y (residual)
-void launch_gemm_generic(const void *W, int dtype, int N, int K, const float *X, int ldx, int rows,
-                         const float *bias, float *Y, int ldy, int accumulate, hipStream_t s,
-                         const int32_t *gate = nullptr);
-void launch_silu_mul(const float *gate_proj, const float *up, int rows, int f, float *out, hipStream_t s,
-                     const int32_t *gate = nullptr);
-void launch_argmax(const float *logits, int rows, int V, int32_t *out_ids, hipStream_t s, const int32_t *gate = nullptr);
-void launch_draft_cat(const float *feat, int feat_ld, const void *emb, int dtype, const int32_t *next_ids,
-                      int rows, int d, float *cat, hipStream_t s, const int32_t *gate = nullptr);
-void launch_pick_draft(DevState *st, int i, hipStream_t s, const int32_t *gate = nullptr);
-// DDD bookkeeping behind draft token i: log softmax(logits / T)[token i] -> st->draft_lp[i], added
-// to st->cum_logp (reset when i == 0); st->draft_len = i + 1; and the exit rule for the NEXT
-// token: st->draft_live = 0 when i + 1 >= k and the sequence log-probability is below theta.
-void launch_draft_logprob(const float *logits, int V, float T, DevState *st, int i, int k, float theta, hipStream_t s,
-                          const int32_t *gate = nullptr);
 // Host arrays (override ids: -1 keeps the head's own token; uniforms; explicit block ids) are
 // passed by value inside the launch; the pointers are read before the call returns.
 void launch_set_draft_inputs(DevState *st, const int32_t *override_ids, int n_ov, const double *u_draft, int n_u,
@@ -191,15 +175,14 @@ void launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 size_t kv_layer_bytes(const ae_config &c);
 size_t kv_v_offset_bytes(const ae_config &c);
 int kv_capacity(const ae_config &c);   // n_ctx_max rounded up to a whole attention chunk
-void launch_rope_append(float *q, const float *k, const float *v, int rows, int pos0, const ae_config &c,
-                        const float2 *rope_tab, void *kv_layer, size_t v_off, bool tiled, hipStream_t s,
-                        const int32_t *gate = nullptr);
 // bf16 MFMA attention over the tiled cache layout (kernels_attn_mfma.hip)
 void attention_mfma_setup();   // once per context set-up: dynamic LDS limit of the kernels
 void launch_attention_mfma(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
                            float *part, void *Xp_out, hipStream_t s, const int32_t *gate = nullptr);
-void launch_attention(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
-                      float *part, float *out, hipStream_t s, const int32_t *gate = nullptr);
+// merge of split-KV partials (log2-domain maxima) into the input of the output projection: packed bf16 hi/lo, or
+// float32 rows [rows][n_heads * head_dim]
+void launch_attention_merge(const float *part, int rows, int n_chunks, const ae_config &c, void *out, bool f32, hipStream_t s,
+                            const int32_t *gate);
 void launch_kv_import(void *kv_layer, size_t v_off, const ae_config &c, const float *k_dev, const float *v_dev, int n,
                       bool tiled, hipStream_t s);
 void launch_kv_export(const void *kv_layer, size_t v_off, const ae_config &c, int which, int slot, float *out_dev,
@@ -215,15 +198,16 @@ void launch_sample_draft(const float *logits, int V, float T, DevState *st, int 
 void launch_accept_sample(const float *tl, const float *dl, int V, int k, bool k_on_device, float T, DevState *st,
                           int32_t *hist, int kv_len, double *prob, hipStream_t s);
 
-// ---- bf16 MFMA path (kernels_mfma.hip) ----
+// ---- bf16 decode GEMMs (kernels_mfma.hip) ----
 // Row-block nb of a row-major [N,K] matrix -> row-block nb_off + nb*nb_stride of a fused
 // k-major tiled matrix with NBtot row-blocks.
 void launch_retile(const void *rowmajor, int N, int K, void *tiled, int NBtot, int nb_off, int nb_stride, int perm_hd,
                    hipStream_t s);
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 struct GemmLaunch {
-  const Mat *W = nullptr;         // fused tiled matrix: N = all output rows, K
-  const void *Xp = nullptr;       // packed activations
+  const Mat *W = nullptr;         // fused matrix: N = all output rows, K
+  const void *Xp = nullptr;       // activations: packed (bf16) or float32 rows of stride ldx
+  int ldx = 0, ldxo = 0;          // float32: row strides of Xp and Xp_out
   int rows = 0, row0 = 0;         // output row m reads packed row row0 + m
   const float *ssq_in = nullptr;  // != nullptr: fused RMSNorm, [P_in][16] partial sums of x^2
   int P_in = 0;
@@ -234,7 +218,7 @@ struct GemmLaunch {
   float *Y[3] = {nullptr, nullptr, nullptr};
   int ldy[3] = {0, 0, 0};
   int seg_N[3] = {0, 0, 0};
-  void *Xp_out = nullptr;         // packed output for the next GEMM
+  void *Xp_out = nullptr;         // output for the next GEMM, in the form of its Xp
   const float *gain_out = nullptr;
   float *ssq_out = nullptr;
   float *amax_val = nullptr;      // LM head: argmax partials per row and row-block [16][N/16]
@@ -252,14 +236,14 @@ void gemm_mfma_setup(int num_cus);   // once per context set-up: compute-unit co
 // Where the kernel that fixes a draft token leaves that token's embedding: row `row`, second
 // half (k = d .. 2d-1) of the draft head's packed input.  Xp == nullptr: nowhere.
 struct DraftCat {
-  const void *emb = nullptr;   // bf16 embedding table [V][d]
-  void *Xp = nullptr;
-  int d = 0, row = 0;
+  const void *emb = nullptr;   // embedding table [V][d]
+  void *Xp = nullptr;          // packed (bf16) or float32 rows [16][2d]
+  int d = 0, row = 0, f32 = 0;
 };
-// DDD bookkeeping folded into the kernel that fixes draft token i (bf16 path): the token's
+// DDD bookkeeping folded into the kernel that fixes draft token i: the token's
 // log-probability under softmax(logits / T) from the LM-head epilogue's row-block statistics
 // (block maxima `val`, block sums `lse_sum`), the running sum, the drafted length and the exit
-// rule for the next token (see launch_draft_logprob).  lse_sum == nullptr: rule off.
+// rule for the next token (st->draft_live = 0 when i + 1 >= k and the sum is below theta).  lse_sum == nullptr: rule off.
 struct DddFinish {
   const float *val = nullptr, *lse_sum = nullptr;
   const float *logits = nullptr;   // the token's logit row
@@ -286,5 +270,18 @@ void launch_draft_cat_dense(const float *x, int rows, int d, const float *gain, 
                             const int32_t *next_ids, void *Xp, int RB, hipStream_t s);
 void launch_attention_prefill(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
                               void *Xp_out, int RB, hipStream_t s);
+
+// ---- float32 models (kernels_f32.hip) ----
+void launch_gemm_f32(const GemmLaunch &L, hipStream_t s);         // 1..16 rows, all epilogues and fusions
+void launch_gemm_f32_dense(const GemmLaunch &L, hipStream_t s);   // any number of rows; Xp already normalised
+void launch_attention_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
+                          float *part, float *out, hipStream_t s, const int32_t *gate = nullptr);
+int attn_f32_chunk_keys();   // keys per split-KV workgroup
+void launch_attention_prefill_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
+                                  float *out, hipStream_t s);
+void launch_embed_f32(const void *emb, const int32_t *ids_dev, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
+                      hipStream_t s);
+void launch_draft_cat_f32(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d, void *cat,
+                          hipStream_t s, const int32_t *gate = nullptr);
 
 }  // namespace ae

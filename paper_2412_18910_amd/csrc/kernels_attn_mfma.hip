@@ -183,11 +183,11 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float *q, int rows
 // single round trip.  Chunk lane cl folds chunks cl, cl+CL, ... in ascending order with a
 // running maximum (rescaling its sums when the maximum grows) and the lanes are then combined
 // in ascending order against the overall maximum: a fixed order that does not depend on the
-// number of rows.  The result is written in packed form as the input of the output
-// projection (k index = h*HD + d).
-template <int HD, bool GATED>
+// number of rows.  The result is written as the input of the output projection (k index =
+// h*HD + d): packed, or with F32 as float32 rows.
+template <int HD, bool F32, bool GATED>
 __global__ __launch_bounds__(256) void attn_merge_log2_kernel(const float *part, int rows, int H, int Hkv, int n_chunks,
-                                                              u32x4 *Xp_out, const int32_t *gate) {
+                                                              void *out, const int32_t *gate) {
   constexpr int DQ = HD / 4, CL = 256 / DQ;
   __shared__ float4 nums[CL][DQ];
   __shared__ float dens[CL], maxs[CL];
@@ -232,7 +232,28 @@ __global__ __launch_bounds__(256) void attn_merge_log2_kernel(const float *part,
         dall = fmaf(wgt, dens[i], dall);
       }
     }
-    packed_store4(Xp_out, mrow, h * HD + dq * 4, acc.x / dall, acc.y / dall, acc.z / dall, acc.w / dall);
+    const float4 o = make_float4(acc.x / dall, acc.y / dall, acc.z / dall, acc.w / dall);
+    if (F32) *reinterpret_cast<float4 *>((float *)out + ((size_t)mrow * H + h) * HD + dq * 4) = o;
+    else packed_store4((u32x4 *)out, mrow, h * HD + dq * 4, o.x, o.y, o.z, o.w);
+  }
+}
+
+template <int HD, bool F32>
+static void launch_merge_cfg(const float *part, int rows, int n_chunks, const ae_config &c, void *out, hipStream_t s,
+                             const int32_t *gate) {
+  const int grid = rows * c.n_heads;
+  if (gate) attn_merge_log2_kernel<HD, F32, true><<<grid, 256, 0, s>>>(part, rows, c.n_heads, c.n_kv_heads, n_chunks, out, gate);
+  else attn_merge_log2_kernel<HD, F32, false><<<grid, 256, 0, s>>>(part, rows, c.n_heads, c.n_kv_heads, n_chunks, out, gate);
+}
+
+void launch_attention_merge(const float *part, int rows, int n_chunks, const ae_config &c, void *out, bool f32, hipStream_t s,
+                            const int32_t *gate) {
+  if (c.head_dim == 128) {
+    if (f32) launch_merge_cfg<128, true>(part, rows, n_chunks, c, out, s, gate);
+    else launch_merge_cfg<128, false>(part, rows, n_chunks, c, out, s, gate);
+  } else {
+    if (f32) launch_merge_cfg<64, true>(part, rows, n_chunks, c, out, s, gate);
+    else launch_merge_cfg<64, false>(part, rows, n_chunks, c, out, s, gate);
   }
 }
 
@@ -260,8 +281,7 @@ static void launch_attention_cfg(const float *q, int rows, int pos0, const ae_co
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
   attn_mfma_kernel<HD, kMfmaKeysPerWave, GATED><<<grid, 256, sm, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c),
                                                                       Kc, Vc, part, scale_log2e, gate);
-  attn_merge_log2_kernel<HD, GATED><<<rows * c.n_heads, 256, 0, s>>>(part, rows, c.n_heads, c.n_kv_heads, n_chunks,
-                                                                     (u32x4 *)Xp_out, gate);
+  launch_attention_merge(part, rows, n_chunks, c, Xp_out, false, s, gate);
 }
 
 void launch_attention_mfma(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,

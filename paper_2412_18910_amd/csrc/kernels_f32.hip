@@ -1,0 +1,774 @@
+// Float32 models (weights, activations and KV cache in float32) on the gfx950 matrix cores.
+//
+// Everything multiplies with v_mfma_f32_16x16x4_f32: operands and accumulators stay float32, the
+// weights are read in the caller's row-major layout.  A lane (g = lane/16, m = lane%16) feeds four
+// consecutive k of one row (one 128-bit load) to four instructions, element e of every lane to
+// instruction e: the order of k inside a sum is free, so the A operand (weight row m) and the B
+// operand (activation row m) need no shuffles.  The accumulator holds weight rows 4g..4g+3 of
+// activation row m: the tile layout of the bf16 kernels, and the same epilogues in float32.
+//
+//  * gemm_f32_kernel: up to 16 activation rows (decode, verify).  HBM-bound: a workgroup owns one
+//    block of 16 weight rows (gate/up: one of each) and all of K, dealt to its waves in pieces of 64.
+//    One kernel for every row count, so a row's result does not depend on the rows beside it.
+//  * gemm_f32_dense_kernel: prompts.  Bound by the float32 matrix rate (about 150 TFLOP/s): 64 x 64 (or
+//    64 x 32) tiles through LDS.
+//  * attn_f32_kernel: split-KV attention of up to 16 rows; attn_prefill_f32_kernel: causal flash
+//    attention of a prompt chunk.
+// Long sums are cut: the decode GEMM keeps four accumulators per wave, the dense GEMM adds its
+// accumulators to a second set every 128 k, the flash attention every 256 keys, so that no chain of
+// roundings grows with K or with the context.
+#include "ae_internal.h"
+#include "gemm_epilogue.h"
+#include "packed.h"
+
+namespace ae {
+
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+struct F32Args {
+  const float *W[3];    // row-major sources: q, k, v (EPI_QKV), gate, up (EPI_SWIGLU), or one
+  int seg_nb[3];        // EPI_QKV: exclusive end of each source in row-blocks
+  int N, K;             // output rows of a source (EPI_QKV: of all), inner dimension (multiple of 8)
+  int NB;               // row-blocks of 16 output rows
+  const float *X;       // activations, row r at X + r * ldx
+  int ldx, rows, row0;  // output row m reads activation row row0 + m
+  const float *ssq_in;  // NORM: [P_in][16] partial sums of x^2
+  int P_in;
+  float eps;
+  const float *bias;
+  float *Y;             // EPI_QKV: q; EPI_RESID: residual stream, updated in place
+  int ldy;
+  float *Xo;            // output times gain_out for the next GEMM (nullable), with partial sums of x^2
+  int ldxo;
+  const float *gain_out;
+  float *ssq_out;
+  float *amax_val, *lse_sum;
+  int32_t *amax_idx;
+  float lse_inv_t;
+  const float2 *rope_tab;
+  float *Kc, *Vc;       // this layer's cache (layouts of kernels_attn.hip)
+  int pos0, n_ctx, hd;
+  const int32_t *gate;
+};
+
+// Weight row that lane m of row-block nb feeds, and its source.  The rows of every q and k head are
+// taken in rotary-pair order: tile j of a head holds rows 8j..8j+7 and their partners hd/2+8j.., so
+// that a pair sits in lanes l and l^32 of one accumulator.
+template <int EPI>
+__device__ __forceinline__ const float *f32_weight_row(const F32Args &a, int nb, int m) {
+  if (EPI == EPI_QKV) {
+    int si = 0, nbs = nb;
+    if (nb >= a.seg_nb[0]) { si = 1; nbs = nb - a.seg_nb[0]; }
+    if (nb >= a.seg_nb[1]) { si = 2; nbs = nb - a.seg_nb[1]; }
+    int row = nbs * 16 + m;
+    if (si < 2) {
+      const int bph = a.hd >> 4, head = nbs / bph, j = nbs % bph;
+      row = head * a.hd + (m < 8 ? 8 * j + m : (a.hd >> 1) + 8 * j + m - 8);
+    }
+    return a.W[si] + (size_t)row * a.K;
+  }
+  return a.W[0] + (size_t)min(nb * 16 + m, a.N - 1) * a.K;
+}
+
+template <int EPI>
+__device__ __forceinline__ EpiPre f32_epi_prefetch(const F32Args &a, int nb, int g, int row, bool row_ok) {
+  EpiPre p;
+  p.a = make_float4(0.f, 0.f, 0.f, 0.f);
+  p.b = make_float4(1.f, 1.f, 1.f, 1.f);
+  if (EPI == EPI_QKV) {
+    if (nb < a.seg_nb[1]) {   // (cos, sin) of the lane's two rotary pairs at the row's slot
+      const int nbs = nb < a.seg_nb[0] ? nb : nb - a.seg_nb[0], j = nbs % (a.hd >> 4);
+      const float2 *t = a.rope_tab + (size_t)(a.pos0 + (row_ok ? row : 0)) * (a.hd >> 1) + 8 * j + 4 * (g & 1);
+      p.a = *reinterpret_cast<const float4 *>(t);
+      p.b = *reinterpret_cast<const float4 *>(t + 2);
+    }
+  } else if (EPI == EPI_RESID || EPI == EPI_STORE) {
+    const int n = nb * 16 + 4 * g;
+    if (row_ok && n < a.N) {
+      if (EPI == EPI_RESID) p.a = *reinterpret_cast<const float4 *>(a.Y + (size_t)row * a.ldy + n);
+      else if (a.bias) p.a = *reinterpret_cast<const float4 *>(a.bias + n);
+      if (a.Xo && a.gain_out) p.b = *reinterpret_cast<const float4 *>(a.gain_out + n);
+    }
+  }
+  return p;
+}
+
+// s = accumulator of row-block nb (EPI_SWIGLU: of the gate, u = of the up projection); the lane holds
+// output columns 16*nb + 4g .. +3 of activation row `row`.  Only the LM head (amax_val set) may have a
+// number of columns that is no multiple of 8.  Every lane of the wave must call this (it shuffles).
+template <int EPI>
+__device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int nb, int g, int m, int row, bool row_ok,
+                                        float rinv, const EpiPre &pre) {
+  const int n = nb * 16 + 4 * g;
+  const bool ok = row_ok && n < a.N;
+  if (EPI == EPI_SWIGLU) {
+    if (ok)
+      *reinterpret_cast<float4 *>(a.Y + (size_t)row * a.ldy + n) =
+          make_float4(silu_dev(s[0] * rinv) * (u[0] * rinv), silu_dev(s[1] * rinv) * (u[1] * rinv),
+                      silu_dev(s[2] * rinv) * (u[2] * rinv), silu_dev(s[3] * rinv) * (u[3] * rinv));
+  } else if (EPI == EPI_QKV) {
+    int si = 0, nbs = nb;
+    if (nb >= a.seg_nb[0]) { si = 1; nbs = nb - a.seg_nb[0]; }
+    if (nb >= a.seg_nb[1]) { si = 2; nbs = nb - a.seg_nb[1]; }
+    const int hd = a.hd, bph = hd >> 4, head = nbs / bph, j = nbs % bph, slot = a.pos0 + row;
+    float4 o = make_float4(s[0] * rinv, s[1] * rinv, s[2] * rinv, s[3] * rinv);
+    if (si < 2) {
+      const float sgn = g < 2 ? -1.f : 1.f;   // first half: a*c - b*s; second half: b*c + a*s
+      const float p0 = __shfl_xor(o.x, 32, 64), p1 = __shfl_xor(o.y, 32, 64);
+      const float p2 = __shfl_xor(o.z, 32, 64), p3 = __shfl_xor(o.w, 32, 64);
+      o.x = o.x * pre.a.x + sgn * p0 * pre.a.y;
+      o.y = o.y * pre.a.z + sgn * p1 * pre.a.w;
+      o.z = o.z * pre.b.x + sgn * p2 * pre.b.y;
+      o.w = o.w * pre.b.z + sgn * p3 * pre.b.w;
+      const int dcol = (g < 2 ? 0 : hd >> 1) + 8 * j + 4 * (g & 1);
+      if (row_ok) {
+        if (si == 0) *reinterpret_cast<float4 *>(a.Y + (size_t)row * a.ldy + head * hd + dcol) = o;
+        else *reinterpret_cast<float4 *>(a.Kc + (((size_t)head * (hd >> 3) + (dcol >> 3)) * a.n_ctx + slot) * 8 + (dcol & 7)) = o;
+      }
+    } else if (row_ok) {
+      *reinterpret_cast<float4 *>(a.Vc + ((size_t)head * a.n_ctx + slot) * hd + j * 16 + 4 * g) = o;
+    }
+  } else if (EPI == EPI_STORE && a.amax_val) {   // LM head: logits, argmax and softmax partials of the row-block
+    float v[4] = {s[0] * rinv, s[1] * rinv, s[2] * rinv, s[3] * rinv};
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    float *yp = a.Y + (size_t)row * a.ldy + n;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (row_ok && n + e < a.N) {
+        yp[e] = v[e];
+        if (v[e] > bv) { bv = v[e]; bi = n + e; }
+      } else {
+        v[e] = -INFINITY;
+      }
+    }
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+      const float ov = __shfl_xor(bv, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    }
+    if (g == 0) { a.amax_val[(size_t)m * a.NB + nb] = bv; a.amax_idx[(size_t)m * a.NB + nb] = bi; }
+    if (a.lse_sum) {
+      float t = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t += v[e] > -INFINITY ? expf((v[e] - bv) * a.lse_inv_t) : 0.f;
+      t += __shfl_xor(t, 16, 64);
+      t += __shfl_xor(t, 32, 64);
+      if (g == 0) a.lse_sum[(size_t)m * a.NB + nb] = t;
+    }
+  } else if (EPI == EPI_STORE && a.N % 8 != 0) {   // LM head without partials (a sampled draft token)
+    if (row_ok)
+      for (int e = 0; e < 4; ++e)
+        if (n + e < a.N) a.Y[(size_t)row * a.ldy + n + e] = s[e] * rinv;
+  } else {
+    const float4 o = make_float4(s[0] * rinv + pre.a.x, s[1] * rinv + pre.a.y, s[2] * rinv + pre.a.z, s[3] * rinv + pre.a.w);
+    float ssq = 0.f;
+    if (ok) {
+      *reinterpret_cast<float4 *>(a.Y + (size_t)row * a.ldy + n) = o;
+      if (a.Xo) {
+        ssq = o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
+        *reinterpret_cast<float4 *>(a.Xo + (size_t)row * a.ldxo + n) =
+            make_float4(o.x * pre.b.x, o.y * pre.b.y, o.z * pre.b.z, o.w * pre.b.w);
+      }
+    }
+    if (a.ssq_out) {
+      ssq += __shfl_xor(ssq, 16, 64);
+      ssq += __shfl_xor(ssq, 32, 64);
+      if (g == 0) a.ssq_out[(size_t)nb * 16 + m] = ssq;
+    }
+  }
+}
+
+// ------------------------------------------------------------------ decode GEMM (1..16 rows)
+// HBM-bound (each weight is read once).  A wave keeps 4 KB (gate/up: 8 KB) of weights in flight in a rolling ring.
+// TAIL: K is no multiple of 64; pieces behind the end are fed as zeros.
+template <int EPI, bool NORM, int NW, bool TAIL, bool GATED>
+__global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
+  constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1, D = 4;
+  __shared__ f32x4 red[NW][NA][64];
+  if constexpr (GATED) AE_GATE(a.gate);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, m = lane & 15;
+  const int nb = blockIdx.x, K = a.K;
+  const bool row_ok = m < a.rows;
+  const int xrow = a.row0 + (row_ok ? m : a.rows - 1);   // rows beyond the block re-read the last row
+  const float *xp = a.X + (size_t)xrow * a.ldx;
+  const float *wp[NA];
+  wp[0] = f32_weight_row<EPI>(a, nb, m);
+  if (NA == 2) wp[NA - 1] = a.W[1] + (size_t)min(nb * 16 + m, a.N - 1) * K;
+
+  EpiPre pre{};
+  if (w == 0) pre = f32_epi_prefetch<EPI>(a, nb, g, m, row_ok);
+
+  f32x4 acc[NA][4], wb[D][NA], xb[D];
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[i][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int c, int j) {
+    const int k = c * (D * 16) + j * 16 + g * 4;
+    const bool in = !TAIL || k < K;
+    const int kk = in ? k : 0;
+    xb[j] = *reinterpret_cast<const f32x4 *>(xp + kk);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) wb[j][i] = *reinterpret_cast<const f32x4 *>(wp[i] + kk);
+    if (TAIL && !in) {
+      xb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NA; ++i) wb[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  const int NC = (K + D * 16 - 1) / (D * 16);
+  if (w < NC) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) load(w, j);
+  }
+
+  // 1/rms of every row from the producer's partial sums of x^2, summed by wave 0 in a fixed order
+  __shared__ float rinv_s[16];
+  if (NORM && w == 0) {
+    const float4 *pp = reinterpret_cast<const float4 *>(a.ssq_in);
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+    for (int i = lane; i < a.P_in * 4; i += 64) {   // lane l covers rows 4*(l%4)..+3
+      const float4 v = pp[i];
+      t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+    }
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) {
+      t.x += __shfl_xor(t.x, o, 64); t.y += __shfl_xor(t.y, o, 64);
+      t.z += __shfl_xor(t.z, o, 64); t.w += __shfl_xor(t.w, o, 64);
+    }
+    if (lane < 4) {
+      rinv_s[lane * 4 + 0] = 1.0f / sqrtf(t.x / (float)K + a.eps);
+      rinv_s[lane * 4 + 1] = 1.0f / sqrtf(t.y / (float)K + a.eps);
+      rinv_s[lane * 4 + 2] = 1.0f / sqrtf(t.z / (float)K + a.eps);
+      rinv_s[lane * 4 + 3] = 1.0f / sqrtf(t.w / (float)K + a.eps);
+    }
+  }
+
+  for (int c = w; c < NC; c += NW) {
+    const int cn = c + NW < NC ? c + NW : c;   // the last piece re-issues its own loads (ignored)
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) acc[i][e] = mfma_f32(wb[j][i][e], xb[j][e], acc[i][e]);
+      __builtin_amdgcn_sched_barrier(0);   // refill slot j at once, not behind the whole piece
+      load(cn, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NA; ++i) red[w][i][lane] = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+  __syncthreads();
+  if (w != 0) return;
+  f32x4 s = red[0][0][lane], u = red[0][NA - 1][lane];
+#pragma unroll
+  for (int ww = 1; ww < NW; ++ww) {
+    s += red[ww][0][lane];
+    u += red[ww][NA - 1][lane];
+  }
+  f32_epi<EPI>(a, s, u, nb, g, m, m, row_ok, NORM ? rinv_s[xrow] : 1.f, pre);
+}
+
+static F32Args f32_args(const GemmLaunch &L) {
+  F32Args a{};
+  const Mat &W = *L.W;
+  for (int i = 0; i < 3; ++i) a.W[i] = (const float *)(W.part[i] ? W.part[i] : W.rowmajor);
+  a.K = W.K;
+  a.N = L.epi == EPI_SWIGLU ? W.N / 2 : W.N;
+  a.NB = (a.N + 15) / 16;
+  int end = 0;
+  for (int i = 0; i < 3; ++i) a.seg_nb[i] = end += L.epi == EPI_QKV ? L.seg_N[i] / 16 : 0;
+  if (L.epi == EPI_QKV) { a.NB = end; a.N = end * 16; }
+  a.X = (const float *)L.Xp; a.ldx = L.ldx; a.rows = L.rows; a.row0 = L.row0;
+  a.ssq_in = L.ssq_in; a.P_in = L.P_in; a.eps = L.eps;
+  a.bias = L.bias;
+  a.Y = L.Y[0]; a.ldy = L.ldy[0];
+  a.Xo = (float *)L.Xp_out; a.ldxo = L.ldxo; a.gain_out = L.gain_out; a.ssq_out = L.ssq_out;
+  if (L.epi == EPI_SWIGLU) { a.Y = (float *)L.Xp_out; a.ldy = L.ldxo; a.Xo = nullptr; }
+  a.amax_val = L.amax_val; a.amax_idx = L.amax_idx;
+  a.lse_sum = L.amax_val ? L.lse_sum : nullptr; a.lse_inv_t = L.lse_inv_t;
+  a.rope_tab = L.rope_tab; a.Kc = (float *)L.Kc; a.Vc = (float *)L.Vc;
+  a.pos0 = L.pos0; a.n_ctx = L.n_ctx; a.hd = L.hd;
+  a.gate = L.gate;
+  return a;
+}
+
+template <int EPI, bool NORM, int NW>
+static void launch_f32_waves(const F32Args &a, hipStream_t s) {
+  const bool tail = a.K % 64 != 0;
+  if (a.gate) {
+    if (tail) gemm_f32_kernel<EPI, NORM, NW, true, true><<<a.NB, NW * 64, 0, s>>>(a);
+    else gemm_f32_kernel<EPI, NORM, NW, false, true><<<a.NB, NW * 64, 0, s>>>(a);
+  } else {
+    if (tail) gemm_f32_kernel<EPI, NORM, NW, true, false><<<a.NB, NW * 64, 0, s>>>(a);
+    else gemm_f32_kernel<EPI, NORM, NW, false, false><<<a.NB, NW * 64, 0, s>>>(a);
+  }
+}
+
+template <int EPI, bool NORM>
+static void launch_f32_cfg(const F32Args &a, hipStream_t s) {
+  if (a.K >= 1024) launch_f32_waves<EPI, NORM, 8>(a, s);   // at least two pieces of 64 for each of 8 waves
+  else launch_f32_waves<EPI, NORM, 4>(a, s);
+}
+
+void launch_gemm_f32(const GemmLaunch &L, hipStream_t s) {
+  const F32Args a = f32_args(L);
+  const bool norm = L.ssq_in != nullptr;
+  if (L.epi == EPI_QKV) launch_f32_cfg<EPI_QKV, true>(a, s);
+  else if (L.epi == EPI_SWIGLU) launch_f32_cfg<EPI_SWIGLU, true>(a, s);
+  else if (L.epi == EPI_RESID) launch_f32_cfg<EPI_RESID, false>(a, s);
+  else if (norm) launch_f32_cfg<EPI_STORE, true>(a, s);
+  else launch_f32_cfg<EPI_STORE, false>(a, s);
+}
+
+// ------------------------------------------------------------------ prompt GEMM
+// Workgroup tile: 64 weight rows (gate/up: 32 of each) x TM activation rows; 4 waves as 2 x 2.  Stages of
+// 32 k go global -> registers -> LDS (in lane order: conflict-free), one stage ahead; few registers, so
+// several workgroups share a compute unit and cover each other's barriers.
+template <int EPI, int TM>
+__global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
+  constexpr int MB = TM / 16, JB = MB / 2;        // activation row-blocks per workgroup / per wave
+  constexpr int STAGE = (4 + MB) * 128, NLB = MB / 2;
+  constexpr int FLUSH = 4;                        // stages (of 32 k) per accumulation chain
+  __shared__ f32x4 sm[2][STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
+  // the activation tiles of one weight tile run side by side on one XCD (ids go round the 8 XCDs) and share it in its L2
+  const int NT = (a.NB + (EPI == EPI_SWIGLU ? 1 : 3)) / (EPI == EPI_SWIGLU ? 2 : 4), MT = (a.rows + TM - 1) / TM;
+  const int per = (NT * MT + 7) >> 3, v = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  if (((int)blockIdx.x >> 3) >= per || v >= NT * MT) return;
+  const int tn = v / MT, row_t = (v % MT) * TM, K = a.K;
+  const int nb_t = tn * (EPI == EPI_SWIGLU ? 2 : 4);
+
+  // the two A pieces and NLB B pieces this thread stages: piece p = (row-block, k half, lane)
+  const float *ap[2], *bp[NLB];
+  int ko[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int p = tid + 256 * i, rb = p >> 7, pl = p & 63;
+    ko[i] = ((p >> 6) & 1) * 16 + (pl >> 4) * 4;   // the same for the B pieces
+    if (EPI == EPI_SWIGLU) {   // row-blocks alternate gate, up
+      const int row = min((nb_t + (rb >> 1)) * 16 + (pl & 15), a.N - 1);
+      ap[i] = a.W[rb & 1] + (size_t)row * K;
+    } else {
+      ap[i] = f32_weight_row<EPI>(a, min(nb_t + rb, a.NB - 1), pl & 15);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NLB; ++i) {
+    const int p = tid + 256 * i;
+    bp[i] = a.X + (size_t)min(row_t + (p >> 7) * 16 + (p & 15), a.rows - 1) * a.ldx;
+  }
+  f32x4 ar[2], br[NLB];
+  auto issue = [&](int k0) {   // pieces behind the end of K are zeros
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = k0 + ko[i];
+      ar[i] = *reinterpret_cast<const f32x4 *>(ap[i] + (k < K ? k : 0));
+      if (k >= K) ar[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int i = 0; i < NLB; ++i) {
+      const int k = k0 + ko[i];
+      br[i] = *reinterpret_cast<const f32x4 *>(bp[i] + (k < K ? k : 0));
+      if (k >= K) br[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  auto stash = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) sm[buf][tid + 256 * i] = ar[i];
+#pragma unroll
+    for (int i = 0; i < NLB; ++i) sm[buf][512 + tid + 256 * i] = br[i];
+  };
+  const int wn = w & 1, wm = w >> 1;
+  f32x4 acc[2][JB], tot[2][JB];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < JB; ++j) acc[i][j] = tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int NS = (K + 31) / 32;
+  issue(0);
+  stash(0);
+  __syncthreads();
+  for (int st = 0; st < NS; ++st) {
+    if (st + 1 < NS) issue((st + 1) * 32);
+    const f32x4 *sa = sm[st & 1] + (wn * 2) * 128 + lane, *sb = sm[st & 1] + 512 + (wm * JB) * 128 + lane;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      f32x4 fa[2], fb[JB];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) fa[i] = sa[i * 128 + ks * 64];
+#pragma unroll
+      for (int j = 0; j < JB; ++j) fb[j] = sb[j * 128 + ks * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < JB; ++j) acc[i][j] = mfma_f32(fa[i][e], fb[j][e], acc[i][j]);
+    }
+    if ((st & (FLUSH - 1)) == FLUSH - 1 || st + 1 == NS) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < JB; ++j) {
+          tot[i][j] += acc[i][j];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    if (st + 1 < NS) stash((st + 1) & 1);
+    __syncthreads();
+  }
+  constexpr int STEP = EPI == EPI_SWIGLU ? 2 : 1;
+#pragma unroll
+  for (int i = 0; i < 2; i += STEP) {
+    const int nb = EPI == EPI_SWIGLU ? nb_t + wn : nb_t + wn * 2 + i;
+    if (nb >= a.NB) continue;
+#pragma unroll
+    for (int j = 0; j < JB; ++j) {
+      const int row = row_t + (wm * JB + j) * 16 + m;
+      const bool row_ok = row < a.rows;
+      const EpiPre pre = f32_epi_prefetch<EPI>(a, nb, g, row, row_ok);
+      f32_epi<EPI>(a, tot[i][j], tot[i + STEP - 1][j], nb, g, m, row, row_ok, 1.f, pre);
+    }
+  }
+}
+
+template <int EPI>
+static void launch_f32_dense_cfg(const F32Args &a, hipStream_t s) {
+  // rounds of one tile per compute unit, times the rows of a tile: the narrower tile pads less and divides the
+  // work more evenly, the wider one reads the weights through LDS half as often (taken when they tie)
+  const int per_t = EPI == EPI_SWIGLU ? 2 : 4, NT = (a.NB + per_t - 1) / per_t;
+  const long t64 = (long)NT * ((a.rows + 63) / 64), t32 = (long)NT * ((a.rows + 31) / 32);
+  const long c64 = (t64 + 255) / 256 * 64, c32 = (t32 + 255) / 256 * 32;
+  if (c32 < c64) gemm_f32_dense_kernel<EPI, 32><<<(t32 + 7) / 8 * 8, 256, 0, s>>>(a);
+  else gemm_f32_dense_kernel<EPI, 64><<<(t64 + 7) / 8 * 8, 256, 0, s>>>(a);
+}
+
+void launch_gemm_f32_dense(const GemmLaunch &L, hipStream_t s) {
+  const F32Args a = f32_args(L);
+  if (L.epi == EPI_QKV) launch_f32_dense_cfg<EPI_QKV>(a, s);
+  else if (L.epi == EPI_SWIGLU) launch_f32_dense_cfg<EPI_SWIGLU>(a, s);
+  else if (L.epi == EPI_RESID) launch_f32_dense_cfg<EPI_RESID>(a, s);
+  else launch_f32_dense_cfg<EPI_STORE>(a, s);
+}
+
+// ------------------------------------------------------------------ attention, 1..16 rows
+// One workgroup = one KV head x 64 keys fixed by absolute slot, 16 keys per wave; the query rows that share
+// the KV head go in tiles of 16.  K operand: lane (key m, g) reads d-octets 4c+g of its key, as cached.  V
+// operand: lane (m, g) reads head-dim elements m*VT.. of keys 4g..4g+3, the keys whose probabilities it
+// holds: all loads are 128 bits wide and issued up front, no shuffles in between.
+constexpr int kF32AttnKeys = 64;
+
+template <int HD, bool GATED>
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
+                                                       const float *Kc, const float *Vc, float *part, float scale_log2e,
+                                                       const int32_t *gate) {
+  constexpr int C = HD / 32, VT = HD / 16;
+  __shared__ float red[4][16][HD];
+  __shared__ float wm[4][16], wl[4][16];
+  if constexpr (GATED) AE_GATE(gate);
+  const int kh = blockIdx.x, chunk = blockIdx.y, n_chunks = gridDim.y;
+  const int G = H / Hkv, R = rows * G, MT = (R + 15) / 16;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
+  const int kbase = chunk * kF32AttnKeys + w * 16;
+  const bool active = kbase < pos0 + rows;   // does this wave own any visible key?
+
+  f32x4 kreg[C][2], vreg[4][VT / 4];
+  if (active) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const float *kp = Kc + (((size_t)kh * (HD / 8) + 4 * c + g) * n_ctx + kbase + m) * 8;
+      kreg[c][0] = *reinterpret_cast<const f32x4 *>(kp);
+      kreg[c][1] = *reinterpret_cast<const f32x4 *>(kp + 4);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float *vp = Vc + ((size_t)kh * n_ctx + kbase + 4 * g + j) * HD + m * VT;
+#pragma unroll
+      for (int i = 0; i < VT / 4; ++i) vreg[j][i] = *reinterpret_cast<const f32x4 *>(vp + 4 * i);
+    }
+  }
+  for (int mt = 0; mt < MT; ++mt) {
+    const int r = mt * 16 + m, rc = r < R ? r : R - 1;
+    float mx = -INFINITY, lsum = 0.f;
+    f32x4 O[VT];
+#pragma unroll
+    for (int dt = 0; dt < VT; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (active) {
+      const float *qp = q + ((size_t)(rc / G) * H + kh * G + rc % G) * HD + g * 8;
+      f32x4 qv[C][2];
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        qv[c][0] = *reinterpret_cast<const f32x4 *>(qp + c * 32);
+        qv[c][1] = *reinterpret_cast<const f32x4 *>(qp + c * 32 + 4);
+      }
+      f32x4 S0 = f32x4{0.f, 0.f, 0.f, 0.f}, S1 = S0;
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          S0 = mfma_f32(kreg[c][0][e], qv[c][0][e], S0);
+          S1 = mfma_f32(kreg[c][1][e], qv[c][1][e], S1);
+        }
+      // causal mask: query row r / G sees slots <= pos0 + r / G
+      const int limit = r < R ? pos0 + r / G : -1;
+      float p[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        p[e] = kbase + 4 * g + e <= limit ? (S0[e] + S1[e]) * scale_log2e : -INFINITY;
+        mx = fmaxf(mx, p[e]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        p[e] = mx > -INFINITY ? __builtin_amdgcn_exp2f(p[e] - mx) : 0.f;
+        lsum += p[e];
+      }
+      lsum += __shfl_xor(lsum, 16, 64);
+      lsum += __shfl_xor(lsum, 32, 64);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int dt = 0; dt < VT; ++dt) O[dt] = mfma_f32(vreg[j][dt >> 2][dt & 3], p[j], O[dt]);
+    }
+    // O[dt][i] is head-dim element (4g + i) * VT + dt of row m
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < VT / 4; ++t)
+        *reinterpret_cast<f32x4 *>(&red[w][m][(4 * g + i) * VT + 4 * t]) =
+            f32x4{O[4 * t][i], O[4 * t + 1][i], O[4 * t + 2][i], O[4 * t + 3][i]};
+    if (g == 0) { wm[w][m] = mx; wl[w][m] = lsum; }
+    __syncthreads();
+    {   // combine the four waves in a fixed order
+      const int m2 = tid >> 4, seg = tid & 15, r2 = mt * 16 + m2;
+      if (r2 < R) {
+        const float ms = fmaxf(fmaxf(wm[0][m2], wm[1][m2]), fmaxf(wm[2][m2], wm[3][m2]));
+        float wgt[4], l = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww) {
+          wgt[ww] = wm[ww][m2] > -INFINITY ? __builtin_amdgcn_exp2f(wm[ww][m2] - ms) : 0.f;
+          l = fmaf(wgt[ww], wl[ww][m2], l);
+        }
+        float *dst = part + (((size_t)kh * n_chunks + chunk) * R + r2) * (HD + 2);
+#pragma unroll
+        for (int i = 0; i < HD / 16; ++i) {
+          float o = 0.f;
+#pragma unroll
+          for (int ww = 0; ww < 4; ++ww) o = fmaf(wgt[ww], red[ww][m2][seg * (HD / 16) + i], o);
+          dst[seg * (HD / 16) + i] = o;
+        }
+        if (seg == 0) { dst[HD] = ms; dst[HD + 1] = l; }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+template <int HD, bool GATED>
+static void launch_attention_f32_cfg(const float *q, int rows, int pos0, const ae_config &c, const float *Kc, const float *Vc,
+                                     float *part, float *out, hipStream_t s, const int32_t *gate) {
+  const int n_chunks = (pos0 + rows + kF32AttnKeys - 1) / kF32AttnKeys;
+  attn_f32_kernel<HD, GATED><<<dim3(c.n_kv_heads, n_chunks), 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc,
+                                                                          Vc, part, 1.4426950408889634f / sqrtf((float)HD), gate);
+  launch_attention_merge(part, rows, n_chunks, c, out, true, s, gate);
+}
+
+void launch_attention_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
+                          float *part, float *out, hipStream_t s, const int32_t *gate) {
+  const float *Kc = (const float *)kv_layer, *Vc = (const float *)((const char *)kv_layer + v_off);
+  if (c.head_dim == 128) {
+    if (gate) launch_attention_f32_cfg<128, true>(q, rows, pos0, c, Kc, Vc, part, out, s, gate);
+    else launch_attention_f32_cfg<128, false>(q, rows, pos0, c, Kc, Vc, part, out, s, gate);
+  } else {
+    if (gate) launch_attention_f32_cfg<64, true>(q, rows, pos0, c, Kc, Vc, part, out, s, gate);
+    else launch_attention_f32_cfg<64, false>(q, rows, pos0, c, Kc, Vc, part, out, s, gate);
+  }
+}
+
+int attn_f32_chunk_keys() { return kF32AttnKeys; }
+
+// ------------------------------------------------------------------ causal attention of a prompt chunk
+// A wave owns 16 (row, query head of the KV head's group) pairs and walks the visible keys 16 at a time with an
+// online softmax (operand mapping of attn_f32_kernel).  Every 256 keys the running output joins a second
+// accumulator.  Late (long) tiles are scheduled first; every wave is independent.
+template <int HD>
+__global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
+                                                               const float *Kc, const float *Vc, float *out, float scale_log2e) {
+  constexpr int C = HD / 32, VT = HD / 16;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, m = lane & 15;
+  const int kh = blockIdx.x, G = H / Hkv, R = rows * G;
+  const int r0 = (((int)gridDim.y - 1 - (int)blockIdx.y) * 4 + w) * 16;
+  if (r0 >= R) return;   // wave-uniform
+  const bool rok = r0 + m < R;
+  const int r = rok ? r0 + m : R - 1, row = r / G, head = kh * G + r % G, limit = pos0 + row;
+  const int last_key = pos0 + min(r0 + 15, R - 1) / G;   // last slot any row of the wave sees
+  f32x4 qv[C][2], kreg[C][2], vreg[4][VT / 4];
+  const float *qp = q + ((size_t)row * H + head) * HD + g * 8;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    qv[c][0] = *reinterpret_cast<const f32x4 *>(qp + c * 32);
+    qv[c][1] = *reinterpret_cast<const f32x4 *>(qp + c * 32 + 4);
+  }
+  auto load_k = [&](int kb) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const float *kp = Kc + (((size_t)kh * (HD / 8) + 4 * c + g) * n_ctx + kb + m) * 8;
+      kreg[c][0] = *reinterpret_cast<const f32x4 *>(kp);
+      kreg[c][1] = *reinterpret_cast<const f32x4 *>(kp + 4);
+    }
+  };
+  auto load_v = [&](int kb) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float *vp = Vc + ((size_t)kh * n_ctx + kb + 4 * g + j) * HD + m * VT;
+#pragma unroll
+      for (int i = 0; i < VT / 4; ++i) vreg[j][i] = *reinterpret_cast<const f32x4 *>(vp + 4 * i);
+    }
+  };
+  float mx = -INFINITY, lsum = 0.f, ltot = 0.f;
+  f32x4 O[VT], T[VT];
+#pragma unroll
+  for (int dt = 0; dt < VT; ++dt) O[dt] = T[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  load_k(0);
+  load_v(0);
+  const int last_kb = last_key & ~15;
+  for (int kb = 0; kb <= last_key; kb += 16) {
+    const int kb_next = min(kb + 16, last_kb);   // the last step re-requests its own tiles (ignored)
+    f32x4 S0 = f32x4{0.f, 0.f, 0.f, 0.f}, S1 = S0;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        S0 = mfma_f32(kreg[c][0][e], qv[c][0][e], S0);
+        S1 = mfma_f32(kreg[c][1][e], qv[c][1][e], S1);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    load_k(kb_next);
+    __builtin_amdgcn_sched_barrier(0);
+    float p[4], bmax = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[e] = kb + 4 * g + e <= limit ? (S0[e] + S1[e]) * scale_log2e : -INFINITY;
+      bmax = fmaxf(bmax, p[e]);
+    }
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+    const float mnew = fmaxf(mx, bmax);   // finite from the first block on: slot 0 is visible to every row
+    const float alpha = __builtin_amdgcn_exp2f(mx - mnew);
+    float bsum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[e] = __builtin_amdgcn_exp2f(p[e] - mnew);
+      bsum += p[e];
+    }
+    lsum = lsum * alpha + bsum;   // this lane's share: the four lane groups are added at the end
+    ltot *= alpha;
+    mx = mnew;
+#pragma unroll
+    for (int dt = 0; dt < VT; ++dt) {
+      O[dt] *= alpha;
+      T[dt] *= alpha;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int dt = 0; dt < VT; ++dt) O[dt] = mfma_f32(vreg[j][dt >> 2][dt & 3], p[j], O[dt]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(kb_next);
+    __builtin_amdgcn_sched_barrier(0);
+    if ((kb & 255) == 240) {
+#pragma unroll
+      for (int dt = 0; dt < VT; ++dt) {
+        T[dt] += O[dt];
+        O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      ltot += lsum;
+      lsum = 0.f;
+    }
+  }
+  ltot += lsum;
+  ltot += __shfl_xor(ltot, 16, 64);
+  ltot += __shfl_xor(ltot, 32, 64);
+  if (rok) {
+    float *op = out + ((size_t)row * H + head) * HD;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < VT / 4; ++t) {
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (T[4 * t + e][i] + O[4 * t + e][i]) / ltot;
+        *reinterpret_cast<f32x4 *>(op + (4 * g + i) * VT + 4 * t) = o;
+      }
+  }
+}
+
+void launch_attention_prefill_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
+                                  float *out, hipStream_t s) {
+  const int G = c.n_heads / c.n_kv_heads, R = rows * G, HD = c.head_dim;
+  const dim3 grid(c.n_kv_heads, (R + 63) / 64);
+  const float scale = 1.4426950408889634f / sqrtf((float)HD);
+  const float *Kc = (const float *)kv_layer, *Vc = (const float *)((const char *)kv_layer + v_off);
+  if (HD == 128)
+    attn_prefill_f32_kernel<128><<<grid, 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, out, scale);
+  else
+    attn_prefill_f32_kernel<64><<<grid, 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, out, scale);
+}
+
+// ------------------------------------------------------------------ row producers
+// Embedding rows -> residual stream, x * gain and the row's sum of x^2 (gain == nullptr: the rows alone)
+__global__ __launch_bounds__(256) void embed_f32_kernel(const float *emb, const int32_t *ids, int d, const float *gain, float *x,
+                                                        float *Xo, float *ssq) {
+  __shared__ float red[4];
+  const int r = blockIdx.x;
+  const float *src = emb + (size_t)ids[r] * d;
+  float ss = 0.f;
+  for (int k = threadIdx.x * 4; k < d; k += 1024) {
+    const float4 v = *reinterpret_cast<const float4 *>(src + k);
+    *reinterpret_cast<float4 *>(x + (size_t)r * d + k) = v;
+    if (gain) {
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+      const float4 gn = *reinterpret_cast<const float4 *>(gain + k);
+      *reinterpret_cast<float4 *>(Xo + (size_t)r * d + k) = make_float4(v.x * gn.x, v.y * gn.y, v.z * gn.z, v.w * gn.w);
+    }
+  }
+  if (!gain) return;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  if (threadIdx.x == 0) ssq[r] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+void launch_embed_f32(const void *emb, const int32_t *ids_dev, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
+                      hipStream_t s) {
+  embed_f32_kernel<<<rows, 256, 0, s>>>((const float *)emb, ids_dev, d, gain, x, (float *)Xo, ssq);
+}
+
+// cat[r] = [feature row r ; embedding of the token that FOLLOWS slot r]  (Sec. 2.2)
+__global__ __launch_bounds__(256) void draft_cat_f32_kernel(const float *feat, int feat_ld, const float *emb,
+                                                            const int32_t *next_ids, int d, float *cat, const int32_t *gate) {
+  AE_GATE(gate);
+  const int r = blockIdx.x;
+  const float *e = emb + (size_t)next_ids[r] * d, *f = feat + (size_t)r * feat_ld;
+  float *o = cat + (size_t)r * 2 * d;
+  for (int k = threadIdx.x * 4; k < d; k += 1024) {
+    *reinterpret_cast<float4 *>(o + k) = *reinterpret_cast<const float4 *>(f + k);
+    *reinterpret_cast<float4 *>(o + d + k) = *reinterpret_cast<const float4 *>(e + k);
+  }
+}
+
+void launch_draft_cat_f32(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d, void *cat,
+                          hipStream_t s, const int32_t *gate) {
+  draft_cat_f32_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const float *)emb, next_ids, d, (float *)cat, gate);
+}
+
+}  // namespace ae

@@ -1,6 +1,5 @@
-// Dtype-generic kernels of the decode step (gfx950, wave64).  They serve the fp32
-// configuration and every small op of the bf16 configuration; the bandwidth-critical
-// bf16 GEMMs have their own MFMA kernels in kernels_mfma.hip.
+// Small kernels of the decode step shared by the bf16 and the float32 configuration (gfx950,
+// wave64): RMSNorm, step inputs, greedy acceptance, LDLP, set-up.
 #include "ae_internal.h"
 
 namespace ae {
@@ -37,21 +36,6 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x)); }
 
-// ------------------------------------------------------------------ embedding
-template <typename T>
-__global__ void embed_kernel(const T *emb, const int32_t *ids, int d, float *out) {
-  const int r = blockIdx.x;
-  const T *src = emb + (size_t)ids[r] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) out[(size_t)r * d + i] = ld1(src + i);
-}
-
-void launch_embed(const void *emb, int dtype, const int32_t *ids_dev, int rows, int d, float *out, hipStream_t s) {
-  if (dtype == AE_BF16)
-    embed_kernel<bf16_t><<<rows, 256, 0, s>>>((const bf16_t *)emb, ids_dev, d, out);
-  else
-    embed_kernel<float><<<rows, 256, 0, s>>>((const float *)emb, ids_dev, d, out);
-}
-
 // ------------------------------------------------------------------ RMSNorm
 // out = (x / sqrt(mean(x^2) + eps)) * g, one workgroup per row
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *x, const float *g, int d, float eps, float *out,
@@ -81,189 +65,7 @@ void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, 
   rmsnorm_kernel<<<rows, 256, 0, s>>>(x, g, d, eps, out, gate);
 }
 
-// ------------------------------------------------------------------ generic skinny GEMM
-// One wave per output column n, all rows at once; lanes stride over K in 8-element
-// pieces.  The per-output summation order does not depend on the number of rows.
-template <typename WT, int MT>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(const WT *W, int N, int K, const float *X, int ldx, int rows,
-                                                           const float *bias, float *Y, int ldy, int accumulate,
-                                                           const int32_t *gate) {
-  AE_GATE(gate);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + wave;
-  if (n >= N) return;
-  float acc[MT];
-#pragma unroll
-  for (int m = 0; m < MT; ++m) acc[m] = 0.f;
-  const WT *wrow = W + (size_t)n * K;
-  for (int k0 = lane * 8; k0 < K; k0 += 512) {
-    float w[8];
-    ld8(wrow + k0, w);
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      if (m < rows) {
-        float xv[8];
-        ld8(X + (size_t)m * ldx + k0, xv);
-        float a = acc[m];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a = fmaf(xv[j], w[j], a);
-        acc[m] = a;
-      }
-    }
-  }
-#pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    if (m < rows) {
-      float v = wave_sum(acc[m]);
-      if (lane == 0) {
-        if (bias) v += bias[n];
-        float *y = Y + (size_t)m * ldy + n;
-        *y = accumulate ? *y + v : v;
-      }
-    }
-  }
-}
-
-template <typename WT>
-static void gemm_generic_dispatch(const WT *W, int N, int K, const float *X, int ldx, int rows, const float *bias,
-                                  float *Y, int ldy, int acc, hipStream_t s, const int32_t *gate) {
-  const dim3 grid((N + 3) / 4);
-  if (rows <= 1)
-    gemm_generic_kernel<WT, 1><<<grid, 256, 0, s>>>(W, N, K, X, ldx, rows, bias, Y, ldy, acc, gate);
-  else if (rows <= 4)
-    gemm_generic_kernel<WT, 4><<<grid, 256, 0, s>>>(W, N, K, X, ldx, rows, bias, Y, ldy, acc, gate);
-  else
-    gemm_generic_kernel<WT, 16><<<grid, 256, 0, s>>>(W, N, K, X, ldx, rows, bias, Y, ldy, acc, gate);
-}
-
-void launch_gemm_generic(const void *W, int dtype, int N, int K, const float *X, int ldx, int rows,
-                         const float *bias, float *Y, int ldy, int accumulate, hipStream_t s, const int32_t *gate) {
-  if (dtype == AE_BF16)
-    gemm_generic_dispatch<bf16_t>((const bf16_t *)W, N, K, X, ldx, rows, bias, Y, ldy, accumulate, s, gate);
-  else
-    gemm_generic_dispatch<float>((const float *)W, N, K, X, ldx, rows, bias, Y, ldy, accumulate, s, gate);
-}
-
-// ------------------------------------------------------------------ SwiGLU elementwise
-__global__ void silu_mul_kernel(const float *gate_proj, const float *up, size_t n, float *out, const int32_t *gate) {
-  AE_GATE(gate);
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    out[i] = silu_f(gate_proj[i]) * up[i];
-}
-
-void launch_silu_mul(const float *gate_proj, const float *up, int rows, int f, float *out, hipStream_t s,
-                     const int32_t *gate) {
-  const size_t n = (size_t)rows * f;
-  const int blocks = (int)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-  silu_mul_kernel<<<blocks, 256, 0, s>>>(gate_proj, up, n, out, gate);
-}
-
-// ------------------------------------------------------------------ argmax (lowest id wins ties)
-__global__ __launch_bounds__(1024) void argmax_kernel(const float *logits, int V, int32_t *out, const int32_t *gate) {
-  __shared__ float bv[16];
-  __shared__ int bi[16];
-  AE_GATE(gate);
-  const float *x = logits + (size_t)blockIdx.x * V;
-  float best = -INFINITY;
-  int idx = 0x7fffffff;
-  for (int i = threadIdx.x; i < V; i += 1024) {
-    const float v = x[i];
-    if (v > best) { best = v; idx = i; }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(best, o, 64);
-    const int oi = __shfl_xor(idx, o, 64);
-    if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-  }
-  if ((threadIdx.x & 63) == 0) { bv[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = idx; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w)
-      if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
-    out[blockIdx.x] = idx == 0x7fffffff ? 0 : idx;
-  }
-}
-
-void launch_argmax(const float *logits, int rows, int V, int32_t *out_ids, hipStream_t s, const int32_t *gate) {
-  argmax_kernel<<<rows, 1024, 0, s>>>(logits, V, out_ids, gate);
-}
-
-// ------------------------------------------------------------------ draft head input
-// cat[r] = [feature row r ; embedding of the token that FOLLOWS slot r]  (Sec. 2.2)
-template <typename T>
-__global__ void draft_cat_kernel(const float *feat, int feat_ld, const T *emb, const int32_t *next_ids, int d,
-                                 float *cat, const int32_t *gate) {
-  AE_GATE(gate);
-  const int r = blockIdx.x;
-  const T *e = emb + (size_t)next_ids[r] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    cat[(size_t)r * 2 * d + i] = feat[(size_t)r * feat_ld + i];
-    cat[(size_t)r * 2 * d + d + i] = ld1(e + i);
-  }
-}
-
-void launch_draft_cat(const float *feat, int feat_ld, const void *emb, int dtype, const int32_t *next_ids, int rows,
-                      int d, float *cat, hipStream_t s, const int32_t *gate) {
-  if (dtype == AE_BF16)
-    draft_cat_kernel<bf16_t><<<rows, 256, 0, s>>>(feat, feat_ld, (const bf16_t *)emb, next_ids, d, cat, gate);
-  else
-    draft_cat_kernel<float><<<rows, 256, 0, s>>>(feat, feat_ld, (const float *)emb, next_ids, d, cat, gate);
-}
-
 // ------------------------------------------------------------------ tiny control kernels
-__global__ void pick_draft_kernel(DevState *st, int i, const int32_t *gate) {
-  AE_GATE(gate);
-  int32_t t = st->argmax[0];
-  if (st->override_ids[i] >= 0) t = st->override_ids[i];
-  st->draft_ids[i] = t;
-}
-void launch_pick_draft(DevState *st, int i, hipStream_t s, const int32_t *gate) {
-  pick_draft_kernel<<<1, 1, 0, s>>>(st, i, gate);
-}
-
-// AdaEAGLE-DDD bookkeeping behind draft token i (Sec. 3.4, 4.2): its log-probability under
-// softmax(logits / T) joins the running sum, the drafted length becomes i + 1, and the exit
-// rule for the next token is evaluated on the device: past the predicted length k the chain
-// goes on only while the sequence log-probability is at least theta (draft_live gates the
-// kernels of the tokens that follow).  One workgroup, fixed-shape reductions.
-__global__ __launch_bounds__(1024) void draft_logprob_kernel(const float *logits, int V, float inv_T, DevState *st, int i,
-                                                             int k, float theta, const int32_t *gate) {
-  __shared__ float sh[1024];
-  AE_GATE(gate);
-  const int t = threadIdx.x;
-  float mx = -INFINITY;
-  for (int x = t; x < V; x += 1024) mx = fmaxf(mx, logits[x]);
-  sh[t] = mx;
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (t < o) sh[t] = fmaxf(sh[t], sh[t + o]);
-    __syncthreads();
-  }
-  mx = sh[0];
-  __syncthreads();
-  float se = 0.f;
-  for (int x = t; x < V; x += 1024) se += expf((logits[x] - mx) * inv_T);
-  sh[t] = se;
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (t < o) sh[t] += sh[t + o];
-    __syncthreads();
-  }
-  if (t == 0) {
-    const float lp = (logits[st->draft_ids[i]] - mx) * inv_T - logf(sh[0]);
-    const float cum = (i == 0 ? 0.f : st->cum_logp) + lp;
-    st->draft_lp[i] = lp;
-    st->cum_logp = cum;
-    st->draft_len = i + 1;
-    if (i + 1 >= k && !(cum >= theta)) st->draft_live = 0;
-  }
-}
-void launch_draft_logprob(const float *logits, int V, float T, DevState *st, int i, int k, float theta, hipStream_t s,
-                          const int32_t *gate) {
-  draft_logprob_kernel<<<1, 1024, 0, s>>>(logits, V, T > 0.f ? 1.0f / T : 1.0f, st, i, k, theta, gate);
-}
-
 // Small host values reach the device state as kernel arguments: the launch carries them, so no
 // staging buffer has to outlive the call and no copy engine is involved.
 struct HostIds { int32_t v[kMaxRows]; };

@@ -263,13 +263,21 @@ void launch_gemm_mfma(const GemmLaunch &L, hipStream_t s) {
   }
 }
 
-// Embedding of token t -> packed row `row`, k = k_off .. k_off + d - 1 (the second half of the
-// draft head's input [feature ; embedding of the next token]); all threads of the workgroup.
-__device__ __forceinline__ void pack_embedding(const uint16_t *emb, int32_t t, int d, u32x4 *Xp, int row, int k_off) {
-  const uint16_t *e = emb + (size_t)t * d;
+// Embedding of token t -> row cat.row, k = d .. 2d - 1 (the second half of the draft head's input
+// [feature ; embedding of the next token]); all threads of the workgroup.
+__device__ __forceinline__ void write_embedding(const DraftCat &cat, int32_t t) {
+  const int d = cat.d;
+  if (cat.f32) {
+    const float *e = (const float *)cat.emb + (size_t)t * d;
+    float *o = (float *)cat.Xp + (size_t)cat.row * 2 * d + d;
+    for (int k0 = threadIdx.x * 4; k0 < d; k0 += blockDim.x * 4)
+      *reinterpret_cast<float4 *>(o + k0) = *reinterpret_cast<const float4 *>(e + k0);
+    return;
+  }
+  const uint16_t *e = (const uint16_t *)cat.emb + (size_t)t * d;
   for (int k0 = threadIdx.x * 4; k0 < d; k0 += blockDim.x * 4) {
     const uint2 raw = *reinterpret_cast<const uint2 *>(e + k0);
-    packed_store4(Xp, row, k_off + k0, __uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
+    packed_store4((u32x4 *)cat.Xp, cat.row, d + k0, __uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
                   __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xffff0000u));
   }
 }
@@ -353,7 +361,7 @@ __global__ __launch_bounds__(256) void argmax_finish_kernel(const float *val, co
   }
   if (pick_i >= 0 && (cat.Xp || ddd.lse_sum)) {
     __syncthreads();
-    if (cat.Xp) pack_embedding((const uint16_t *)cat.emb, tok_s, cat.d, (u32x4 *)cat.Xp, cat.row, cat.d);
+    if (cat.Xp) write_embedding(cat, tok_s);
     if (ddd.lse_sum) ddd_finish(ddd, tok_s, pick_i, st);
   }
 }
@@ -371,7 +379,7 @@ __global__ __launch_bounds__(256) void pick_draft_packed_kernel(DevState *st, in
   int32_t t = st->argmax[0];
   if (st->override_ids[i] >= 0) t = st->override_ids[i];
   if (threadIdx.x == 0) st->draft_ids[i] = t;
-  pack_embedding((const uint16_t *)cat.emb, t, cat.d, (u32x4 *)cat.Xp, cat.row, cat.d);
+  write_embedding(cat, t);
   if (ddd.lse_sum) ddd_finish(ddd, t, i, st);
 }
 
