@@ -15,8 +15,10 @@ COMMON = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc")]
 # Per-source additions.  The dense prompt GEMM keeps 128 accumulator registers per lane; with
 # the MFMA results allocated in ordinary VGPRs the compiler needs no accumulator-file copies
-# in its loop and the kernel fits 2 waves per SIMD.
-EXTRA = {"kernels_dense.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# in its loop and the kernel fits 2 waves per SIMD.  The float32 kernels add their accumulators to a
+# second set every few stages: the same copies.
+EXTRA = {"kernels_dense.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "kernels_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def sources():

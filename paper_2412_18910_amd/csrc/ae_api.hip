@@ -276,10 +276,12 @@ int ensure_dense(ae_ctx *c, int n) {
   c->dense_cap = 0;
   const size_t cap = want, d = g.d_model, dq = (size_t)g.n_heads * g.head_dim, f = g.d_ffn;
   const size_t dmax = dq > d ? dq : d;
+  const size_t part_rows = cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048;   // up to 8 pieces of K for short prompts
+  c->ppart_floats = part_rows * d;
   struct Buf { void **p; size_t bytes; };
   const std::vector<Buf> bufs = !c->fast ? std::vector<Buf>{
       {(void **)&c->px, cap * d * 4}, {(void **)&c->pq, cap * dq * 4}, {&c->pxa, cap * d * 4}, {&c->pxatt, cap * dmax * 4},
-      {&c->pxh, cap * f * 4}, {&c->pxcat, cap * 2 * d * 4}} : std::vector<Buf>{
+      {&c->pxh, cap * f * 4}, {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, part_rows * d * 4}} : std::vector<Buf>{
       {(void **)&c->px, cap * d * 4},      {(void **)&c->pq, cap * dq * 4},   {(void **)&c->prinv, cap * 4},
       {(void **)&c->pssq_a, cap * d * 4 / 16 * 1 + cap * 4}, {(void **)&c->pssq_f, cap * d * 4 / 16 + cap * 4},
       {&c->pxa, cap * d * 4},              {&c->pxf, cap * d * 4},            {&c->pxatt, cap * dq * 4},
@@ -353,48 +355,49 @@ void dense_chunk(ae_ctx *c, int p0, int rows, int drows) {
   }
 }
 
-// The same in float32: wide GEMMs over rows, RMSNorm in kernels of its own.
+// The same in float32: wide GEMMs over rows; the sum kernel behind the o, down and fc projections normalises
+// the rows for the next one.
 void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
   const int d = g.d_model, dq = g.n_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn;
   float *xn = (float *)c->pxa, *att = (float *)c->pxatt;
   launch_embed_f32(c->tok_emb, c->hist + p0, rows, d, nullptr, c->px, nullptr, nullptr, s);
-  auto qkv_pass = [&](int li, const float *x, int nrows, bool with_q) {   // RMSNorm, projections, rotary, append
-    const LayerW &w = c->layers[li];
-    launch_rmsnorm(x, w.attn_norm, nrows, d, g.rms_eps, xn, s);
+  launch_rmsnorm(c->px, c->layers[0].attn_norm, rows, d, g.rms_eps, xn, s);
+  auto qkv_pass = [&](int li, int nrows, bool with_q) {   // projections, rotary embedding, cache append
     GemmLaunch qkv;
-    qkv.W = &w.f_qkv; qkv.Xp = xn; qkv.ldx = d; qkv.rows = nrows; qkv.epi = EPI_QKV;
+    qkv.W = &c->layers[li].f_qkv; qkv.Xp = xn; qkv.ldx = d; qkv.rows = nrows; qkv.epi = EPI_QKV;
     qkv.Y[0] = c->pq; qkv.ldy[0] = dq;
     qkv.seg_N[0] = with_q ? dq : 0; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
     qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
     qkv.pos0 = p0; qkv.n_ctx = kv_capacity(g); qkv.hd = g.head_dim;
     launch_gemm_f32_dense(qkv, s);
   };
+  auto project = [&](const Mat *W, const void *X, int ldx, int nrows, const float *bias, float *x, const float *gain) {
+    GemmLaunch L;
+    L.W = W; L.Xp = X; L.ldx = ldx; L.rows = nrows; L.bias = bias; L.eps = g.rms_eps;
+    launch_gemm_f32_resid_norm(L, c->ppart, c->ppart_floats, x, gain, xn, s);
+  };
   for (int l = 0; l < g.n_layers; ++l) {
     const LayerW &w = c->layers[l];
-    qkv_pass(l, c->px, rows, true);
+    qkv_pass(l, rows, true);
     launch_attention_prefill_f32(c->pq, rows, p0, g, kv_layer_ptr(c, l), c->kv_v_offset, att, s);
-    GemmLaunch o;
-    o.W = &w.wo; o.Xp = att; o.ldx = dq; o.rows = rows; o.epi = EPI_RESID; o.Y[0] = c->px; o.ldy[0] = d;
-    launch_gemm_f32_dense(o, s);
-    launch_rmsnorm(c->px, w.ffn_norm, rows, d, g.rms_eps, xn, s);
+    project(&w.wo, att, dq, rows, nullptr, c->px, w.ffn_norm);
     GemmLaunch gu;
     gu.W = &w.f_gu; gu.Xp = xn; gu.ldx = d; gu.rows = rows; gu.epi = EPI_SWIGLU; gu.Xp_out = c->pxh; gu.ldxo = f;
     launch_gemm_f32_dense(gu, s);
-    GemmLaunch dn;
-    dn.W = &w.w_down; dn.Xp = c->pxh; dn.ldx = f; dn.rows = rows; dn.epi = EPI_RESID; dn.Y[0] = c->px; dn.ldy[0] = d;
-    launch_gemm_f32_dense(dn, s);
+    project(&w.w_down, c->pxh, f, rows, nullptr, c->px, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : c->final_norm);
   }
   if (drows > 0) {
     // Eq. 2 catch-up of prompt slots: only the head's K/V rows are ever read again
-    launch_rmsnorm(c->px, c->final_norm, drows, d, g.rms_eps, xn, s);
     launch_draft_cat_f32(xn, d, c->tok_emb, c->hist + p0 + 1, drows, d, c->pxcat, s);
-    GemmLaunch fc;
-    fc.W = &c->draft_fc; fc.Xp = c->pxcat; fc.ldx = 2 * d; fc.rows = drows; fc.epi = EPI_STORE; fc.bias = c->draft_fc_b;
-    fc.Y[0] = att; fc.ldy[0] = d;
-    launch_gemm_f32_dense(fc, s);
-    qkv_pass(g.n_layers, att, drows, false);
+    if (c->draft_fc_b) {
+      project(&c->draft_fc, c->pxcat, 2 * d, drows, c->draft_fc_b, att, c->layers[g.n_layers].attn_norm);
+    } else {
+      launch_fill_zero(att, (size_t)drows * d * 4, s);
+      project(&c->draft_fc, c->pxcat, 2 * d, drows, nullptr, att, c->layers[g.n_layers].attn_norm);
+    }
+    qkv_pass(g.n_layers, drows, false);
   }
 }
 

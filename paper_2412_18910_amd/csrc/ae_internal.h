@@ -117,6 +117,8 @@ struct ae_ctx {
   std::vector<void *> dense_owned;
   float *px = nullptr, *pq = nullptr, *prinv = nullptr, *pssq_a = nullptr, *pssq_f = nullptr;
   void *pxa = nullptr, *pxf = nullptr, *pxatt = nullptr, *pxh = nullptr, *pxcat = nullptr;
+  float *ppart = nullptr;          // float32: partial sums of the GEMMs that split K
+  size_t ppart_floats = 0;
 
   // host-side state machine
   int kv_len = 0, dlen = 0, nF = 0;
@@ -273,7 +275,11 @@ void launch_attention_prefill(const float *q, int rows, int pos0, const ae_confi
 
 // ---- float32 models (kernels_f32.hip) ----
 void launch_gemm_f32(const GemmLaunch &L, hipStream_t s);         // 1..16 rows, all epilogues and fusions
-void launch_gemm_f32_dense(const GemmLaunch &L, hipStream_t s);   // any number of rows; Xp already normalised
+// prompt GEMMs, any number of rows, Xp already normalised: EPI_QKV and EPI_SWIGLU
+void launch_gemm_f32_dense(const GemmLaunch &L, hipStream_t s);
+// x = Xp . W^T + (L.bias, or x), xn = RMSNorm(x) * gain; part: room for max_part floats, at least rows * N
+void launch_gemm_f32_resid_norm(const GemmLaunch &L, float *part, size_t max_part, float *x, const float *gain, float *xn,
+                                hipStream_t s);
 void launch_attention_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
                           float *part, float *out, hipStream_t s, const int32_t *gate = nullptr);
 int attn_f32_chunk_keys();   // keys per split-KV workgroup

@@ -51,7 +51,9 @@ struct F32Args {
   float *Kc, *Vc;       // this layer's cache (layouts of kernels_attn.hip)
   int pos0, n_ctx, hd;
   const int32_t *gate;
+  int splits;           // EPI_PART: pieces of K, piece s -> Y + s * rows * N
 };
+enum { EPI_PART = 4 };  // prompt GEMM: raw partial sums over a piece of K
 
 // Weight row that lane m of row-block nb feeds, and its source.  The rows of every q and k head are
 // taken in rotary-pair order: tile j of a head holds rows 8j..8j+7 and their partners hd/2+8j.., so
@@ -103,7 +105,9 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
                                         float rinv, const EpiPre &pre) {
   const int n = nb * 16 + 4 * g;
   const bool ok = row_ok && n < a.N;
-  if (EPI == EPI_SWIGLU) {
+  if (EPI == EPI_PART) {
+    if (ok) *reinterpret_cast<f32x4 *>(a.Y + ((size_t)blockIdx.y * a.rows + row) * a.N + n) = s;
+  } else if (EPI == EPI_SWIGLU) {
     if (ok)
       *reinterpret_cast<float4 *>(a.Y + (size_t)row * a.ldy + n) =
           make_float4(silu_dev(s[0] * rinv) * (u[0] * rinv), silu_dev(s[1] * rinv) * (u[1] * rinv),
@@ -183,8 +187,13 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
 }
 
 // ------------------------------------------------------------------ decode GEMM (1..16 rows)
-// HBM-bound (each weight is read once).  A wave keeps 4 KB (gate/up: 8 KB) of weights in flight in a rolling ring.
-// TAIL: K is no multiple of 64; pieces behind the end are fed as zeros.
+// HBM-bound: each weight is read once.  A workgroup owns one block of 16 weight rows (gate/up: one of each) and all
+// of K, dealt to its waves in chunks of 64; a wave keeps a chunk (4 KB; gate/up: 8 KB) in flight in a rolling ring.
+// The rows of a row-major matrix lie a power of two apart, so workgroups that walk K in step ask the same few memory
+// channels: each starts at a chunk of its own (7B widths, microseconds: o / down 29.6 -> 25.7, draft fc 35.0 -> 24.0,
+// LM head 105 -> 96 = 5.5 TB/s; gate/up 76 -> 75 and QKV 42 -> 40 were spread by themselves).  Twice the depth, 4 or
+// 16 waves, and 4x4x1 products that read 256 bytes of a row per load were no faster.
+// TAIL: K is no multiple of 64; pieces behind the end count as zeros.
 template <int EPI, bool NORM, int NW, bool TAIL, bool GATED>
 __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
   constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1, D = 4;
@@ -207,20 +216,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
   for (int i = 0; i < NA; ++i)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[i][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int NC = (K + D * 16 - 1) / (D * 16), rot = (int)((unsigned)nb * 7u % (unsigned)NC);
+  auto at = [&](int c) { const int r = c + rot; return r < NC ? r : r - NC; };
   auto load = [&](int c, int j) {
-    const int k = c * (D * 16) + j * 16 + g * 4;
-    const bool in = !TAIL || k < K;
-    const int kk = in ? k : 0;
+    const int k = at(c) * (D * 16) + j * 16 + g * 4, kk = !TAIL || k < K ? k : 0;
     xb[j] = *reinterpret_cast<const f32x4 *>(xp + kk);
 #pragma unroll
     for (int i = 0; i < NA; ++i) wb[j][i] = *reinterpret_cast<const f32x4 *>(wp[i] + kk);
-    if (TAIL && !in) {
-      xb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < NA; ++i) wb[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
   };
-  const int NC = (K + D * 16 - 1) / (D * 16);
   if (w < NC) {
 #pragma unroll
     for (int j = 0; j < D; ++j) load(w, j);
@@ -253,6 +256,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
     const int cn = c + NW < NC ? c + NW : c;   // the last piece re-issues its own loads (ignored)
 #pragma unroll
     for (int j = 0; j < D; ++j) {
+      if (TAIL && at(c) + 1 == NC && at(c) * (D * 16) + j * 16 + g * 4 >= K) {
+        xb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < NA; ++i) wb[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -328,110 +336,123 @@ void launch_gemm_f32(const GemmLaunch &L, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ prompt GEMM
-// Workgroup tile: 64 weight rows (gate/up: 32 of each) x TM activation rows; 4 waves as 2 x 2.  Stages of
-// 32 k go global -> registers -> LDS (in lane order: conflict-free), one stage ahead; few registers, so
-// several workgroups share a compute unit and cover each other's barriers.
-template <int EPI, int TM>
+// Workgroup tile: 128 weight rows (gate/up: 64 of each) x 16*J activation rows; each of the 4 waves owns two
+// weight row-blocks and all J activation row-blocks.  Stages of 32 k go global -> registers -> LDS (in lane
+// order: conflict-free), two stages ahead.
+template <int EPI, int J>
 __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
-  constexpr int MB = TM / 16, JB = MB / 2;        // activation row-blocks per workgroup / per wave
-  constexpr int STAGE = (4 + MB) * 128, NLB = MB / 2;
-  constexpr int FLUSH = 4;                        // stages (of 32 k) per accumulation chain
+  constexpr int TM = 16 * J;
+  constexpr int STAGE = (8 + J) * 128, NLB = (J + 1) / 2;   // 16-byte pieces per LDS stage; B pieces per thread
+  constexpr int PD = 2;                                     // register sets: stages in flight
+  constexpr int UN = 4, FLUSH = 2;                          // stages per loop pass, per accumulation chain
   __shared__ f32x4 sm[2][STAGE];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
   // the activation tiles of one weight tile run side by side on one XCD (ids go round the 8 XCDs) and share it in its L2
-  const int NT = (a.NB + (EPI == EPI_SWIGLU ? 1 : 3)) / (EPI == EPI_SWIGLU ? 2 : 4), MT = (a.rows + TM - 1) / TM;
+  constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;            // output row-blocks per workgroup
+  const int NT = (a.NB + NBT - 1) / NBT, MT = (a.rows + TM - 1) / TM;
   const int per = (NT * MT + 7) >> 3, v = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
   if (((int)blockIdx.x >> 3) >= per || v >= NT * MT) return;
-  const int tn = v / MT, row_t = (v % MT) * TM, K = a.K;
-  const int nb_t = tn * (EPI == EPI_SWIGLU ? 2 : 4);
+  const int nb_t = v / MT * NBT, row_t = (v % MT) * TM;
+  // this workgroup's piece of K, in stages of 32
+  int NS = (a.K + 31) / 32, lo = 0;
+  if (EPI == EPI_PART) {
+    lo = NS * (int)blockIdx.y / a.splits;
+    NS = NS * ((int)blockIdx.y + 1) / a.splits - lo;
+  }
+  const int K = min(a.K, (lo + NS) * 32) - lo * 32;
 
-  // the two A pieces and NLB B pieces this thread stages: piece p = (row-block, k half, lane)
-  const float *ap[2], *bp[NLB];
-  int ko[2];
+  // the 4 A pieces and NLB B pieces this thread stages: piece p = (row-block, k half, lane)
+  const float *ap[4], *bp[NLB];
+  const int kt = ((tid >> 6) & 1) * 16 + ((tid & 63) >> 4) * 4;   // k inside the stage, the same for all of them
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int p = tid + 256 * i, rb = p >> 7, pl = p & 63;
-    ko[i] = ((p >> 6) & 1) * 16 + (pl >> 4) * 4;   // the same for the B pieces
-    if (EPI == EPI_SWIGLU) {   // row-blocks alternate gate, up
-      const int row = min((nb_t + (rb >> 1)) * 16 + (pl & 15), a.N - 1);
-      ap[i] = a.W[rb & 1] + (size_t)row * K;
-    } else {
-      ap[i] = f32_weight_row<EPI>(a, min(nb_t + rb, a.NB - 1), pl & 15);
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int rb = 2 * i + (tid >> 7);
+    if (EPI == EPI_SWIGLU)   // row-blocks alternate gate, up
+      ap[i] = a.W[rb & 1] + (size_t)min((nb_t + (rb >> 1)) * 16 + m, a.N - 1) * a.K + kt;
+    else
+      ap[i] = f32_weight_row<EPI>(a, min(nb_t + rb, a.NB - 1), m) + lo * 32 + kt;
   }
 #pragma unroll
-  for (int i = 0; i < NLB; ++i) {
-    const int p = tid + 256 * i;
-    bp[i] = a.X + (size_t)min(row_t + (p >> 7) * 16 + (p & 15), a.rows - 1) * a.ldx;
-  }
-  f32x4 ar[2], br[NLB];
-  auto issue = [&](int k0) {   // pieces behind the end of K are zeros
+  for (int i = 0; i < NLB; ++i)
+    bp[i] = a.X + (size_t)min(row_t + (2 * i + (tid >> 7)) * 16 + m, a.rows - 1) * a.ldx + lo * 32 + kt;
+  f32x4 areg[PD][4], breg[PD][NLB];
+  auto issue = [&](int k0, f32x4 (&ar)[4], f32x4 (&br)[NLB]) {
+    const int off = k0 + kt < K ? k0 : -kt;   // pieces behind the end of K re-read the row's start
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int k = k0 + ko[i];
-      ar[i] = *reinterpret_cast<const f32x4 *>(ap[i] + (k < K ? k : 0));
-      if (k >= K) ar[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 4; ++i) ar[i] = *reinterpret_cast<const f32x4 *>(ap[i] + off);
+#pragma unroll
+    for (int i = 0; i < NLB; ++i) br[i] = *reinterpret_cast<const f32x4 *>(bp[i] + off);
+  };
+  // (zeroing here and not at the load: a use of the loaded values there would wait for them)
+  auto stash = [&](int k0, int buf, f32x4 (&ar)[4], f32x4 (&br)[NLB]) {
+    if (k0 + 32 > K && k0 + kt >= K) {   // ... and count as zeros
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ar[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NLB; ++i) br[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
-    for (int i = 0; i < NLB; ++i) {
-      const int k = k0 + ko[i];
-      br[i] = *reinterpret_cast<const f32x4 *>(bp[i] + (k < K ? k : 0));
-      if (k >= K) br[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  auto stash = [&](int buf) {
+    for (int i = 0; i < 4; ++i) sm[buf][tid + 256 * i] = ar[i];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) sm[buf][tid + 256 * i] = ar[i];
-#pragma unroll
-    for (int i = 0; i < NLB; ++i) sm[buf][512 + tid + 256 * i] = br[i];
+    for (int i = 0; i < NLB; ++i)
+      if (J % 2 == 0 || i + 1 < NLB || tid < 128) sm[buf][1024 + tid + 256 * i] = br[i];
   };
-  const int wn = w & 1, wm = w >> 1;
-  f32x4 acc[2][JB], tot[2][JB];
+  f32x4 acc[2][J], tot[2][J];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < JB; ++j) acc[i][j] = tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int NS = (K + 31) / 32;
-  issue(0);
-  stash(0);
+    for (int j = 0; j < J; ++j) acc[i][j] = tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // stage st waits in LDS, stages st+1 .. st+PD are on their way in register sets (stage mod PD)
+#pragma unroll
+  for (int u = 0; u < PD; ++u) issue(u * 32, areg[u], breg[u]);
+  stash(0, 0, areg[0], breg[0]);
   __syncthreads();
-  for (int st = 0; st < NS; ++st) {
-    if (st + 1 < NS) issue((st + 1) * 32);
-    const f32x4 *sa = sm[st & 1] + (wn * 2) * 128 + lane, *sb = sm[st & 1] + 512 + (wm * JB) * 128 + lane;
+  for (int st0 = 0; st0 < NS; st0 += UN) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      f32x4 fa[2], fb[JB];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = sa[i * 128 + ks * 64];
-#pragma unroll
-      for (int j = 0; j < JB; ++j) fb[j] = sb[j * 128 + ks * 64];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
+    for (int u = 0; u < UN; ++u) {
+      const int st = st0 + u;
+      if (st >= NS) break;
+      issue((st + PD) * 32, areg[u % PD], breg[u % PD]);
+      __builtin_amdgcn_sched_barrier(0);
+      const f32x4 *sa = sm[u & 1] + w * 256 + lane, *sb = sm[u & 1] + 1024 + lane;
+      if (u % FLUSH == 0) {   // the chain before this one; its products ended behind the barrier
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < JB; ++j) acc[i][j] = mfma_f32(fa[i][e], fb[j][e], acc[i][j]);
-    }
-    if ((st & (FLUSH - 1)) == FLUSH - 1 || st + 1 == NS) {
+          for (int j = 0; j < J; ++j) tot[i][j] += acc[i][j];
+      }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int ks = 0; ks < 2; ++ks) {
+        f32x4 fa[2], fb[J];
 #pragma unroll
-        for (int j = 0; j < JB; ++j) {
-          tot[i][j] += acc[i][j];
-          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int i = 0; i < 2; ++i) fa[i] = sa[i * 128 + ks * 64];
+#pragma unroll
+        for (int j = 0; j < J; ++j) fb[j] = sb[j * 128 + ks * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+              acc[i][j] = mfma_f32(fa[i][e], fb[j][e], u % FLUSH == 0 && ks == 0 && e == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      stash((st + 1) * 32, (u + 1) & 1, areg[(u + 1) % PD], breg[(u + 1) % PD]);
+      __syncthreads();
     }
-    if (st + 1 < NS) stash((st + 1) & 1);
-    __syncthreads();
   }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < J; ++j) tot[i][j] += acc[i][j];
   constexpr int STEP = EPI == EPI_SWIGLU ? 2 : 1;
 #pragma unroll
   for (int i = 0; i < 2; i += STEP) {
-    const int nb = EPI == EPI_SWIGLU ? nb_t + wn : nb_t + wn * 2 + i;
+    const int nb = EPI == EPI_SWIGLU ? nb_t + w : nb_t + w * 2 + i;
     if (nb >= a.NB) continue;
 #pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      const int row = row_t + (wm * JB + j) * 16 + m;
+    for (int j = 0; j < J; ++j) {
+      const int row = row_t + j * 16 + m;
       const bool row_ok = row < a.rows;
       const EpiPre pre = f32_epi_prefetch<EPI>(a, nb, g, row, row_ok);
       f32_epi<EPI>(a, tot[i][j], tot[i + STEP - 1][j], nb, g, m, row, row_ok, 1.f, pre);
@@ -439,23 +460,77 @@ __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
   }
 }
 
+template <int EPI, int J>
+static void launch_f32_dense_tile(const F32Args &a, hipStream_t s) {
+  constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;
+  const int tiles = (a.NB + NBT - 1) / NBT * ((a.rows + 16 * J - 1) / (16 * J));
+  gemm_f32_dense_kernel<EPI, J><<<dim3((tiles + 7) / 8 * 8, a.splits), 256, 0, s>>>(a);
+}
+
+// Rows of a tile and (EPI_PART) pieces of K: the least of tiles per compute unit times rows of a tile over pieces.  A
+// narrow tile reads more of LDS and L2 per product (7B widths, 333 rows: gate/up 1078, 705, 622, 751 us with J = 1, 2,
+// 3, 4), a lone workgroup per compute unit has nothing to cover its barriers with, and each piece costs a pass over the
+// partial sums.
 template <int EPI>
-static void launch_f32_dense_cfg(const F32Args &a, hipStream_t s) {
-  // rounds of one tile per compute unit, times the rows of a tile: the narrower tile pads less and divides the
-  // work more evenly, the wider one reads the weights through LDS half as often (taken when they tie)
-  const int per_t = EPI == EPI_SWIGLU ? 2 : 4, NT = (a.NB + per_t - 1) / per_t;
-  const long t64 = (long)NT * ((a.rows + 63) / 64), t32 = (long)NT * ((a.rows + 31) / 32);
-  const long c64 = (t64 + 255) / 256 * 64, c32 = (t32 + 255) / 256 * 32;
-  if (c32 < c64) gemm_f32_dense_kernel<EPI, 32><<<(t32 + 7) / 8 * 8, 256, 0, s>>>(a);
-  else gemm_f32_dense_kernel<EPI, 64><<<(t64 + 7) / 8 * 8, 256, 0, s>>>(a);
+static int launch_f32_dense_cfg(F32Args a, hipStream_t s, size_t max_part = 0) {   // returns the pieces of K
+  const long NT = EPI == EPI_SWIGLU ? (a.NB + 3) / 4 : (a.NB + 7) / 8;
+  const double per_row[5] = {0, 1.4, 1.1, 1.0, 1.0};
+  int best = 4;
+  double cost = 1e30;
+  for (int J = 4; J >= 1; --J)
+    for (int S = 1; S <= (EPI == EPI_PART ? 8 : 1); ++S) {
+      if (S > 1 && (a.K < S * 256 || (size_t)S * a.rows * a.N > max_part)) break;
+      const long tiles = NT * ((a.rows + 16 * J - 1) / (16 * J)) * S;
+      const double c = (double)((tiles + 255) / 256 * J) / S * per_row[J] * (tiles <= 256 ? 1.25 : 1.0) * (1.0 + 0.03 * S);
+      if (c < cost) { cost = c; best = J; a.splits = S; }
+    }
+  if (best == 4) launch_f32_dense_tile<EPI, 4>(a, s);
+  else if (best == 3) launch_f32_dense_tile<EPI, 3>(a, s);
+  else if (best == 2) launch_f32_dense_tile<EPI, 2>(a, s);
+  else launch_f32_dense_tile<EPI, 1>(a, s);
+  return a.splits;
+}
+
+// Adds the partial sums of a row to its residual (or to the bias), and normalises the new row for the next GEMM.
+__global__ __launch_bounds__(256) void sum_rmsnorm_f32_kernel(const float *part, int splits, size_t stride, const float *base,
+                                                              size_t base_ld, int d, const float *gain, float eps, float *x,
+                                                              float *xn) {
+  __shared__ float red[4];
+  const size_t r = blockIdx.x;
+  float ss = 0.f;
+  for (int k = threadIdx.x * 4; k < d; k += 1024) {
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (base) v = *reinterpret_cast<const f32x4 *>(base + r * base_ld + k);
+    for (int p = 0; p < splits; ++p) v += *reinterpret_cast<const f32x4 *>(part + p * stride + r * d + k);
+    *reinterpret_cast<f32x4 *>(x + r * d + k) = v;
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float rn = 1.0f / sqrtf(((red[0] + red[1]) + (red[2] + red[3])) / (float)d + eps);
+  for (int k = threadIdx.x * 4; k < d; k += 1024) {
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(x + r * d + k), gn = *reinterpret_cast<const f32x4 *>(gain + k);
+    *reinterpret_cast<f32x4 *>(xn + r * d + k) = f32x4{(v[0] * rn) * gn[0], (v[1] * rn) * gn[1], (v[2] * rn) * gn[2], (v[3] * rn) * gn[3]};
+  }
 }
 
 void launch_gemm_f32_dense(const GemmLaunch &L, hipStream_t s) {
-  const F32Args a = f32_args(L);
+  F32Args a = f32_args(L);
+  a.splits = 1;
   if (L.epi == EPI_QKV) launch_f32_dense_cfg<EPI_QKV>(a, s);
-  else if (L.epi == EPI_SWIGLU) launch_f32_dense_cfg<EPI_SWIGLU>(a, s);
-  else if (L.epi == EPI_RESID) launch_f32_dense_cfg<EPI_RESID>(a, s);
-  else launch_f32_dense_cfg<EPI_STORE>(a, s);
+  else launch_f32_dense_cfg<EPI_SWIGLU>(a, s);
+}
+
+void launch_gemm_f32_resid_norm(const GemmLaunch &L, float *part, size_t max_part, float *x, const float *gain, float *xn,
+                                hipStream_t s) {
+  F32Args a = f32_args(L);
+  a.Y = part;
+  a.splits = 1;
+  const int S = launch_f32_dense_cfg<EPI_PART>(a, s, max_part);
+  sum_rmsnorm_f32_kernel<<<a.rows, 256, 0, s>>>(part, S, (size_t)a.rows * a.N, L.bias ? L.bias : x, L.bias ? 0 : a.N, a.N, gain,
+                                                L.eps, x, xn);
 }
 
 // ------------------------------------------------------------------ attention, 1..16 rows
