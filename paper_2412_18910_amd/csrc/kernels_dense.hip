@@ -307,20 +307,35 @@ void launch_draft_cat_dense(const float *x, int rows, int d, const float *gain, 
 // q: float [rows][H*HD] of the chunk (already rotated); chunk row i sits at slot pos0 + i and
 // sees slots 0..pos0+i of the tiled cache (which already holds the chunk's own K and V).
 // Pairs (row, query head of the KV head's group) are numbered r = row*G + head%G; a wave owns
-// MT tiles of 16 consecutive pairs and walks the visible keys 32 at a time: the K and V tiles
-// of a step (16 KB at head_dim 128) are loaded once and multiplied against all MT tiles, which
-// halves the cache traffic per MFMA against one tile per wave.  Late (long) tiles are
-// scheduled first.  No barriers, no LDS: every wave is independent.
+// MT tiles of 16 consecutive pairs, a workgroup 64*MT pairs, and walks the visible keys 32 at a time with an
+// online softmax.  The K and V tiles of a step (16 KB at head_dim 128) are shared through
+// double-buffered LDS: read by every wave for itself they take the whole 64 bytes a cycle of the vector cache.
+// Per step the softmax is worth about as many cycles as the products, and the waves of a workgroup are in the same
+// phase, so each wave runs the two side by side: the scores of step s+1 (buffer: K of s+1 beside V of s) are
+// multiplied while the probabilities of step s are worked out.  The mask is applied only where the diagonal
+// crosses the tile, rescaling only where a maximum grew, row sums stay per lane until the end, maxima are exchanged
+// by row swaps.
+__device__ __forceinline__ float max_across_groups(float v) {   // maximum over the four lane groups (l, l^16, l^32, l^48)
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 template <int HD, int MT>
-__global__ __launch_bounds__(256) void attn_prefill_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
-                                                           const u32x4 *Kc, const u32x4 *Vc, u32x4 *Xp_out, size_t kts,
-                                                           float scale_log2e) {
-  constexpr int DT = HD / 32, VT = HD / 16;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, m = lane & 15;
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
+                                                              const u32x4 *Kc, const u32x4 *Vc, u32x4 *Xp_out, size_t kts,
+                                                              float scale_log2e) {
+  constexpr int DT = HD / 32, VT = HD / 16, KP = 2 * DT * 64, VP = VT * 64, NL = KP / 256;   // 16-byte pieces of a step
+  __shared__ u32x4 kv[2][KP + VP];   // K tiles [2][DT][64] of step s+1, V tiles [VT][64] of step s
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, m = lane & 15;
   const int kh = blockIdx.x, G = H / Hkv, R = rows * G;
-  const int r0 = (((int)gridDim.y - 1 - (int)blockIdx.y) * 4 + w) * (16 * MT);
-  if (r0 >= R) return;   // wave-uniform
-  int row[MT], head[MT], limit[MT];
+  // Long tiles (late rows) first; with at most two workgroups per compute unit all are resident at once, and the
+  // second half of the list runs the other way so that every unit gets a long and a short one.
+  const int T = gridDim.y, y = blockIdx.y, half = (T + 1) / 2;
+  const int tile = (int)(gridDim.x * gridDim.y) > 512 || y < half ? T - 1 - y : y - half;
+  const int r0 = (tile * 4 + w) * (16 * MT);
+  int row[MT], head[MT], limit[MT], clear_kb[MT];
   bool rok[MT];
   u32x4 qh[MT][DT], ql[MT][DT];
 #pragma unroll
@@ -331,6 +346,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const float *q, int r
     row[t] = rr / G;
     head[t] = kh * G + rr % G;
     limit[t] = pos0 + row[t];   // last slot this lane's row may see
+    clear_kb[t] = pos0 + min(r0 + t * 16, R - 1) / G - 31;   // steps up to here are visible to every row of the tile
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
       const float *src = q + ((size_t)row[t] * H + head[t]) * HD + dt * 32 + g * 8;
@@ -344,7 +360,9 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const float *q, int r
       ql[t][dt] = u32x4{l0, l1, l2, l3};
     }
   }
-  const int last_key = pos0 + min(r0 + 16 * MT - 1, R - 1) / G;   // last slot any row of the wave sees
+  // last slot any row of the wave sees (a wave behind the last pair only helps to load); last step of the workgroup
+  const int last_key = r0 < R ? pos0 + min(r0 + 16 * MT - 1, R - 1) / G : -1;
+  const int last_step = (pos0 + min((tile + 1) * (64 * MT) - 1, R - 1) / G) >> 5;
 
   float mx[MT], lsum[MT];
   f32x4 O[MT][VT];
@@ -356,73 +374,78 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const float *q, int r
     for (int dt = 0; dt < VT; ++dt) O[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  // K and V tiles of a step live in registers; the K tiles of the next step are requested as soon as
-  // this step's scores are done and the V tiles as soon as its P.V products are issued, so the loads
-  // fly behind the softmax / MFMA work instead of in front of it (no extra registers).
-  u32x4 kreg[2][DT], vreg[VT];
-  auto load_k = [&](int kb) {
-    const u32x4 *kp = Kc + (((size_t)kh * (n_ctx / 16) + (kb >> 4)) * DT) * 64 + lane;
+  // the K tiles of a step are contiguous in the cache, and so are its V tiles; steps behind the last repeat it (ignored)
+  const u32x4 *kp = Kc + (size_t)kh * (n_ctx / 16) * DT * 64 + tid, *vp = Vc + (size_t)kh * (n_ctx / 32) * VP + tid;
+  u32x4 sa[2 * NL], sb[2 * NL];
+  auto issue_k = [&](u32x4 *st, int s) {
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) kreg[kt][dt] = kp[(kt * DT + dt) * 64];
+    for (int i = 0; i < NL; ++i) st[i] = kp[(size_t)min(s, last_step) * KP + i * 256];
   };
-  auto load_v = [&](int kb) {
-    const u32x4 *vp = Vc + (((size_t)kh * (n_ctx / 32) + (kb >> 5)) * VT) * 64 + lane;
+  auto issue = [&](u32x4 (&st)[2 * NL], int s) {   // K of step s+1, V of step s
+    issue_k(st, s + 1);
 #pragma unroll
-    for (int dt = 0; dt < VT; ++dt) vreg[dt] = vp[dt * 64];
+    for (int i = 0; i < NL; ++i) st[NL + i] = vp[(size_t)min(s, last_step) * VP + i * 256];
   };
-  load_k(0);
-  load_v(0);
-  const int last_kb = last_key & ~31;
-  for (int kb = 0; kb <= last_key; kb += 32) {
-    const int kb_next = min(kb + 32, last_kb);   // the last step re-requests its own tiles (ignored)
-    f32x4 S[MT][2];
+  auto stash = [&](const u32x4 (&st)[2 * NL], int buf) {
+#pragma unroll
+    for (int i = 0; i < 2 * NL; ++i) kv[buf][tid + i * 256] = st[i];
+  };
+  auto scores = [&](f32x4 (&S)[MT][2], const u32x4 *ks) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) S[t][0] = S[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const u32x4 k0 = ks[dt * 64], k1 = ks[(DT + dt) * 64];
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        S[t][0] = mfma_bf16(k0, qh[t][dt], S[t][0]);
+        S[t][1] = mfma_bf16(k1, qh[t][dt], S[t][1]);
+      }
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        S[t][0] = mfma_bf16(k0, ql[t][dt], S[t][0]);
+        S[t][1] = mfma_bf16(k1, ql[t][dt], S[t][1]);
+      }
+    }
+  };
+  // step s: S holds its scores, N receives those of step s+1
+  auto step = [&](int s, int buf, f32x4 (&S)[MT][2], f32x4 (&N)[MT][2]) {
+    const int kb = s * 32;
+    if (kb > last_key) return;   // wave-uniform
+    const u32x4 *ks = kv[buf] + lane, *vs = ks + KP;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      S[t][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-      S[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (kb > clear_kb[t]) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        S[t][0] = mfma_bf16(kreg[0][dt], qh[t][dt], S[t][0]);
-        S[t][1] = mfma_bf16(kreg[1][dt], qh[t][dt], S[t][1]);
-        S[t][0] = mfma_bf16(kreg[0][dt], ql[t][dt], S[t][0]);
-        S[t][1] = mfma_bf16(kreg[1][dt], ql[t][dt], S[t][1]);
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) S[t][kt][e] = kb + kt * 16 + 4 * g + e <= limit[t] ? S[t][kt][e] : -INFINITY;
+      }
+      float bmax = fmaxf(fmaxf(fmaxf(S[t][0][0], S[t][0][1]), fmaxf(S[t][0][2], S[t][0][3])),
+                         fmaxf(fmaxf(S[t][1][0], S[t][1][1]), fmaxf(S[t][1][2], S[t][1][3])));
+      bmax = max_across_groups(bmax);
+      if (__any(bmax > mx[t])) {   // finite from the first step on: slot 0 is visible to every row
+        const float mnew = fmaxf(mx[t], bmax), alpha = __builtin_amdgcn_exp2f(mx[t] - mnew);
+        mx[t] = mnew;
+        lsum[t] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < VT; ++dt) O[t][dt] *= alpha;
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    load_k(kb_next);
-    __builtin_amdgcn_sched_barrier(0);
+    scores(N, ks);
     u32x4 ph[MT], pl[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      float bmax = -INFINITY;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int key = kb + kt * 16 + 4 * g + e;
-          S[t][kt][e] = key <= limit[t] ? S[t][kt][e] : -INFINITY;
-          bmax = fmaxf(bmax, S[t][kt][e]);
-        }
-      bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
-      bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-      const float mnew = fmaxf(mx[t], bmax);   // finite from the first block on: slot 0 is visible to every row
-      const float alpha = __builtin_amdgcn_exp2f(mx[t] - mnew);
       float bsum = 0.f;
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          S[t][kt][e] = __builtin_amdgcn_exp2f(S[t][kt][e] - mnew);
+          S[t][kt][e] = __builtin_amdgcn_exp2f(S[t][kt][e] - mx[t]);
           bsum += S[t][kt][e];
         }
-      bsum += __shfl_xor(bsum, 16, 64);
-      bsum += __shfl_xor(bsum, 32, 64);
-      lsum[t] = lsum[t] * alpha + bsum;
-      mx[t] = mnew;
-#pragma unroll
-      for (int dt = 0; dt < VT; ++dt) O[t][dt] *= alpha;
+      lsum[t] += bsum;   // this lane's share of the row
       // P^T as B operand: k-slot e of lane group g = key 16*(e/4) + 4g + e%4 of the 32-key block
       uint32_t h0, h1, h2, h3, l0, l1, l2, l3;
       split2(S[t][0][0], S[t][0][1], h0, l0);
@@ -432,19 +455,64 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const float *q, int r
       ph[t] = u32x4{h0, h1, h2, h3};
       pl[t] = u32x4{l0, l1, l2, l3};
     }
+    // interleave: K tiles ahead of their products, about 3 vector instructions to an MFMA
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-#pragma unroll
-      for (int dt = 0; dt < VT; ++dt) O[t][dt] = mfma_bf16(vreg[dt], ph[t], O[t][dt]);
-#pragma unroll
-      for (int dt = 0; dt < VT; ++dt) O[t][dt] = mfma_bf16(vreg[dt], pl[t], O[t][dt]);
+    for (int i = 0; i < 4 * DT * MT / 2; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x402, 7, 0);
+      if (i % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    load_v(kb_next);
+#pragma unroll
+    for (int dt = 0; dt < VT; dt += 2) {   // two tiles at a time: four products between the two of an accumulator
+      const u32x4 v0 = vs[dt * 64], v1 = vs[(dt + 1) * 64];
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        O[t][dt] = mfma_bf16(v0, ph[t], O[t][dt]);
+        O[t][dt + 1] = mfma_bf16(v1, ph[t], O[t][dt + 1]);
+      }
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        O[t][dt] = mfma_bf16(v0, pl[t], O[t][dt]);
+        O[t][dt + 1] = mfma_bf16(v1, pl[t], O[t][dt + 1]);
+      }
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+    for (int i = 0; i < VT * MT / 2; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      if (i < VT - 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+  };
+  f32x4 SA[MT][2], SB[MT][2];
+  issue_k(sb, 0);
+#pragma unroll
+  for (int i = 0; i < NL; ++i) kv[1][tid + i * 256] = sb[i];
+  issue(sa, 0);
+  issue(sb, 1);
+  __syncthreads();
+  scores(SA, kv[1] + lane);
+  stash(sa, 0);
+  __syncthreads();
+  for (int s = 0; s <= last_step; s += 2) {
+    issue(sa, s + 2);
     __builtin_amdgcn_sched_barrier(0);
+    step(s, 0, SA, SB);
+    __builtin_amdgcn_sched_barrier(0);
+    stash(sb, 1);
+    __syncthreads();
+    issue(sb, s + 3);
+    __builtin_amdgcn_sched_barrier(0);
+    step(s + 1, 1, SB, SA);
+    __builtin_amdgcn_sched_barrier(0);
+    stash(sa, 0);
+    __syncthreads();
   }
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
+    lsum[t] += __shfl_xor(lsum[t], 16, 64);
+    lsum[t] += __shfl_xor(lsum[t], 32, 64);
     if (rok[t]) {
       const float inv = 1.0f / lsum[t];
       u32x4 *xp = Xp_out + (size_t)(row[t] >> 4) * 128;
@@ -456,9 +524,9 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const float *q, int r
   }
 }
 
-void launch_attention_prefill(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
-                              void *Xp_out, int RB, hipStream_t s) {
-  constexpr int MT = 2;
+template <int MT>
+static void launch_attention_prefill_tiles(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer,
+                                           size_t v_off, void *Xp_out, int RB, hipStream_t s) {
   const int G = c.n_heads / c.n_kv_heads, R = rows * G, HD = c.head_dim;
   const dim3 grid(c.n_kv_heads, (R + 64 * MT - 1) / (64 * MT));
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
@@ -470,6 +538,17 @@ void launch_attention_prefill(const float *q, int rows, int pos0, const ae_confi
   else
     attn_prefill_kernel<64, MT><<<grid, 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, cap, Kc, Vc, (u32x4 *)Xp_out,
                                                     (size_t)RB * 128, scale_log2e);
+}
+
+// Two tiles a wave read each K and V tile from LDS half as often, one tile a wave gives twice the workgroups.  The
+// larger reuse pays where the walks are long (most keys lie before the chunk) and there is work for all 256 compute
+// units: 32 heads of 128, 2048 rows, 83 us with one tile and 96 with two without a context, 310 and 286 behind 2048 or
+// 4096 slots, 1633 rows (416 workgroups of two tiles a wave) behind 6144 slots 456 and 438; 100 rows 7.6 and 11.6.
+void launch_attention_prefill(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
+                              void *Xp_out, int RB, hipStream_t s) {
+  const long wgs = (long)c.n_kv_heads * ((rows * (c.n_heads / c.n_kv_heads) + 127) / 128);
+  if (pos0 >= rows && wgs >= 384) launch_attention_prefill_tiles<2>(q, rows, pos0, c, kv_layer, v_off, Xp_out, RB, s);
+  else launch_attention_prefill_tiles<1>(q, rows, pos0, c, kv_layer, v_off, Xp_out, RB, s);
 }
 
 }  // namespace ae
