@@ -274,10 +274,13 @@ int ensure_dense(ae_ctx *c, int n) {
   for (void *p : c->dense_owned) hipFree(p);
   c->dense_owned.clear();
   c->dense_cap = 0;
-  const size_t cap = want, d = g.d_model, dq = (size_t)g.n_heads * g.head_dim, f = g.d_ffn;
+  const size_t cap = want, d = g.d_model, dq = (size_t)g.n_heads * g.head_dim, dkv = (size_t)g.n_kv_heads * g.head_dim, f = g.d_ffn;
   const size_t dmax = dq > d ? dq : d;
-  const size_t part_rows = cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048;   // up to 8 pieces of K for short prompts
-  c->ppart_floats = part_rows * d;
+  // sums over pieces of K.  float32: up to 8 pieces for short prompts; bf16: 768 tiles of 128 x 128, no more than
+  // 16 pieces of the widest output
+  const size_t part_rows = cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048;
+  const size_t widest = 2 * f > dq + 2 * dkv ? 2 * f : dq + 2 * dkv, most = (size_t)768 * 128 * 128;
+  c->ppart_floats = !c->fast ? part_rows * d : 16 * cap * widest < most ? 16 * cap * widest : most;
   struct Buf { void **p; size_t bytes; };
   const std::vector<Buf> bufs = !c->fast ? std::vector<Buf>{
       {(void **)&c->px, cap * d * 4}, {(void **)&c->pq, cap * dq * 4}, {&c->pxa, cap * d * 4}, {&c->pxatt, cap * dmax * 4},
@@ -285,7 +288,7 @@ int ensure_dense(ae_ctx *c, int n) {
       {(void **)&c->px, cap * d * 4},      {(void **)&c->pq, cap * dq * 4},   {(void **)&c->prinv, cap * 4},
       {(void **)&c->pssq_a, cap * d * 4 / 16 * 1 + cap * 4}, {(void **)&c->pssq_f, cap * d * 4 / 16 + cap * 4},
       {&c->pxa, cap * d * 4},              {&c->pxf, cap * d * 4},            {&c->pxatt, cap * dq * 4},
-      {&c->pxh, cap * f * 4},              {&c->pxcat, cap * 2 * d * 4}};
+      {&c->pxh, cap * f * 4},              {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, c->ppart_floats * 4}};
   for (auto &b : bufs) {
     void *q = nullptr;
     const size_t bytes = (b.bytes + 255) / 256 * 256;
@@ -296,7 +299,7 @@ int ensure_dense(ae_ctx *c, int n) {
     }
     c->dense_owned.push_back(q);
     *b.p = q;
-    if (c->fast) launch_fill_zero(q, bytes, c->stream);
+    if (c->fast && b.p != (void **)&c->ppart) launch_fill_zero(q, bytes, c->stream);
   }
   c->dense_cap = want;
   return AE_OK;
@@ -311,16 +314,20 @@ void dense_chunk(ae_ctx *c, int p0, int rows, int drows) {
   const int RB = c->dense_cap / 16, RBu = (rows + 15) / 16, Pd = d / 16, cap = kv_capacity(g);
   launch_embed_dense(c->tok_emb, c->hist + p0, rows, d, c->layers[0].attn_norm, c->px, c->pxa, RB, c->pssq_a, s);
   int Pa = 1;
+  bool have_rinv = false;   // 1/rms of the rows in pxa is in prinv already
+  auto gemm_dense = [&](const GemmLaunch &L, const float *rinv) {
+    return launch_gemm_dense(L, RB, rinv, s, c->ppart, c->ppart_floats, c->prinv);
+  };
   auto qkv_pass = [&](int li, int nrows) {
     const LayerW &w = c->layers[li];
-    launch_rinv_finalize(c->pssq_a, (nrows + 15) / 16, Pa, d, g.rms_eps, c->prinv, s);
+    if (!have_rinv) launch_rinv_finalize(c->pssq_a, (nrows + 15) / 16, Pa, d, g.rms_eps, c->prinv, s);
     GemmLaunch qkv;
     qkv.W = &w.f_qkv; qkv.Xp = c->pxa; qkv.rows = nrows; qkv.epi = EPI_QKV; qkv.nseg = 3;
     qkv.Y[0] = c->pq; qkv.ldy[0] = dq;
     qkv.seg_N[0] = dq; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
     qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
     qkv.pos0 = p0; qkv.n_ctx = cap; qkv.hd = g.head_dim;
-    launch_gemm_dense(qkv, RB, c->prinv, s);
+    gemm_dense(qkv, c->prinv);
   };
   for (int l = 0; l < g.n_layers; ++l) {
     const LayerW &w = c->layers[l];
@@ -328,17 +335,16 @@ void dense_chunk(ae_ctx *c, int p0, int rows, int drows) {
     launch_attention_prefill(c->pq, rows, p0, g, kv_layer_ptr(c, l), c->kv_v_offset, c->pxatt, RB, s);
     GemmLaunch o;
     o.W = &w.wo; o.Xp = c->pxatt; o.rows = rows; o.epi = EPI_RESID; o.Y[0] = c->px; o.ldy[0] = d; o.seg_N[0] = d;
-    o.Xp_out = c->pxf; o.gain_out = w.ffn_norm; o.ssq_out = c->pssq_f;
-    launch_gemm_dense(o, RB, nullptr, s);
-    launch_rinv_finalize(c->pssq_f, RBu, Pd, d, g.rms_eps, c->prinv, s);
+    o.Xp_out = c->pxf; o.gain_out = w.ffn_norm; o.ssq_out = c->pssq_f; o.eps = g.rms_eps;
+    if (!gemm_dense(o, nullptr)) launch_rinv_finalize(c->pssq_f, RBu, Pd, d, g.rms_eps, c->prinv, s);
     GemmLaunch gu;
     gu.W = &w.f_gu; gu.Xp = c->pxf; gu.rows = rows; gu.epi = EPI_SWIGLU; gu.Xp_out = c->pxh; gu.seg_N[0] = 2 * f;
-    launch_gemm_dense(gu, RB, c->prinv, s);
+    gemm_dense(gu, c->prinv);
     GemmLaunch dn;
     dn.W = &w.w_down; dn.Xp = c->pxh; dn.rows = rows; dn.epi = EPI_RESID; dn.Y[0] = c->px; dn.ldy[0] = d; dn.seg_N[0] = d;
     dn.Xp_out = c->pxa; dn.gain_out = l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : c->final_norm;
-    dn.ssq_out = c->pssq_a;
-    launch_gemm_dense(dn, RB, nullptr, s);
+    dn.ssq_out = c->pssq_a; dn.eps = g.rms_eps;
+    have_rinv = gemm_dense(dn, nullptr);
     Pa = Pd;
   }
   if (drows > 0) {
@@ -348,8 +354,8 @@ void dense_chunk(ae_ctx *c, int p0, int rows, int drows) {
     GemmLaunch fc;
     fc.W = &c->draft_fc; fc.Xp = c->pxcat; fc.rows = drows; fc.epi = EPI_STORE; fc.bias = c->draft_fc_b;
     fc.seg_N[0] = d; fc.ldy[0] = d;
-    fc.Xp_out = c->pxa; fc.gain_out = dl.attn_norm; fc.ssq_out = c->pssq_a;
-    launch_gemm_dense(fc, RB, nullptr, s);
+    fc.Xp_out = c->pxa; fc.gain_out = dl.attn_norm; fc.ssq_out = c->pssq_a; fc.eps = g.rms_eps;
+    have_rinv = gemm_dense(fc, nullptr);
     Pa = Pd;
     qkv_pass(g.n_layers, drows);
   }

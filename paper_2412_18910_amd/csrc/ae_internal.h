@@ -117,7 +117,7 @@ struct ae_ctx {
   std::vector<void *> dense_owned;
   float *px = nullptr, *pq = nullptr, *prinv = nullptr, *pssq_a = nullptr, *pssq_f = nullptr;
   void *pxa = nullptr, *pxf = nullptr, *pxatt = nullptr, *pxh = nullptr, *pxcat = nullptr;
-  float *ppart = nullptr;          // float32: partial sums of the GEMMs that split K
+  float *ppart = nullptr;          // sums over pieces of K of the GEMMs that split it
   size_t ppart_floats = 0;
 
   // host-side state machine
@@ -263,8 +263,12 @@ void launch_draft_cat_packed(const float *feat, int feat_ld, const void *emb, co
 
 // ---- dense prompt pass (kernels_dense.hip); packed buffers hold RB row-blocks ----
 // Same GemmLaunch as the decode GEMM (rows = rows of the chunk, row0 unused); rinv != nullptr
-// folds RMSNorm in (1/rms per row from launch_rinv_finalize).
-void launch_gemm_dense(const GemmLaunch &L, int RB, const float *rinv, hipStream_t s);
+// folds RMSNorm in (1/rms per row, from launch_rinv_finalize or rinv_out below).  part: room for
+// part_floats floats, used where K is split.  Returns true if so: EPI_RESID and EPI_STORE (L.gain_out
+// set, Y stored for EPI_RESID only) have then left 1/rms (with L.eps) of every output row in rinv_out,
+// else partial sums of x^2 in L.ssq_out.
+bool launch_gemm_dense(const GemmLaunch &L, int RB, const float *rinv, hipStream_t s, float *part, size_t part_floats,
+                       float *rinv_out = nullptr);
 void launch_rinv_finalize(const float *ssq, int RBused, int P, int K, float eps, float *rinv, hipStream_t s);
 void launch_embed_dense(const void *emb, const int32_t *ids_dev, int rows, int d, const float *gain, float *x, void *Xp,
                         int RB, float *ssq, hipStream_t s);

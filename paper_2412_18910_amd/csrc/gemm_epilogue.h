@@ -39,6 +39,7 @@ struct GemmArgs {
   uint16_t *Kc, *Vc;        // this layer's tiled bf16 cache (layouts of kernels_attn_mfma.hip)
   int pos0, n_ctx, hd;
   const int32_t *gate;      // nullable: the kernel does nothing when *gate == 0
+  float *part;              // dense: sums over pieces of K [piece][rows][N]
 };
 
 __device__ __forceinline__ uint16_t f2bf_rne(float f) {

@@ -23,13 +23,14 @@
 
 namespace ae {
 
-constexpr int DN = 4;    // weight row-blocks per wave
 constexpr int DKS = 2;   // k-tiles per pipeline stage
+constexpr int EPI_PART = 4;   // raw float32 sums over a piece of K -> a.part[piece][row][N]
 
 // DM = activation row-blocks per workgroup: 8 (128 rows), or 4 when the wide tile would leave
-// compute units without two resident workgroups.
-template <int EPI, bool NORM, int DM>
-__global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
+// compute units without two resident workgroups.  DN = weight row-blocks per wave, NW = waves: 4 x 4, or
+// 2 x 8 (half the accumulators, twice the waves) where K is split over workgroups (gridDim.y pieces, EPI_PART).
+template <int EPI, bool NORM, int DM, int DN, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a) {
   extern __shared__ u32x4 bs[];   // [2][DKS][DM][2][64]
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, m = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps operand bases in scalar registers
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
   // ~64 workgroups resident on an XCD then cover about 8 x 8 tiles and share their operands in
   // that L2 (7B gate/up GEMM over 2048 rows: 1.4 GB fetched from HBM instead of 3.3 GB with
   // the plain row-major order).
-  const int NT = (a.NBtot + 4 * DN - 1) / (4 * DN), MT = (a.rows + DM * 16 - 1) / (DM * 16);
+  const int NT = (a.NBtot + NW * DN - 1) / (NW * DN), MT = (a.rows + DM * 16 - 1) / (DM * 16);
   const int per = (NT * MT + 7) >> 3;
   const int v = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
   if (v >= NT * MT) return;
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
   }
   const int rb0 = tm * DM;
   // a workgroup hanging over the end of the matrix slides back (recomputes, stores nothing new)
-  const int nbw = min(tn * (4 * DN), a.NBtot - 4 * DN) + w * DN;
+  const int nbw = min(tn * (NW * DN), a.NBtot - NW * DN) + w * DN;
   const size_t kts = (size_t)a.RB * 128;
   // Operands come through buffer loads: resource descriptor and per-stage byte offset in
   // scalar registers, one fixed per-lane offset register each (out-of-range reads return 0).
@@ -69,6 +70,13 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
   const unsigned wl = lane * 16, xl = (m * 4 + g) * 16;                  // per-lane byte offsets
   const unsigned kstride_b = a.NBtot * 1024u, kts_b = a.RB * 2048u;      // bytes per k-tile
   unsigned wq = nbw * 1024u, xq = (rb0 * 128u + w * 64u) * 16u;           // stage to load next (uniform)
+  int NS = a.KT / DKS;   // even: K is a multiple of 256
+  if (EPI == EPI_PART) {   // a piece of K in units of 4 k-tiles
+    const int u0 = a.KT / 4 * (int)blockIdx.y / (int)gridDim.y, u1 = a.KT / 4 * ((int)blockIdx.y + 1) / (int)gridDim.y;
+    wq += u0 * 4 * kstride_b;
+    xq += u0 * 4 * kts_b;
+    NS = (u1 - u0) * (4 / DKS);
+  }
   constexpr int STAGE = DKS * DM * 128;                 // pieces per LDS stage
 
   f32x4 acc[DN][DM];
@@ -81,13 +89,14 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
   // loaded"; B tiles go global -> registers (xs) -> the other LDS stage.  The loads of stage
   // s+1 are issued before the MFMAs of stage s (sched_barrier keeps them there) and are
   // parked in LDS half-way through them, so nothing but the barrier separates two stages.
-  u32x4 wa[DKS][DN], wb[DKS][DN], xs[DKS][DM / 2];
+  constexpr int XI = DM * 2 / NW;   // B pieces per thread and k-tile
+  u32x4 wa[DKS][DN], wb[DKS][DN], xs[DKS][XI];
   auto issue = [&](u32x4 (&wr)[DKS][DN]) {
     // B first: the LDS write only has to wait for these (the counter retires loads in order)
 #pragma unroll
     for (int ks = 0; ks < DKS; ++ks)
 #pragma unroll
-      for (int i = 0; i < DM / 2; ++i) xs[ks][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, xl, xq + ks * kts_b + i * 4096, 0);
+      for (int i = 0; i < XI; ++i) xs[ks][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, xl, xq + ks * kts_b + i * (NW * 1024), 0);
 #pragma unroll
     for (int ks = 0; ks < DKS; ++ks)
 #pragma unroll
@@ -98,7 +107,7 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
 #pragma unroll
     for (int ks = 0; ks < DKS; ++ks)
 #pragma unroll
-      for (int i = 0; i < DM / 2; ++i) dst[ks * (DM * 128) + i * 256] = xs[ks][i];
+      for (int i = 0; i < XI; ++i) dst[ks * (DM * 128) + i * (NW * 64)] = xs[ks][i];
   };
   // MFMAs of one stage.  The B tiles of step t+1 are read from LDS while the 2*DN MFMAs of
   // step t run, and the next stage's B tiles are written to the other LDS stage after half of
@@ -127,10 +136,9 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
     for (int t = 0; t < T; ++t) {
       if (t + 1 < T) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // DS reads of step t+1
       __builtin_amdgcn_sched_group_barrier(0x008, 2 * DN, 0);            // MFMAs of step t
-      if (t == STASH_AT) __builtin_amdgcn_sched_group_barrier(0x200, DKS * DM / 2, 0);   // DS writes
+      if (t == STASH_AT) __builtin_amdgcn_sched_group_barrier(0x200, DKS * XI, 0);   // DS writes
     }
   };
-  const int NS = a.KT / DKS;   // even: K is a multiple of 256
   const unsigned wstep = DKS * kstride_b, xstep = DKS * kts_b;
   issue(wa);
   stash(0);
@@ -155,41 +163,142 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
 #pragma unroll
   for (int i = 0; i < DN; i += STEP) {
     const int nb = nbw + i;
-    if (nb < tn * (4 * DN)) continue;   // slid-back duplicate of a neighbour's row-block
+    if (nb < tn * (NW * DN)) continue;   // slid-back duplicate of a neighbour's row-block
 #pragma unroll
     for (int j = 0; j < DM; ++j) {
       const int rb = rb0 + j, row = rb * 16 + m;
       const bool row_ok = row < a.rows;
+      if (EPI == EPI_PART) {
+        if (row_ok)
+          *reinterpret_cast<f32x4 *>(a.part + (((size_t)blockIdx.y * a.rows + row) * a.NBtot + nb) * 16 + 4 * g) = acc[i][j];
+        continue;
+      }
       const float rinv = NORM ? a.rinv[row] : 1.f;
       epi_tile<EPI>(a, acc[i][j], acc[i + STEP - 1][j], nb, g, m, rb, row_ok, rinv, kts);
     }
   }
 }
 
-template <int EPI, bool NORM, int DM>
-static void launch_dense_tile(const GemmArgs &a, hipStream_t s) {
+template <int EPI, bool NORM, int DM, int DN, int NW>
+static void launch_dense_tile(const GemmArgs &a, int splits, hipStream_t s) {
   constexpr int sm = 2 * DKS * DM * 128 * 16;
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void *)gemm_dense_kernel<EPI, NORM, DM>, hipFuncAttributeMaxDynamicSharedMemorySize, sm);
-    attr_set = true;
+  static const hipError_t attr =   // once per process
+      hipFuncSetAttribute((const void *)gemm_dense_kernel<EPI, NORM, DM, DN, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, sm);
+  (void)attr;
+  const int tiles = ((a.NBtot + NW * DN - 1) / (NW * DN)) * ((a.rows + DM * 16 - 1) / (DM * 16));
+  gemm_dense_kernel<EPI, NORM, DM, DN, NW><<<dim3((tiles + 7) / 8 * 8, splits), NW * 64, sm, s>>>(a);
+}
+
+// A GEMM whose tiles of 256 weight rows x 64 rows number less than 384 would leave compute units idle (256, two
+// workgroups each).  It runs in workgroups of 8 waves, at most one per compute unit, that take 256 or 384 weight rows
+// (DN = 2, 3) and a piece of K, and a pass that adds the pieces.  7B widths, 100 rows: o/down 155 -> 27 + 8 us, QKV
+// 90 -> 35 + 10, gate/up 92 -> 54 + 9.  The line: a prompt of 256 rows over 4 layers (gate/up 344 tiles) takes 1297 us
+// split and 1320 whole, one of 320 rows (430 tiles) 1670 split and 1557 whole.  splits == 0: the GEMM is not one of
+// those, or there is no room for the pieces.
+struct DenseSplit {
+  int splits = 0, dn = 2;
+};
+static DenseSplit dense_splits(const GemmArgs &a, size_t part_floats) {
+  DenseSplit best;
+  if ((long)((a.NBtot + 15) / 16) * ((a.rows + 63) / 64) >= 384) return best;
+  const long mt = a.rows > 64 ? (a.rows + 127) / 128 : 1;
+  double cost = 1e30;
+  for (int dn = 2; dn <= 3; ++dn) {
+    if (a.NBtot < 8 * dn) break;
+    const long tiles = (a.NBtot + 8 * dn - 1) / (8 * dn) * mt;
+    for (int S = 1; S <= 16 && S <= a.KT / 8; ++S) {   // at least two pairs of stages per piece
+      if ((size_t)S * a.rows * a.NBtot * 16 > part_floats) break;
+      const double c = (double)((tiles * S + 255) / 256) * dn / S + 0.005 * S;   // rounds x work of a piece, its pass
+      if (c < cost) { cost = c; best.splits = S; best.dn = dn; }
+    }
   }
-  const int tiles = ((a.NBtot + 4 * DN - 1) / (4 * DN)) * ((a.rows + DM * 16 - 1) / (DM * 16));
-  gemm_dense_kernel<EPI, NORM, DM><<<(tiles + 7) / 8 * 8, 256, sm, s>>>(a);
+  return best;
+}
+
+static void launch_dense_part(const GemmArgs &a, DenseSplit sp, hipStream_t s) {
+  if (sp.dn == 2) {
+    if (a.rows > 64) launch_dense_tile<EPI_PART, false, 8, 2, 8>(a, sp.splits, s);
+    else launch_dense_tile<EPI_PART, false, 4, 2, 8>(a, sp.splits, s);
+  } else {
+    if (a.rows > 64) launch_dense_tile<EPI_PART, false, 8, 3, 8>(a, sp.splits, s);
+    else launch_dense_tile<EPI_PART, false, 4, 3, 8>(a, sp.splits, s);
+  }
+}
+
+// Adds the pieces of one 16x16 tile (EPI_SWIGLU: of a gate and an up tile) per wave and runs the GEMM's epilogue on it.
+template <int EPI>
+__global__ __launch_bounds__(256) void dense_finish_kernel(const GemmArgs a, int splits) {
+  constexpr int STEP = EPI == EPI_SWIGLU ? 2 : 1;
+  const int lane = threadIdx.x & 63, g = lane >> 4, m = lane & 15;
+  const int NU = a.NBtot / STEP, v = blockIdx.x * 4 + (threadIdx.x >> 6), nb = v % NU * STEP, rb = v / NU;
+  const int row = rb * 16 + m;
+  const bool row_ok = row < a.rows;
+  if (rb * 16 >= a.rows) return;   // wave-uniform
+  const float *p = a.part + ((size_t)(row_ok ? row : a.rows - 1) * a.NBtot + nb) * 16 + 4 * g;
+  const size_t stride = (size_t)a.rows * a.NBtot * 16;
+  f32x4 t = *reinterpret_cast<const f32x4 *>(p), u = t;
+  if (STEP == 2) u = *reinterpret_cast<const f32x4 *>(p + 16);
+#pragma unroll 4
+  for (int i = 1; i < splits; ++i) {
+    t += *reinterpret_cast<const f32x4 *>(p + i * stride);
+    if (STEP == 2) u += *reinterpret_cast<const f32x4 *>(p + i * stride + 16);
+  }
+  epi_tile<EPI>(a, t, u, nb, g, m, rb, row_ok, a.rinv[row], (size_t)a.RB * 128);
+}
+
+// Adds the pieces of a row to its residual (x, updated in place) or to the bias, leaves row * gain packed for the next
+// GEMM and the row's 1/rms.
+__global__ __launch_bounds__(1024) void dense_sum_rows_kernel(const GemmArgs a, int splits, float *rinv, float eps) {
+  __shared__ float red[16];
+  const int r = blockIdx.x, d = a.NBtot * 16;
+  const float *p = a.part + (size_t)r * d;
+  const size_t stride = (size_t)a.rows * d;
+  float *x = a.seg[0].Y ? a.seg[0].Y + (size_t)r * a.seg[0].ldy : nullptr;
+  float ss = 0.f;
+  for (int k = threadIdx.x * 4; k < d; k += 4096) {
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (x) v = *reinterpret_cast<const f32x4 *>(x + k);
+    else if (a.bias) v = *reinterpret_cast<const f32x4 *>(a.bias + k);
+    for (int i = 0; i < splits; i += 4) {   // by fours: loads in flight together, one rounding at the residual's magnitude
+      f32x4 q = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 t = *reinterpret_cast<const f32x4 *>(p + min(i + j, splits - 1) * stride + k);
+        q += i + j < splits ? t : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      v += q;
+    }
+    if (x) *reinterpret_cast<f32x4 *>(x + k) = v;
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    const f32x4 gn = *reinterpret_cast<const f32x4 *>(a.gain_out + k);
+    packed_store4(a.Xp_out + (size_t)(r >> 4) * 128, r & 15, k, v[0] * gn[0], v[1] * gn[1], v[2] * gn[2], v[3] * gn[3],
+                  (size_t)a.RB * 128);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t += red[i];
+    rinv[r] = 1.0f / sqrtf(t / (float)d + eps);
+  }
 }
 
 template <int EPI, bool NORM>
 static void launch_dense_cfg(const GemmArgs &a, hipStream_t s) {
   // 256 compute units x 2 resident workgroups: estimate both tilings in rounds of 512
   // workgroups; a 64-row tile costs about 0.55 of a 128-row one.
-  const long nt = (a.NBtot + 4 * DN - 1) / (4 * DN);
+  const long nt = (a.NBtot + 15) / 16;
   const long t8 = nt * ((a.rows + 127) / 128), t4 = nt * ((a.rows + 63) / 64);
   const double c8 = (double)((t8 + 511) / 512), c4 = 0.55 * (double)((t4 + 511) / 512);
-  if (c4 < c8) launch_dense_tile<EPI, NORM, 4>(a, s);
-  else launch_dense_tile<EPI, NORM, 8>(a, s);
+  if (c4 < c8) launch_dense_tile<EPI, NORM, 4, 4, 4>(a, 1, s);
+  else launch_dense_tile<EPI, NORM, 8, 4, 4>(a, 1, s);
 }
 
-void launch_gemm_dense(const GemmLaunch &L, int RB, const float *rinv, hipStream_t s) {
+bool launch_gemm_dense(const GemmLaunch &L, int RB, const float *rinv, hipStream_t s, float *part, size_t part_floats,
+                       float *rinv_out) {
   GemmArgs a{};
   a.W = (const u32x4 *)L.W->tiled;
   a.NBtot = L.W->N / 16;
@@ -209,12 +318,22 @@ void launch_gemm_dense(const GemmLaunch &L, int RB, const float *rinv, hipStream
   }
   a.rope_tab = L.rope_tab; a.Kc = (uint16_t *)L.Kc; a.Vc = (uint16_t *)L.Vc;
   a.pos0 = L.pos0; a.n_ctx = L.n_ctx; a.hd = L.hd;
-  const bool norm = rinv != nullptr;
+  a.part = part;
+  const DenseSplit sp = dense_splits(a, part_floats);
+  const int S = sp.splits;
+  if (S > 0) {
+    launch_dense_part(a, sp, s);
+    const int rb = (a.rows + 15) / 16;
+    if (L.epi == EPI_QKV) dense_finish_kernel<EPI_QKV><<<(a.NBtot * rb + 3) / 4, 256, 0, s>>>(a, S);
+    else if (L.epi == EPI_SWIGLU) dense_finish_kernel<EPI_SWIGLU><<<(a.NBtot / 2 * rb + 3) / 4, 256, 0, s>>>(a, S);
+    else dense_sum_rows_kernel<<<a.rows, 1024, 0, s>>>(a, S, rinv_out, L.eps);
+    return true;
+  }
   if (L.epi == EPI_QKV) launch_dense_cfg<EPI_QKV, true>(a, s);
   else if (L.epi == EPI_SWIGLU) launch_dense_cfg<EPI_SWIGLU, true>(a, s);
   else if (L.epi == EPI_RESID) launch_dense_cfg<EPI_RESID, false>(a, s);
-  else if (norm) launch_dense_cfg<EPI_STORE, true>(a, s);
   else launch_dense_cfg<EPI_STORE, false>(a, s);
+  return false;
 }
 
 // ------------------------------------------------------------------ 1/rms of every row
