@@ -542,8 +542,8 @@ constexpr int kF32AttnKeys = 64;
 
 template <int HD, bool GATED>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
-                                                       const float *Kc, const float *Vc, float *part, float scale_log2e,
-                                                       const int32_t *gate) {
+                                                       const float *Kc, const float *Vc, float *part, float *out,
+                                                       float scale_log2e, const int32_t *gate) {
   constexpr int C = HD / 32, VT = HD / 16;
   __shared__ float red[4][16][HD];
   __shared__ float wm[4][16], wl[4][16];
@@ -632,15 +632,18 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows,
           wgt[ww] = wm[ww][m2] > -INFINITY ? __builtin_amdgcn_exp2f(wm[ww][m2] - ms) : 0.f;
           l = fmaf(wgt[ww], wl[ww][m2], l);
         }
-        float *dst = part + (((size_t)kh * n_chunks + chunk) * R + r2) * (HD + 2);
+        // one workgroup holds the whole context: the result itself, as the merge of a single partial gives it
+        const bool whole = n_chunks == 1;
+        float *dst = whole ? out + ((size_t)(r2 / G) * H + kh * G + r2 % G) * HD
+                           : part + (((size_t)kh * n_chunks + chunk) * R + r2) * (HD + 2);
 #pragma unroll
         for (int i = 0; i < HD / 16; ++i) {
           float o = 0.f;
 #pragma unroll
           for (int ww = 0; ww < 4; ++ww) o = fmaf(wgt[ww], red[ww][m2][seg * (HD / 16) + i], o);
-          dst[seg * (HD / 16) + i] = o;
+          dst[seg * (HD / 16) + i] = whole ? o / l : o;
         }
-        if (seg == 0) { dst[HD] = ms; dst[HD + 1] = l; }
+        if (seg == 0 && !whole) { dst[HD] = ms; dst[HD + 1] = l; }
       }
     }
     __syncthreads();
@@ -652,8 +655,8 @@ static void launch_attention_f32_cfg(const float *q, int rows, int pos0, const a
                                      float *part, float *out, hipStream_t s, const int32_t *gate) {
   const int n_chunks = (pos0 + rows + kF32AttnKeys - 1) / kF32AttnKeys;
   attn_f32_kernel<HD, GATED><<<dim3(c.n_kv_heads, n_chunks), 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc,
-                                                                          Vc, part, 1.4426950408889634f / sqrtf((float)HD), gate);
-  launch_attention_merge(part, rows, n_chunks, c, out, true, s, gate);
+                                                                          Vc, part, out, 1.4426950408889634f / sqrtf((float)HD), gate);
+  if (n_chunks > 1) launch_attention_merge(part, rows, n_chunks, c, out, true, s, gate);
 }
 
 void launch_attention_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
