@@ -196,7 +196,7 @@ void draft_rows(ae_ctx *c, const float *feat, int feat_ld, const int32_t *next_i
 // LM head (shared with the target) on draft-head output row `row` -> dlogits[i], then the
 // head's token i: argmax (greedy) or an inverse-CDF sample driven by u_draft[i] (temperature
 // > 0); the caller's override table is applied last.
-void draft_lm_head(ae_ctx *c, int row, int i, int k) {
+void draft_lm_head(ae_ctx *c, int row, int i, int k, bool flag_decision) {
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
   float *dl = c->dlogits + (size_t)i * g.vocab;
@@ -210,6 +210,7 @@ void draft_lm_head(ae_ctx *c, int row, int i, int k) {
     ddd.val = c->amax_val; ddd.lse_sum = c->lse_sum; ddd.logits = dl; ddd.NB = NB; ddd.k = k;
     ddd.inv_t = greedy ? 1.f : 1.f / g.temperature; ddd.theta = g.ddd_threshold;
     lm.lse_sum = c->lse_sum; lm.lse_inv_t = ddd.inv_t;
+    if (flag_decision) { ddd.flag = &c->hm_dev->decision; ddd.seq = c->seq; }
   }
   if (greedy || g.ddd_enabled) { lm.amax_val = c->amax_val; lm.amax_idx = c->amax_idx; }
   lm.gate = c->gate;
@@ -230,7 +231,7 @@ void enqueue_ldlp(ae_ctx *c, int slot, int f_row, bool relative_to_accept) {
   launch_ldlp_in(c->ldlp_in.rowmajor, c->ldlp_b_in, c->tok_emb, g.dtype, c->hist, c->F, g.d_model, g.ldlp_in_mode,
                  g.ldlp_hidden, slot, f_row, relative_to_accept ? c->st : nullptr, c->ldlp_z, s);
   launch_ldlp_tail(c->ldlp_z, c->ldlp_w_res, g.dtype, c->ldlp_b_res, c->ldlp_w_out, c->ldlp_b_out, g.ldlp_hidden,
-                   g.ldlp_n_res, g.k_max, g.ldlp_cls, c->st, c->h_st_dev, s);
+                   g.ldlp_n_res, g.k_max, g.ldlp_cls, c->st, c->hm_dev, ++c->seq, s);
 }
 
 // after a stream synchronisation: fold the finished event pairs into the totals
@@ -245,14 +246,33 @@ void drain_kernel_timing(ae_ctx *c) {
   c->kt_used = 0;
 }
 
-// Bring the host's mirror of the device state up to date and wait for it.  The mirror is pinned
-// host memory that the device writes itself; `published`: the last kernel enqueued (the LDLP
-// tail) has already done so.
-int read_state(ae_ctx *c, bool published = false) {
-  if (!published) launch_publish_state(c->st, c->h_st_dev, c->stream);
+// Wait until the device has set a flag word of the mirror to `want`.  Polling is bounded: work that is not there
+// after 50 ms (a long prompt), or never will be (a device error), is waited for by the stream, which reports errors.
+int wait_flag(ae_ctx *c, const uint32_t *word, uint32_t want, uint32_t shift = 0) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int spins = 0;; ++spins) {
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) >> shift == want) return AE_OK;
+    if ((spins & 255) == 255 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) break;
+    __builtin_ia32_pause();
+  }
   HIPCHK(c, hipStreamSynchronize(c->stream));
   HIPCHK(c, hipGetLastError());
-  if (c->kt_used) drain_kernel_timing(c);
+  if (__atomic_load_n(word, __ATOMIC_ACQUIRE) >> shift != want) return fail(c, AE_EHIP, "the device did not answer");
+  return AE_OK;
+}
+
+// Bring the host's mirror of the device state up to date and wait for it.  The mirror is pinned
+// host memory that the device writes itself; `published`: the last kernel enqueued (the LDLP
+// tail) does so for request c->seq.
+int read_state(ae_ctx *c, bool published = false) {
+  if (!published) launch_publish_state(c->st, c->hm_dev, ++c->seq, c->stream);
+  HIPCHK(c, hipGetLastError());   // a launch that failed answers nothing
+  int rc = wait_flag(c, &c->hm->published, c->seq);
+  if (rc) return rc;
+  if (c->kt_used) {
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    drain_kernel_timing(c);
+  }
   return AE_OK;
 }
 
@@ -628,12 +648,22 @@ int ae_init(const ae_config *cfg, const ae_weights *w, void *hip_stream, ae_ctx 
   launch_rope_table(c->rope_tab, g.n_ctx_max, g.head_dim, g.rope_base, c->stream);
   launch_fill_zero(c->st, (sizeof(DevState) + 15) / 16 * 16, c->stream);
   launch_fill_zero(c->hist, ((size_t)(g.n_ctx_max + 2) * 4 + 15) / 16 * 16, c->stream);
-  if (hipHostMalloc((void **)&c->h_st, sizeof(DevState), hipHostMallocMapped) != hipSuccess) {
+  size_t row = V > d ? V : d;   // the longest row that ae_get_* returns
+  if ((size_t)dkv > row) row = dkv;
+  const size_t pieces = (row + kExportPiece - 1) / kExportPiece;
+  c->row_floats = pieces * kExportPiece;
+  if (hipHostMalloc((void **)&c->hm, sizeof(HostMirror), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+      hipHostMalloc((void **)&c->h_feat, d * sizeof(float), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+      hipHostMalloc((void **)&c->h_rows, c->row_floats * sizeof(float) + pieces * sizeof(uint32_t),
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     c->err = "hipHostMalloc failed";
     return bail(AE_ENOMEM);
   }
-  memset(c->h_st, 0, sizeof(DevState));
-  if (hipHostGetDevicePointer((void **)&c->h_st_dev, c->h_st, 0) != hipSuccess) {
+  memset(c->hm, 0, sizeof(HostMirror));
+  memset(c->h_rows + c->row_floats, 0, pieces * sizeof(uint32_t));
+  if (hipHostGetDevicePointer((void **)&c->hm_dev, c->hm, 0) != hipSuccess ||
+      hipHostGetDevicePointer((void **)&c->h_feat_dev, c->h_feat, 0) != hipSuccess ||
+      hipHostGetDevicePointer((void **)&c->h_rows_dev, c->h_rows, 0) != hipSuccess) {
     c->err = "hipHostGetDevicePointer failed";
     return bail(AE_EHIP);
   }
@@ -653,7 +683,9 @@ void ae_free(ae_ctx *c) {
   hipStreamSynchronize(c->stream);
   for (void *p : c->owned) hipFree(p);
   for (void *p : c->dense_owned) hipFree(p);
-  if (c->h_st) hipHostFree(c->h_st);
+  if (c->hm) hipHostFree(c->hm);
+  if (c->h_feat) hipHostFree(c->h_feat);
+  if (c->h_rows) hipHostFree(c->h_rows);
   for (auto &e : c->ev)
     if (e) hipEventDestroy(e);
   for (auto &e : c->kt_ev) hipEventDestroy(e);
@@ -697,9 +729,9 @@ int ae_prefill(ae_ctx *c, const int32_t *ids, int n) {
   enqueue_ldlp(c, n - 1, c->nF - 1, false);
   int rc = read_state(c, true);
   if (rc) return rc;
-  c->pending = c->h_st->bonus;
+  c->pending = c->hm->st.bonus;
   c->h_hist[n] = c->pending;
-  c->k_next = c->h_st->k_next; c->y_next = c->h_st->y_next; c->k_next_valid = true;
+  c->k_next = c->hm->st.k_next; c->y_next = c->hm->st.y_next; c->k_next_valid = true;
   c->have_pending = true;
   c->cur_k = 0;
   return AE_OK;
@@ -772,10 +804,16 @@ int ae_set_state(ae_ctx *c, int kv_len, int32_t last_tok, int32_t pending, const
   const ae_config &g = c->cfg;
   if (kv_len < 1 || kv_len + g.k_max + 1 > g.n_ctx_max || !feat) return fail(c, AE_EINVAL, "ae_set_state: bad kv_len");
   if (!ids_ok(c, &last_tok, 1) || !ids_ok(c, &pending, 1)) return fail(c, AE_EINVAL, "ae_set_state: id out of range");
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  HIPCHK(c, hipMemcpy(c->F, feat, sizeof(float) * g.d_model, hipMemcpyHostToDevice));
-  const int32_t two[2] = {last_tok, pending};
-  HIPCHK(c, hipMemcpy(c->hist + kv_len - 1, two, sizeof(two), hipMemcpyHostToDevice));
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;   // a replay would read whatever the staging row holds then
+  HIPCHK(c, hipStreamIsCapturing(c->stream, &cap));
+  if (cap != hipStreamCaptureStatusNone) return fail(c, AE_EHIP, "ae_set_state: the stream is being captured");
+  int rc = wait_flag(c, &c->hm->imported, c->feat_seq);   // the staging row is free again (the call: 6 us, not 28)
+  if (rc) return rc;
+  memcpy(c->h_feat, feat, sizeof(float) * g.d_model);
+  (void)hipGetLastError();   // only this launch is judged
+  launch_set_state(c->h_feat_dev, g.d_model, c->F, c->hist + kv_len - 1, last_tok, pending, c->hm_dev, ++c->seq, c->stream);
+  HIPCHK(c, hipGetLastError());
+  c->feat_seq = c->seq;
   c->h_hist[kv_len - 1] = last_tok; c->h_hist[kv_len] = pending;
   c->kv_len = kv_len; c->dlen = kv_len - 1; c->nF = 1; c->pending = pending;
   c->have_pending = true; c->have_draft = c->have_verify = false; c->k_next_valid = false; c->cur_k = 0;
@@ -790,14 +828,15 @@ int ae_ldlp(ae_ctx *c, int *k_out, float *y_out) {
     enqueue_ldlp(c, c->kv_len - 1, c->nF - 1, false);
     int rc = read_state(c, true);
     if (rc) return rc;
-    c->k_next = c->h_st->k_next; c->y_next = c->h_st->y_next; c->k_next_valid = true;
+    c->k_next = c->hm->st.k_next; c->y_next = c->hm->st.y_next; c->k_next_valid = true;
   }
   *k_out = c->k_next;
   if (y_out) *y_out = c->y_next;
   return AE_OK;
 }
 
-int ae_draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draft, int32_t *out) {
+// poll_rule: the device's exit decisions are awaited token by token (ae_step)
+static int draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draft, int32_t *out, bool poll_rule) {
   if (!c) return AE_EINVAL;
   const ae_config &g = c->cfg;
   if (!c->have_pending) return fail(c, AE_ESTATE, "ae_draft: no pending token (prefill first)");
@@ -827,8 +866,12 @@ int ae_draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draf
   // reads the running sum back before every such token; device mode enqueues all k_max tokens
   // and lets the kernels of the tokens past k return at entry once the device-side rule says
   // stop (the verify block is then padded to k_max + 1 rows and ae_accept takes the drafted
-  // length from the device).
-  const bool dev_rule = g.ddd_enabled && c->ddd_mode == AE_DDD_DEVICE;
+  // length from the device).  Inside ae_step nothing else can happen meanwhile: there the host waits for the
+  // flag that the kernel behind each such token sets (about 8 us of an idle device; each token that is
+  // skipped would cost 10 launches of 3 us) and the block has its true length: 857 us instead of 1012 for a step of
+  // 2 tokens of at most 8, 4 layers of 7B.
+  const bool dev_rule = g.ddd_enabled && c->ddd_mode == AE_DDD_DEVICE && !poll_rule;
+  const bool poll = g.ddd_enabled && poll_rule;
   bool gated = false;
   int i = 0;
   for (; i < g.k_max; ++i) {
@@ -839,18 +882,24 @@ int ae_draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draf
       } else if (dev_rule) {
         c->gate = &c->st->draft_live;
         gated = true;
+      } else if (poll) {
+        HIPCHK(c, hipGetLastError());
+        int rc = wait_flag(c, &c->hm->decision, c->seq & 0x7fffffffu, 1);
+        if (rc) return rc;
+        if (!(c->hm->decision & 1u)) break;
       } else {
         c->gate = nullptr;
         int rc = read_state(c);
         if (rc) return rc;
-        if (!(c->h_st->cum_logp >= g.ddd_threshold)) break;
+        if (!(c->hm->st.cum_logp >= g.ddd_threshold)) break;
       }
     }
     if (i > 0) {  // chain: the head's previous output replaces the feature
       draft_rows(c, nullptr, 0, nullptr, 1, n - 1 + i, fh_row);
       fh_row = 0;
     }
-    draft_lm_head(c, fh_row, i, k);
+    if (poll) ++c->seq;
+    draft_lm_head(c, fh_row, i, k, poll);
   }
   c->gate = nullptr;
   k = i;   // tokens enqueued; with a gated tail the number drafted is st->draft_len <= k
@@ -863,13 +912,17 @@ int ae_draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draf
     int rc = read_state(c);
     if (rc) return rc;
     if (gated) {   // the caller synchronised anyway: from here on the host knows the length
-      k = c->h_st->draft_len;
+      k = c->hm->st.draft_len;
       c->cur_k = c->cur_k_last = k;
       c->k_on_device = false;
     }
-    memcpy(out, c->h_st->draft_ids, sizeof(int32_t) * k);
+    memcpy(out, c->hm->st.draft_ids, sizeof(int32_t) * k);
   }
   return AE_OK;
+}
+
+int ae_draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_draft, int32_t *out) {
+  return draft(c, k, override_ids, u_draft, out, false);
 }
 
 int ae_verify(ae_ctx *c, const int32_t *block_ids, int rows) {
@@ -914,19 +967,19 @@ int ae_accept(ae_ctx *c, const double *u, int *n_accepted, int32_t *bonus) {
   if (spec) enqueue_ldlp(c, n, 0, true);
   int rc = read_state(c, spec);
   if (rc) return rc;
-  const int acc = c->h_st->n_acc;
-  for (int i = 0; i <= acc; ++i) c->h_hist[n + i] = c->h_st->block[i];
+  const int acc = c->hm->st.n_acc;
+  for (int i = 0; i <= acc; ++i) c->h_hist[n + i] = c->hm->st.block[i];
   c->kv_len = n + 1 + acc;   // rollback: rows beyond the accepted prefix are dead
-  c->pending = c->h_st->bonus;
+  c->pending = c->hm->st.bonus;
   c->h_hist[c->kv_len] = c->pending;
-  memcpy(c->h_block.data(), c->h_st->block, sizeof(int32_t) * kMaxRows);
+  memcpy(c->h_block.data(), c->hm->st.block, sizeof(int32_t) * kMaxRows);
   c->nF = acc + 1;
-  if (c->k_on_device) c->cur_k_last = c->h_st->draft_len;   // padded block: the drafted length arrives here
+  if (c->k_on_device) c->cur_k_last = c->hm->st.draft_len;   // padded block: the drafted length arrives here
   c->k_on_device = false;
   c->have_verify = c->have_draft = false;
   c->cur_k = 0;
   c->k_next_valid = spec;
-  if (spec) { c->k_next = c->h_st->k_next; c->y_next = c->h_st->y_next; }
+  if (spec) { c->k_next = c->hm->st.k_next; c->y_next = c->hm->st.y_next; }
   if (n_accepted) *n_accepted = acc;
   if (bonus) *bonus = c->pending;
   return AE_OK;
@@ -946,10 +999,14 @@ int ae_step(ae_ctx *c, ae_step_io *io) {
     return rc;
   }
   if (prof) hipEventRecord(c->ev[1], s);
-  if ((rc = ae_draft(c, k, io->override_ids, io->u_draft, nullptr))) return rc;
-  k = c->cur_k;   // the DDD rule may have extended the draft (device rule: padded to k_max)
+  if ((rc = draft(c, k, io->override_ids, io->u_draft, nullptr, c->ddd_mode == AE_DDD_DEVICE))) return rc;
+  k = c->cur_k;   // the DDD rule may have extended the draft
   if (prof) hipEventRecord(c->ev[2], s);
   if ((rc = ae_verify(c, nullptr, k + 1))) return rc;
+  // with the rule on the device u_accept holds k_max + 1 uniforms, wherever the draft ended
+  if (c->cfg.ddd_enabled && c->ddd_mode == AE_DDD_DEVICE && c->cfg.temperature > 0.f && io->u_accept && k > 0)
+    for (int i = k + 1; i <= c->cfg.k_max; ++i)
+      if (!(io->u_accept[i] >= 0.0 && io->u_accept[i] < 1.0)) return fail(c, AE_EINVAL, "ae_accept: u outside [0,1)");
   if (prof) hipEventRecord(c->ev[3], s);
   int acc = 0;
   int32_t b = 0;
@@ -1017,14 +1074,27 @@ int ae_get_draft_logprob(ae_ctx *c, float *out) {
   if (!out) return fail(c, AE_EINVAL, "ae_get_draft_logprob: NULL output");
   int rc = read_state(c);
   if (rc) return rc;
-  *out = c->h_st->cum_logp;
+  *out = c->hm->st.cum_logp;
   return AE_OK;
 }
 int32_t ae_pending(const ae_ctx *c) { return c && c->have_pending ? c->pending : -1; }
 
+// One row of device floats to the caller, through pinned memory that the device writes (n <= c->row_floats): 4096
+// floats 10 us instead of 22-28 with a stream synchronisation and a copy, 32000 floats 15 instead of 16.5, 128256
+// floats 34-36 either way (page faults of the caller's memory).  A first
+// copy into fresh memory of the caller faults on every page: that happens while the device is at work.
 static int copy_out(ae_ctx *c, const float *src, size_t n, float *dst) {
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  HIPCHK(c, hipMemcpy(dst, src, n * sizeof(float), hipMemcpyDeviceToHost));
+  (void)hipGetLastError();   // only this launch is judged
+  const uint32_t *flags = (const uint32_t *)(c->h_rows + c->row_floats);
+  launch_export_row(src, n, c->h_rows_dev, (uint32_t *)(c->h_rows_dev + c->row_floats), ++c->seq, c->stream);
+  HIPCHK(c, hipGetLastError());
+  for (size_t i = 0; i < n; i += 1024) *(volatile float *)(dst + i) = *(volatile float *)(dst + i);
+  for (size_t p = 0; p * kExportPiece < n; ++p) {
+    int rc = wait_flag(c, flags + p, c->seq);
+    if (rc) return rc;
+    const size_t first = p * kExportPiece;
+    memcpy(dst + first, c->h_rows + first, (n - first < kExportPiece ? n - first : kExportPiece) * sizeof(float));
+  }
   return AE_OK;
 }
 

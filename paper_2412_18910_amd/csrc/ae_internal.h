@@ -43,6 +43,15 @@ struct DevState {
 };
 static_assert(offsetof(DevState, u_draft) % 8 == 0, "doubles must stay aligned");
 
+// Pinned host memory that the device writes and the host polls: a copy of the device state, and flag words that a
+// kernel sets behind its last write (release, system scope).  A flag holds the number of the request it answers.
+struct HostMirror {
+  DevState st;
+  alignas(64) uint32_t published;   // state copies
+  uint32_t imported;                // feature rows taken over (ae_set_state)
+  uint32_t decision;                // DDD rule behind a draft token: number << 1 | go on
+};
+
 // A kernel launched with a non-null gate pointer does nothing when *gate == 0.
 #define AE_GATE(gate)                          \
   do {                                         \
@@ -106,8 +115,15 @@ struct ae_ctx {
   double *prob = nullptr;          // T>0 scratch: segment / row statistics of the sampling kernels
   int32_t *hist = nullptr;         // device token history by slot
   ae::DevState *st = nullptr;      // device state
-  ae::DevState *h_st = nullptr;    // pinned host mirror of *st, written by the device (publish_state)
-  ae::DevState *h_st_dev = nullptr;   // the device's address of that mirror
+  ae::HostMirror *hm = nullptr;    // pinned host memory the device writes; hm_dev: its address on the device
+  ae::HostMirror *hm_dev = nullptr;
+  float *h_rows = nullptr;         // pinned: one exported row (logits, feature, K/V); h_rows_dev: on the device
+  float *h_rows_dev = nullptr;
+  float *h_feat = nullptr;         // pinned: the feature row of ae_set_state; read by request feat_seq
+  float *h_feat_dev = nullptr;
+  uint32_t feat_seq = 0;
+  size_t row_floats = 0;           // floats of that row, a multiple of kExportPiece; a flag word per piece follows it
+  uint32_t seq = 0;                // number of the last request to the device
 
   // dense prompt pass: chunk buffers, allocated at the first long prompt (float32: pxa normalised rows, pxh FFN
   // rows, pxcat draft head input, pxatt attention output; pxf and the partial sums are bf16 only)
@@ -164,12 +180,18 @@ void launch_accept_greedy(DevState *st, int32_t *hist, int kv_len, int rows, boo
 // row relative to the acceptance result in *st_nacc
 void launch_ldlp_in(const void *W, const float *bias, const void *emb, int dtype, const int32_t *hist, const float *F, int d,
                     int in_mode, int h, int slot, int f_row, const DevState *st_nacc, float *z0, hipStream_t s);
-// also copies the whole device state to `mirror` (device-visible pinned host memory)
+// also copies the whole device state to `mirror` and answers request `seq` there
 void launch_ldlp_tail(const float *z0, const void *w_res, int dtype, const float *b_res, const float *w_out,
-                      const float *b_out, int h, int n_res, int k_max, int cls, DevState *st, DevState *mirror,
-                      hipStream_t s);
-// *mirror = *st, written by the device itself
-void launch_publish_state(const DevState *st, DevState *mirror, hipStream_t s);
+                      const float *b_out, int h, int n_res, int k_max, int cls, DevState *st, HostMirror *mirror,
+                      uint32_t seq, hipStream_t s);
+// mirror->st = *st, written by the device itself, as the answer to request `seq`
+void launch_publish_state(const DevState *st, HostMirror *mirror, uint32_t seq, hipStream_t s);
+// F[0..d) = feat[0..d) (pinned host memory), hist2[0..2) = two ids, then mirror->imported = seq
+void launch_set_state(const float *feat, int d, float *F, int32_t *hist2, int32_t last_tok, int32_t pending, HostMirror *mirror,
+                      uint32_t seq, hipStream_t s);
+// dst[0..n) = src[0..n), dst in pinned host memory; flags[p] = seq behind piece p of kExportPiece floats
+constexpr size_t kExportPiece = 4096;
+void launch_export_row(const float *src, size_t n, float *dst, uint32_t *flags, uint32_t seq, hipStream_t s);
 void launch_rope_table(float2 *tab, int n_pos, int head_dim, float base, hipStream_t s);
 void launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 
@@ -251,6 +273,8 @@ struct DddFinish {
   const float *logits = nullptr;   // the token's logit row
   int NB = 0, k = 0;
   float inv_t = 1.f, theta = 0.f;
+  uint32_t *flag = nullptr;        // nullable: host word that receives seq << 1 | (the rule goes on)
+  uint32_t seq = 0;
 };
 void launch_argmax_finish(const float *val, const int32_t *idx, int NB, int rows, DevState *st, int pick_i, hipStream_t s,
                           const int32_t *gate = nullptr, DraftCat cat = DraftCat(), DddFinish ddd = DddFinish());

@@ -136,17 +136,57 @@ void launch_accept_greedy(DevState *st, int32_t *hist, int kv_len, int rows, boo
 }
 
 // The host reads the device state through a mirror in pinned host memory that the device
-// writes itself (no copy engine, no blit kernel): all threads of a workgroup call this behind
-// a barrier that follows the last write to *st; the words in [skip0, skip1) are left to the caller.
-__device__ __forceinline__ void publish_state(const DevState *st, DevState *mirror, int skip0 = 0, int skip1 = 0) {
+// writes itself (no copy engine, no blit kernel) and polls its flag word (a stream synchronisation takes
+// about 10 us longer to notice): all threads of a workgroup call this behind a barrier that follows the last
+// write to *st; the words in [skip0, skip1) have been written by thread 0.
+__device__ __forceinline__ void publish_state(const DevState *st, HostMirror *mirror, uint32_t seq, int skip0 = 0, int skip1 = 0) {
   const uint32_t *src = reinterpret_cast<const uint32_t *>(st);
-  uint32_t *dst = reinterpret_cast<uint32_t *>(mirror);
+  uint32_t *dst = reinterpret_cast<uint32_t *>(&mirror->st);
   for (int i = threadIdx.x; i < (int)(sizeof(DevState) / 4); i += blockDim.x)
     if (i < skip0 || i >= skip1) dst[i] = src[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(&mirror->published, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__global__ void publish_state_kernel(const DevState *st, DevState *mirror) { publish_state(st, mirror); }
-void launch_publish_state(const DevState *st, DevState *mirror, hipStream_t s) {
-  publish_state_kernel<<<1, 128, 0, s>>>(st, mirror);
+__global__ void publish_state_kernel(const DevState *st, HostMirror *mirror, uint32_t seq) { publish_state(st, mirror, seq); }
+void launch_publish_state(const DevState *st, HostMirror *mirror, uint32_t seq, hipStream_t s) {
+  publish_state_kernel<<<1, 128, 0, s>>>(st, mirror, seq);
+}
+
+// The state a sequence goes on from, out of pinned host memory (the host does not wait for it).
+__global__ __launch_bounds__(1024) void set_state_kernel(const float *feat, int d, float *F, int32_t *hist2, int32_t last_tok,
+                                                         int32_t pending, HostMirror *mirror, uint32_t seq) {
+  for (int i = threadIdx.x; i < d; i += 1024) F[i] = feat[i];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    hist2[0] = last_tok;
+    hist2[1] = pending;
+    __hip_atomic_store(&mirror->imported, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+void launch_set_state(const float *feat, int d, float *F, int32_t *hist2, int32_t last_tok, int32_t pending, HostMirror *mirror,
+                      uint32_t seq, hipStream_t s) {
+  set_state_kernel<<<1, 1024, 0, s>>>(feat, d, F, hist2, last_tok, pending, mirror, seq);
+}
+
+// One row to pinned host memory, a workgroup and a flag per piece: the host copies a piece on while the next ones are
+// on their way.
+__global__ __launch_bounds__(256) void export_row_kernel(const float *src, size_t n, float *dst, uint32_t *flags, uint32_t seq) {
+  const size_t first = blockIdx.x * kExportPiece, end = first + kExportPiece < n ? first + kExportPiece : n;
+  size_t i = first + threadIdx.x;
+  if ((reinterpret_cast<uintptr_t>(src) & 15) == 0) {   // else: a row of an odd vocabulary
+#pragma unroll
+    for (size_t k = first + threadIdx.x * 4; k < first + kExportPiece; k += 1024)
+      if (k + 4 <= end) *reinterpret_cast<float4 *>(dst + k) = *reinterpret_cast<const float4 *>(src + k);
+    i += (end - first) / 4 * 4;
+  }
+  for (; i < end; i += 256) dst[i] = src[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flags + blockIdx.x, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+void launch_export_row(const float *src, size_t n, float *dst, uint32_t *flags, uint32_t seq, hipStream_t s) {
+  export_row_kernel<<<(int)((n + kExportPiece - 1) / kExportPiece), 256, 0, s>>>(src, n, dst, flags, seq);
 }
 
 // ------------------------------------------------------------------ LDLP (Eq. 3)
@@ -201,7 +241,8 @@ void launch_ldlp_in(const void *W, const float *bias, const void *emb, int dtype
 template <typename T>
 __global__ __launch_bounds__(1024) void ldlp_tail_kernel(const float *z0, const T *w_res, const float *b_res,
                                                          const float *w_out, const float *b_out, int h, int n_res,
-                                                         int k_max, int cls, DevState *st, DevState *mirror) {
+                                                         int k_max, int cls, DevState *st, HostMirror *mirror,
+                                                         uint32_t seq) {
   __shared__ float z[kMaxLdlpHidden];
   __shared__ float t[kMaxLdlpHidden];
   const int i = threadIdx.x;
@@ -242,23 +283,23 @@ __global__ __launch_bounds__(1024) void ldlp_tail_kernel(const float *z0, const 
     }
     st->y_next = best_y;
     st->k_next = k;
-    mirror->y_next = best_y;
-    mirror->k_next = k;
+    mirror->st.y_next = best_y;
+    mirror->st.k_next = k;
   }
   // the rest of the state (acceptance result, block ids, draft bookkeeping) was written by earlier kernels
   static_assert(offsetof(DevState, y_next) == offsetof(DevState, k_next) + 4, "k_next and y_next are adjacent words");
-  publish_state(st, mirror, offsetof(DevState, k_next) / 4, offsetof(DevState, y_next) / 4 + 1);
+  publish_state(st, mirror, seq, offsetof(DevState, k_next) / 4, offsetof(DevState, y_next) / 4 + 1);
 }
 
 void launch_ldlp_tail(const float *z0, const void *w_res, int dtype, const float *b_res, const float *w_out,
-                      const float *b_out, int h, int n_res, int k_max, int cls, DevState *st, DevState *mirror,
-                      hipStream_t s) {
+                      const float *b_out, int h, int n_res, int k_max, int cls, DevState *st, HostMirror *mirror,
+                      uint32_t seq, hipStream_t s) {
   if (dtype == AE_BF16)
     ldlp_tail_kernel<bf16_t><<<1, 1024, 0, s>>>(z0, (const bf16_t *)w_res, b_res, w_out, b_out, h, n_res, k_max, cls, st,
-                                                mirror);
+                                                mirror, seq);
   else
     ldlp_tail_kernel<float><<<1, 1024, 0, s>>>(z0, (const float *)w_res, b_res, w_out, b_out, h, n_res, k_max, cls, st,
-                                               mirror);
+                                               mirror, seq);
 }
 
 // ------------------------------------------------------------------ set-up helpers

@@ -308,7 +308,9 @@ __device__ void ddd_finish(const DddFinish &d, int32_t tok, int i, DevState *st)
     st->draft_lp[i] = lp;
     st->cum_logp = cum;
     st->draft_len = i + 1;
-    if (i + 1 >= d.k && !(cum >= d.theta)) st->draft_live = 0;
+    const bool stop = i + 1 >= d.k && !(cum >= d.theta);
+    if (stop) st->draft_live = 0;
+    if (d.flag) __hip_atomic_store(d.flag, d.seq << 1 | (stop ? 0u : 1u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
