@@ -146,25 +146,28 @@ void run_layer(ae_ctx *c, int li, float *x, int rows, int pos0, const float *nex
   c->Pa = Pd;
 }
 
-// Target forward of `rows` tokens (device ids) at slots pos0..; features -> F rows 0..rows-1;
+// Target forward of `rows` tokens at slots pos0..; features -> F rows 0..rows-1;
 // logits (+ per-row argmax into st->argmax) for rows >= logit_from.
-void target_forward(ae_ctx *c, const int32_t *ids_dev, int rows, int pos0, int logit_from) {
+void target_forward(ae_ctx *c, const BlockIds &ids, int rows, int pos0, int logit_from) {
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
   const int nr = rows - logit_from;
-  if (c->fast) launch_embed_packed(c->tok_emb, ids_dev, rows, g.d_model, c->layers[0].attn_norm, c->x, c->xp_a, c->ssq_a, s);
-  else launch_embed_f32(c->tok_emb, ids_dev, rows, g.d_model, c->layers[0].attn_norm, c->x, c->xp_a, c->ssq_a, s);
+  if (c->fast) launch_embed_packed(c->tok_emb, ids, rows, g.d_model, c->layers[0].attn_norm, c->x, c->xp_a, c->ssq_a, s);
+  else launch_embed_f32(c->tok_emb, ids, rows, g.d_model, c->layers[0].attn_norm, c->x, c->xp_a, c->ssq_a, s);
   c->Pa = 1;
   for (int l = 0; l < g.n_layers; ++l)
     run_layer(c, l, c->x, rows, pos0, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : c->final_norm);
-  launch_rmsnorm(c->x, c->final_norm, rows, g.d_model, g.rms_eps, c->F, s);   // feature rows (LDLP, draft head)
+  NormRows feat;   // feature rows (LDLP, draft head)
+  feat.x = c->x; feat.gain = c->final_norm; feat.out = c->F; feat.rows = rows; feat.d = g.d_model; feat.eps = g.rms_eps;
   if (nr > 0) {
     GemmLaunch lm;   // final RMSNorm folded into the LM head
     lm.W = &c->lm_head; lm.Xp = c->xp_a; lm.ldx = g.d_model; lm.rows = nr; lm.row0 = logit_from; lm.ssq_in = c->ssq_a; lm.P_in = c->Pa;
     lm.eps = g.rms_eps; lm.epi = EPI_STORE; lm.Y[0] = c->logits; lm.ldy[0] = g.vocab; lm.seg_N[0] = g.vocab;
     lm.amax_val = c->amax_val; lm.amax_idx = c->amax_idx;   // per-row argmax rides on the epilogue
     gemm(c, lm);
-    launch_argmax_finish(c->amax_val, c->amax_idx, (g.vocab + 15) / 16, nr, c->st, -1, s);
+    launch_argmax_finish(c->amax_val, c->amax_idx, (g.vocab + 15) / 16, nr, c->st, -1, s, nullptr, DraftCat(), DddFinish(), feat);
+  } else {
+    launch_rmsnorm(feat.x, feat.gain, rows, feat.d, feat.eps, feat.out, s);
   }
 }
 
@@ -172,15 +175,15 @@ void target_forward(ae_ctx *c, const int32_t *ids_dev, int rows, int pos0, int l
 // Leaves the head's outputs in x rows 0..rows-1 and in the first halves of xp_cat's rows.
 // chained_row >= 0 (one row): the input is already in row chained_row of xp_cat, the
 // head's previous output (left there by its down projection) and the embedding of the token
-// picked from it (left there by the kernel that picked it).
+// picked from it (left there by the kernel that picked it).  in: the inputs of a draft that begins here.
 void draft_rows(ae_ctx *c, const float *feat, int feat_ld, const int32_t *next_ids_dev, int rows, int slot0,
-                int chained_row = -1) {
+                int chained_row = -1, const DraftInputs &in = DraftInputs()) {
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
   const int d = g.d_model;
   if (chained_row < 0) {
-    if (c->fast) launch_draft_cat_packed(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate);
-    else launch_draft_cat_f32(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate);
+    if (c->fast) launch_draft_cat_packed(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate, in);
+    else launch_draft_cat_f32(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate, in);
   }
   GemmLaunch fc;
   fc.W = &c->draft_fc; fc.Xp = c->xp_cat; fc.ldx = 2 * d; fc.rows = rows; fc.epi = EPI_STORE; fc.bias = c->draft_fc_b;
@@ -225,11 +228,11 @@ void draft_lm_head(ae_ctx *c, int row, int i, int k, bool flag_decision) {
   }
 }
 
-void enqueue_ldlp(ae_ctx *c, int slot, int f_row, bool relative_to_accept) {
+void enqueue_ldlp(ae_ctx *c, int slot, int f_row, bool relative_to_accept, const GreedyAccept &ga = GreedyAccept()) {
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
   launch_ldlp_in(c->ldlp_in.rowmajor, c->ldlp_b_in, c->tok_emb, g.dtype, c->hist, c->F, g.d_model, g.ldlp_in_mode,
-                 g.ldlp_hidden, slot, f_row, relative_to_accept ? c->st : nullptr, c->ldlp_z, s);
+                 g.ldlp_hidden, slot, f_row, relative_to_accept ? c->st : nullptr, ga, c->ldlp_z, s);
   launch_ldlp_tail(c->ldlp_z, c->ldlp_w_res, g.dtype, c->ldlp_b_res, c->ldlp_w_out, c->ldlp_b_out, g.ldlp_hidden,
                    g.ldlp_n_res, g.k_max, g.ldlp_cls, c->st, c->hm_dev, ++c->seq, s);
 }
@@ -388,7 +391,9 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   hipStream_t s = c->stream;
   const int d = g.d_model, dq = g.n_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn;
   float *xn = (float *)c->pxa, *att = (float *)c->pxatt;
-  launch_embed_f32(c->tok_emb, c->hist + p0, rows, d, nullptr, c->px, nullptr, nullptr, s);
+  BlockIds ids;
+  ids.ids = c->hist + p0;
+  launch_embed_f32(c->tok_emb, ids, rows, d, nullptr, c->px, nullptr, nullptr, s);
   launch_rmsnorm(c->px, c->layers[0].attn_norm, rows, d, g.rms_eps, xn, s);
   auto qkv_pass = [&](int li, int nrows, bool with_q) {   // projections, rotary embedding, cache append
     GemmLaunch qkv;
@@ -416,7 +421,7 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   }
   if (drows > 0) {
     // Eq. 2 catch-up of prompt slots: only the head's K/V rows are ever read again
-    launch_draft_cat_f32(xn, d, c->tok_emb, c->hist + p0 + 1, drows, d, c->pxcat, s);
+    launch_draft_cat_f32(xn, d, c->tok_emb, c->hist + p0 + 1, drows, d, c->pxcat, s, nullptr, DraftInputs());
     if (c->draft_fc_b) {
       project(&c->draft_fc, c->pxcat, 2 * d, drows, c->draft_fc_b, att, c->layers[g.n_layers].attn_norm);
     } else {
@@ -717,7 +722,9 @@ int ae_prefill(ae_ctx *c, const int32_t *ids, int n) {
       // keep the number of launches in flight bounded (a block is ~200 launches): tools that
       // keep a record per outstanding dispatch have been seen to fail on tens of thousands
       if (p0 > 0 && (p0 / kMaxRows) % 16 == 0) HIPCHK(c, hipStreamSynchronize(c->stream));
-      target_forward(c, c->hist + p0, rows, p0, last ? rows - 1 : rows);
+      BlockIds ids_p;
+      ids_p.ids = c->hist + p0;
+      target_forward(c, ids_p, rows, p0, last ? rows - 1 : rows);
       const int drows = last ? rows - 1 : rows;  // slots whose next token is in the prompt
       if (drows > 0) draft_rows(c, c->F, g.d_model, c->hist + p0 + 1, drows, p0);
       c->nF = rows;
@@ -856,9 +863,15 @@ static int draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_
       if (!(u_draft[i] >= 0.0 && u_draft[i] < 1.0)) return fail(c, AE_EINVAL, "ae_draft: u_draft outside [0,1)");
   hipStream_t s = c->stream;
   // override table (-1 = keep the head's own token), chain gate reset and the sampling uniforms
-  launch_set_draft_inputs(c->st, override_ids, n_ov, sampling ? u_draft : nullptr, n_ov, s);
+  DraftInputs in;
+  in.st = c->st;
+  in.n_u = sampling ? n_ov : 0;
+  for (int i = 0; i < kMaxRows; ++i) {
+    in.override_ids[i] = override_ids && i < n_ov ? override_ids[i] : -1;
+    in.u[i] = i < in.n_u ? u_draft[i] : 0.0;
+  }
   // catch-up over the slots validated by the last accept: true feature + following token
-  draft_rows(c, c->F + (size_t)(c->nF - catch_rows) * g.d_model, g.d_model, c->hist + c->dlen + 1, catch_rows, c->dlen);
+  draft_rows(c, c->F + (size_t)(c->nF - catch_rows) * g.d_model, g.d_model, c->hist + c->dlen + 1, catch_rows, c->dlen, -1, in);
   c->dlen = n;
   int fh_row = catch_rows - 1;
   // AdaEAGLE-DDD (Sec. 3.4, 4.2): past the predicted length the head exits unless the
@@ -931,16 +944,18 @@ int ae_verify(ae_ctx *c, const int32_t *block_ids, int rows) {
   if (!c->have_pending) return fail(c, AE_ESTATE, "ae_verify: no pending token (prefill first)");
   if (rows < 1 || rows > g.k_max + 1) return fail(c, AE_EINVAL, "ae_verify: rows outside [1, k_max+1]");
   if (c->kv_len + rows > g.n_ctx_max) return fail(c, AE_EINVAL, "ae_verify: KV capacity exceeded");
-  hipStream_t s = c->stream;
+  BlockIds ids;
+  ids.st = c->st;
   if (block_ids) {
     if (!ids_ok(c, block_ids, rows)) return fail(c, AE_EINVAL, "ae_verify: token id out of range");
-    launch_set_block(c->st, block_ids, rows, s);
+    for (int i = 0; i < rows; ++i) ids.v[i] = block_ids[i];
   } else {
     if (!c->have_draft || rows != c->cur_k + 1)
       return fail(c, AE_ESTATE, "ae_verify: implicit block needs a draft of rows-1 tokens");
-    launch_build_block(c->st, c->hist, c->kv_len, c->cur_k, s);
+    ids.hist = c->hist;
+    ids.kv_len = c->kv_len;
   }
-  target_forward(c, c->st->block, rows, c->kv_len, 0);
+  target_forward(c, ids, rows, c->kv_len, 0);
   c->block_rows = rows;
   c->have_verify = true;
   return AE_OK;
@@ -959,12 +974,15 @@ int ae_accept(ae_ctx *c, const double *u, int *n_accepted, int32_t *bonus) {
     launch_set_u_accept(c->st, u, rows, c->stream);
     launch_accept_sample(c->logits, c->dlogits, g.vocab, rows - 1, c->k_on_device, g.temperature, c->st, c->hist, n,
                          c->prob, c->stream);
-  } else {
-    launch_accept_greedy(c->st, c->hist, n, rows, c->k_on_device, c->stream);
   }
   // Alg. 1 predicts the next draft length right after the verification
   const bool spec = c->have_draft;
-  if (spec) enqueue_ldlp(c, n, 0, true);
+  GreedyAccept ga;
+  if (!(g.temperature > 0.f)) {
+    ga.st = c->st; ga.hist = c->hist; ga.kv_len = n; ga.rows = rows; ga.k_on_device = c->k_on_device;
+  }
+  if (spec) enqueue_ldlp(c, n, 0, true, ga);
+  else if (ga.st) launch_accept_greedy(c->st, c->hist, n, rows, c->k_on_device, c->stream);
   int rc = read_state(c, spec);
   if (rc) return rc;
   const int acc = c->hm->st.n_acc;

@@ -164,22 +164,45 @@ struct ae_ctx {
 
 namespace ae {
 
+// Where the embedding kernels take the ids of their rows from: a device array; or the block of a verification, put
+// together and recorded in st->block on the way: host values (v), or hist[kv_len] and the draft tokens.
+struct BlockIds {
+  const int32_t *ids = nullptr;
+  DevState *st = nullptr;
+  const int32_t *hist = nullptr;
+  int32_t kv_len = 0, v[kMaxRows] = {};
+};
+// Host inputs of a draft (-1: no override); they travel as kernel arguments.  st == nullptr: none.
+struct DraftInputs {
+  DevState *st = nullptr;
+  int32_t override_ids[kMaxRows] = {}, n_u = 0;
+  double u[kMaxRows] = {};
+};
+// Rows that argmax_finish normalises beside its own work (the features of a forward).
+struct NormRows {
+  const float *x = nullptr, *gain = nullptr;
+  float *out = nullptr;
+  int rows = 0, d = 0;
+  float eps = 0.f;
+};
+// Greedy acceptance evaluated by the LDLP's input kernel (st == nullptr: not).
+struct GreedyAccept {
+  DevState *st = nullptr;
+  int32_t *hist = nullptr;
+  int kv_len = 0, rows = 0, k_on_device = 0;
+};
+
 // ---- dtype-independent kernels (kernels_generic.hip); all launches are asynchronous on `s` ----
 void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s,
                     const int32_t *gate = nullptr);
-// Host arrays (override ids: -1 keeps the head's own token; uniforms; explicit block ids) are
-// passed by value inside the launch; the pointers are read before the call returns.
-void launch_set_draft_inputs(DevState *st, const int32_t *override_ids, int n_ov, const double *u_draft, int n_u,
-                             hipStream_t s);
-void launch_set_block(DevState *st, const int32_t *ids, int rows, hipStream_t s);
 void launch_set_u_accept(DevState *st, const double *u, int rows, hipStream_t s);
-void launch_build_block(DevState *st, const int32_t *hist, int kv_len, int k, hipStream_t s);
 // k_on_device: the draft length is st->draft_len (the block is padded to `rows` rows)
 void launch_accept_greedy(DevState *st, int32_t *hist, int kv_len, int rows, bool k_on_device, hipStream_t s);
 // z0 = W_in [e ; f] + b_in (Eq. 3 input layer), e and f read in place; st_nacc != nullptr: slot and
-// row relative to the acceptance result in *st_nacc
+// row relative to the acceptance result in *st_nacc; ga.st: the greedy acceptance is evaluated here first
 void launch_ldlp_in(const void *W, const float *bias, const void *emb, int dtype, const int32_t *hist, const float *F, int d,
-                    int in_mode, int h, int slot, int f_row, const DevState *st_nacc, float *z0, hipStream_t s);
+                    int in_mode, int h, int slot, int f_row, const DevState *st_nacc, const GreedyAccept &ga, float *z0,
+                    hipStream_t s);
 // also copies the whole device state to `mirror` and answers request `seq` there
 void launch_ldlp_tail(const float *z0, const void *w_res, int dtype, const float *b_res, const float *w_out,
                       const float *b_out, int h, int n_res, int k_max, int cls, DevState *st, HostMirror *mirror,
@@ -277,13 +300,14 @@ struct DddFinish {
   uint32_t seq = 0;
 };
 void launch_argmax_finish(const float *val, const int32_t *idx, int NB, int rows, DevState *st, int pick_i, hipStream_t s,
-                          const int32_t *gate = nullptr, DraftCat cat = DraftCat(), DddFinish ddd = DddFinish());
+                          const int32_t *gate = nullptr, DraftCat cat = DraftCat(), DddFinish ddd = DddFinish(),
+                          const NormRows &norm = NormRows());
 void launch_pick_draft_packed(DevState *st, int i, hipStream_t s, const int32_t *gate, DraftCat cat, DddFinish ddd);
-void launch_embed_packed(const void *emb, const int32_t *ids_dev, int rows, int d, const float *gain, float *x,
+void launch_embed_packed(const void *emb, const BlockIds &ids, int rows, int d, const float *gain, float *x,
                          void *Xp, float *ssq, hipStream_t s);
 void launch_pack_rows(const float *src, int ld, int rows, int K, const float *gain, void *Xp, hipStream_t s);
 void launch_draft_cat_packed(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d,
-                             void *Xp, hipStream_t s, const int32_t *gate = nullptr);
+                             void *Xp, hipStream_t s, const int32_t *gate, const DraftInputs &in);
 
 // ---- dense prompt pass (kernels_dense.hip); packed buffers hold RB row-blocks ----
 // Same GemmLaunch as the decode GEMM (rows = rows of the chunk, row0 unused); rinv != nullptr
@@ -313,9 +337,9 @@ void launch_attention_f32(const float *q, int rows, int pos0, const ae_config &c
 int attn_f32_chunk_keys();   // keys per split-KV workgroup
 void launch_attention_prefill_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
                                   float *out, hipStream_t s);
-void launch_embed_f32(const void *emb, const int32_t *ids_dev, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
+void launch_embed_f32(const void *emb, const BlockIds &ids, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
                       hipStream_t s);
 void launch_draft_cat_f32(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d, void *cat,
-                          hipStream_t s, const int32_t *gate = nullptr);
+                          hipStream_t s, const int32_t *gate, const DraftInputs &in);
 
 }  // namespace ae

@@ -20,6 +20,7 @@
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
 #include "packed.h"
+#include "step_inputs.h"
 
 namespace ae {
 
@@ -803,11 +804,11 @@ void launch_attention_prefill_f32(const float *q, int rows, int pos0, const ae_c
 
 // ------------------------------------------------------------------ row producers
 // Embedding rows -> residual stream, x * gain and the row's sum of x^2 (gain == nullptr: the rows alone)
-__global__ __launch_bounds__(256) void embed_f32_kernel(const float *emb, const int32_t *ids, int d, const float *gain, float *x,
+__global__ __launch_bounds__(256) void embed_f32_kernel(const float *emb, const BlockIds ids, int d, const float *gain, float *x,
                                                         float *Xo, float *ssq) {
   __shared__ float red[4];
   const int r = blockIdx.x;
-  const float *src = emb + (size_t)ids[r] * d;
+  const float *src = emb + (size_t)block_id(ids, r) * d;
   float ss = 0.f;
   for (int k = threadIdx.x * 4; k < d; k += 1024) {
     const float4 v = *reinterpret_cast<const float4 *>(src + k);
@@ -826,16 +827,18 @@ __global__ __launch_bounds__(256) void embed_f32_kernel(const float *emb, const 
   if (threadIdx.x == 0) ssq[r] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-void launch_embed_f32(const void *emb, const int32_t *ids_dev, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
+void launch_embed_f32(const void *emb, const BlockIds &ids, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
                       hipStream_t s) {
-  embed_f32_kernel<<<rows, 256, 0, s>>>((const float *)emb, ids_dev, d, gain, x, (float *)Xo, ssq);
+  embed_f32_kernel<<<rows, 256, 0, s>>>((const float *)emb, ids, d, gain, x, (float *)Xo, ssq);
 }
 
 // cat[r] = [feature row r ; embedding of the token that FOLLOWS slot r]  (Sec. 2.2)
 __global__ __launch_bounds__(256) void draft_cat_f32_kernel(const float *feat, int feat_ld, const float *emb,
-                                                            const int32_t *next_ids, int d, float *cat, const int32_t *gate) {
+                                                            const int32_t *next_ids, int d, float *cat, const int32_t *gate,
+                                                            const DraftInputs in) {
   AE_GATE(gate);
   const int r = blockIdx.x;
+  if (r == 0 && in.st) store_draft_inputs(in);
   const float *e = emb + (size_t)next_ids[r] * d, *f = feat + (size_t)r * feat_ld;
   float *o = cat + (size_t)r * 2 * d;
   for (int k = threadIdx.x * 4; k < d; k += 1024) {
@@ -845,8 +848,8 @@ __global__ __launch_bounds__(256) void draft_cat_f32_kernel(const float *feat, i
 }
 
 void launch_draft_cat_f32(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d, void *cat,
-                          hipStream_t s, const int32_t *gate) {
-  draft_cat_f32_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const float *)emb, next_ids, d, (float *)cat, gate);
+                          hipStream_t s, const int32_t *gate, const DraftInputs &in) {
+  draft_cat_f32_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const float *)emb, next_ids, d, (float *)cat, gate, in);
 }
 
 }  // namespace ae

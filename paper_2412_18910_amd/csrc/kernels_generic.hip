@@ -1,6 +1,7 @@
 // Small kernels of the decode step shared by the bf16 and the float32 configuration (gfx950,
 // wave64): RMSNorm, step inputs, greedy acceptance, LDLP, set-up.
 #include "ae_internal.h"
+#include "step_inputs.h"
 
 namespace ae {
 
@@ -40,24 +41,8 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x));
 // out = (x / sqrt(mean(x^2) + eps)) * g, one workgroup per row
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *x, const float *g, int d, float eps, float *out,
                                                       const int32_t *gate) {
-  __shared__ float red[4];
   AE_GATE(gate);
-  const float *xr = x + (size_t)blockIdx.x * d;
-  float ss = 0.f;
-  for (int i = threadIdx.x * 4; i < d; i += 1024) {   // d is a multiple of 8
-    const float4 v = *reinterpret_cast<const float4 *>(xr + i);
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-  }
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  const float tot = (red[0] + red[1]) + (red[2] + red[3]);
-  const float r = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int i = threadIdx.x * 4; i < d; i += 1024) {
-    const float4 v = *reinterpret_cast<const float4 *>(xr + i), gn = *reinterpret_cast<const float4 *>(g + i);
-    *reinterpret_cast<float4 *>(out + (size_t)blockIdx.x * d + i) =
-        make_float4((v.x * r) * gn.x, (v.y * r) * gn.y, (v.z * r) * gn.z, (v.w * r) * gn.w);
-  }
+  rmsnorm_row(x + (size_t)blockIdx.x * d, g, d, eps, out + (size_t)blockIdx.x * d);
 }
 
 void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s,
@@ -68,39 +53,7 @@ void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, 
 // ------------------------------------------------------------------ tiny control kernels
 // Small host values reach the device state as kernel arguments: the launch carries them, so no
 // staging buffer has to outlive the call and no copy engine is involved.
-struct HostIds { int32_t v[kMaxRows]; };
 struct HostUniforms { double v[kMaxRows]; };
-
-__global__ void set_draft_inputs_kernel(DevState *st, HostIds ov, HostUniforms u, int n_u) {
-  const int t = threadIdx.x;
-  if (t < kMaxRows) {
-    st->override_ids[t] = ov.v[t];
-    if (t < n_u) st->u_draft[t] = u.v[t];
-  }
-  if (t == 0) {
-    st->draft_live = 1;
-    st->draft_len = 0;
-  }
-}
-void launch_set_draft_inputs(DevState *st, const int32_t *override_ids, int n_ov, const double *u_draft, int n_u,
-                             hipStream_t s) {
-  HostIds ov;
-  HostUniforms u;
-  for (int i = 0; i < kMaxRows; ++i) {
-    ov.v[i] = (override_ids && i < n_ov) ? override_ids[i] : -1;
-    u.v[i] = (u_draft && i < n_u) ? u_draft[i] : 0.0;
-  }
-  set_draft_inputs_kernel<<<1, 64, 0, s>>>(st, ov, u, u_draft ? n_u : 0);
-}
-
-__global__ void set_block_kernel(DevState *st, HostIds ids, int rows) {
-  if ((int)threadIdx.x < rows) st->block[threadIdx.x] = ids.v[threadIdx.x];
-}
-void launch_set_block(DevState *st, const int32_t *ids, int rows, hipStream_t s) {
-  HostIds h;
-  for (int i = 0; i < kMaxRows; ++i) h.v[i] = i < rows ? ids[i] : 0;
-  set_block_kernel<<<1, 64, 0, s>>>(st, h, rows);
-}
 
 __global__ void set_u_accept_kernel(DevState *st, HostUniforms u, int rows) {
   if ((int)threadIdx.x < rows) st->u_accept[threadIdx.x] = u.v[threadIdx.x];
@@ -111,28 +64,14 @@ void launch_set_u_accept(DevState *st, const double *u, int rows, hipStream_t s)
   set_u_accept_kernel<<<1, 64, 0, s>>>(st, h, rows);
 }
 
-__global__ void build_block_kernel(DevState *st, const int32_t *hist, int kv_len, int k) {
-  if (threadIdx.x == 0) st->block[0] = hist[kv_len];
-  if ((int)threadIdx.x < k) st->block[1 + threadIdx.x] = st->draft_ids[threadIdx.x];
-}
-void launch_build_block(DevState *st, const int32_t *hist, int kv_len, int k, hipStream_t s) {
-  build_block_kernel<<<1, 64, 0, s>>>(st, hist, kv_len, k);
-}
-
 // Greedy acceptance (longest draft prefix equal to the target argmax, then the target's
-// own token) and the token-history side of the rollback.
+// own token) and the token-history side of the rollback, where no LDLP follows (one wave).
 __global__ void accept_greedy_kernel(DevState *st, int32_t *hist, int kv_len, int rows, int k_on_device) {
-  const int k = k_on_device ? min(st->draft_len, rows - 1) : rows - 1;
-  int acc = 0;
-  while (acc < k && st->block[1 + acc] == st->argmax[acc]) ++acc;
-  const int32_t bonus = st->argmax[acc];
-  for (int i = 0; i <= acc; ++i) hist[kv_len + i] = st->block[i];
-  hist[kv_len + 1 + acc] = bonus;
-  st->n_acc = acc;
-  st->bonus = bonus;
+  const int acc = greedy_accepted(st, k_on_device ? min(st->draft_len, rows - 1) : rows - 1);
+  if (threadIdx.x == 0) greedy_record(st, hist, kv_len, acc);
 }
 void launch_accept_greedy(DevState *st, int32_t *hist, int kv_len, int rows, bool k_on_device, hipStream_t s) {
-  accept_greedy_kernel<<<1, 1, 0, s>>>(st, hist, kv_len, rows, k_on_device ? 1 : 0);
+  accept_greedy_kernel<<<1, 64, 0, s>>>(st, hist, kv_len, rows, k_on_device ? 1 : 0);
 }
 
 // The host reads the device state through a mirror in pinned host memory that the device
@@ -193,23 +132,33 @@ void launch_export_row(const float *src, size_t n, float *dst, uint32_t *flags, 
 // Input layer z0 = W_in u + b_in with u = [e ; f] (in_mode 0) or f (in_mode 1) read in place:
 // e = embedding of the last validated token (hist[slot]), f = its feature row F[f_row].  When
 // use_nacc is set, slot and row are taken relative to the acceptance result that an earlier
-// kernel left in *st.  One wave per output, lanes stride over the input in 8-element pieces
+// kernel left in *st; with ga.st set it is the greedy one, which every wave works out for itself (one load
+// of block and argmax) and the first workgroup records.  One wave per output, lanes stride over the input in 8-element pieces
 // (the summation order of the generic GEMM).
 template <typename T>
 __global__ __launch_bounds__(256) void ldlp_in_kernel(const T *W, const float *bias, const T *emb, const int32_t *hist,
                                                       const float *F, int d, int in_mode, int h, int slot, int f_row,
-                                                      int use_nacc, const DevState *st, float *z0) {
+                                                      int use_nacc, const DevState *st, const GreedyAccept ga, float *z0) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = blockIdx.x * 4 + wave;
+  int add = 0;
+  int32_t tok;
+  if (ga.st) {
+    add = greedy_accepted(ga.st, ga.k_on_device ? min(ga.st->draft_len, ga.rows - 1) : ga.rows - 1);
+    tok = ga.st->block[add];
+    if (blockIdx.x == 0 && threadIdx.x == 0) greedy_record(ga.st, ga.hist, ga.kv_len, add);
+  } else {
+    if (use_nacc) add = st->n_acc;
+    tok = hist[slot + add];
+  }
   if (n >= h) return;
-  const int add = use_nacc ? st->n_acc : 0;
   const float *f = F + (size_t)(f_row + add) * d;
-  const T *e = emb + (size_t)hist[slot + add] * d;
+  const T *e = emb + (size_t)tok * d;
   const int K = in_mode == 0 ? 2 * d : d;
   const T *wrow = W + (size_t)n * K;
   float acc = 0.f;
   // unrolled so that several iterations' loads are in flight; the products still join acc in index order
-#pragma unroll 4
+#pragma unroll 8
   for (int k0 = lane * 8; k0 < K; k0 += 512) {
     float w[8], x[8];
     ld8(wrow + k0, w);
@@ -223,15 +172,16 @@ __global__ __launch_bounds__(256) void ldlp_in_kernel(const T *W, const float *b
 }
 
 void launch_ldlp_in(const void *W, const float *bias, const void *emb, int dtype, const int32_t *hist, const float *F, int d,
-                    int in_mode, int h, int slot, int f_row, const DevState *st_nacc, float *z0, hipStream_t s) {
+                    int in_mode, int h, int slot, int f_row, const DevState *st_nacc, const GreedyAccept &ga, float *z0,
+                    hipStream_t s) {
   const int use = st_nacc != nullptr;
   const dim3 grid((h + 3) / 4);
   if (dtype == AE_BF16)
     ldlp_in_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)W, bias, (const bf16_t *)emb, hist, F, d, in_mode, h, slot,
-                                                f_row, use, st_nacc, z0);
+                                                f_row, use, st_nacc, ga, z0);
   else
     ldlp_in_kernel<float><<<grid, 256, 0, s>>>((const float *)W, bias, (const float *)emb, hist, F, d, in_mode, h, slot,
-                                               f_row, use, st_nacc, z0);
+                                               f_row, use, st_nacc, ga, z0);
 }
 
 // z0 = W_in u + b_in comes from the GEMM; here: residual blocks z += silu(W_r z + b_r),

@@ -28,6 +28,7 @@
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
 #include "packed.h"
+#include "step_inputs.h"
 
 namespace ae {
 
@@ -317,14 +318,21 @@ __device__ void ddd_finish(const DddFinish &d, int32_t tok, int i, DevState *st)
 // Final argmax over the LM head's row-block partials (lowest token id wins ties), one
 // workgroup per row.  pick_i >= 0 (draft head, one row): also applies the caller's override
 // table, records draft token pick_i and, when cat.Xp is set, writes that token's embedding into
-// the draft head's packed input row for the next chained forward.
+// the draft head's packed input row for the next chained forward.  Workgroups behind the first n_am
+// rows normalise the rows of `norm`.
 __global__ __launch_bounds__(256) void argmax_finish_kernel(const float *val, const int32_t *idx, int NB, DevState *st,
-                                                            int pick_i, const int32_t *gate, DraftCat cat, DddFinish ddd) {
+                                                            int pick_i, const int32_t *gate, DraftCat cat, DddFinish ddd,
+                                                            int n_am, NormRows norm) {
   __shared__ float bv[4];
   __shared__ int bi[4];
   __shared__ int32_t tok_s;
   AE_GATE(gate);
   const int row = blockIdx.x;
+  if (row >= n_am) {
+    const size_t at = (size_t)(row - n_am) * norm.d;
+    rmsnorm_row(norm.x + at, norm.gain, norm.d, norm.eps, norm.out + at);
+    return;
+  }
   float best = -INFINITY;
   int best_i = 0x7fffffff;
   const float *vr = val + (size_t)row * NB;
@@ -369,8 +377,8 @@ __global__ __launch_bounds__(256) void argmax_finish_kernel(const float *val, co
 }
 
 void launch_argmax_finish(const float *val, const int32_t *idx, int NB, int rows, DevState *st, int pick_i, hipStream_t s,
-                          const int32_t *gate, DraftCat cat, DddFinish ddd) {
-  argmax_finish_kernel<<<rows, 256, 0, s>>>(val, idx, NB, st, pick_i, gate, cat, ddd);
+                          const int32_t *gate, DraftCat cat, DddFinish ddd, const NormRows &norm) {
+  argmax_finish_kernel<<<rows + norm.rows, 256, 0, s>>>(val, idx, NB, st, pick_i, gate, cat, ddd, rows, norm);
 }
 
 // temperature > 0: the sampled token (st->argmax[0]) with the override table applied becomes draft
@@ -391,11 +399,11 @@ void launch_pick_draft_packed(DevState *st, int i, hipStream_t s, const int32_t 
 
 // ------------------------------------------------------------------ packed-form producers
 // Embedding rows -> float residual stream, packed(x * gain) and the full-row sum of x^2.
-__global__ __launch_bounds__(256) void embed_packed_kernel(const uint16_t *emb, const int32_t *ids, int d,
+__global__ __launch_bounds__(256) void embed_packed_kernel(const uint16_t *emb, const BlockIds ids, int d,
                                                            const float *gain, float *x, u32x4 *Xp, float *ssq) {
   __shared__ float red[4];
   const int r = blockIdx.x;
-  const uint16_t *src = emb + (size_t)ids[r] * d;
+  const uint16_t *src = emb + (size_t)block_id(ids, r) * d;
   float ss = 0.f;
   for (int k0 = threadIdx.x * 4; k0 < d; k0 += 1024) {
     const uint2 raw = *reinterpret_cast<const uint2 *>(src + k0);
@@ -413,9 +421,9 @@ __global__ __launch_bounds__(256) void embed_packed_kernel(const uint16_t *emb, 
   if (threadIdx.x == 0) ssq[r] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-void launch_embed_packed(const void *emb, const int32_t *ids_dev, int rows, int d, const float *gain, float *x,
+void launch_embed_packed(const void *emb, const BlockIds &ids, int rows, int d, const float *gain, float *x,
                          void *Xp, float *ssq, hipStream_t s) {
-  embed_packed_kernel<<<rows, 256, 0, s>>>((const uint16_t *)emb, ids_dev, d, gain, x, (u32x4 *)Xp, ssq);
+  embed_packed_kernel<<<rows, 256, 0, s>>>((const uint16_t *)emb, ids, d, gain, x, (u32x4 *)Xp, ssq);
 }
 
 // float rows [rows][ld] (* gain) -> packed; one workgroup per row
@@ -437,9 +445,10 @@ void launch_pack_rows(const float *src, int ld, int rows, int K, const float *ga
 
 // draft head input [feature ; embedding of the following token] -> packed, K = 2d
 __global__ void draft_cat_packed_kernel(const float *feat, int feat_ld, const uint16_t *emb, const int32_t *next_ids,
-                                        int d, u32x4 *Xp, const int32_t *gate) {
+                                        int d, u32x4 *Xp, const int32_t *gate, const DraftInputs in) {
   AE_GATE(gate);
   const int r = blockIdx.x;
+  if (r == 0 && in.st) store_draft_inputs(in);
   const uint16_t *e = emb + (size_t)next_ids[r] * d;
   for (int k0 = threadIdx.x * 4; k0 < d; k0 += blockDim.x * 4) {
     const float4 f = *reinterpret_cast<const float4 *>(feat + (size_t)r * feat_ld + k0);
@@ -451,8 +460,8 @@ __global__ void draft_cat_packed_kernel(const float *feat, int feat_ld, const ui
 }
 
 void launch_draft_cat_packed(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d,
-                             void *Xp, hipStream_t s, const int32_t *gate) {
-  draft_cat_packed_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const uint16_t *)emb, next_ids, d, (u32x4 *)Xp, gate);
+                             void *Xp, hipStream_t s, const int32_t *gate, const DraftInputs &in) {
+  draft_cat_packed_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const uint16_t *)emb, next_ids, d, (u32x4 *)Xp, gate, in);
 }
 
 }  // namespace ae
