@@ -104,9 +104,10 @@ const char *ae_last_error(const ae_ctx *ctx);
 /* First iteration of Algorithm 1 (k = 0, T = prompt): runs the n prompt tokens (host
  * ids) through the target and through the draft head for every slot whose next token is
  * known; leaves kv_len = n and pending = first new token.  Prompts of up to 16 tokens go through
- * the decode kernels as one block; longer bf16 prompts take the dense pass
+ * the decode kernels as one block; longer prompts take the dense pass
  * (matrix-core bound GEMMs over chunks of up to chunk_rows rows, causal attention straight
- * off the cache; the draft head only needs its K/V rows there).  Both give the same state
+ * off the cache; the draft head only needs its K/V rows there; fp32 prompts go back to blocks of
+ * 16 where its buffers cannot be allocated).  Both give the same state
  * up to rounding order. */
 int ae_prefill(ae_ctx *ctx, const int32_t *prompt_ids, int n);
 
