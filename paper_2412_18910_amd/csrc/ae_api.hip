@@ -53,6 +53,13 @@ int fail(ae_ctx *c, int code, const std::string &msg) {
                   std::string(#call) + ": " + hipGetErrorString(e_));                            \
   } while (0)
 
+// Judges the launches made in its lifetime.  An error that was pending before them stays for the call that reports it
+// (read_state), and hides theirs until then.
+struct LaunchCheck {
+  const bool clean = hipPeekAtLastError() == hipSuccess;
+  hipError_t result() const { return clean ? hipGetLastError() : hipSuccess; }
+};
+
 template <typename T>
 int dev_alloc(ae_ctx *c, T **p, size_t count) {
   void *q = nullptr;
@@ -259,9 +266,9 @@ int wait_flag(ae_ctx *c, const uint32_t *word, uint32_t want, uint32_t shift = 0
     __builtin_ia32_pause();
   }
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  if (__atomic_load_n(word, __ATOMIC_ACQUIRE) >> shift == want) return AE_OK;
   HIPCHK(c, hipGetLastError());
-  if (__atomic_load_n(word, __ATOMIC_ACQUIRE) >> shift != want) return fail(c, AE_EHIP, "the device did not answer");
-  return AE_OK;
+  return fail(c, AE_EHIP, "the device did not answer");
 }
 
 // Bring the host's mirror of the device state up to date and wait for it.  The mirror is pinned
@@ -817,9 +824,7 @@ int ae_set_state(ae_ctx *c, int kv_len, int32_t last_tok, int32_t pending, const
   int rc = wait_flag(c, &c->hm->imported, c->feat_seq);   // the staging row is free again (the call: 6 us, not 28)
   if (rc) return rc;
   memcpy(c->h_feat, feat, sizeof(float) * g.d_model);
-  (void)hipGetLastError();   // only this launch is judged
-  launch_set_state(c->h_feat_dev, g.d_model, c->F, c->hist + kv_len - 1, last_tok, pending, c->hm_dev, ++c->seq, c->stream);
-  HIPCHK(c, hipGetLastError());
+  HIPCHK(c, launch_set_state(c->h_feat_dev, g.d_model, c->F, c->hist + kv_len - 1, last_tok, pending, c->hm_dev, ++c->seq, c->stream));
   c->feat_seq = c->seq;
   c->h_hist[kv_len - 1] = last_tok; c->h_hist[kv_len] = pending;
   c->kv_len = kv_len; c->dlen = kv_len - 1; c->nF = 1; c->pending = pending;
@@ -870,9 +875,10 @@ static int draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_
     in.override_ids[i] = override_ids && i < n_ov ? override_ids[i] : -1;
     in.u[i] = i < in.n_u ? u_draft[i] : 0.0;
   }
+  c->have_draft = c->have_verify = false;
+  const LaunchCheck launches;
   // catch-up over the slots validated by the last accept: true feature + following token
   draft_rows(c, c->F + (size_t)(c->nF - catch_rows) * g.d_model, g.d_model, c->hist + c->dlen + 1, catch_rows, c->dlen, -1, in);
-  c->dlen = n;
   int fh_row = catch_rows - 1;
   // AdaEAGLE-DDD (Sec. 3.4, 4.2): past the predicted length the head exits unless the
   // log-probability of the tokens drafted so far is still at least the threshold.  Host mode
@@ -915,12 +921,13 @@ static int draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_
     draft_lm_head(c, fh_row, i, k, poll);
   }
   c->gate = nullptr;
+  HIPCHK(c, launches.result());
+  c->dlen = n;   // (a draft that fails before this can be made again)
   k = i;   // tokens enqueued; with a gated tail the number drafted is st->draft_len <= k
   c->cur_k = k;
   c->cur_k_last = k;
   c->k_on_device = gated;
   c->have_draft = true;
-  c->have_verify = false;
   if (out && k > 0) {
     int rc = read_state(c);
     if (rc) return rc;
@@ -955,7 +962,10 @@ int ae_verify(ae_ctx *c, const int32_t *block_ids, int rows) {
     ids.hist = c->hist;
     ids.kv_len = c->kv_len;
   }
+  c->have_verify = false;
+  const LaunchCheck launches;
   target_forward(c, ids, rows, c->kv_len, 0);
+  HIPCHK(c, launches.result());
   c->block_rows = rows;
   c->have_verify = true;
   return AE_OK;
@@ -1102,10 +1112,8 @@ int32_t ae_pending(const ae_ctx *c) { return c && c->have_pending ? c->pending :
 // floats 34-36 either way (page faults of the caller's memory).  A first
 // copy into fresh memory of the caller faults on every page: that happens while the device is at work.
 static int copy_out(ae_ctx *c, const float *src, size_t n, float *dst) {
-  (void)hipGetLastError();   // only this launch is judged
   const uint32_t *flags = (const uint32_t *)(c->h_rows + c->row_floats);
-  launch_export_row(src, n, c->h_rows_dev, (uint32_t *)(c->h_rows_dev + c->row_floats), ++c->seq, c->stream);
-  HIPCHK(c, hipGetLastError());
+  HIPCHK(c, launch_export_row(src, n, c->h_rows_dev, (uint32_t *)(c->h_rows_dev + c->row_floats), ++c->seq, c->stream));
   for (size_t i = 0; i < n; i += 1024) *(volatile float *)(dst + i) = *(volatile float *)(dst + i);
   for (size_t p = 0; p * kExportPiece < n; ++p) {
     int rc = wait_flag(c, flags + p, c->seq);
@@ -1139,7 +1147,7 @@ int ae_get_kv_row(ae_ctx *c, int layer, int which, int slot, float *out) {
   const ae_config &g = c->cfg;
   if (!out || layer < 0 || layer > g.n_layers || (which != 0 && which != 1) || slot < 0 || slot >= g.n_ctx_max)
     return fail(c, AE_EINVAL, "ae_get_kv_row: argument out of range");
-  launch_kv_export(kv_layer_ptr(c, layer), c->kv_v_offset, g, which, slot, c->attn_part, c->fast, c->stream);
+  HIPCHK(c, launch_kv_export(kv_layer_ptr(c, layer), c->kv_v_offset, g, which, slot, c->attn_part, c->fast, c->stream));
   return copy_out(c, c->attn_part, (size_t)g.n_kv_heads * g.head_dim, out);
 }
 

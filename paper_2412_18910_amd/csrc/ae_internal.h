@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "adaeagle.h"
@@ -51,6 +52,21 @@ struct HostMirror {
   uint32_t imported;                // feature rows taken over (ae_set_state)
   uint32_t decision;                // DDD rule behind a draft token: number << 1 | go on
 };
+
+// Launch whose own result is returned, whatever error was pending before it: such an error stays pending (a failed
+// launch itself leaves none behind).
+template <typename... P, typename... A>
+hipError_t launch_checked(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t s, A... args) {
+  std::tuple<P...> typed(args...);
+  const hipError_t e = std::apply(
+      [&](P &...p) {
+        void *ptrs[] = {(void *)&p...};
+        return hipLaunchKernel((const void *)kernel, grid, block, ptrs, 0, s);
+      },
+      typed);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
 
 // A kernel launched with a non-null gate pointer does nothing when *gate == 0.
 #define AE_GATE(gate)                          \
@@ -210,11 +226,11 @@ void launch_ldlp_tail(const float *z0, const void *w_res, int dtype, const float
 // mirror->st = *st, written by the device itself, as the answer to request `seq`
 void launch_publish_state(const DevState *st, HostMirror *mirror, uint32_t seq, hipStream_t s);
 // F[0..d) = feat[0..d) (pinned host memory), hist2[0..2) = two ids, then mirror->imported = seq
-void launch_set_state(const float *feat, int d, float *F, int32_t *hist2, int32_t last_tok, int32_t pending, HostMirror *mirror,
-                      uint32_t seq, hipStream_t s);
+hipError_t launch_set_state(const float *feat, int d, float *F, int32_t *hist2, int32_t last_tok, int32_t pending, HostMirror *mirror,
+                            uint32_t seq, hipStream_t s);
 // dst[0..n) = src[0..n), dst in pinned host memory; flags[p] = seq behind piece p of kExportPiece floats
 constexpr size_t kExportPiece = 4096;
-void launch_export_row(const float *src, size_t n, float *dst, uint32_t *flags, uint32_t seq, hipStream_t s);
+hipError_t launch_export_row(const float *src, size_t n, float *dst, uint32_t *flags, uint32_t seq, hipStream_t s);
 void launch_rope_table(float2 *tab, int n_pos, int head_dim, float base, hipStream_t s);
 void launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 
@@ -232,8 +248,8 @@ void launch_attention_merge(const float *part, int rows, int n_chunks, const ae_
                             const int32_t *gate);
 void launch_kv_import(void *kv_layer, size_t v_off, const ae_config &c, const float *k_dev, const float *v_dev, int n,
                       bool tiled, hipStream_t s);
-void launch_kv_export(const void *kv_layer, size_t v_off, const ae_config &c, int which, int slot, float *out_dev,
-                      bool tiled, hipStream_t s);
+hipError_t launch_kv_export(const void *kv_layer, size_t v_off, const ae_config &c, int which, int slot, float *out_dev,
+                            bool tiled, hipStream_t s);
 size_t attn_part_floats(const ae_config &c);
 
 // ---- T > 0 sampling (kernels_sample.hip) ----

@@ -91,15 +91,14 @@ __global__ void kv_export_kernel(const T *Kc, const T *Vc, int which, int slot, 
   }
 }
 
-void launch_kv_export(const void *kv_layer, size_t v_off, const ae_config &c, int which, int slot, float *out_dev,
-                      bool tiled, hipStream_t s) {
+hipError_t launch_kv_export(const void *kv_layer, size_t v_off, const ae_config &c, int which, int slot, float *out_dev,
+                            bool tiled, hipStream_t s) {
   const void *vc = (const char *)kv_layer + v_off;
   if (c.dtype == AE_BF16)
-    kv_export_kernel<bf16_t><<<1, 256, 0, s>>>((const bf16_t *)kv_layer, (const bf16_t *)vc, which, slot, c.n_kv_heads,
-                                               c.head_dim, kv_capacity(c), tiled, out_dev);
-  else
-    kv_export_kernel<float><<<1, 256, 0, s>>>((const float *)kv_layer, (const float *)vc, which, slot, c.n_kv_heads,
-                                              c.head_dim, kv_capacity(c), tiled, out_dev);
+    return launch_checked(kv_export_kernel<bf16_t>, dim3(1), dim3(256), s, (const bf16_t *)kv_layer, (const bf16_t *)vc, which, slot,
+                          c.n_kv_heads, c.head_dim, kv_capacity(c), tiled, out_dev);
+  return launch_checked(kv_export_kernel<float>, dim3(1), dim3(256), s, (const float *)kv_layer, (const float *)vc, which, slot,
+                        c.n_kv_heads, c.head_dim, kv_capacity(c), tiled, out_dev);
 }
 
 }  // namespace ae

@@ -103,9 +103,9 @@ __global__ __launch_bounds__(1024) void set_state_kernel(const float *feat, int 
     __hip_atomic_store(&mirror->imported, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
-void launch_set_state(const float *feat, int d, float *F, int32_t *hist2, int32_t last_tok, int32_t pending, HostMirror *mirror,
-                      uint32_t seq, hipStream_t s) {
-  set_state_kernel<<<1, 1024, 0, s>>>(feat, d, F, hist2, last_tok, pending, mirror, seq);
+hipError_t launch_set_state(const float *feat, int d, float *F, int32_t *hist2, int32_t last_tok, int32_t pending, HostMirror *mirror,
+                            uint32_t seq, hipStream_t s) {
+  return launch_checked(set_state_kernel, dim3(1), dim3(1024), s, feat, d, F, hist2, last_tok, pending, mirror, seq);
 }
 
 // One row to pinned host memory, a workgroup and a flag per piece: the host copies a piece on while the next ones are
@@ -124,8 +124,8 @@ __global__ __launch_bounds__(256) void export_row_kernel(const float *src, size_
   __syncthreads();
   if (threadIdx.x == 0) __hip_atomic_store(flags + blockIdx.x, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-void launch_export_row(const float *src, size_t n, float *dst, uint32_t *flags, uint32_t seq, hipStream_t s) {
-  export_row_kernel<<<(int)((n + kExportPiece - 1) / kExportPiece), 256, 0, s>>>(src, n, dst, flags, seq);
+hipError_t launch_export_row(const float *src, size_t n, float *dst, uint32_t *flags, uint32_t seq, hipStream_t s) {
+  return launch_checked(export_row_kernel, dim3((n + kExportPiece - 1) / kExportPiece), dim3(256), s, src, n, dst, flags, seq);
 }
 
 // ------------------------------------------------------------------ LDLP (Eq. 3)
