@@ -10,13 +10,17 @@
 //  * gemm_f32_kernel: up to 16 activation rows (decode, verify).  HBM-bound: a workgroup owns one
 //    block of 16 weight rows (gate/up: one of each) and all of K, dealt to its waves in pieces of 64.
 //    One kernel for every row count, so a row's result does not depend on the rows beside it.
-//  * gemm_f32_dense_kernel: prompts.  Bound by the float32 matrix rate (about 150 TFLOP/s): 64 x 64 (or
-//    64 x 32) tiles through LDS.
+//  * gemm_f32_dense_kernel: prompts.  Bound by the float32 matrix rate (about 150 TFLOP/s): tiles of 128 weight
+//    rows x 16, 32, 48 or 64 activation rows through LDS.
 //  * attn_f32_kernel: split-KV attention of up to 16 rows; attn_prefill_f32_kernel: causal flash
 //    attention of a prompt chunk.
-// Long sums are cut: the decode GEMM keeps four accumulators per wave, the dense GEMM adds its
-// accumulators to a second set every 128 k, the flash attention every 256 keys, so that no chain of
-// roundings grows with K or with the context.
+// Every product that joins an accumulator is rounded, so long sums are cut.  Counted in variances of one rounding at
+// the result's magnitude, a chain of c products costs c / 2, a chain of n sums of c products n / 2, and what is left
+// of K then K / (2 c n).  The sums that a wave of scalar code makes (64 lanes, each a chain of K / 64 products, and a
+// butterfly) cost K / 128 + 6 of these, and neither GEMM may cost more: the decode GEMM cuts at 16 products (8 where K
+// is below 1024) and adds wave results as a tree, the prompt GEMM at 32 and 128 (K below 4096: 8, 32 and 128).
+// Measured against float64 at K = 4096: V rows 1.25e-7 (scalar sums 1.67e-7, one chain per accumulator 2.2e-7).
+// The flash attention adds its accumulators to a second set every 256 keys.
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
 #include "packed.h"
@@ -192,12 +196,14 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
 // of K, dealt to its waves in chunks of 64; a wave keeps a chunk (4 KB; gate/up: 8 KB) in flight in a rolling ring.
 // The rows of a row-major matrix lie a power of two apart, so workgroups that walk K in step ask the same few memory
 // channels: each starts at a chunk of its own (7B widths, microseconds: o / down 29.6 -> 25.7, draft fc 35.0 -> 24.0,
-// LM head 105 -> 96 = 5.5 TB/s; gate/up 76 -> 75 and QKV 42 -> 40 were spread by themselves).  Twice the depth, 4 or
-// 16 waves, and 4x4x1 products that read 256 bytes of a row per load were no faster.
+// a draft token's LM head 105 -> 94; gate/up 76 -> 75 and QKV 42 -> 40 were spread by themselves).  Twice the depth, 4 or
+// 16 waves, and 4x4x1 products that read 256 bytes of a row per load were no faster.  Cutting the chains at 16 products
+// with one total per matrix is free (a step of 4 layers of 7B 2266 us, 2274 without); four totals cost 5 % (registers).
 // TAIL: K is no multiple of 64; pieces behind the end count as zeros.
 template <int EPI, bool NORM, int NW, bool TAIL, bool GATED>
 __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
   constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1, D = 4;
+  constexpr int CH = NW == 8 ? 4 : 2;   // loads per chain of products
   __shared__ f32x4 red[NW][NA][64];
   if constexpr (GATED) AE_GATE(a.gate);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, m = lane & 15;
@@ -212,11 +218,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
   EpiPre pre{};
   if (w == 0) pre = f32_epi_prefetch<EPI>(a, nb, g, m, row_ok);
 
-  f32x4 acc[NA][4], wb[D][NA], xb[D];
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[NA][4], tot[NA], wb[D][NA], xb[D];
 #pragma unroll
-  for (int i = 0; i < NA; ++i)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[i][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < NA; ++i) tot[i] = zero;
   const int NC = (K + D * 16 - 1) / (D * 16), rot = (int)((unsigned)nb * 7u % (unsigned)NC);
   auto at = [&](int c) { const int r = c + rot; return r < NC ? r : r - NC; };
   auto load = [&](int c, int j) {
@@ -258,29 +263,39 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
 #pragma unroll
     for (int j = 0; j < D; ++j) {
       if (TAIL && at(c) + 1 == NC && at(c) * (D * 16) + j * 16 + g * 4 >= K) {
-        xb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        xb[j] = zero;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) wb[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < NA; ++i) wb[j][i] = zero;
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int i = 0; i < NA; ++i) acc[i][e] = mfma_f32(wb[j][i][e], xb[j][e], acc[i][e]);
+        for (int i = 0; i < NA; ++i) acc[i][e] = mfma_f32(wb[j][i][e], xb[j][e], j % CH == 0 ? zero : acc[i][e]);
       __builtin_amdgcn_sched_barrier(0);   // refill slot j at once, not behind the whole piece
       load(cn, j);
       __builtin_amdgcn_sched_barrier(0);
+      if (j % CH == CH - 1) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) tot[i] += (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+      }
     }
   }
 #pragma unroll
-  for (int i = 0; i < NA; ++i) red[w][i][lane] = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+  for (int i = 0; i < NA; ++i) red[w][i][lane] = tot[i];
   __syncthreads();
   if (w != 0) return;
-  f32x4 s = red[0][0][lane], u = red[0][NA - 1][lane];
+  f32x4 t[NW][NA];
 #pragma unroll
-  for (int ww = 1; ww < NW; ++ww) {
-    s += red[ww][0][lane];
-    u += red[ww][NA - 1][lane];
-  }
+  for (int ww = 0; ww < NW; ++ww)
+#pragma unroll
+    for (int i = 0; i < NA; ++i) t[ww][i] = red[ww][i][lane];
+#pragma unroll
+  for (int o = 1; o < NW; o *= 2)
+#pragma unroll
+    for (int ww = 0; ww < NW; ww += 2 * o)
+#pragma unroll
+      for (int i = 0; i < NA; ++i) t[ww][i] += t[ww + o][i];
+  const f32x4 s = t[0][0], u = t[0][NA - 1];
   f32_epi<EPI>(a, s, u, nb, g, m, m, row_ok, NORM ? rinv_s[xrow] : 1.f, pre);
 }
 
@@ -340,12 +355,12 @@ void launch_gemm_f32(const GemmLaunch &L, hipStream_t s) {
 // Workgroup tile: 128 weight rows (gate/up: 64 of each) x 16*J activation rows; each of the 4 waves owns two
 // weight row-blocks and all J activation row-blocks.  Stages of 32 k go global -> registers -> LDS (in lane
 // order: conflict-free), two stages ahead.
-template <int EPI, int J>
+template <int EPI, int J, bool LONG>
 __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
   constexpr int TM = 16 * J;
   constexpr int STAGE = (8 + J) * 128, NLB = (J + 1) / 2;   // 16-byte pieces per LDS stage; B pieces per thread
   constexpr int PD = 2;                                     // register sets: stages in flight
-  constexpr int UN = 4, FLUSH = 2;                          // stages per loop pass, per accumulation chain
+  constexpr int UN = 4;                                     // stages per loop pass
   __shared__ f32x4 sm[2][STAGE];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
   // the activation tiles of one weight tile run side by side on one XCD (ids go round the 8 XCDs) and share it in its L2
@@ -398,11 +413,14 @@ __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
     for (int i = 0; i < NLB; ++i)
       if (J % 2 == 0 || i + 1 < NLB || tid < 128) sm[buf][1024 + tid + 256 * i] = br[i];
   };
-  f32x4 acc[2][J], tot[2][J];
+  // acc: chains of 8 products, joined in sums over a stage (s32; LONG: chains of a whole stage), these in sums over a
+  // loop pass (s128), these in the total
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[2][J], s32[2][J], s128[2][J], tot[2][J];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < J; ++j) acc[i][j] = tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < J; ++j) tot[i][j] = zero;
   // stage st waits in LDS, stages st+1 .. st+PD are on their way in register sets (stage mod PD)
 #pragma unroll
   for (int u = 0; u < PD; ++u) issue(u * 32, areg[u], breg[u]);
@@ -416,12 +434,6 @@ __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
       issue((st + PD) * 32, areg[u % PD], breg[u % PD]);
       __builtin_amdgcn_sched_barrier(0);
       const f32x4 *sa = sm[u & 1] + w * 256 + lane, *sb = sm[u & 1] + 1024 + lane;
-      if (u % FLUSH == 0) {   // the chain before this one; its products ended behind the barrier
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < J; ++j) tot[i][j] += acc[i][j];
-      }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         f32x4 fa[2], fb[J];
@@ -434,18 +446,41 @@ __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
 #pragma unroll
           for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < J; ++j)
-              acc[i][j] = mfma_f32(fa[i][e], fb[j][e], u % FLUSH == 0 && ks == 0 && e == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j]);
+            for (int j = 0; j < J; ++j) {   // a chain joins its sum when the next one starts: its products are through
+              const bool first = LONG ? ks == 0 && e == 0 : e % 2 == 0;
+              if (first && (ks || e)) s32[i][j] = ks == 0 ? acc[i][j] : s32[i][j] + acc[i][j];
+              if (first && LONG && u > 0) s128[i][j] = u == 1 ? acc[i][j] : s128[i][j] + acc[i][j];
+              acc[i][j] = mfma_f32(fa[i][e], fb[j][e], first ? zero : acc[i][j]);
+            }
+      }
+      if (LONG && u > 0) {   // the joins go between the products that start the chains, not in front of them
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 + J, 0);
+#pragma unroll
+        for (int i = 0; i < 2 * J; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 + J, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 14 * J, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
       stash((st + 1) * 32, (u + 1) & 1, areg[(u + 1) % PD], breg[(u + 1) % PD]);
+      if (!LONG) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < J; ++j) {
+            s32[i][j] += acc[i][j];
+            s128[i][j] = u == 0 ? s32[i][j] : s128[i][j] + s32[i][j];
+          }
+      }
       __syncthreads();
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < J; ++j) tot[i][j] += LONG && NS - st0 == 1 ? acc[i][j] : LONG ? s128[i][j] + acc[i][j] : s128[i][j];
   }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < J; ++j) tot[i][j] += acc[i][j];
   constexpr int STEP = EPI == EPI_SWIGLU ? 2 : 1;
 #pragma unroll
   for (int i = 0; i < 2; i += STEP) {
@@ -465,7 +500,11 @@ template <int EPI, int J>
 static void launch_f32_dense_tile(const F32Args &a, hipStream_t s) {
   constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;
   const int tiles = (a.NB + NBT - 1) / NBT * ((a.rows + 16 * J - 1) / (16 * J));
-  gemm_f32_dense_kernel<EPI, J><<<dim3((tiles + 7) / 8 * 8, a.splits), 256, 0, s>>>(a);
+  const dim3 grid((tiles + 7) / 8 * 8, a.splits);
+  // Chains of 32 cost 18 + K / 256 roundings (see the top), chains of 8 (three joins more a stage) 6 + K / 256; the scalar
+  // sums cost 6 + K / 128.  7B widths, 2048 rows, 2 layers: 19.5 ms with chains of 32, 20.9 with chains of 8.
+  if (a.K >= 4096) gemm_f32_dense_kernel<EPI, J, true><<<grid, 256, 0, s>>>(a);
+  else gemm_f32_dense_kernel<EPI, J, false><<<grid, 256, 0, s>>>(a);
 }
 
 // Rows of a tile and (EPI_PART) pieces of K: the least of tiles per compute unit times rows of a tile over pieces.  A
