@@ -580,6 +580,16 @@ void launch_gemm_f32_resid_norm(const GemmLaunch &L, float *part, size_t max_par
 // holds: all loads are 128 bits wide and issued up front, no shuffles in between.
 constexpr int kF32AttnKeys = 64;
 
+// V rows j >= live of a lane's four keys lie behind the end of the block: rolled back or left by an earlier sequence,
+// perhaps not finite.  Their probabilities are 0, but 0 * Inf is not.  (Only the last key tile of a launch has any.)
+template <int N>
+__device__ __forceinline__ void clear_dead_rows(f32x4 (&v)[4][N], int live) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[j][i] = j < live ? v[j][i] : f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
 template <int HD, bool GATED>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
                                                        const float *Kc, const float *Vc, float *part, float *out,
@@ -648,6 +658,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows,
       }
       lsum += __shfl_xor(lsum, 16, 64);
       lsum += __shfl_xor(lsum, 32, 64);
+      if (kbase + 16 > pos0 + rows) clear_dead_rows(vreg, pos0 + rows - kbase - 4 * g);
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -795,6 +806,7 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const float *q, i
       O[dt] *= alpha;
       T[dt] *= alpha;
     }
+    if (kb + 16 > pos0 + rows) clear_dead_rows(vreg, pos0 + rows - kb - 4 * g);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
