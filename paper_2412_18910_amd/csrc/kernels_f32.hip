@@ -163,7 +163,7 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
     if (a.lse_sum) {
       float t = 0.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) t += v[e] > -INFINITY ? expf((v[e] - bv) * a.lse_inv_t) : 0.f;
+      for (int e = 0; e < 4; ++e) t += v[e] == -INFINITY ? 0.f : expf((v[e] - bv) * a.lse_inv_t);   // NaN stays NaN
       t += __shfl_xor(t, 16, 64);
       t += __shfl_xor(t, 32, 64);
       if (g == 0) a.lse_sum[(size_t)m * a.NB + nb] = t;
