@@ -293,43 +293,55 @@ bool dense_ok(const ae_ctx *c) {
   return c->fast && g.d_model >= 256 && 2 * g.d_ffn >= 256 && (g.n_heads + 2 * g.n_kv_heads) * g.head_dim >= 256;
 }
 
+void release_dense(ae_ctx *c) {
+  for (void *p : c->dense_owned) hipFree(p);
+  c->dense_owned.clear();
+  c->dense_cap = 0;
+  c->ppart = nullptr;
+  c->ppart_floats = 0;
+}
+
 // Chunk buffers for `cap` rows (a multiple of 128): float residual stream and queries, the
 // inputs of the five GEMMs; bf16: RMSNorm partial sums and 1/rms, zero-filled so that the
-// padding rows of a packed chunk are finite.
+// padding rows of a packed chunk are finite.  Nothing is held where they do not fit; bf16 prompts
+// do without room for pieces of K (no GEMM is split then).
 int ensure_dense(ae_ctx *c, int n) {
   const ae_config &g = c->cfg;
   const int want = ((n < c->dense_chunk ? n : c->dense_chunk) + 127) / 128 * 128;
   if (want <= c->dense_cap) return AE_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  for (void *p : c->dense_owned) hipFree(p);
-  c->dense_owned.clear();
-  c->dense_cap = 0;
+  release_dense(c);
   const size_t cap = want, d = g.d_model, dq = (size_t)g.n_heads * g.head_dim, dkv = (size_t)g.n_kv_heads * g.head_dim, f = g.d_ffn;
   const size_t dmax = dq > d ? dq : d;
   // sums over pieces of K.  float32: up to 8 pieces for short prompts; bf16: 768 tiles of 128 x 128, no more than
   // 16 pieces of the widest output
   const size_t part_rows = cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048;
   const size_t widest = 2 * f > dq + 2 * dkv ? 2 * f : dq + 2 * dkv, most = (size_t)768 * 128 * 128;
-  c->ppart_floats = !c->fast ? part_rows * d : 16 * cap * widest < most ? 16 * cap * widest : most;
+  const size_t part_floats = !c->fast ? part_rows * d : 16 * cap * widest < most ? 16 * cap * widest : most;
   struct Buf { void **p; size_t bytes; };
   const std::vector<Buf> bufs = !c->fast ? std::vector<Buf>{
       {(void **)&c->px, cap * d * 4}, {(void **)&c->pq, cap * dq * 4}, {&c->pxa, cap * d * 4}, {&c->pxatt, cap * dmax * 4},
-      {&c->pxh, cap * f * 4}, {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, part_rows * d * 4}} : std::vector<Buf>{
+      {&c->pxh, cap * f * 4}, {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, part_floats * 4}} : std::vector<Buf>{
       {(void **)&c->px, cap * d * 4},      {(void **)&c->pq, cap * dq * 4},   {(void **)&c->prinv, cap * 4},
       {(void **)&c->pssq_a, cap * d * 4 / 16 * 1 + cap * 4}, {(void **)&c->pssq_f, cap * d * 4 / 16 + cap * 4},
       {&c->pxa, cap * d * 4},              {&c->pxf, cap * d * 4},            {&c->pxatt, cap * dq * 4},
-      {&c->pxh, cap * f * 4},              {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, c->ppart_floats * 4}};
+      {&c->pxh, cap * f * 4},              {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, part_floats * 4}};
   for (auto &b : bufs) {
     void *q = nullptr;
     const size_t bytes = (b.bytes + 255) / 256 * 256;
     hipError_t e = hipMalloc(&q, bytes);
+    const bool part = b.p == (void **)&c->ppart;
     if (e != hipSuccess) {
       (void)hipGetLastError();
+      if (c->fast && part) break;   // the last buffer
+      (void)hipStreamSynchronize(c->stream);   // the buffers before this one are being cleared
+      release_dense(c);
       return fail(c, AE_ENOMEM, std::string("dense prefill buffers: ") + hipGetErrorString(e));
     }
     c->dense_owned.push_back(q);
     *b.p = q;
-    if (c->fast && b.p != (void **)&c->ppart) launch_fill_zero(q, bytes, c->stream);
+    if (part) c->ppart_floats = part_floats;
+    else if (c->fast) launch_fill_zero(q, bytes, c->stream);
   }
   c->dense_cap = want;
   return AE_OK;
@@ -762,9 +774,7 @@ int ae_set_prefill_mode(ae_ctx *c, int mode, int chunk_rows) {
   c->prefill_mode = mode;
   if (chunk_rows && chunk_rows != c->dense_chunk) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    for (void *p : c->dense_owned) hipFree(p);
-    c->dense_owned.clear();
-    c->dense_cap = 0;
+    release_dense(c);
     c->dense_chunk = chunk_rows;
   }
   return AE_OK;
