@@ -18,8 +18,11 @@
  *    own re-tiled copy of every matrix (made in ae_init, 2 bytes per parameter), so
  *    the caller's copies are only read during ae_init and by the embedding lookup.
  *    Everything else (KV cache, activations, logits, scratch) is owned by the ctx.
- *  - Output arrays are caller-owned host memory, filled before the call returns
- *    (such calls synchronise the stream).
+ *  - Output arrays are caller-owned host memory, filled before the call returns: such calls
+ *    (and ae_step, ae_accept, ae_ldlp, ae_prefill) wait until everything the ctx has enqueued is done.
+ *    They poll pinned host memory that the device writes, on the calling thread: it keeps its core busy
+ *    for up to 10 ms (yielding to other threads), then sleeps in a stream synchronisation.
+ *    ae_set_state copies its inputs and returns without waiting for the device.
  *  - Token positions in the paper are 1-based; cache slots and rotary positions
  *    here are 0-based: token t_{s+1} lives in slot s.  kv_len = n = number of tokens
  *    whose K/V are cached; the pending token (last bonus) is t_{n+1}, not yet cached.

@@ -1,6 +1,8 @@
 // C ABI of libadaeagle: context set-up, the state machine of one sequence, and the
 // host-side sequencing of the kernels of one decode step (LDLP -> draft -> verify ->
 // accept + rollback, i.e. one iteration of Algorithm 1 of arxiv 2412.18910).
+#include <sched.h>
+
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
@@ -263,13 +265,19 @@ void drain_kernel_timing(ae_ctx *c) {
   c->kt_used = 0;
 }
 
-// Wait until the device has set a flag word of the mirror to `want`.  Polling is bounded: work that is not there
-// after 50 ms (a long prompt), or never will be (a device error), is waited for by the stream, which reports errors.
+// Wait until the device has set a flag word of the mirror to `want`.  The caller's core polls (a stream synchronisation
+// notices 10 to 17 us later), but lets other threads in from the first 20 us on, and for 10 ms at most: the longest decode
+// step takes 7.  Work that is not there then (a long prompt), or never will be (a device error), is waited for by the
+// stream, which sleeps and reports errors.
 int wait_flag(ae_ctx *c, const uint32_t *word, uint32_t want, uint32_t shift = 0) {
   const auto t0 = std::chrono::steady_clock::now();
   for (int spins = 0;; ++spins) {
     if (__atomic_load_n(word, __ATOMIC_ACQUIRE) >> shift == want) return AE_OK;
-    if ((spins & 255) == 255 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) break;
+    if ((spins & 63) == 63) {
+      const auto waited = std::chrono::steady_clock::now() - t0;
+      if (waited > std::chrono::milliseconds(10)) break;
+      if (waited > std::chrono::microseconds(20)) sched_yield();
+    }
     __builtin_ia32_pause();
   }
   HIPCHK(c, hipStreamSynchronize(c->stream));
