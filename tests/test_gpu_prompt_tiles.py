@@ -1,0 +1,103 @@
+"""Prompts that reach every tile shape of the prompt GEMMs, at ragged row counts (needs an MI355X).
+
+The rules that choose a tile go by the number of tiles, so each case names the kernels it is there for; tests/
+test_host_prompt_tiles.py checks that it still reaches them.  The prompt pass is compared row by row with the 16-row
+pass of the decode kernels, and where the oracle is quick enough with the oracle."""
+from dataclasses import dataclass
+
+import numpy as np
+import pytest
+
+from paper_2412_18910_amd import synth
+from paper_2412_18910_amd.binding import Engine
+from paper_2412_18910_amd.config import BF16, FP32, Config
+
+from .gpu_helpers import make_pair, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(dtype, d, heads, kv, hd, ffn):
+    return Config(1, d, heads, kv, hd, ffn, 515 if dtype == FP32 else 512, dtype=dtype, k_max=5, ldlp_hidden=64)
+
+
+@dataclass(frozen=True)
+class Case:
+    cfg: Config
+    n: int
+    reaches: tuple
+    oracle: bool = True
+    chunk: int = 0
+
+    @property
+    def config(self):
+        return self.cfg.with_(n_ctx_max=self.n + 16)
+
+
+# float32: (epilogue, 16-row blocks of a tile, chains of 32); widths leave tails in K and half row-blocks
+F_SHORT, F_LONG = _cfg(FP32, 1032, 16, 8, 128, 4104), _cfg(FP32, 4104, 16, 8, 128, 4104)
+F_MID = _cfg(FP32, 1032, 12, 6, 64, 2056)
+# bf16, whole K: (epilogue, row-blocks of a tile, weight row-blocks of a wave); the widths of the QKV cases end in half a tile
+B_FFN, B_WIDE, B_QKV = _cfg(BF16, 256, 4, 2, 64, 4096), _cfg(BF16, 4096, 4, 4, 64, 256), _cfg(BF16, 256, 20, 5, 64, 512)
+# bf16, K in pieces
+B_SPLIT = _cfg(BF16, 1024, 4, 2, 64, 11008)
+CASES = {
+    "f32-61": Case(F_SHORT, 61, (("PART", 1, 0), ("QKV", 1, 0), ("SWIGLU", 2, 0), ("PART", 1, 1))),
+    "f32-101": Case(F_MID, 101, (("PART", 1, 0), ("QKV", 1, 0), ("SWIGLU", 1, 0))),
+    "f32-131": Case(F_SHORT, 131, (("QKV", 2, 0), ("SWIGLU", 3, 0))),
+    "f32-301": Case(F_SHORT, 301, (("PART", 2, 0), ("PART", 2, 1), ("QKV", 3, 0))),
+    "f32-403": Case(F_SHORT, 403, (("QKV", 2, 0), ("SWIGLU", 4, 0)), oracle=False),
+    "f32-1001": Case(F_SHORT, 1001, (("PART", 3, 0), ("QKV", 4, 0), ("SWIGLU", 3, 0)), oracle=False),
+    "f32-long-21": Case(F_LONG, 21, (("PART", 2, 1), ("QKV", 1, 1), ("SWIGLU", 1, 1))),
+    "f32-long-61": Case(F_LONG, 61, (("PART", 2, 1), ("QKV", 1, 1), ("SWIGLU", 2, 1))),
+    "f32-long-403": Case(F_LONG, 403, (("PART", 3, 0), ("PART", 3, 1), ("QKV", 2, 1), ("SWIGLU", 4, 1)), oracle=False),
+    "f32-long-601": Case(F_LONG, 601, (("PART", 4, 0), ("PART", 4, 1), ("QKV", 3, 1), ("SWIGLU", 2, 1)), oracle=False),
+    "f32-long-901": Case(F_LONG, 901, (("PART", 3, 1), ("QKV", 4, 1), ("SWIGLU", 3, 1)), oracle=False),
+    "bf16-ffn-777": Case(B_FFN, 777, (("SWIGLU", 4, 4),)),
+    "bf16-ffn-1950": Case(B_FFN, 1950, (("SWIGLU", 8, 4),)),
+    "bf16-wide-1500": Case(B_WIDE, 1500, (("RESID", 4, 4), ("STORE", 4, 4))),
+    "bf16-wide-2501": Case(B_WIDE, 2501, (("RESID", 8, 4), ("STORE", 8, 4)), oracle=False, chunk=8192),
+    "bf16-qkv-3100": Case(B_QKV, 3100, (("QKV", 4, 4),), oracle=False, chunk=8192),
+    "bf16-qkv-8100": Case(B_QKV, 8100, (("QKV", 8, 4), ("SWIGLU", 4, 4)), oracle=False, chunk=8192),
+    "bf16-split-50": Case(B_SPLIT, 50, (("PART", 4, 2), ("PART", 4, 3))),
+    "bf16-split-101": Case(B_SPLIT, 101, (("PART", 8, 2), ("PART", 8, 3))),
+}
+
+
+def rows_of(src, cfg, slots):
+    """K and V rows of the target layer and of the draft head (behind all of the layer's GEMMs)."""
+    return {(layer, which): np.stack([src.kv_row(layer, which, s) for s in slots]) for layer in (0, 1) for which in (0, 1)}
+
+
+def compare(cfg, a, b):
+    for key in a:
+        if cfg.dtype == FP32:   # the bar of the parity tests, for values of order one
+            assert np.max(np.abs(a[key] - b[key])) <= 1e-4 * max(1.0, float(np.std(a[key]))), key
+        else:   # a flipped bf16 rounding is 2^-8 of an element
+            assert np.max(np.abs(a[key] - b[key])) <= np.max(np.abs(a[key])) * 2 ** -7 + 1e-6, key
+            assert np.mean(a[key] != b[key]) < (0.02 if key[0] == 0 else 0.3), key
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_every_row_of_every_tile(name):
+    c = CASES[name]
+    cfg, tol = c.config, 1e-4 if c.cfg.dtype == FP32 else 2e-2
+    if c.oracle:
+        eng, orc, _ = make_pair(cfg, 101)
+    else:
+        eng, orc = Engine(cfg, to_device(synth.make_weights(cfg, 101))), None
+    ids = synth.token_ids(c.n, cfg.vocab, 102)
+    slots = list(range(c.n - 1))
+    got = {}
+    for mode in (Engine.PREFILL_BLOCKS, Engine.PREFILL_AUTO):
+        eng.set_prefill_mode(mode, c.chunk)
+        eng.prefill(ids)
+        got[mode] = eng.logits(0), rows_of(eng, cfg, slots)
+    (lb, rb), (la, ra) = got[Engine.PREFILL_BLOCKS], got[Engine.PREFILL_AUTO]
+    assert np.max(np.abs(lb - la)) <= tol
+    compare(cfg, rb, ra)
+    if orc is not None:
+        orc.prefill(ids)
+        assert np.max(np.abs(orc.logits(0) - la)) <= tol
+        compare(cfg, rows_of(orc, cfg, slots), ra)
+    eng.close()
