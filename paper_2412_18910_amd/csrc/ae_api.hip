@@ -204,8 +204,8 @@ void draft_rows(ae_ctx *c, const float *feat, int feat_ld, const int32_t *next_i
   hipStream_t s = c->stream;
   const int d = g.d_model;
   if (chained_row < 0) {
-    if (c->fast) launch_draft_cat_packed(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate, in);
-    else launch_draft_cat_f32(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, c->gate, in);
+    if (c->fast) launch_draft_cat_packed(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, in);
+    else launch_draft_cat_f32(feat, feat_ld, c->tok_emb, next_ids_dev, rows, d, c->xp_cat, s, in);
   }
   if (!fc_done) draft_fc(c, rows, chained_row < 0 ? 0 : chained_row);
   c->Pa = (d + 15) / 16;
@@ -455,7 +455,7 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   }
   if (drows > 0) {
     // Eq. 2 catch-up of prompt slots: only the head's K/V rows are ever read again
-    launch_draft_cat_f32(xn, d, c->tok_emb, c->hist + p0 + 1, drows, d, c->pxcat, s, nullptr, DraftInputs());
+    launch_draft_cat_f32(xn, d, c->tok_emb, c->hist + p0 + 1, drows, d, c->pxcat, s, DraftInputs());
     if (c->draft_fc_b) {
       project(&c->draft_fc, c->pxcat, 2 * d, drows, c->draft_fc_b, att, c->layers[g.n_layers].attn_norm);
     } else {

@@ -19,7 +19,6 @@ constexpr int kMaxSplits = 64;     // n_ctx_max / kAttnChunk upper bound
 constexpr int kMfmaKeysPerWave = 64;                     // bf16 matrix-core attention: keys per wave,
 constexpr int kMfmaAttnChunk = 4 * kMfmaKeysPerWave;     // keys per workgroup (4 waves)
 constexpr int kMaxLdlpHidden = 1024;
-constexpr int kDenseRB = 8;        // activation row-blocks per workgroup of the dense prompt GEMM (128 rows)
 constexpr int kDenseMinPrompt = 17;   // prompts of one 16-row block go through the decode kernels
 
 // Device-resident step state.  The host mirrors kv_len (it learns it at every accept).
@@ -209,8 +208,7 @@ struct GreedyAccept {
 };
 
 // ---- dtype-independent kernels (kernels_generic.hip); all launches are asynchronous on `s` ----
-void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s,
-                    const int32_t *gate = nullptr);
+void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s);
 void launch_set_u_accept(DevState *st, const double *u, int rows, hipStream_t s);
 // k_on_device: the draft length is st->draft_len (the block is padded to `rows` rows)
 void launch_accept_greedy(DevState *st, int32_t *hist, int kv_len, int rows, bool k_on_device, hipStream_t s);
@@ -323,7 +321,7 @@ void launch_embed_packed(const void *emb, const BlockIds &ids, int rows, int d, 
                          void *Xp, float *ssq, hipStream_t s);
 void launch_pack_rows(const float *src, int ld, int rows, int K, const float *gain, void *Xp, hipStream_t s);
 void launch_draft_cat_packed(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d,
-                             void *Xp, hipStream_t s, const int32_t *gate, const DraftInputs &in);
+                             void *Xp, hipStream_t s, const DraftInputs &in);
 
 // ---- dense prompt pass (kernels_dense.hip); packed buffers hold RB row-blocks ----
 // Same GemmLaunch as the decode GEMM (rows = rows of the chunk, row0 unused); rinv != nullptr
@@ -356,6 +354,6 @@ void launch_attention_prefill_f32(const float *q, int rows, int pos0, const ae_c
 void launch_embed_f32(const void *emb, const BlockIds &ids, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
                       hipStream_t s);
 void launch_draft_cat_f32(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d, void *cat,
-                          hipStream_t s, const int32_t *gate, const DraftInputs &in);
+                          hipStream_t s, const DraftInputs &in);
 
 }  // namespace ae

@@ -885,9 +885,7 @@ void launch_embed_f32(const void *emb, const BlockIds &ids, int rows, int d, con
 
 // cat[r] = [feature row r ; embedding of the token that FOLLOWS slot r]  (Sec. 2.2)
 __global__ __launch_bounds__(256) void draft_cat_f32_kernel(const float *feat, int feat_ld, const float *emb,
-                                                            const int32_t *next_ids, int d, float *cat, const int32_t *gate,
-                                                            const DraftInputs in) {
-  AE_GATE(gate);
+                                                            const int32_t *next_ids, int d, float *cat, const DraftInputs in) {
   const int r = blockIdx.x;
   if (r == 0 && in.st) store_draft_inputs(in);
   const float *e = emb + (size_t)next_ids[r] * d, *f = feat + (size_t)r * feat_ld;
@@ -899,8 +897,8 @@ __global__ __launch_bounds__(256) void draft_cat_f32_kernel(const float *feat, i
 }
 
 void launch_draft_cat_f32(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d, void *cat,
-                          hipStream_t s, const int32_t *gate, const DraftInputs &in) {
-  draft_cat_f32_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const float *)emb, next_ids, d, (float *)cat, gate, in);
+                          hipStream_t s, const DraftInputs &in) {
+  draft_cat_f32_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const float *)emb, next_ids, d, (float *)cat, in);
 }
 
 }  // namespace ae

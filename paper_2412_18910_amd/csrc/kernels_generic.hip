@@ -39,15 +39,12 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x));
 
 // ------------------------------------------------------------------ RMSNorm
 // out = (x / sqrt(mean(x^2) + eps)) * g, one workgroup per row
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float *x, const float *g, int d, float eps, float *out,
-                                                      const int32_t *gate) {
-  AE_GATE(gate);
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const float *x, const float *g, int d, float eps, float *out) {
   rmsnorm_row(x + (size_t)blockIdx.x * d, g, d, eps, out + (size_t)blockIdx.x * d);
 }
 
-void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s,
-                    const int32_t *gate) {
-  rmsnorm_kernel<<<rows, 256, 0, s>>>(x, g, d, eps, out, gate);
+void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s) {
+  rmsnorm_kernel<<<rows, 256, 0, s>>>(x, g, d, eps, out);
 }
 
 // ------------------------------------------------------------------ tiny control kernels
@@ -114,7 +111,6 @@ __global__ __launch_bounds__(256) void export_row_kernel(const float *src, size_
   const size_t first = blockIdx.x * kExportPiece, end = first + kExportPiece < n ? first + kExportPiece : n;
   size_t i = first + threadIdx.x;
   if ((reinterpret_cast<uintptr_t>(src) & 15) == 0) {   // else: a row of an odd vocabulary
-#pragma unroll
     for (size_t k = first + threadIdx.x * 4; k < first + kExportPiece; k += 1024)
       if (k + 4 <= end) *reinterpret_cast<float4 *>(dst + k) = *reinterpret_cast<const float4 *>(src + k);
     i += (end - first) / 4 * 4;

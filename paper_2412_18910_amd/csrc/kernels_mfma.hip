@@ -445,8 +445,7 @@ void launch_pack_rows(const float *src, int ld, int rows, int K, const float *ga
 
 // draft head input [feature ; embedding of the following token] -> packed, K = 2d
 __global__ void draft_cat_packed_kernel(const float *feat, int feat_ld, const uint16_t *emb, const int32_t *next_ids,
-                                        int d, u32x4 *Xp, const int32_t *gate, const DraftInputs in) {
-  AE_GATE(gate);
+                                        int d, u32x4 *Xp, const DraftInputs in) {
   const int r = blockIdx.x;
   if (r == 0 && in.st) store_draft_inputs(in);
   const uint16_t *e = emb + (size_t)next_ids[r] * d;
@@ -460,8 +459,8 @@ __global__ void draft_cat_packed_kernel(const float *feat, int feat_ld, const ui
 }
 
 void launch_draft_cat_packed(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d,
-                             void *Xp, hipStream_t s, const int32_t *gate, const DraftInputs &in) {
-  draft_cat_packed_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const uint16_t *)emb, next_ids, d, (u32x4 *)Xp, gate, in);
+                             void *Xp, hipStream_t s, const DraftInputs &in) {
+  draft_cat_packed_kernel<<<rows, 256, 0, s>>>(feat, feat_ld, (const uint16_t *)emb, next_ids, d, (u32x4 *)Xp, in);
 }
 
 }  // namespace ae
