@@ -539,9 +539,9 @@ __global__ __launch_bounds__(256) void sum_rmsnorm_f32_kernel(const float *part,
   const size_t r = blockIdx.x;
   float ss = 0.f;
   for (int k = threadIdx.x * 4; k < d; k += 1024) {
-    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (base) v = *reinterpret_cast<const f32x4 *>(base + r * base_ld + k);
-    for (int p = 0; p < splits; ++p) v += *reinterpret_cast<const f32x4 *>(part + p * stride + r * d + k);
+    f32x4 v = *reinterpret_cast<const f32x4 *>(part + r * d + k);   // one rounding at the residual's magnitude
+    for (int p = 1; p < splits; ++p) v += *reinterpret_cast<const f32x4 *>(part + p * stride + r * d + k);
+    v += *reinterpret_cast<const f32x4 *>(base + r * base_ld + k);
     *reinterpret_cast<f32x4 *>(x + r * d + k) = v;
     ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   }
