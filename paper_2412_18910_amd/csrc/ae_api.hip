@@ -308,6 +308,17 @@ bool dense_ok(const ae_ctx *c) {
   return c->fast && g.d_model >= 256 && 2 * g.d_ffn >= 256 && (g.n_heads + 2 * g.n_kv_heads) * g.head_dim >= 256;
 }
 
+// The context's device for as long as it lives (the caller's thread may be on another one).
+struct OnDevice {
+  int before = -1;
+  explicit OnDevice(int device) {
+    if (hipGetDevice(&before) != hipSuccess || before == device || hipSetDevice(device) != hipSuccess) before = -1;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
+
 void release_dense(ae_ctx *c) {
   for (void *p : c->dense_owned) hipFree(p);
   c->dense_owned.clear();
@@ -326,6 +337,7 @@ int ensure_dense(ae_ctx *c, int n) {
   if (want <= c->dense_cap) return AE_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   release_dense(c);
+  const OnDevice here(c->device);   // float32 prompts never depended on the thread's device
   const size_t cap = want, d = g.d_model, dq = (size_t)g.n_heads * g.head_dim, dkv = (size_t)g.n_kv_heads * g.head_dim, f = g.d_ffn;
   const size_t dmax = dq > d ? dq : d;
   // sums over pieces of K.  float32: up to 8 pieces for short prompts; bf16: 768 tiles of 128 x 128, no more than

@@ -4,7 +4,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
-#include <set>
 #include <string>
 #include <vector>
 
@@ -15,13 +14,12 @@ namespace {
 struct Launch {
   std::string name;
   unsigned gx, gy, threads;
-  const void *arg0;   // first kernel argument by value, where it is a pointer
 };
 
 std::map<const void *, std::string> g_names;
 std::vector<Launch> g_launches;
 std::map<void *, size_t> g_live;
-std::vector<size_t> g_freed;
+int g_device = 0, g_malloc_device = -1;   // current one, that of the last device allocation
 hipError_t g_last = hipSuccess;
 long g_fail_launch = -1;     // launches until one fails
 size_t g_fail_alloc = 0;     // device allocations of this size and more fail (0: none)
@@ -50,22 +48,20 @@ const char *fake_name(int i) { return g_launches[i].name.c_str(); }
 void fake_grid(int i, unsigned *gx, unsigned *gy, unsigned *threads) {
   *gx = g_launches[i].gx; *gy = g_launches[i].gy; *threads = g_launches[i].threads;
 }
-void fake_clear() { g_launches.clear(); g_freed.clear(); }
+void fake_clear() { g_launches.clear(); }
 void fake_fail_launch(long after) { g_fail_launch = after; }
 void fake_fail_alloc(size_t bytes) { g_fail_alloc = bytes; }
 void fake_set_error(int e) { g_last = (hipError_t)e; }
 int fake_last_error() { return (int)g_last; }
 void fake_mute(int mute) { g_mute = mute != 0; }
 int fake_syncs() { return g_syncs; }
+void fake_set_device(int d) { g_device = d; }
+int fake_device() { return g_device; }
+int fake_malloc_device() { return g_malloc_device; }
 void fake_rule(int go_on) { g_go_on = go_on != 0; }
 size_t fake_live_bytes() {
   size_t t = 0;
   for (auto &a : g_live) t += a.second;
-  return t;
-}
-size_t fake_largest_free() {
-  size_t t = 0;
-  for (size_t b : g_freed) t = b > t ? b : t;
   return t;
 }
 
@@ -87,7 +83,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shm, hipSt
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t, hipStream_t) {
   if (g_fail_launch >= 0 && g_fail_launch-- == 0) return note(hipErrorLaunchOutOfResources);
   const std::string &name = g_names[f];
-  g_launches.push_back(Launch{name, grid.x, grid.y, block.x, arg<const void *>(args, 0)});
+  g_launches.push_back(Launch{name, grid.x, grid.y, block.x});
   if (g_mute) return hipSuccess;
   if (is(name, "export_row_kernel")) {
     memcpy(arg<float *>(args, 2), arg<const float *>(args, 0), arg<size_t>(args, 1) * sizeof(float));
@@ -115,10 +111,10 @@ hipError_t hipMalloc(void **p, size_t n) {
   if (g_fail_alloc && n >= g_fail_alloc) return note(hipErrorOutOfMemory);
   *p = calloc(1, n);
   g_live[*p] = n;
+  g_malloc_device = g_device;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
-  if (p) g_freed.push_back(g_live[p]);
   g_live.erase(p);
   free(p);
   return hipSuccess;
@@ -141,7 +137,8 @@ hipError_t hipGetLastError() {
 }
 hipError_t hipPeekAtLastError() { return g_last; }
 const char *hipGetErrorString(hipError_t) { return "planted"; }
-hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = g_device; return hipSuccess; }
+hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }

@@ -32,8 +32,7 @@ def load():
             binding._lib = saved
             os.remove(out)
         _lib.fake_name.restype = C.c_char_p
-        for f in ("fake_live_bytes", "fake_largest_free"):
-            getattr(_lib, f).restype = C.c_size_t
+        _lib.fake_live_bytes.restype = C.c_size_t
         _lib.fake_fail_alloc.argtypes = [C.c_size_t]
         _lib.fake_fail_launch.argtypes = [C.c_long]
     return _lib

@@ -79,3 +79,12 @@ def test_a_failed_larger_prompt_leaves_the_shorter_ones_working(make):
         assert c.prefill(2000) == (AE_ENOMEM if cfg.dtype == BF16 else AE_OK)
         assert c.prefill(100) == AE_OK
         c.lib.fake_fail_alloc(0)
+
+
+@pytest.mark.parametrize("cfg", [MID, TINY], ids=["bf16", "fp32"])
+def test_prompt_buffers_are_on_the_device_of_the_context(make, cfg):
+    c = make(cfg)
+    c.lib.fake_set_device(1)   # the thread has moved on to another GPU
+    assert c.prefill(100) == AE_OK
+    assert c.lib.fake_malloc_device() == 0 and c.lib.fake_device() == 1
+    c.lib.fake_set_device(0)
