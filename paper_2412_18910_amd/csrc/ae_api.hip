@@ -923,9 +923,9 @@ static int draft(ae_ctx *c, int k, const int32_t *override_ids, const double *u_
   // and lets the kernels of the tokens past k return at entry once the device-side rule says
   // stop (the verify block is then padded to k_max + 1 rows and ae_accept takes the drafted
   // length from the device).  Inside ae_step nothing else can happen meanwhile: there the host waits for the
-  // flag that the kernel behind each such token sets (about 8 us of an idle device; each token that is
-  // skipped would cost 10 launches of 3 us) and the block has its true length: 857 us instead of 1012 for a step of
-  // 2 tokens of at most 8, 4 layers of 7B.
+  // flag that the kernel behind each such token sets (each token that is skipped would cost 10 launches of
+  // 3 us) and the block has its true length: 854 us instead of 1015 for a step of 2 tokens of at most 8, 4 layers
+  // of 7B at 517 slots.
   const bool dev_rule = g.ddd_enabled && c->ddd_mode == AE_DDD_DEVICE && !poll_rule;
   const bool poll = g.ddd_enabled && poll_rule;
   // Ahead of each such wait goes the token's first kernel: it reads the head's input projection while the decision travels

@@ -198,7 +198,7 @@ static DenseSplit dense_splits(const GemmArgs &a, size_t part_floats) {
   for (int dn = 2; dn <= 3; ++dn) {
     if (a.NBtot < 8 * dn) break;
     const long tiles = (a.NBtot + 8 * dn - 1) / (8 * dn) * mt;
-    for (int S = 1; S <= 16 && S <= a.KT / 8; ++S) {   // at least two pairs of stages per piece
+    for (int S = 1; S <= 16 && S <= a.KT / 8; ++S) {   // a piece: two passes of the k-loop at least
       if ((size_t)S * a.rows * a.NBtot * 16 > part_floats) break;
       const double c = (double)((tiles * S + 255) / 256) * dn / S + 0.005 * S;   // rounds x work of a piece, its pass
       if (c < cost) { cost = c; best.splits = S; best.dn = dn; }

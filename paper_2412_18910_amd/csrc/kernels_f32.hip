@@ -19,7 +19,8 @@
 // of K then K / (2 c n).  The sums that a wave of scalar code makes (64 lanes, each a chain of K / 64 products, and a
 // butterfly) cost K / 128 + 6 of these, and neither GEMM may cost more: the decode GEMM cuts at 16 products (8 where K
 // is below 1024) and adds wave results as a tree, the prompt GEMM at 32 and 128 (K below 4096: 8, 32 and 128).
-// Measured against float64 at K = 4096: V rows 1.25e-7 (scalar sums 1.67e-7, one chain per accumulator 2.2e-7).
+// Measured against float64 at K = 4096, V rows: decode 1.19e-7, prompt 1.63e-7 (scalar sums 1.67e-7, one chain per
+// accumulator 2.2e-7).
 // The flash attention adds its accumulators to a second set every 256 keys.
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
@@ -195,8 +196,8 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
 // HBM-bound: each weight is read once.  A workgroup owns one block of 16 weight rows (gate/up: one of each) and all
 // of K, dealt to its waves in chunks of 64; a wave keeps a chunk (4 KB; gate/up: 8 KB) in flight in a rolling ring.
 // The rows of a row-major matrix lie a power of two apart, so workgroups that walk K in step ask the same few memory
-// channels: each starts at a chunk of its own (7B widths, microseconds: o / down 29.6 -> 25.7, draft fc 35.0 -> 24.0,
-// a draft token's LM head 105 -> 94; gate/up 76 -> 75 and QKV 42 -> 40 were spread by themselves).  Twice the depth, 4 or
+// channels: each starts at a chunk of its own (7B widths, microseconds: o / down 29.6 -> 25.5, draft fc 35.0 -> 23.9,
+// a draft token's LM head 105 -> 95; gate/up 76 -> 74 and QKV 42 -> 40 were spread by themselves).  Twice the depth, 4 or
 // 16 waves, and 4x4x1 products that read 256 bytes of a row per load were no faster.  Cutting the chains at 16 products
 // with one total per matrix is free (a step of 4 layers of 7B 2266 us, 2274 without); four totals cost 5 % (registers).
 // TAIL: K is no multiple of 64; pieces behind the end count as zeros.
@@ -501,14 +502,14 @@ static void launch_f32_dense_tile(const F32Args &a, hipStream_t s) {
   constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;
   const int tiles = (a.NB + NBT - 1) / NBT * ((a.rows + 16 * J - 1) / (16 * J));
   const dim3 grid((tiles + 7) / 8 * 8, a.splits);
-  // Chains of 32 cost 18 + K / 256 roundings (see the top), chains of 8 (three joins more a stage) 6 + K / 256; the scalar
+  // Chains of 32 cost 18 + K / 256 roundings (see the top), chains of 8 (three joins more a stage) 8 + K / 256; the scalar
   // sums cost 6 + K / 128.  7B widths, 2048 rows, 2 layers: 19.5 ms with chains of 32, 20.9 with chains of 8.
   if (a.K >= 4096) gemm_f32_dense_kernel<EPI, J, true><<<grid, 256, 0, s>>>(a);
   else gemm_f32_dense_kernel<EPI, J, false><<<grid, 256, 0, s>>>(a);
 }
 
 // Rows of a tile and (EPI_PART) pieces of K: the least of tiles per compute unit times rows of a tile over pieces.  A
-// narrow tile reads more of LDS and L2 per product (7B widths, 333 rows: gate/up 1078, 705, 622, 751 us with J = 1, 2,
+// narrow tile reads more of LDS and L2 per product (7B widths, 333 rows: gate/up 1083, 683, 649, 806 us with J = 1, 2,
 // 3, 4), a lone workgroup per compute unit has nothing to cover its barriers with, and each piece costs a pass over the
 // partial sums.
 template <int EPI>

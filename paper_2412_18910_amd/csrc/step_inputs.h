@@ -1,7 +1,7 @@
 // Small per-step work that rides on a kernel that is launched anyway instead of a launch of its own (a dependent
 // launch costs 1.5-4 us, whatever it does): the ids of the verify block, the inputs of a draft, feature rows, the greedy
 // acceptance test.  Four launches of a step fall away: float32 tiny model 334 -> 323 us, 4 layers of 7B with the exit
-// rule 842 -> 835, 32 layers 3789 -> 3783.
+// rule 842 -> 835; in a step of 32 layers (3.8 ms) that is less than runs differ by.
 #pragma once
 #include "ae_internal.h"
 

@@ -8,8 +8,8 @@ comparable with the paper: weights are random and acceptance is scripted.
 
 Two more rows run AdaEAGLE-DDD (Sec. 3.4: LDLP length, then keep drafting while the draft
 sequence's log-probability stays above a threshold) with the exit rule evaluated on the host
-(one synchronisation per decision past k) and on the device (no synchronisation inside the
-draft, skipped tokens cost empty launches, padded verify block).  The random-init head gives
+(one read-back of the device state per decision past k) and on the device (the host polls for each
+decision while the next token's first kernel runs).  The random-init head gives
 every token a near-uniform probability, so the paper's threshold of -0.6 would never extend a
 draft; the default threshold here is the log-probability of 3.5 tokens at the uniform rate,
 which extends short predicted lengths to 3-4 tokens.

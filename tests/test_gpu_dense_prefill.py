@@ -3,7 +3,8 @@
 The oracle runs the prompt in blocks of k_max+1 rows; the dense pass runs it in chunks of
 128..8192 rows with other kernels.  Both must leave the same state up to rounding: first
 token, last-position logits and feature, K/V rows of every layer and of the draft head, and
-the decode steps that follow.
+the decode steps that follow.  At these widths the GEMMs split K over workgroups; the kernels
+that take the whole of K are reached by the long prompts here and by test_gpu_prompt_tiles.py.
 """
 import numpy as np
 import pytest

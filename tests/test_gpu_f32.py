@@ -45,7 +45,8 @@ def one_step(cfg, eng, orc, k):
 @pytest.mark.parametrize("cfg", [RAGGED, WIDE], ids=["ragged-hd64", "wide-hd128"])
 @pytest.mark.parametrize("n,chunk", [(17, 0), (32, 0), (33, 0), (64, 0), (65, 0), (130, 128), (257, 128), (300, 0)])
 def test_prompt_and_steps_match_oracle(cfg, n, chunk):
-    """Prompts around the tiles of 32 and 64 rows, in one chunk and in several (a one-row last chunk among them)."""
+    """Prompts around the multiples of 16, 32 and 64 rows, in one chunk and in several (a one-row last chunk among
+    them).  These widths take tiles of 16 rows nearly everywhere; the other tiles: test_gpu_prompt_tiles.py."""
     eng, orc, _ = make_pair(cfg, 41)
     ids = synth.token_ids(n, cfg.vocab, 900 + n)
     orc.prefill(ids)
