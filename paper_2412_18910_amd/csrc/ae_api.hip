@@ -453,7 +453,9 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   auto project = [&](const Mat *W, const void *X, int ldx, int nrows, const float *bias, float *x, const float *gain) {
     GemmLaunch L;
     L.W = W; L.Xp = X; L.ldx = ldx; L.rows = nrows; L.bias = bias; L.eps = g.rms_eps;
-    launch_gemm_f32_resid_norm(L, c->ppart, c->ppart_floats, x, gain, xn, s);
+    // no more pieces than a buffer of this chunk's own size has room for: sums do not depend on earlier prompts
+    const size_t room = (size_t)(nrows > 2048 ? nrows : 2048) * d;
+    launch_gemm_f32_resid_norm(L, c->ppart, c->ppart_floats < room ? c->ppart_floats : room, x, gain, xn, s);
   };
   for (int l = 0; l < g.n_layers; ++l) {
     const LayerW &w = c->layers[l];
