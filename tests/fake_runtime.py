@@ -1,6 +1,5 @@
 """The library's host code over tests/fake_hip.cpp: no GPU, kernels recorded instead of run."""
 import ctypes as C
-import glob
 import os
 import subprocess
 
@@ -16,10 +15,9 @@ _lib = None
 def load():
     global _lib
     if _lib is None:
-        objs = sorted(glob.glob(os.path.join(build.OBJ_DIR, "*.o")))
-        if build.is_stale() or len(objs) != len(build.sources()):
+        objs = [os.path.join(build.OBJ_DIR, os.path.basename(s)[:-4] + ".o") for s in build.sources()]
+        if build.is_stale() or not all(map(os.path.exists, objs)):
             build.build()
-            objs = sorted(glob.glob(os.path.join(build.OBJ_DIR, "*.o")))
         out = os.path.join(build.OBJ_DIR, "fake", f"libadaeagle_fake_{os.getpid()}.so")
         os.makedirs(os.path.dirname(out), exist_ok=True)
         subprocess.check_call(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
