@@ -329,11 +329,16 @@ void release_dense(ae_ctx *c) {
 
 // Chunk buffers for `cap` rows (a multiple of 128): float residual stream and queries, the
 // inputs of the five GEMMs; bf16: RMSNorm partial sums and 1/rms, zero-filled so that the
-// padding rows of a packed chunk are finite.  Nothing is held where they do not fit; bf16 prompts
+// padding rows of a packed chunk are finite (float32: so that what lies behind the end of K is zero).  Nothing is held where they do not fit; bf16 prompts
 // do without room for pieces of K (no GEMM is split then).
 int ensure_dense(ae_ctx *c, int n) {
   const ae_config &g = c->cfg;
-  const int want = ((n < c->dense_chunk ? n : c->dense_chunk) + 127) / 128 * 128;
+  int want = ((n < c->dense_chunk ? n : c->dense_chunk) + 127) / 128 * 128;
+  if (!c->fast) {   // offsets into a plane buffer have 32 bits
+    const int widest = g.d_ffn > 2 * g.d_model ? g.d_ffn : 2 * g.d_model, dq = g.n_heads * g.head_dim;
+    const size_t fits = 0xffff0000u / planes_bytes(128, widest > dq ? widest : dq) * 128;
+    if ((size_t)want > fits && fits) want = (int)fits;
+  }
   if (want <= c->dense_cap) return AE_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   release_dense(c);
@@ -345,10 +350,12 @@ int ensure_dense(ae_ctx *c, int n) {
   const size_t part_rows = cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048;
   const size_t widest = 2 * f > dq + 2 * dkv ? 2 * f : dq + 2 * dkv, most = (size_t)768 * 128 * 128;
   const size_t part_floats = !c->fast ? part_rows * d : 16 * cap * widest < most ? 16 * cap * widest : most;
-  struct Buf { void **p; size_t bytes; };
+  struct Buf { void **p; size_t bytes; bool clear = true; };
+  const int w = want;
   const std::vector<Buf> bufs = !c->fast ? std::vector<Buf>{
-      {(void **)&c->px, cap * d * 4}, {(void **)&c->pq, cap * dq * 4}, {&c->pxa, cap * d * 4}, {&c->pxatt, cap * dmax * 4},
-      {&c->pxh, cap * f * 4}, {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, part_floats * 4}} : std::vector<Buf>{
+      {(void **)&c->px, cap * d * 4, false}, {(void **)&c->pq, cap * dmax * 4, false}, {(void **)&c->ppart, part_floats * 4},
+      {&c->pxa, planes_bytes(w, g.d_model), d % 32 != 0}, {&c->pxatt, planes_bytes(w, (int)dq), dq % 32 != 0},
+      {&c->pxh, planes_bytes(w, g.d_ffn), f % 32 != 0}, {&c->pxcat, planes_bytes(w, 2 * g.d_model), 2 * d % 32 != 0}} : std::vector<Buf>{
       {(void **)&c->px, cap * d * 4},      {(void **)&c->pq, cap * dq * 4},   {(void **)&c->prinv, cap * 4},
       {(void **)&c->pssq_a, cap * d * 4 / 16 * 1 + cap * 4}, {(void **)&c->pssq_f, cap * d * 4 / 16 + cap * 4},
       {&c->pxa, cap * d * 4},              {&c->pxf, cap * d * 4},            {&c->pxatt, cap * dq * 4},
@@ -368,7 +375,7 @@ int ensure_dense(ae_ctx *c, int n) {
     c->dense_owned.push_back(q);
     *b.p = q;
     if (part) c->ppart_floats = part_floats;
-    else if (c->fast) launch_fill_zero(q, bytes, c->stream);
+    else if (b.clear) launch_fill_zero(q, bytes, c->stream);
   }
   c->dense_cap = want;
   return AE_OK;
@@ -430,52 +437,46 @@ void dense_chunk(ae_ctx *c, int p0, int rows, int drows) {
   }
 }
 
-// The same in float32: wide GEMMs over rows; the sum kernel behind the o, down and fc projections normalises
-// the rows for the next one.
+// The same in float32: the sum kernel behind the o, down and fc projections normalises the rows for the next GEMM.
 void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   const ae_config &g = c->cfg;
   hipStream_t s = c->stream;
-  const int d = g.d_model, dq = g.n_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn;
-  float *xn = (float *)c->pxa, *att = (float *)c->pxatt;
+  const int d = g.d_model, dq = g.n_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn, RB = c->dense_cap / 16;
   BlockIds ids;
   ids.ids = c->hist + p0;
   launch_embed_f32(c->tok_emb, ids, rows, d, nullptr, c->px, nullptr, nullptr, s);
-  launch_rmsnorm(c->px, c->layers[0].attn_norm, rows, d, g.rms_eps, xn, s);
+  launch_norm_cat_f32(c->px, rows, d, c->layers[0].attn_norm, g.rms_eps, nullptr, nullptr, c->pxa, RB, s);
   auto qkv_pass = [&](int li, int nrows, bool with_q) {   // projections, rotary embedding, cache append
     GemmLaunch qkv;
-    qkv.W = &c->layers[li].f_qkv; qkv.Xp = xn; qkv.ldx = d; qkv.rows = nrows; qkv.epi = EPI_QKV;
+    qkv.W = &c->layers[li].f_qkv; qkv.Xp = c->pxa; qkv.rows = nrows; qkv.epi = EPI_QKV;
     qkv.Y[0] = c->pq; qkv.ldy[0] = dq;
     qkv.seg_N[0] = with_q ? dq : 0; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
     qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
     qkv.pos0 = p0; qkv.n_ctx = kv_capacity(g); qkv.hd = g.head_dim;
-    launch_gemm_f32_dense(qkv, s);
+    launch_gemm_f32_dense(qkv, RB, s);
   };
-  auto project = [&](const Mat *W, const void *X, int ldx, int nrows, const float *bias, float *x, const float *gain) {
+  auto project = [&](const Mat *W, const void *X, int nrows, const float *base, size_t base_ld, float *x, const float *gain) {
     GemmLaunch L;
-    L.W = W; L.Xp = X; L.ldx = ldx; L.rows = nrows; L.bias = bias; L.eps = g.rms_eps;
+    L.W = W; L.Xp = X; L.rows = nrows; L.eps = g.rms_eps;
     // no more pieces than a buffer of this chunk's own size has room for: sums do not depend on earlier prompts
     const size_t room = (size_t)(nrows > 2048 ? nrows : 2048) * d;
-    launch_gemm_f32_resid_norm(L, c->ppart, c->ppart_floats < room ? c->ppart_floats : room, x, gain, xn, s);
+    launch_gemm_f32_resid_norm(L, RB, c->ppart, c->ppart_floats < room ? c->ppart_floats : room, base, base_ld, x, gain,
+                               gain ? c->pxa : nullptr, s);
   };
   for (int l = 0; l < g.n_layers; ++l) {
     const LayerW &w = c->layers[l];
     qkv_pass(l, rows, true);
-    launch_attention_prefill_f32(c->pq, rows, p0, g, kv_layer_ptr(c, l), c->kv_v_offset, att, s);
-    project(&w.wo, att, dq, rows, nullptr, c->px, w.ffn_norm);
+    launch_attention_prefill_f32(c->pq, rows, p0, g, kv_layer_ptr(c, l), c->kv_v_offset, c->pxatt, RB, s);
+    project(&w.wo, c->pxatt, rows, c->px, d, c->px, w.ffn_norm);
     GemmLaunch gu;
-    gu.W = &w.f_gu; gu.Xp = xn; gu.ldx = d; gu.rows = rows; gu.epi = EPI_SWIGLU; gu.Xp_out = c->pxh; gu.ldxo = f;
-    launch_gemm_f32_dense(gu, s);
-    project(&w.w_down, c->pxh, f, rows, nullptr, c->px, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : c->final_norm);
+    gu.W = &w.f_gu; gu.Xp = c->pxa; gu.rows = rows; gu.epi = EPI_SWIGLU; gu.Xp_out = c->pxh; gu.ldxo = f;
+    launch_gemm_f32_dense(gu, RB, s);
+    project(&w.w_down, c->pxh, rows, c->px, d, c->px, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : nullptr);
   }
   if (drows > 0) {
-    // Eq. 2 catch-up of prompt slots: only the head's K/V rows are ever read again
-    launch_draft_cat_f32(xn, d, c->tok_emb, c->hist + p0 + 1, drows, d, c->pxcat, s, DraftInputs());
-    if (c->draft_fc_b) {
-      project(&c->draft_fc, c->pxcat, 2 * d, drows, c->draft_fc_b, att, c->layers[g.n_layers].attn_norm);
-    } else {
-      launch_fill_zero(att, (size_t)drows * d * 4, s);
-      project(&c->draft_fc, c->pxcat, 2 * d, drows, nullptr, att, c->layers[g.n_layers].attn_norm);
-    }
+    // Eq. 2 catch-up of prompt slots: only the head's K/V rows are ever read again (pq: the head's residual rows)
+    launch_norm_cat_f32(c->px, drows, d, c->final_norm, g.rms_eps, c->tok_emb, c->hist + p0 + 1, c->pxcat, RB, s);
+    project(&c->draft_fc, c->pxcat, drows, c->draft_fc_b, 0, c->pq, c->layers[g.n_layers].attn_norm);
     qkv_pass(g.n_layers, drows, false);
   }
 }

@@ -140,8 +140,8 @@ struct ae_ctx {
   size_t row_floats = 0;           // floats of that row, a multiple of kExportPiece; a flag word per piece follows it
   uint32_t seq = 0;                // number of the last request to the device
 
-  // dense prompt pass: chunk buffers, allocated at the first long prompt (float32: pxa normalised rows, pxh FFN
-  // rows, pxcat draft head input, pxatt attention output; pxf and the partial sums are bf16 only)
+  // dense prompt pass: chunk buffers, allocated at the first long prompt (pxa normalised rows, pxh FFN rows, pxcat draft head
+  // input, pxatt attention output, packed or float32 planes; pxf and the partial sums are bf16 only)
   int prefill_mode = 0;            // AE_PREFILL_AUTO / _BLOCKS / _DENSE
   int dense_chunk = 2048;          // rows per dense pass (multiple of 128)
   int dense_cap = 0;               // rows the buffers below hold
@@ -341,16 +341,22 @@ void launch_attention_prefill(const float *q, int rows, int pos0, const ae_confi
 
 // ---- float32 models (kernels_f32.hip) ----
 void launch_gemm_f32(const GemmLaunch &L, hipStream_t s);         // 1..16 rows, all epilogues and fusions
-// prompt GEMMs, any number of rows, Xp already normalised: EPI_QKV and EPI_SWIGLU
-void launch_gemm_f32_dense(const GemmLaunch &L, hipStream_t s);
-// x = Xp . W^T + (L.bias, or x), xn = RMSNorm(x) * gain; part: room for max_part floats, at least rows * N
-void launch_gemm_f32_resid_norm(const GemmLaunch &L, float *part, size_t max_part, float *x, const float *gain, float *xn,
-                                hipStream_t s);
+// Prompt GEMMs, any number of rows; activations in planes of RB row-blocks (kernels_f32.hip), already normalised: EPI_QKV
+// and EPI_SWIGLU (planes out)
+void launch_gemm_f32_dense(const GemmLaunch &L, int RB, hipStream_t s);
+// x = Xp . W^T + base (row stride base_ld, nullable), Xp_out = RMSNorm(x) * gain (nullable); part: room for max_part
+// floats, at least rows * N
+void launch_gemm_f32_resid_norm(const GemmLaunch &L, int RB, float *part, size_t max_part, const float *base, size_t base_ld, float *x,
+                                const float *gain, void *Xp_out, hipStream_t s);
+// [RMSNorm(x) * gain ; embedding of the token that follows (emb == nullptr: no second half)] -> planes
+void launch_norm_cat_f32(const float *x, int rows, int d, const float *gain, float eps, const void *emb, const int32_t *next_ids,
+                         void *Xp, int RB, hipStream_t s);
+size_t planes_bytes(int rows, int K);   // activations of K columns
 void launch_attention_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
                           float *part, float *out, hipStream_t s, const int32_t *gate = nullptr);
 int attn_f32_chunk_keys();   // keys per split-KV workgroup
 void launch_attention_prefill_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
-                                  float *out, hipStream_t s);
+                                  void *Xp, int RB, hipStream_t s);
 void launch_embed_f32(const void *emb, const BlockIds &ids, int rows, int d, const float *gain, float *x, void *Xo, float *ssq,
                       hipStream_t s);
 void launch_draft_cat_f32(const float *feat, int feat_ld, const void *emb, const int32_t *next_ids, int rows, int d, void *cat,

@@ -1,6 +1,6 @@
 // Float32 models (weights, activations and KV cache in float32) on the gfx950 matrix cores.
 //
-// Everything multiplies with v_mfma_f32_16x16x4_f32: operands and accumulators stay float32, the
+// Everything but the prompt GEMM multiplies with v_mfma_f32_16x16x4_f32: operands and accumulators stay float32, the
 // weights are read in the caller's row-major layout.  A lane (g = lane/16, m = lane%16) feeds four
 // consecutive k of one row (one 128-bit load) to four instructions, element e of every lane to
 // instruction e: the order of k inside a sum is free, so the A operand (weight row m) and the B
@@ -10,17 +10,16 @@
 //  * gemm_f32_kernel: up to 16 activation rows (decode, verify).  HBM-bound: a workgroup owns one
 //    block of 16 weight rows (gate/up: one of each) and all of K, dealt to its waves in pieces of 64.
 //    One kernel for every row count, so a row's result does not depend on the rows beside it.
-//  * gemm_f32_dense_kernel: prompts.  Bound by the float32 matrix rate (about 150 TFLOP/s): tiles of 128 weight
-//    rows x 16, 32, 48 or 64 activation rows through LDS.
+//  * gemm_f32_dense_kernel: prompts.  Bound by the matrix cores, which there multiply float32 numbers as three bf16 parts
+//    each: tiles of 128 weight rows x 16, 32, 48 or 64 activation rows through LDS.
 //  * attn_f32_kernel: split-KV attention of up to 16 rows; attn_prefill_f32_kernel: causal flash
 //    attention of a prompt chunk.
 // Every product that joins an accumulator is rounded, so long sums are cut.  Counted in variances of one rounding at
 // the result's magnitude, a chain of c products costs c / 2, a chain of n sums of c products n / 2, and what is left
 // of K then K / (2 c n).  The sums that a wave of scalar code makes (64 lanes, each a chain of K / 64 products, and a
 // butterfly) cost K / 128 + 6 of these, and neither GEMM may cost more: the decode GEMM cuts at 16 products (8 where K
-// is below 1024) and adds wave results as a tree, the prompt GEMM at 32 and 128 (K below 4096: 8, 32 and 128).
-// Measured against float64 at K = 4096, V rows: decode 1.19e-7, prompt 1.63e-7 (scalar sums 1.67e-7, one chain per
-// accumulator 2.2e-7).
+// is below 1024) and adds wave results as a tree.  The prompt GEMM's instruction adds 32 products with fewer roundings;
+// its chains of three instructions join one total.
 // The flash attention adds its accumulators to a second set every 256 keys.
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
@@ -40,6 +39,9 @@ struct F32Args {
   int NB;               // row-blocks of 16 output rows
   const float *X;       // activations, row r at X + r * ldx
   int ldx, rows, row0;  // output row m reads activation row row0 + m
+  const u32x4 *Xp;      // prompt GEMM: activations in three bf16 planes (see below) of RB row-blocks
+  u32x4 *Xp_out;        // ... EPI_SWIGLU: and its output
+  int RB;
   const float *ssq_in;  // NORM: [P_in][16] partial sums of x^2
   int P_in;
   float eps;
@@ -64,20 +66,28 @@ enum { EPI_PART = 4 };  // prompt GEMM: raw partial sums over a piece of K
 // Weight row that lane m of row-block nb feeds, and its source.  The rows of every q and k head are
 // taken in rotary-pair order: tile j of a head holds rows 8j..8j+7 and their partners hd/2+8j.., so
 // that a pair sits in lanes l and l^32 of one accumulator.
+struct F32Rows {
+  const float *base;   // the same for all lanes
+  int row;             // this lane's row behind it
+};
 template <int EPI>
-__device__ __forceinline__ const float *f32_weight_row(const F32Args &a, int nb, int m) {
+__device__ __forceinline__ F32Rows f32_weight_rows(const F32Args &a, int nb, int m) {
   if (EPI == EPI_QKV) {
     int si = 0, nbs = nb;
     if (nb >= a.seg_nb[0]) { si = 1; nbs = nb - a.seg_nb[0]; }
     if (nb >= a.seg_nb[1]) { si = 2; nbs = nb - a.seg_nb[1]; }
-    int row = nbs * 16 + m;
     if (si < 2) {
       const int bph = a.hd >> 4, head = nbs / bph, j = nbs % bph;
-      row = head * a.hd + (m < 8 ? 8 * j + m : (a.hd >> 1) + 8 * j + m - 8);
+      return F32Rows{a.W[si] + (size_t)head * a.hd * a.K, m < 8 ? 8 * j + m : (a.hd >> 1) + 8 * j + m - 8};
     }
-    return a.W[si] + (size_t)row * a.K;
+    return F32Rows{a.W[si] + (size_t)nbs * 16 * a.K, m};
   }
-  return a.W[0] + (size_t)min(nb * 16 + m, a.N - 1) * a.K;
+  return F32Rows{a.W[0] + (size_t)nb * 16 * a.K, min(m, a.N - 1 - nb * 16)};
+}
+template <int EPI>
+__device__ __forceinline__ const float *f32_weight_row(const F32Args &a, int nb, int m) {
+  const F32Rows r = f32_weight_rows<EPI>(a, nb, m);
+  return r.base + (size_t)r.row * a.K;
 }
 
 template <int EPI>
@@ -353,17 +363,91 @@ void launch_gemm_f32(const GemmLaunch &L, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ prompt GEMM
+// Products of float32 numbers on the bf16 matrix instruction.  x = hi + mid + lo in bf16 (round to nearest even; the
+// remainders are exact) holds all 24 bits; of the nine products the three smallest (2^-26 of the whole) are left out.  The
+// instruction takes 6 x 16 cycles for what v_mfma_f32_16x16x4_f32 takes 256 for, and rounds once for several products
+// where that rounds each.  Activations come split ("planes", written by the kernels before), weights are split on the way.
+//
+// Planes: Xp[kt][rb][hi, mid, lo][slot = row * 4 + k octet] of 16 bytes, the packed form of packed.h with three parts; what
+// lies behind the end of K in the last k-tile is zero.  hi + mid + lo is x for every x, Inf and NaN included.
+__device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
+  bf16x2 h;
+  h[0] = (__bf16)x0; h[1] = (__bf16)x1;
+  uint32_t p = __builtin_bit_cast(uint32_t, h);
+  asm("" : "+v"(p));   // (else every half is converted a second time where its value is needed)
+  return p;
+}
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t (&p)[3]) {
+  p[0] = pack_bf16(x0, x1);
+  const float r0 = x0 - __uint_as_float(p[0] << 16), r1 = x1 - __uint_as_float(p[0] & 0xffff0000u);
+  p[1] = pack_bf16(r0, r1);
+  p[2] = pack_bf16(r0 - __uint_as_float(p[1] << 16), r1 - __uint_as_float(p[1] & 0xffff0000u));
+}
+constexpr int kPlanePieces = 192;   // 16-byte pieces of a row-block and k-tile
+
+// Four consecutive k (k0 % 4 == 0) of row m of the row-block whose first tile is at xp; kts: pieces from k-tile to k-tile
+__device__ __forceinline__ void planes_store4(u32x4 *xp, int m, int k0, f32x4 x, size_t kts) {
+  uint32_t p[2][3];
+  split3(x[0], x[1], p[0]);
+  split3(x[2], x[3], p[1]);
+  // what rounds up to Inf is cut off instead, Inf and NaN stand alone
+  constexpr float kBf16Max = 3.3895313892515355e38f;
+  const float big = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])));
+  if (!(big < kBf16Max) || x[0] != x[0] || x[1] != x[1] || x[2] != x[2] || x[3] != x[3]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool finite = x[e] - x[e] == 0.f;
+      const float h = fminf(fmaxf(x[e], -kBf16Max), kBf16Max);
+      uint32_t q[3] = {(__float_as_uint(x[e]) >> 16) | (x[e] != x[e] ? 0x40u : 0u), 0u, 0u};
+      if (finite) split3(h, 0.f, q);
+      if (finite && h != x[e]) {   // h is one bf16 number; the remainder has 16 bits
+        uint32_t r[3];
+        split3(x[e] - h, 0.f, r);
+        q[1] = r[0];
+        q[2] = r[1];
+      }
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        const uint32_t v = q[n] & 0xffffu;
+        p[e >> 1][n] = e & 1 ? (p[e >> 1][n] & 0xffffu) | v << 16 : (p[e >> 1][n] & 0xffff0000u) | v;
+      }
+    }
+  }
+  const int g = (k0 & 31) >> 3, half = (k0 & 7) >> 2;
+#pragma unroll
+  for (int n = 0; n < 3; ++n) reinterpret_cast<u32x2 *>(xp + (size_t)(k0 >> 5) * kts + n * 64 + m * 4 + g)[half] = u32x2{p[0][n], p[1][n]};
+}
+__device__ __forceinline__ f32x4 planes_load4(const u32x4 *xp, int m, int k0, size_t kts) {
+  u32x2 v[3];
+#pragma unroll
+  for (int n = 0; n < 3; ++n)
+    v[n] = reinterpret_cast<const u32x2 *>(xp + (size_t)(k0 >> 5) * kts + n * 64 + m * 4 + ((k0 & 31) >> 3))[(k0 & 7) >> 2];
+  f32x4 x;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float f[3];
+#pragma unroll
+    for (int n = 0; n < 3; ++n) f[n] = __uint_as_float(e & 1 ? v[n][e >> 1] & 0xffff0000u : v[n][e >> 1] << 16);
+    x[e] = f[0] + (f[1] + f[2]);
+  }
+  return x;
+}
+
 // Workgroup tile: 128 weight rows (gate/up: 64 of each) x 16*J activation rows; each of the 4 waves owns two
-// weight row-blocks and all J activation row-blocks.  Stages of 32 k go global -> registers -> LDS (in lane
-// order: conflict-free), two stages ahead.
+// weight row-blocks and all J activation row-blocks.  Stages of 32 k go straight into LDS, weights three stages ahead,
+// activations one.  While a stage is multiplied the weights of the next one are split, vector instructions between the
+// matrix instructions: an MFMA of 16 cycles leaves room for two.  7B widths, 333 rows, against the float32 instruction:
+// gate/up 649 -> 382 us, QKV 408 -> 238, o / down 247 -> 146 on average; activations split here too (44 vector instructions
+// more a stage) 478 / 295 / 182.  What is left of the matrix rate (40 %): 3.7 vector instructions an MFMA at J = 3, rounds
+// of 512 workgroups that are not full (2.35 and 1.3 of them), clocks of 2.05 GHz.
 template <int EPI, int J, bool LONG>
-__global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
-  constexpr int TM = 16 * J;
-  constexpr int STAGE = (8 + J) * 128, NLB = (J + 1) / 2;   // 16-byte pieces per LDS stage; B pieces per thread
-  constexpr int PD = 2;                                     // register sets: stages in flight
-  constexpr int UN = 4;                                     // stages per loop pass
-  __shared__ f32x4 sm[2][STAGE];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
+__global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a) {
+  constexpr int TM = 16 * J, CH = LONG ? 6 : 3;             // CH: stages in a chain of products
+  constexpr int NX = (3 * J + 3) / 4;                       // activation tiles of 1 KB that a wave loads per stage
+  // Activations of two stages [row-block][hi, mid, lo][lane], weights of three as they are [wave][row-block][slot]: arrays
+  // of their own, so that the compiler can tell a read of one from a load into another.
+  __shared__ u32x4 x0[J * kPlanePieces], x1[J * kPlanePieces], a0[4 * 256], a1[4 * 256], a2[4 * 256];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, m = lane & 15;
   // the activation tiles of one weight tile run side by side on one XCD (ids go round the 8 XCDs) and share it in its L2
   constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;            // output row-blocks per workgroup
   const int NT = (a.NB + NBT - 1) / NBT, MT = (a.rows + TM - 1) / TM;
@@ -371,116 +455,201 @@ __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
   if (((int)blockIdx.x >> 3) >= per || v >= NT * MT) return;
   const int nb_t = v / MT * NBT, row_t = (v % MT) * TM;
   // this workgroup's piece of K, in stages of 32
-  int NS = (a.K + 31) / 32, lo = 0;
+  int NS = (a.K + 95) / 96 * 3, lo = 0;                     // in threes
   if (EPI == EPI_PART) {
-    lo = NS * (int)blockIdx.y / a.splits;
-    NS = NS * ((int)blockIdx.y + 1) / a.splits - lo;
+    const int np = NS / 3;
+    lo = np * (int)blockIdx.y / a.splits * 3;
+    NS = np * ((int)blockIdx.y + 1) / a.splits * 3 - lo;
   }
   const int K = min(a.K, (lo + NS) * 32) - lo * 32;
 
-  // the 4 A pieces and NLB B pieces this thread stages: piece p = (row-block, k half, lane)
-  const float *ap[4], *bp[NLB];
-  const int kt = ((tid >> 6) & 1) * 16 + ((tid & 63) >> 4) * 4;   // k inside the stage, the same for all of them
+  // Operands come through buffer loads: a base for the wave from the piece's first k on, a byte offset a lane, the stage in
+  // a scalar; pieces behind the end of K are out of range and read as zeros.  Eight lanes take the 128 bytes of a weight row
+  // one after the other: with a row a lane, as the products want them, the address unit takes four times as long.
+  constexpr int kRange = 0x7ffffff0;
+  const size_t kts = (size_t)a.RB * kPlanePieces;
+  const unsigned kts_b = a.RB * (kPlanePieces * 16u);
+  const int q = lane & 7;
+  __amdgpu_buffer_rsrc_t ra[2];
+  unsigned va[2][2], vx[NX];
+  int ka[2];
+  // row-blocks behind the last one of the chunk are not read
+  const u32x4 *xbase = a.Xp + (size_t)lo * kts + (size_t)(row_t >> 4) * kPlanePieces;
+  const int rbs = min(J, a.RB - (row_t >> 4));
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)xbase, 0, -1, 0x00020000);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int rb = 2 * i + (tid >> 7);
-    if (EPI == EPI_SWIGLU)   // row-blocks alternate gate, up
-      ap[i] = a.W[rb & 1] + (size_t)min((nb_t + (rb >> 1)) * 16 + m, a.N - 1) * a.K + kt;
-    else
-      ap[i] = f32_weight_row<EPI>(a, min(nb_t + rb, a.NB - 1), m) + lo * 32 + kt;
-  }
+  for (int i = 0; i < NX; ++i) vx[i] = (min(w + 4 * i, 3 * rbs - 1) * 64 + m * 4 + g) * 16;   // in lane order in LDS
 #pragma unroll
-  for (int i = 0; i < NLB; ++i)
-    bp[i] = a.X + (size_t)min(row_t + (2 * i + (tid >> 7)) * 16 + m, a.rows - 1) * a.ldx + lo * 32 + kt;
-  f32x4 areg[PD][4], breg[PD][NLB];
-  auto issue = [&](int k0, f32x4 (&ar)[4], f32x4 (&br)[NLB]) {
-    const int off = k0 + kt < K ? k0 : -kt;   // pieces behind the end of K re-read the row's start
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ar[i] = *reinterpret_cast<const f32x4 *>(ap[i] + off);
-#pragma unroll
-    for (int i = 0; i < NLB; ++i) br[i] = *reinterpret_cast<const f32x4 *>(bp[i] + off);
-  };
-  // (zeroing here and not at the load: a use of the loaded values there would wait for them)
-  auto stash = [&](int k0, int buf, f32x4 (&ar)[4], f32x4 (&br)[NLB]) {
-    if (k0 + 32 > K && k0 + kt >= K) {   // ... and count as zeros
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ar[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < NLB; ++i) br[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sm[buf][tid + 256 * i] = ar[i];
-#pragma unroll
-    for (int i = 0; i < NLB; ++i)
-      if (J % 2 == 0 || i + 1 < NLB || tid < 128) sm[buf][1024 + tid + 256 * i] = br[i];
-  };
-  // acc: chains of 8 products, joined in sums over a stage (s32; LONG: chains of a whole stage), these in sums over a
-  // loop pass (s128), these in the total
-  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[2][J], s32[2][J], s128[2][J], tot[2][J];
+  for (int h = 0; h < 2; ++h) ka[h] = 4 * (q ^ ((h * 8 + (lane >> 3)) >> 1));   // slot r * 8 + q holds piece q ^ (r / 2) of row r
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < J; ++j) tot[i][j] = zero;
-  // stage st waits in LDS, stages st+1 .. st+PD are on their way in register sets (stage mod PD)
-#pragma unroll
-  for (int u = 0; u < PD; ++u) issue(u * 32, areg[u], breg[u]);
-  stash(0, 0, areg[0], breg[0]);
-  __syncthreads();
-  for (int st0 = 0; st0 < NS; st0 += UN) {
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const int st = st0 + u;
-      if (st >= NS) break;
-      issue((st + PD) * 32, areg[u % PD], breg[u % PD]);
-      __builtin_amdgcn_sched_barrier(0);
-      const f32x4 *sa = sm[u & 1] + w * 256 + lane, *sb = sm[u & 1] + 1024 + lane;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        f32x4 fa[2], fb[J];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) fa[i] = sa[i * 128 + ks * 64];
-#pragma unroll
-        for (int j = 0; j < J; ++j) fb[j] = sb[j * 128 + ks * 64];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < J; ++j) {   // a chain joins its sum when the next one starts: its products are through
-              const bool first = LONG ? ks == 0 && e == 0 : e % 2 == 0;
-              if (first && (ks || e)) s32[i][j] = ks == 0 ? acc[i][j] : s32[i][j] + acc[i][j];
-              if (first && LONG && u > 0) s128[i][j] = u == 1 ? acc[i][j] : s128[i][j] + acc[i][j];
-              acc[i][j] = mfma_f32(fa[i][e], fb[j][e], first ? zero : acc[i][j]);
-            }
+    for (int h = 0; h < 2; ++h) {
+      const int r = h * 8 + (lane >> 3);
+      F32Rows t;
+      if (EPI == EPI_SWIGLU) {   // a gate and an up block
+        const int nb = min(nb_t + w, a.NB - 1);
+        t = F32Rows{a.W[i] + (size_t)nb * 16 * a.K, min(r, a.N - 1 - nb * 16)};
+      } else {
+        t = f32_weight_rows<EPI>(a, min(nb_t + w * 2 + i, a.NB - 1), r);
       }
-      if (LONG && u > 0) {   // the joins go between the products that start the chains, not in front of them
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 + J, 0);
-#pragma unroll
-        for (int i = 0; i < 2 * J; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 + J, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 14 * J, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      stash((st + 1) * 32, (u + 1) & 1, areg[(u + 1) % PD], breg[(u + 1) % PD]);
-      if (!LONG) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < J; ++j) {
-            s32[i][j] += acc[i][j];
-            s128[i][j] = u == 0 ? s32[i][j] : s128[i][j] + s32[i][j];
-          }
-      }
-      __syncthreads();
+      ra[i] = __builtin_amdgcn_make_buffer_rsrc((void *)(t.base + lo * 32), 0, kRange, 0x00020000);
+      va[i][h] = ((unsigned)t.row * a.K + ka[h]) * 4;
     }
+  auto issue_a = [&](int st, u32x4 *slot) {
+    const int s = min(st, NS) * 128;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const bool in = st * 32 + ka[h] < K;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra[i], (__attribute__((address_space(3))) void *)(slot + w * 256 + i * 128 + h * 64),
+                                                 16, in ? va[i][h] : kRange, s, 0, 0);
+    }
+  };
+  auto issue_x = [&](int st, u32x4 *slot) {   // stages without k repeat the last one (its weights are zeros)
+    const unsigned s = (unsigned)min(st, (K + 31) / 32 - 1) * kts_b;
+#pragma unroll
+    for (int i = 0; i < NX; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(slot + min(w + 4 * i, 3 * J - 1) * 64),
+                                               16, (int)vx[i], s, 0, 0);
+  };
+  // every wave waits for its own loads (all but the 4 newest, weights that have two stages left), then for the others
+  auto gate = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xf74);   // vmcnt(4)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int as = m * 8 + ((2 * g) ^ (m >> 1));   // where this lane's weights are in a tile
+  f32x4 raw[2][2];   // weights of the stage that is split next
+  auto read_raw = [&](const u32x4 *slot) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < J; ++j) tot[i][j] += LONG && NS - st0 == 1 ? acc[i][j] : LONG ? s128[i][j] + acc[i][j] : s128[i][j];
+      for (int e = 0; e < 2; ++e) raw[i][e] = __builtin_bit_cast(f32x4, slot[w * 256 + i * 128 + (as ^ e)]);
+  };
+  auto split = [&](u32x4 (&f)[2][3]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      uint32_t p[4][3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) split3(raw[i][e >> 1][e % 2 * 2], raw[i][e >> 1][e % 2 * 2 + 1], p[e]);
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        f[i][n] = u32x4{p[0][n], p[1][n], p[2][n], p[3][n]};
+        asm volatile("" : "+v"(f[i][n]));   // here, not where it is used
+      }
+    }
+  };
+  // acc: chains of CH stages of the large products, joined in tot; sml: the small ones, whose roundings do not matter
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[2][J], tot[2][J], sml[2][J];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < J; ++j) acc[i][j] = tot[i][j] = sml[i][j] = zero;
+  u32x4 fa[2][2][3];   // split weights of stages st and st+1
+  // Stage st: products with the activations xs, beside them the splitting of the weights of stage st+1 (in raw).  x1st: room for
+  // the activations of stage st+1; a2nd: weights of stage st+2; far: room for those of stage st+3.
+  auto stage = [&](int st, int u, const u32x4 *xs, u32x4 *x1st, const u32x4 *a2nd, u32x4 *far) {
+    issue_x(st + 1, x1st);
+    issue_a(st + 3, far);
+    __builtin_amdgcn_sched_barrier(0);
+    const u32x4 *sb = xs + lane;
+    const u32x4 (&f)[2][3] = fa[u & 1];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const u32x4 b0 = sb[(j * 3 + 0) * 64], b1 = sb[(j * 3 + 1) * 64], b2 = sb[(j * 3 + 2) * 64];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (u % CH == 0) tot[i][j] += acc[i][j];
+        acc[i][j] = mfma_bf16(f[i][0], b0, u % CH == 0 ? zero : acc[i][j]);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) sml[i][j] = mfma_bf16(f[i][2], b0, sml[i][j]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) sml[i][j] = mfma_bf16(f[i][0], b2, sml[i][j]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) sml[i][j] = mfma_bf16(f[i][1], b1, sml[i][j]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) sml[i][j] = mfma_bf16(f[i][1], b0, sml[i][j]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) sml[i][j] = mfma_bf16(f[i][0], b1, sml[i][j]);
+    }
+    split(fa[(u + 1) & 1]);
+    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+    for (int n = 0; n < 12 * J; ++n) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, (96 + 12 * J - 1) / (12 * J), 0);
+      if (n % 4 == 0 && n / 4 < 3 * (J - 1)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xf70 | (NX + 4));   // vmcnt: all but what this stage asked for
+    asm volatile("" ::: "memory");
+    read_raw(a2nd);
+    gate();
+  };
+  issue_a(0, a0);
+  issue_a(1, a1);
+  issue_x(0, x0);
+  issue_a(2, a2);
+  gate();
+  read_raw(a0);
+  split(fa[0]);
+  read_raw(a1);
+  for (int st = 0; st < NS; st += 6) {
+    stage(st, 0, x0, x1, a2, a0);
+    stage(st + 1, 1, x1, x0, a0, a1);
+    stage(st + 2, 2, x0, x1, a1, a2);
+    if (st + 3 >= NS) break;
+    stage(st + 3, 3, x1, x0, a2, a0);
+    stage(st + 4, 4, x0, x1, a0, a1);
+    stage(st + 5, 5, x1, x0, a1, a2);
+  }
+  __builtin_amdgcn_s_waitcnt(0xf70);   // vmcnt(0): no load into LDS outlives the loop
+  bool odd = false;
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      tot[i][j] += acc[i][j] + sml[i][j];
+      const f32x4 d = tot[i][j] - tot[i][j];
+      odd |= row_t + j * 16 + m < a.rows && !((d[0] + d[1]) + (d[2] + d[3]) == 0.f);
+    }
+  if (__any(odd)) {   // Inf or NaN somewhere, or a weight that rounds to Inf in 16 bits: these sums again in float32
+#pragma unroll 1
+    for (int j = 0; j < J; ++j) {
+      const u32x4 *xp = xbase + min(j, rbs - 1) * kPlanePieces;
+      const float *wp[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        wp[i] = (EPI == EPI_SWIGLU ? a.W[i] + (size_t)min((nb_t + w) * 16 + m, a.N - 1) * a.K
+                                   : f32_weight_row<EPI>(a, min(nb_t + w * 2 + i, a.NB - 1), m)) + lo * 32;
+      f32x4 s[2] = {zero, zero};
+#pragma unroll 1
+      for (int k = 4 * g; k - 4 * g < K; k += 16) {
+        const f32x4 b = k < K ? planes_load4(xp, m, k, kts) : zero;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const f32x4 wv = k < K ? *reinterpret_cast<const f32x4 *>(wp[i] + k) : zero;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[i] = mfma_f32(wv[e], b[e], s[i]);
+        }
+      }
+#pragma unroll
+      for (int jj = 0; jj < J; ++jj)
+        if (jj == j)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (!(tot[i][jj][e] - tot[i][jj][e] == 0.f)) tot[i][jj][e] = s[i][e];
+    }
   }
   constexpr int STEP = EPI == EPI_SWIGLU ? 2 : 1;
 #pragma unroll
@@ -491,8 +660,16 @@ __global__ __launch_bounds__(256) void gemm_f32_dense_kernel(const F32Args a) {
     for (int j = 0; j < J; ++j) {
       const int row = row_t + j * 16 + m;
       const bool row_ok = row < a.rows;
+      if (EPI == EPI_SWIGLU) {
+        const int n = nb * 16 + 4 * g;
+        const f32x4 s = tot[0][j], u = tot[1][j];
+        if (row_ok && n < a.N)
+          planes_store4(a.Xp_out + (size_t)(row >> 4) * kPlanePieces, m, n,
+                        f32x4{silu_dev(s[0]) * u[0], silu_dev(s[1]) * u[1], silu_dev(s[2]) * u[2], silu_dev(s[3]) * u[3]}, kts);
+        continue;
+      }
       const EpiPre pre = f32_epi_prefetch<EPI>(a, nb, g, row, row_ok);
-      f32_epi<EPI>(a, tot[i][j], tot[i + STEP - 1][j], nb, g, m, row, row_ok, 1.f, pre);
+      f32_epi<EPI>(a, tot[i][j], tot[i][j], nb, g, m, row, row_ok, 1.f, pre);
     }
   }
 }
@@ -502,15 +679,14 @@ static void launch_f32_dense_tile(const F32Args &a, hipStream_t s) {
   constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;
   const int tiles = (a.NB + NBT - 1) / NBT * ((a.rows + 16 * J - 1) / (16 * J));
   const dim3 grid((tiles + 7) / 8 * 8, a.splits);
-  // Chains of 32 cost 18 + K / 256 roundings (see the top), chains of 8 (three joins more a stage) 8 + K / 256; the scalar
-  // sums cost 6 + K / 128.  7B widths, 2048 rows, 2 layers: 19.5 ms with chains of 32, 20.9 with chains of 8.
+  // the joins of a chain cost vector instructions; of a long sum half as many keep the error below that of scalar sums
   if (a.K >= 4096) gemm_f32_dense_kernel<EPI, J, true><<<grid, 256, 0, s>>>(a);
   else gemm_f32_dense_kernel<EPI, J, false><<<grid, 256, 0, s>>>(a);
 }
 
 // Rows of a tile and (EPI_PART) pieces of K: the least of tiles per compute unit times rows of a tile over pieces.  A
-// narrow tile reads more of LDS and L2 per product (7B widths, 333 rows: gate/up 1083, 683, 649, 806 us with J = 1, 2,
-// 3, 4), a lone workgroup per compute unit has nothing to cover its barriers with, and each piece costs a pass over the
+// narrow tile splits its weights for fewer products (7B widths, 333 rows: gate/up 472, 387, 411, 416 us with J = 2, 3, 4,
+// 5, QKV 302, 246, 256, 223, o / down 180, 146, 132, 142 on average), a lone workgroup per compute unit has nothing to cover its barriers with, and each piece costs a pass over the
 // partial sums.
 template <int EPI>
 static int launch_f32_dense_cfg(F32Args a, hipStream_t s, size_t max_part = 0) {   // returns the pieces of K
@@ -532,46 +708,81 @@ static int launch_f32_dense_cfg(F32Args a, hipStream_t s, size_t max_part = 0) {
   return a.splits;
 }
 
-// Adds the partial sums of a row to its residual (or to the bias), and normalises the new row for the next GEMM.
-__global__ __launch_bounds__(256) void sum_rmsnorm_f32_kernel(const float *part, int splits, size_t stride, const float *base,
-                                                              size_t base_ld, int d, const float *gain, float eps, float *x,
-                                                              float *xn) {
+// Normalised row (x / rms * gain) -> planes, 256 threads; ss: this thread's share of the sum of squares.
+__device__ __forceinline__ void norm_row_planes(const float *x, float ss, int d, const float *gain, float eps, u32x4 *xp, int m, size_t kts) {
   __shared__ float red[4];
-  const size_t r = blockIdx.x;
-  float ss = 0.f;
-  for (int k = threadIdx.x * 4; k < d; k += 1024) {
-    f32x4 v = *reinterpret_cast<const f32x4 *>(part + r * d + k);   // one rounding at the residual's magnitude
-    for (int p = 1; p < splits; ++p) v += *reinterpret_cast<const f32x4 *>(part + p * stride + r * d + k);
-    v += *reinterpret_cast<const f32x4 *>(base + r * base_ld + k);
-    *reinterpret_cast<f32x4 *>(x + r * d + k) = v;
-    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
   const float rn = 1.0f / sqrtf(((red[0] + red[1]) + (red[2] + red[3])) / (float)d + eps);
   for (int k = threadIdx.x * 4; k < d; k += 1024) {
-    const f32x4 v = *reinterpret_cast<const f32x4 *>(x + r * d + k), gn = *reinterpret_cast<const f32x4 *>(gain + k);
-    *reinterpret_cast<f32x4 *>(xn + r * d + k) = f32x4{(v[0] * rn) * gn[0], (v[1] * rn) * gn[1], (v[2] * rn) * gn[2], (v[3] * rn) * gn[3]};
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(x + k), gn = *reinterpret_cast<const f32x4 *>(gain + k);
+    planes_store4(xp, m, k, f32x4{(v[0] * rn) * gn[0], (v[1] * rn) * gn[1], (v[2] * rn) * gn[2], (v[3] * rn) * gn[3]}, kts);
   }
 }
 
-void launch_gemm_f32_dense(const GemmLaunch &L, hipStream_t s) {
+// Adds the partial sums of a row to its residual (or to the bias) and, where Xp is set, normalises the new row for the next GEMM.
+__global__ __launch_bounds__(256) void sum_rmsnorm_f32_kernel(const float *part, int splits, size_t stride, const float *base,
+                                                              size_t base_ld, int d, const float *gain, float eps, float *x,
+                                                              u32x4 *Xp, size_t kts) {
+  const size_t r = blockIdx.x;
+  float ss = 0.f;
+  for (int k = threadIdx.x * 4; k < d; k += 1024) {
+    f32x4 v = *reinterpret_cast<const f32x4 *>(part + r * d + k);   // one rounding at the residual's magnitude
+    for (int p = 1; p < splits; ++p) v += *reinterpret_cast<const f32x4 *>(part + p * stride + r * d + k);
+    if (base) v += *reinterpret_cast<const f32x4 *>(base + r * base_ld + k);
+    *reinterpret_cast<f32x4 *>(x + r * d + k) = v;
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  }
+  if (Xp) norm_row_planes(x + r * d, ss, d, gain, eps, Xp + (r >> 4) * kPlanePieces, r & 15, kts);
+}
+
+// [RMSNorm(x_r) * gain ; embedding of the token behind slot r, where emb is set] -> planes
+__global__ __launch_bounds__(256) void norm_cat_f32_kernel(const float *x, int d, const float *gain, float eps, const float *emb,
+                                                           const int32_t *next_ids, u32x4 *Xp, size_t kts) {
+  const size_t r = blockIdx.x;
+  u32x4 *xp = Xp + (r >> 4) * kPlanePieces;
+  float ss = 0.f;
+  for (int k = threadIdx.x * 4; k < d; k += 1024) {
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(x + r * d + k);
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  }
+  norm_row_planes(x + r * d, ss, d, gain, eps, xp, r & 15, kts);
+  if (!emb) return;
+  const float *e = emb + (size_t)next_ids[r] * d;
+  for (int k = threadIdx.x * 4; k < d; k += 1024) planes_store4(xp, r & 15, d + k, *reinterpret_cast<const f32x4 *>(e + k), kts);
+}
+
+void launch_norm_cat_f32(const float *x, int rows, int d, const float *gain, float eps, const void *emb, const int32_t *next_ids,
+                         void *Xp, int RB, hipStream_t s) {
+  norm_cat_f32_kernel<<<rows, 256, 0, s>>>(x, d, gain, eps, (const float *)emb, next_ids, (u32x4 *)Xp, (size_t)RB * kPlanePieces);
+}
+
+size_t planes_bytes(int rows, int K) { return (size_t)(rows + 15) / 16 * ((K + 31) / 32) * kPlanePieces * 16; }
+
+static F32Args f32_dense_args(const GemmLaunch &L, int RB) {
   F32Args a = f32_args(L);
+  a.Xp = (const u32x4 *)L.Xp;
+  a.Xp_out = (u32x4 *)L.Xp_out;
+  a.RB = RB;
   a.splits = 1;
+  return a;
+}
+
+void launch_gemm_f32_dense(const GemmLaunch &L, int RB, hipStream_t s) {
+  const F32Args a = f32_dense_args(L, RB);
   if (L.epi == EPI_QKV) launch_f32_dense_cfg<EPI_QKV>(a, s);
   else launch_f32_dense_cfg<EPI_SWIGLU>(a, s);
 }
 
-void launch_gemm_f32_resid_norm(const GemmLaunch &L, float *part, size_t max_part, float *x, const float *gain, float *xn,
-                                hipStream_t s) {
-  F32Args a = f32_args(L);
+void launch_gemm_f32_resid_norm(const GemmLaunch &L, int RB, float *part, size_t max_part, const float *base, size_t base_ld, float *x,
+                                const float *gain, void *Xp_out, hipStream_t s) {
+  F32Args a = f32_dense_args(L, RB);
   a.Y = part;
-  a.splits = 1;
   const int S = launch_f32_dense_cfg<EPI_PART>(a, s, max_part);
-  sum_rmsnorm_f32_kernel<<<a.rows, 256, 0, s>>>(part, S, (size_t)a.rows * a.N, L.bias ? L.bias : x, L.bias ? 0 : a.N, a.N, gain,
-                                                L.eps, x, xn);
+  sum_rmsnorm_f32_kernel<<<a.rows, 256, 0, s>>>(part, S, (size_t)a.rows * a.N, base, base_ld, a.N, gain, L.eps, x, (u32x4 *)Xp_out,
+                                                (size_t)RB * kPlanePieces);
 }
 
 // ------------------------------------------------------------------ attention, 1..16 rows
@@ -731,7 +942,8 @@ int attn_f32_chunk_keys() { return kF32AttnKeys; }
 // accumulator.  Late (long) tiles are scheduled first; every wave is independent.
 template <int HD>
 __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
-                                                               const float *Kc, const float *Vc, float *out, float scale_log2e) {
+                                                               const float *Kc, const float *Vc, u32x4 *Xp, size_t kts,
+                                                               float scale_log2e) {
   constexpr int C = HD / 32, VT = HD / 16;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, m = lane & 15;
   const int kh = blockIdx.x, G = H / Hkv, R = rows * G;
@@ -829,29 +1041,30 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const float *q, i
   ltot += __shfl_xor(ltot, 16, 64);
   ltot += __shfl_xor(ltot, 32, 64);
   if (rok) {
-    float *op = out + ((size_t)row * H + head) * HD;
-#pragma unroll
+    u32x4 *xp = Xp + (size_t)(row >> 4) * kPlanePieces;
+#pragma unroll 1   // (unrolled, the handling of large numbers makes the kernel long)
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int t = 0; t < VT / 4; ++t) {
         f32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (T[4 * t + e][i] + O[4 * t + e][i]) / ltot;
-        *reinterpret_cast<f32x4 *>(op + (4 * g + i) * VT + 4 * t) = o;
+        planes_store4(xp, row & 15, head * HD + (4 * g + i) * VT + 4 * t, o, kts);
       }
   }
 }
 
 void launch_attention_prefill_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
-                                  float *out, hipStream_t s) {
+                                  void *Xp, int RB, hipStream_t s) {
   const int G = c.n_heads / c.n_kv_heads, R = rows * G, HD = c.head_dim;
   const dim3 grid(c.n_kv_heads, (R + 63) / 64);
+  const size_t kts = (size_t)RB * kPlanePieces;
   const float scale = 1.4426950408889634f / sqrtf((float)HD);
   const float *Kc = (const float *)kv_layer, *Vc = (const float *)((const char *)kv_layer + v_off);
   if (HD == 128)
-    attn_prefill_f32_kernel<128><<<grid, 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, out, scale);
+    attn_prefill_f32_kernel<128><<<grid, 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, (u32x4 *)Xp, kts, scale);
   else
-    attn_prefill_f32_kernel<64><<<grid, 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, out, scale);
+    attn_prefill_f32_kernel<64><<<grid, 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, (u32x4 *)Xp, kts, scale);
 }
 
 // ------------------------------------------------------------------ row producers
