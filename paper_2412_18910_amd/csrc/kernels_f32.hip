@@ -204,46 +204,116 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
 
 // ------------------------------------------------------------------ decode GEMM (1..16 rows)
 // HBM-bound: each weight is read once.  A workgroup owns one block of 16 weight rows (gate/up: one of each) and all
-// of K, dealt to its waves in chunks of 64; a wave keeps a chunk (4 KB; gate/up: 8 KB) in flight in a rolling ring.
+// of K, dealt to its waves in chunks of 64 in two parts; a wave keeps 8 KB of weights in flight.
 // The rows of a row-major matrix lie a power of two apart, so workgroups that walk K in step ask the same few memory
 // channels: each starts at a chunk of its own (7B widths, microseconds: o / down 29.6 -> 25.5, draft fc 35.0 -> 23.9,
-// a draft token's LM head 105 -> 95; gate/up 76 -> 74 and QKV 42 -> 40 were spread by themselves).  Twice the depth, 4 or
-// 16 waves, and 4x4x1 products that read 256 bytes of a row per load were no faster.  Cutting the chains at 16 products
-// with one total per matrix is free (a step of 4 layers of 7B 2266 us, 2274 without); four totals cost 5 % (registers).
-// TAIL: K is no multiple of 64; pieces behind the end count as zeros.
-template <int EPI, bool NORM, int NW, bool TAIL, bool GATED>
+// a draft token's LM head 105 -> 95; gate/up 76 -> 74 and QKV 42 -> 40 were spread by themselves).
+// The address unit takes 16 lanes at a time and a cycle for every line they touch: with a row a lane, as the products
+// want the weights, 64 cycles for 1 KB (a CU then gets 16 bytes a cycle at most).  So eight lanes read the 128 bytes of a row
+// one after the other, straight into LDS, and the products take them from there.
+// Cutting the chains at 16 products with one total per matrix is free; four totals cost 5 % (registers).
+// What lies behind the end of K is out of range of the loads and read as zeros.
+template <int EPI, bool NORM, int NW, bool GATED>
 __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
-  constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1, D = 4;
-  constexpr int CH = NW == 8 ? 4 : 2;   // loads per chain of products
-  __shared__ f32x4 red[NW][NA][64];
+  constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1, RC = 2 / NA;   // matrices; chunks in the ring
+  constexpr int VM = 2 * NA + 2;                               // loads of half a chunk
+  constexpr int CH = NW == 8 ? 4 : 2;                          // loads per chain of products
+  // ring [wave][matrix][slot] for each half of each chunk: arrays of their own, so that the compiler can tell a read of one
+  // from a load into another
+  __shared__ u32x4 r0[NW * NA * 128], r1[NW * NA * 128], r2[RC == 2 ? NW * NA * 128 : 1], r3[RC == 2 ? NW * NA * 128 : 1];
   if constexpr (GATED) AE_GATE(a.gate);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, m = lane & 15;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, m = lane & 15;
   const int nb = blockIdx.x, K = a.K;
   const bool row_ok = m < a.rows;
   const int xrow = a.row0 + (row_ok ? m : a.rows - 1);   // rows beyond the block re-read the last row
-  const float *xp = a.X + (size_t)xrow * a.ldx;
-  const float *wp[NA];
-  wp[0] = f32_weight_row<EPI>(a, nb, m);
-  if (NA == 2) wp[NA - 1] = a.W[1] + (size_t)min(nb * 16 + m, a.N - 1) * K;
 
   EpiPre pre{};
   if (w == 0) pre = f32_epi_prefetch<EPI>(a, nb, g, m, row_ok);
 
+  constexpr int kRange = 0x7ffffff0;
+  __amdgpu_buffer_rsrc_t rw[2];
+  unsigned vw[2][2];
+  int kw[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = h * 8 + (lane >> 3);
+    kw[h] = 4 * ((lane & 7) ^ (r >> 1));   // slot r * 8 + q holds piece q ^ (r / 2) of row r: reads without conflicts
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const F32Rows t = EPI == EPI_SWIGLU ? F32Rows{a.W[i] + (size_t)nb * 16 * K, min(r, a.N - 1 - nb * 16)} : f32_weight_rows<EPI>(a, nb, r);
+      rw[i] = __builtin_amdgcn_make_buffer_rsrc((void *)t.base, 0, kRange, 0x00020000);
+      vw[i][h] = ((unsigned)t.row * K + kw[h]) * 4;
+    }
+  }
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, kRange, 0x00020000);
+  const unsigned vx = ((unsigned)xrow * a.ldx + 4 * g) * 4;
+  const int as = m * 8 + (g ^ (m >> 1));   // where this lane's weights are: piece g, and piece 4 + g at as ^ 4
+
   const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[NA][4], tot[NA], wb[D][NA], xb[D];
+  f32x4 acc[NA][4], tot[NA];
+  u32x4 xb[2 * RC][2];
 #pragma unroll
   for (int i = 0; i < NA; ++i) tot[i] = zero;
-  const int NC = (K + D * 16 - 1) / (D * 16), rot = (int)((unsigned)nb * 7u % (unsigned)NC);
-  auto at = [&](int c) { const int r = c + rot; return r < NC ? r : r - NC; };
-  auto load = [&](int c, int j) {
-    const int k = at(c) * (D * 16) + j * 16 + g * 4, kk = !TAIL || k < K ? k : 0;
-    xb[j] = *reinterpret_cast<const f32x4 *>(xp + kk);
-#pragma unroll
-    for (int i = 0; i < NA; ++i) wb[j][i] = *reinterpret_cast<const f32x4 *>(wp[i] + kk);
+  const int NC = (K + 63) / 64, rot = (int)((unsigned)nb * 7u % (unsigned)NC);
+  auto first_k = [&](int c, int half) {   // chunks behind the last one read nothing
+    const int r = c + rot;
+    return c < NC ? (r < NC ? r : r - NC) * 64 + half * 32 : K;
   };
-  if (w < NC) {
+  auto issue_w = [&](int c, int half, u32x4 *slot) {
+    const int k = first_k(c, half);
 #pragma unroll
-    for (int j = 0; j < D; ++j) load(w, j);
+    for (int h = 0; h < 2; ++h) {
+      const bool in = k + kw[h] < K;
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw[i], (__attribute__((address_space(3))) void *)(slot + (w * NA + i) * 128 + h * 64), 16,
+                                                 in ? vw[i][h] : kRange, k * 4, 0, 0);
+    }
+  };
+  auto issue_x = [&](int c, int half, u32x4 (&x)[2]) {
+    const int k = first_k(c, half);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b128(rx, k + 16 * j + 4 * g < K ? vx + 64 * j : kRange, k * 4, 0);
+  };
+  auto part = [&](int c, int half, u32x4 *slot, u32x4 (&x)[2]) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xf70 | ((2 * RC - 1) * VM & 15) | ((2 * RC - 1) * VM >> 4 << 14));   // vmcnt: all but the parts behind
+    asm volatile("" ::: "memory");
+    f32x4 wv[NA][2];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) wv[i][j] = __builtin_bit_cast(f32x4, slot[(w * NA + i) * 128 + (j ? as ^ 4 : as)]);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(wv[i][0]), "+v"(wv[i][1]));   // read before the slot is filled again
+    issue_w(c + RC * NW, half, slot);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int n = half * 2 + j;
+      const f32x4 xv = __builtin_bit_cast(f32x4, x[j]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) acc[i][e] = mfma_f32(wv[i][j][e], xv[e], n % CH == 0 ? zero : acc[i][e]);
+      if (n % CH == CH - 1) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) tot[i] += (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    issue_x(c + RC * NW, half, x);
+  };
+  issue_w(w, 0, r0);
+  issue_x(w, 0, xb[0]);
+  issue_w(w, 1, r1);
+  issue_x(w, 1, xb[1]);
+  if (RC == 2) {
+    issue_w(w + NW, 0, r2);
+    issue_x(w + NW, 0, xb[2 * RC - 2]);
+    issue_w(w + NW, 1, r3);
+    issue_x(w + NW, 1, xb[2 * RC - 1]);
   }
 
   // 1/rms of every row from the producer's partial sums of x^2, summed by wave 0 in a fixed order
@@ -269,37 +339,25 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
     }
   }
 
-  for (int c = w; c < NC; c += NW) {
-    const int cn = c + NW < NC ? c + NW : c;   // the last piece re-issues its own loads (ignored)
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      if (TAIL && at(c) + 1 == NC && at(c) * (D * 16) + j * 16 + g * 4 >= K) {
-        xb[j] = zero;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) wb[j][i] = zero;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < NA; ++i) acc[i][e] = mfma_f32(wb[j][i][e], xb[j][e], j % CH == 0 ? zero : acc[i][e]);
-      __builtin_amdgcn_sched_barrier(0);   // refill slot j at once, not behind the whole piece
-      load(cn, j);
-      __builtin_amdgcn_sched_barrier(0);
-      if (j % CH == CH - 1) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) tot[i] += (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
-      }
+  for (int c = w; c < NC; c += RC * NW) {
+    part(c, 0, r0, xb[0]);
+    part(c, 1, r1, xb[1]);
+    if (RC == 2) {
+      if (c + NW >= NC) break;
+      part(c + NW, 0, r2, xb[2 * RC - 2]);
+      part(c + NW, 1, r3, xb[2 * RC - 1]);
     }
   }
+  __builtin_amdgcn_s_waitcnt(0xf70);   // vmcnt(0): no load into LDS outlives the loop
 #pragma unroll
-  for (int i = 0; i < NA; ++i) red[w][i][lane] = tot[i];
+  for (int i = 0; i < NA; ++i) r0[(w * NA + i) * 128 + lane] = __builtin_bit_cast(u32x4, tot[i]);   // the wave's own part of the ring
   __syncthreads();
   if (w != 0) return;
   f32x4 t[NW][NA];
 #pragma unroll
   for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
-    for (int i = 0; i < NA; ++i) t[ww][i] = red[ww][i][lane];
+    for (int i = 0; i < NA; ++i) t[ww][i] = __builtin_bit_cast(f32x4, r0[(ww * NA + i) * 128 + lane]);
 #pragma unroll
   for (int o = 1; o < NW; o *= 2)
 #pragma unroll
@@ -336,14 +394,8 @@ static F32Args f32_args(const GemmLaunch &L) {
 
 template <int EPI, bool NORM, int NW>
 static void launch_f32_waves(const F32Args &a, hipStream_t s) {
-  const bool tail = a.K % 64 != 0;
-  if (a.gate) {
-    if (tail) gemm_f32_kernel<EPI, NORM, NW, true, true><<<a.NB, NW * 64, 0, s>>>(a);
-    else gemm_f32_kernel<EPI, NORM, NW, false, true><<<a.NB, NW * 64, 0, s>>>(a);
-  } else {
-    if (tail) gemm_f32_kernel<EPI, NORM, NW, true, false><<<a.NB, NW * 64, 0, s>>>(a);
-    else gemm_f32_kernel<EPI, NORM, NW, false, false><<<a.NB, NW * 64, 0, s>>>(a);
-  }
+  if (a.gate) gemm_f32_kernel<EPI, NORM, NW, true><<<a.NB, NW * 64, 0, s>>>(a);
+  else gemm_f32_kernel<EPI, NORM, NW, false><<<a.NB, NW * 64, 0, s>>>(a);
 }
 
 template <int EPI, bool NORM>
