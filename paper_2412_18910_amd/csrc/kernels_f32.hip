@@ -204,7 +204,8 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
 
 // ------------------------------------------------------------------ decode GEMM (1..16 rows)
 // HBM-bound: each weight is read once.  A workgroup owns one block of 16 weight rows (gate/up: one of each) and all
-// of K, dealt to its waves in chunks of 64 in two parts; a wave keeps 8 KB of weights in flight.
+// of K, dealt to its waves in chunks of 64 in two parts; a wave keeps a chunk (4 KB; gate/up: 8 KB) in flight.  (Twice as
+// much takes 1 % longer, four times 6 %: fewer workgroups fit.)
 // The rows of a row-major matrix lie a power of two apart, so workgroups that walk K in step ask the same few memory
 // channels: each starts at a chunk of its own (7B widths, microseconds: o / down 29.6 -> 25.5, draft fc 35.0 -> 23.9,
 // a draft token's LM head 105 -> 95; gate/up 76 -> 74 and QKV 42 -> 40 were spread by themselves).
@@ -215,12 +216,12 @@ __device__ __forceinline__ void f32_epi(const F32Args &a, f32x4 s, f32x4 u, int 
 // What lies behind the end of K is out of range of the loads and read as zeros.
 template <int EPI, bool NORM, int NW, bool GATED>
 __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
-  constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1, RC = 2 / NA;   // matrices; chunks in the ring
+  constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1;                // matrices
   constexpr int VM = 2 * NA + 2;                               // loads of half a chunk
   constexpr int CH = NW == 8 ? 4 : 2;                          // loads per chain of products
-  // ring [wave][matrix][slot] for each half of each chunk: arrays of their own, so that the compiler can tell a read of one
-  // from a load into another
-  __shared__ u32x4 r0[NW * NA * 128], r1[NW * NA * 128], r2[RC == 2 ? NW * NA * 128 : 1], r3[RC == 2 ? NW * NA * 128 : 1];
+  // [wave][matrix][slot] for each half of a chunk: arrays of their own, so that the compiler can tell a read of one from a
+  // load into the other
+  __shared__ u32x4 r0[NW * NA * 128], r1[NW * NA * 128];
   if constexpr (GATED) AE_GATE(a.gate);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, m = lane & 15;
   const int nb = blockIdx.x, K = a.K;
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
 
   const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
   f32x4 acc[NA][4], tot[NA];
-  u32x4 xb[2 * RC][2];
+  u32x4 xb[2][2];
 #pragma unroll
   for (int i = 0; i < NA; ++i) tot[i] = zero;
   const int NC = (K + 63) / 64, rot = (int)((unsigned)nb * 7u % (unsigned)NC);
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
   auto part = [&](int c, int half, u32x4 *slot, u32x4 (&x)[2]) {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xf70 | ((2 * RC - 1) * VM & 15) | ((2 * RC - 1) * VM >> 4 << 14));   // vmcnt: all but the parts behind
+    __builtin_amdgcn_s_waitcnt(0xf70 | VM);   // vmcnt: all but the part behind
     asm volatile("" ::: "memory");
     f32x4 wv[NA][2];
 #pragma unroll
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
       for (int j = 0; j < 2; ++j) wv[i][j] = __builtin_bit_cast(f32x4, slot[(w * NA + i) * 128 + (j ? as ^ 4 : as)]);
 #pragma unroll
     for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(wv[i][0]), "+v"(wv[i][1]));   // read before the slot is filled again
-    issue_w(c + RC * NW, half, slot);
+    issue_w(c + NW, half, slot);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -303,18 +304,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    issue_x(c + RC * NW, half, x);
+    issue_x(c + NW, half, x);
   };
   issue_w(w, 0, r0);
   issue_x(w, 0, xb[0]);
   issue_w(w, 1, r1);
   issue_x(w, 1, xb[1]);
-  if (RC == 2) {
-    issue_w(w + NW, 0, r2);
-    issue_x(w + NW, 0, xb[2 * RC - 2]);
-    issue_w(w + NW, 1, r3);
-    issue_x(w + NW, 1, xb[2 * RC - 1]);
-  }
 
   // 1/rms of every row from the producer's partial sums of x^2, summed by wave 0 in a fixed order
   __shared__ float rinv_s[16];
@@ -339,14 +334,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
     }
   }
 
-  for (int c = w; c < NC; c += RC * NW) {
+  for (int c = w; c < NC; c += NW) {
     part(c, 0, r0, xb[0]);
     part(c, 1, r1, xb[1]);
-    if (RC == 2) {
-      if (c + NW >= NC) break;
-      part(c + NW, 0, r2, xb[2 * RC - 2]);
-      part(c + NW, 1, r3, xb[2 * RC - 1]);
-    }
   }
   __builtin_amdgcn_s_waitcnt(0xf70);   // vmcnt(0): no load into LDS outlives the loop
 #pragma unroll
