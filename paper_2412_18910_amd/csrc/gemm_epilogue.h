@@ -91,8 +91,8 @@ __device__ __forceinline__ EpiPre epi_prefetch(const GemmArgs &a, int nb, int g,
 
 // s = accumulator of row-block nb (EPI_SWIGLU: the gate block, u = the up block nb + 1).
 // rb = row-block of the activations, the lane's row is rb*16 + m; kts = k-tile stride of the
-// packed output (pieces).  Every lane of the wave must call this (it shuffles).
-template <int EPI>
+// packed output (pieces); DENSE: prompt pass.  Every lane of the wave must call this (it shuffles).
+template <int EPI, bool DENSE>
 __device__ __forceinline__ void epi_tile(const GemmArgs &a, f32x4 s, f32x4 u, int nb, int g, int m, int rb, bool row_ok,
                                          float rinv, size_t kts, const EpiPre *pre = nullptr) {
   const int row = rb * 16 + m;
@@ -101,7 +101,7 @@ __device__ __forceinline__ void epi_tile(const GemmArgs &a, f32x4 s, f32x4 u, in
     // fused matrix interleaves gate (even row-blocks) and up (odd): h = silu(gate) * up
     if (row_ok) {
       const int n = (nb >> 1) * 16 + g * 4;
-      packed_store4(xpo, m, n, silu_dev(s[0] * rinv) * (u[0] * rinv), silu_dev(s[1] * rinv) * (u[1] * rinv),
+      packed_store4<DENSE>(xpo, m, n, silu_dev(s[0] * rinv) * (u[0] * rinv), silu_dev(s[1] * rinv) * (u[1] * rinv),
                     silu_dev(s[2] * rinv) * (u[2] * rinv), silu_dev(s[3] * rinv) * (u[3] * rinv), kts);
     }
   } else if (EPI == EPI_QKV) {
@@ -177,7 +177,7 @@ __device__ __forceinline__ void epi_tile(const GemmArgs &a, f32x4 s, f32x4 u, in
         ssq = o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
         float4 gn = make_float4(1.f, 1.f, 1.f, 1.f);
         if (a.gain_out) gn = pre ? pre->b : *reinterpret_cast<const float4 *>(a.gain_out + n);
-        packed_store4(xpo, m, n, o.x * gn.x, o.y * gn.y, o.z * gn.z, o.w * gn.w, kts);
+        packed_store4<DENSE>(xpo, m, n, o.x * gn.x, o.y * gn.y, o.z * gn.z, o.w * gn.w, kts);
       }
     }
     if (EPI == EPI_STORE && a.amax_val) {

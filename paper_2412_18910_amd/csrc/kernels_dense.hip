@@ -64,11 +64,10 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
   // Operands come through buffer loads: resource descriptor and per-k-tile byte offset in
   // scalar registers, one fixed per-lane offset register each (out-of-range reads return 0).
   // The DM row-blocks of one k-tile are 2*DM tiles of 64 contiguous pieces; a wave loads tiles w + NW*i straight
-  // into LDS, each lane the piece its MFMA lane position needs (packed slot m*4+g), so LDS
-  // holds the tiles in lane order and its accesses are conflict-free.
+  // into LDS in lane order, so its accesses are conflict-free.
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)a.W, 0, a.w_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)a.Xp, 0, a.xp_bytes, 0x00020000);
-  const unsigned wl = lane * 16, xl = (m * 4 + g) * 16;                  // per-lane byte offsets
+  const unsigned wl = lane * 16;                                         // per-lane byte offset
   const unsigned kstride_b = a.NBtot * 1024u, kts_b = a.RB * 2048u;      // bytes per k-tile
   unsigned wq = nbw * 1024u, xq = (rb0 * 128u + w * 64u) * 16u;           // first k-tile (uniform)
   int NK = a.KT;   // k-tiles, a multiple of 4
@@ -95,7 +94,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
     const unsigned k = min(kt, NK - 1);
 #pragma unroll
     for (int i = 0; i < XI; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(slot + (w + NW * i) * 64), 16, xl,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(slot + (w + NW * i) * 64), 16, wl,
                                                xq + k * kts_b + i * (NW * 1024), 0, 0);
 #pragma unroll
     for (int i = 0; i < DN; ++i) wr[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, wl + i * 1024, wq + k * kstride_b, 0);
@@ -170,7 +169,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
         continue;
       }
       const float rinv = NORM ? a.rinv[row] : 1.f;
-      epi_tile<EPI>(a, acc[i][j], acc[i + STEP - 1][j], nb, g, m, rb, row_ok, rinv, kts);
+      epi_tile<EPI, true>(a, acc[i][j], acc[i + STEP - 1][j], nb, g, m, rb, row_ok, rinv, kts);
     }
   }
 }
@@ -235,7 +234,7 @@ __global__ __launch_bounds__(256) void dense_finish_kernel(const GemmArgs a, int
     t += *reinterpret_cast<const f32x4 *>(p + i * stride);
     if (STEP == 2) u += *reinterpret_cast<const f32x4 *>(p + i * stride + 16);
   }
-  epi_tile<EPI>(a, t, u, nb, g, m, rb, row_ok, a.rinv[row], (size_t)a.RB * 128);
+  epi_tile<EPI, true>(a, t, u, nb, g, m, rb, row_ok, a.rinv[row], (size_t)a.RB * 128);
 }
 
 // Adds the pieces of a row to its residual (x, updated in place) or to the bias, leaves row * gain packed for the next
@@ -263,7 +262,7 @@ __global__ __launch_bounds__(1024) void dense_sum_rows_kernel(const GemmArgs a, 
     if (x) *reinterpret_cast<f32x4 *>(x + k) = v;
     ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
     const f32x4 gn = *reinterpret_cast<const f32x4 *>(a.gain_out + k);
-    packed_store4(a.Xp_out + (size_t)(r >> 4) * 128, r & 15, k, v[0] * gn[0], v[1] * gn[1], v[2] * gn[2], v[3] * gn[3],
+    packed_store4<true>(a.Xp_out + (size_t)(r >> 4) * 128, r & 15, k, v[0] * gn[0], v[1] * gn[1], v[2] * gn[2], v[3] * gn[3],
                   (size_t)a.RB * 128);
   }
 #pragma unroll
@@ -366,7 +365,7 @@ __global__ __launch_bounds__(256) void embed_dense_kernel(const uint16_t *emb, c
     *reinterpret_cast<float4 *>(x + (size_t)r * d + k0) = make_float4(v0, v1, v2, v3);
     ss += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
     const float4 gn = *reinterpret_cast<const float4 *>(gain + k0);
-    packed_store4(xp, m, k0, v0 * gn.x, v1 * gn.y, v2 * gn.z, v3 * gn.w, kts);
+    packed_store4<true>(xp, m, k0, v0 * gn.x, v1 * gn.y, v2 * gn.z, v3 * gn.w, kts);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
@@ -403,9 +402,9 @@ __global__ __launch_bounds__(256) void draft_cat_dense_kernel(const float *x, in
   for (int k0 = threadIdx.x * 4; k0 < d; k0 += 1024) {
     const float4 v = *reinterpret_cast<const float4 *>(xr + k0);
     const float4 gn = *reinterpret_cast<const float4 *>(gain + k0);
-    packed_store4(xp, m, k0, v.x * rinv * gn.x, v.y * rinv * gn.y, v.z * rinv * gn.z, v.w * rinv * gn.w, kts);
+    packed_store4<true>(xp, m, k0, v.x * rinv * gn.x, v.y * rinv * gn.y, v.z * rinv * gn.z, v.w * rinv * gn.w, kts);
     const uint2 raw = *reinterpret_cast<const uint2 *>(e + k0);
-    packed_store4(xp, m, d + k0, __uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
+    packed_store4<true>(xp, m, d + k0, __uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
                   __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xffff0000u), kts);
   }
 }
@@ -630,7 +629,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const float *q, in
       u32x4 *xp = Xp_out + (size_t)(row[t] >> 4) * 128;
 #pragma unroll
       for (int dt = 0; dt < VT; ++dt)
-        packed_store4(xp, row[t] & 15, head[t] * HD + dt * 16 + 4 * g, O[t][dt][0] * inv, O[t][dt][1] * inv,
+        packed_store4<true>(xp, row[t] & 15, head[t] * HD + dt * 16 + 4 * g, O[t][dt][0] * inv, O[t][dt][1] * inv,
                       O[t][dt][2] * inv, O[t][dt][3] * inv, kts);
     }
   }

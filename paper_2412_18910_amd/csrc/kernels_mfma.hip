@@ -185,7 +185,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_mfma_kernel(const GemmArgs a) {
 #pragma unroll
       for (int ww = 1; ww < NW; ++ww) u += red[ww][rb + 1][lane];
     }
-    epi_tile<EPI>(a, s, u, nb, g, m, 0, row_ok, rinv, 128, EPI != EPI_SWIGLU ? &pre[e] : nullptr);
+    epi_tile<EPI, false>(a, s, u, nb, g, m, 0, row_ok, rinv, 128, EPI != EPI_SWIGLU ? &pre[e] : nullptr);
   }
 }
 

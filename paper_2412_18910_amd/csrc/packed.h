@@ -6,7 +6,9 @@
 //   ceil(r/2) cache lines per tile.
 // The decode step has one block of 16 rows (k-tile stride 128 pieces).  The dense prompt
 // pass keeps RB row-blocks side by side, Xp[kt][rb][h][slot] (k-tile stride RB*128), so the
-// row-blocks a workgroup multiplies are contiguous for every k-tile.
+// row-blocks a workgroup multiplies are contiguous for every k-tile; its tiles are full, so they are kept in lane order,
+// slot = (k%32)/8*16 + row: the address unit takes a cycle for each line that 16 lanes touch, and 16 lanes with a row each touch
+// two lines instead of eight.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -32,15 +34,17 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_
 }
 
 // Store 4 consecutive k-values (k0 % 4 == 0) of row m (0..15) of one row-block into a packed
-// activation buffer; Xp points at the row-block's first tile, kts = k-tile stride in pieces.
+// activation buffer; Xp points at the row-block's first tile, kts = k-tile stride in pieces; DENSE: prompt pass.
+template <bool DENSE = false>
 __device__ __forceinline__ void packed_store4(u32x4 *Xp, int m, int k0, float a, float b, float c, float d,
                                               size_t kts = 128) {
   uint32_t h0, l0, h1, l1;
   split2(a, b, h0, l0);
   split2(c, d, h1, l1);
   const int kt = k0 >> 5, g = (k0 & 31) >> 3, half = (k0 & 7) >> 2;
-  u32x2 *ph = reinterpret_cast<u32x2 *>(Xp + (size_t)kt * kts + m * 4 + g) + half;
-  u32x2 *pl = reinterpret_cast<u32x2 *>(Xp + (size_t)kt * kts + 64 + m * 4 + g) + half;
+  const int slot = DENSE ? g * 16 + m : m * 4 + g;
+  u32x2 *ph = reinterpret_cast<u32x2 *>(Xp + (size_t)kt * kts + slot) + half;
+  u32x2 *pl = reinterpret_cast<u32x2 *>(Xp + (size_t)kt * kts + 64 + slot) + half;
   *ph = u32x2{h0, h1};
   *pl = u32x2{l0, l1};
 }
