@@ -132,12 +132,17 @@ struct ae_ctx {
   ae::DevState *st = nullptr;      // device state
   ae::HostMirror *hm = nullptr;    // pinned host memory the device writes; hm_dev: its address on the device
   ae::HostMirror *hm_dev = nullptr;
-  float *h_rows = nullptr;         // pinned: one exported row (logits, feature, K/V); h_rows_dev: on the device
+  float *h_rows = nullptr;         // pinned: two exported rows (logits, feature, K/V); h_rows_dev: on the device
   float *h_rows_dev = nullptr;
   float *h_feat = nullptr;         // pinned: the feature row of ae_set_state; read by request feat_seq
   float *h_feat_dev = nullptr;
   uint32_t feat_seq = 0;
-  size_t row_floats = 0;           // floats of that row, a multiple of kExportPiece; a flag word per piece follows it
+  size_t row_floats = 0;           // floats of such a row, a multiple of kExportPiece; a flag word per piece follows the two
+  // rows fetched one after the other (ae_get_logits, ae_get_draft_logits): the last one, and the one behind it, on its way
+  const float *last_row = nullptr, *ahead_row = nullptr;
+  uint32_t ahead_seq = 0;
+  int row_half = 0;                // of h_rows, where the last row went
+  int logit_rows = 0, draft_rows = 0;   // rows that the last verification, prompt or draft wrote
   uint32_t seq = 0;                // number of the last request to the device
 
   // dense prompt pass: chunk buffers, allocated at the first long prompt (pxa normalised rows, pxh FFN rows, pxcat draft head

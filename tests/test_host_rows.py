@@ -1,0 +1,62 @@
+"""Rows on their way to the host: which fetches launch what (host code over a recorded HIP runtime, no GPU), and the memory
+they are returned in."""
+import numpy as np
+import pytest
+
+from paper_2412_18910_amd.binding import AE_OK, _RowMemory
+from paper_2412_18910_amd.config import BF16, FP32, Config
+
+from .fake_runtime import Ctx
+
+
+@pytest.fixture(params=[BF16, FP32], ids=["bf16", "fp32"])
+def ctx(request):
+    cfg = Config(1, 256, 4, 2, 64, 512, 515 if request.param == FP32 else 512, dtype=request.param, k_max=5, n_ctx_max=128, ldlp_hidden=64)
+    c = Ctx(cfg)
+    assert c.prefill(20) == AE_OK
+    yield c
+    c.close()
+
+
+def test_only_a_second_row_in_order_brings_the_next_one(ctx):
+    n = ctx.count
+    assert n(lambda: ctx.verify(4)) > 0
+    assert [n(lambda: ctx.logits(i)) for i in (0, 1, 2, 3)] == [1, 2, 1, 0]
+    assert [n(lambda: ctx.logits(i)) for i in (0, 0, 2, 3, 1)] == [1, 1, 1, 1, 1]   # 3 follows 2, but is the last
+    assert [n(lambda: ctx.logits(i)) for i in (0, 1, 3, 2)] == [1, 2, 1, 1]          # 2 came for nothing
+    assert [n(lambda: ctx.logits(i)) for i in (3, 4, 5)] == [1, 1, 1]                # behind the block
+
+
+def test_a_row_ahead_is_dropped_by_whatever_writes_rows(ctx):
+    n = ctx.count
+    for again in (lambda: ctx.verify(4), lambda: ctx.draft(3) or ctx.verify(4), lambda: ctx.prefill(20) or ctx.verify(4)):
+        assert ctx.verify(4) == AE_OK
+        assert [n(lambda: ctx.logits(i)) for i in (0, 1)] == [1, 2]
+        assert again() == AE_OK
+        assert [n(lambda: ctx.logits(i)) for i in (2, 3)] == [1, 1]
+    for other in (lambda: ctx.feature(0), ctx.kv_row):
+        assert [n(lambda: ctx.logits(i)) for i in (0, 1)] == [1, 2]
+        assert other() == AE_OK
+        assert n(lambda: ctx.logits(2)) == 1
+
+
+def test_rows_are_reused_only_when_nobody_has_them():
+    mem = _RowMemory()
+    a = mem.take(100)
+    a[:] = 1.0
+    part = mem.take(100)[10:20]
+    part[:] = 2.0
+    b = mem.take(100)
+    b[:] = 3.0
+    assert np.all(a == 1.0) and np.all(part == 2.0)
+    where = b.ctypes.data
+    del b
+    c = mem.take(100)
+    assert c.ctypes.data == where and np.all(a == 1.0) and np.all(part == 2.0)
+    a.shape = (10, 10)      # a row is the caller's own array
+    a.flags.writeable = False
+    del a
+    d = mem.take(100)
+    assert d.shape == (100,) and d.flags.writeable
+    many = [mem.take(64) for _ in range(2 * mem.KEEP)]
+    assert len({m.ctypes.data for m in many}) == len(many) and len(mem.kept[64]) == mem.KEEP
