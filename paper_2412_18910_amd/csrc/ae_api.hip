@@ -446,6 +446,11 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   ids.ids = c->hist + p0;
   launch_embed_f32(c->tok_emb, ids, rows, d, nullptr, c->px, nullptr, nullptr, s);
   launch_norm_cat_f32(c->px, rows, d, c->layers[0].attn_norm, g.rms_eps, nullptr, nullptr, c->pxa, RB, s);
+  // no more pieces than a buffer of this chunk's own size has room for: sums do not depend on earlier prompts
+  auto part_room = [&](int nrows) {
+    const size_t room = (size_t)(nrows > 2048 ? nrows : 2048) * d;
+    return c->ppart_floats < room ? c->ppart_floats : room;
+  };
   auto qkv_pass = [&](int li, int nrows, bool with_q) {   // projections, rotary embedding, cache append
     GemmLaunch qkv;
     qkv.W = &c->layers[li].f_qkv; qkv.Xp = c->pxa; qkv.rows = nrows; qkv.epi = EPI_QKV;
@@ -453,15 +458,12 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
     qkv.seg_N[0] = with_q ? dq : 0; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
     qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
     qkv.pos0 = p0; qkv.n_ctx = kv_capacity(g); qkv.hd = g.head_dim;
-    launch_gemm_f32_dense(qkv, RB, s);
+    launch_gemm_f32_dense(qkv, RB, c->ppart, part_room(nrows), s);
   };
   auto project = [&](const Mat *W, const void *X, int nrows, const float *base, size_t base_ld, float *x, const float *gain) {
     GemmLaunch L;
     L.W = W; L.Xp = X; L.rows = nrows; L.eps = g.rms_eps;
-    // no more pieces than a buffer of this chunk's own size has room for: sums do not depend on earlier prompts
-    const size_t room = (size_t)(nrows > 2048 ? nrows : 2048) * d;
-    launch_gemm_f32_resid_norm(L, RB, c->ppart, c->ppart_floats < room ? c->ppart_floats : room, base, base_ld, x, gain,
-                               gain ? c->pxa : nullptr, s);
+    launch_gemm_f32_resid_norm(L, RB, c->ppart, part_room(nrows), base, base_ld, x, gain, gain ? c->pxa : nullptr, s);
   };
   for (int l = 0; l < g.n_layers; ++l) {
     const LayerW &w = c->layers[l];
@@ -470,7 +472,7 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
     project(&w.wo, c->pxatt, rows, c->px, d, c->px, w.ffn_norm);
     GemmLaunch gu;
     gu.W = &w.f_gu; gu.Xp = c->pxa; gu.rows = rows; gu.epi = EPI_SWIGLU; gu.Xp_out = c->pxh; gu.ldxo = f;
-    launch_gemm_f32_dense(gu, RB, s);
+    launch_gemm_f32_dense(gu, RB, c->ppart, part_room(rows), s);
     project(&w.w_down, c->pxh, rows, c->px, d, c->px, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : nullptr);
   }
   if (drows > 0) {

@@ -347,8 +347,8 @@ void launch_attention_prefill(const float *q, int rows, int pos0, const ae_confi
 // ---- float32 models (kernels_f32.hip) ----
 void launch_gemm_f32(const GemmLaunch &L, hipStream_t s);         // 1..16 rows, all epilogues and fusions
 // Prompt GEMMs, any number of rows; activations in planes of RB row-blocks (kernels_f32.hip), already normalised: EPI_QKV
-// and EPI_SWIGLU (planes out)
-void launch_gemm_f32_dense(const GemmLaunch &L, int RB, hipStream_t s);
+// and EPI_SWIGLU (planes out); part: room for max_part floats, used where the last tiles are made in pieces of K
+void launch_gemm_f32_dense(const GemmLaunch &L, int RB, float *part, size_t max_part, hipStream_t s);
 // x = Xp . W^T + base (row stride base_ld, nullable), Xp_out = RMSNorm(x) * gain (nullable); part: room for max_part
 // floats, at least rows * N
 void launch_gemm_f32_resid_norm(const GemmLaunch &L, int RB, float *part, size_t max_part, const float *base, size_t base_ld, float *x,

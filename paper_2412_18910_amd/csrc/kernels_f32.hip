@@ -60,6 +60,10 @@ struct F32Args {
   int pos0, n_ctx, hd;
   const int32_t *gate;
   int splits;           // EPI_PART: pieces of K, piece s -> Y + s * rows * N
+  // prompt GEMM, EPI_QKV and EPI_SWIGLU: tiles behind the first `whole` (`tail` of them) are made in tail_splits pieces of K,
+  // tile t's piece s -> tail_part, for f32_tail_kernel
+  int whole, tail, tail_splits;
+  f32x4 *tail_part;
 };
 enum { EPI_PART = 4 };  // prompt GEMM: raw partial sums over a piece of K
 
@@ -475,16 +479,43 @@ __device__ __forceinline__ f32x4 planes_load4(const u32x4 *xp, int m, int k0, si
   return x;
 }
 
+// Epilogue of a wave's tiles (two weight row-blocks, J activation row-blocks).
+template <int EPI, int J>
+__device__ __forceinline__ void f32_dense_epilogue(const F32Args &a, const f32x4 (&tot)[2][J], int nb_t, int row_t, int w, int g, int m) {
+  constexpr int STEP = EPI == EPI_SWIGLU ? 2 : 1;
+#pragma unroll
+  for (int i = 0; i < 2; i += STEP) {
+    const int nb = EPI == EPI_SWIGLU ? nb_t + w : nb_t + w * 2 + i;
+    if (nb >= a.NB) continue;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int row = row_t + j * 16 + m;
+      const bool row_ok = row < a.rows;
+      if (EPI == EPI_SWIGLU) {
+        const int n = nb * 16 + 4 * g;
+        const f32x4 s = tot[0][j], u = tot[1][j];
+        if (row_ok && n < a.N)
+          planes_store4(a.Xp_out + (size_t)(row >> 4) * kPlanePieces, m, n,
+                        f32x4{silu_dev(s[0]) * u[0], silu_dev(s[1]) * u[1], silu_dev(s[2]) * u[2], silu_dev(s[3]) * u[3]},
+                        (size_t)a.RB * kPlanePieces);
+        continue;
+      }
+      const EpiPre pre = f32_epi_prefetch<EPI>(a, nb, g, row, row_ok);
+      f32_epi<EPI>(a, tot[i][j], tot[i][j], nb, g, m, row, row_ok, 1.f, pre);
+    }
+  }
+}
+
 // Workgroup tile: 128 weight rows (gate/up: 64 of each) x 16*J activation rows; each of the 4 waves owns two
 // weight row-blocks and all J activation row-blocks.  Stages of 32 k go straight into LDS, weights three stages ahead,
 // activations one.  While a stage is multiplied the weights of the next one are split, vector instructions between the
 // matrix instructions: an MFMA of 16 cycles leaves room for two.  7B widths, 333 rows, against the float32 instruction:
 // gate/up 649 -> 382 us, QKV 408 -> 238, o / down 247 -> 146 on average; activations split here too (44 vector instructions
-// more a stage) 478 / 295 / 182.  What is left of the matrix rate (40 %): 3.7 vector instructions an MFMA at J = 3, rounds
-// of 512 workgroups that are not full (2.35 and 1.3 of them), clocks of 2.05 GHz.
+// more a stage) 478 / 295 / 182.  What is left of the matrix rate (40 %): 3.7 vector instructions an MFMA at J = 3,
+// latencies that two waves a SIMD do not cover, clocks of 2.05 GHz.
 template <int EPI, int J, bool LONG>
 __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a) {
-  constexpr int TM = 16 * J, CH = LONG ? 6 : 3;             // CH: stages in a chain of products
+  constexpr int TM = 16 * J, CH = LONG && J < 4 ? 6 : 3;    // CH: stages in a chain of products (J = 4: registers)
   constexpr int NX = (3 * J + 3) / 4;                       // activation tiles of 1 KB that a wave loads per stage
   // Activations of two stages [row-block][hi, mid, lo][lane], weights of three as they are [wave][row-block][slot]: arrays
   // of their own, so that the compiler can tell a read of one from a load into another.
@@ -493,15 +524,27 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
   // the activation tiles of one weight tile run side by side on one XCD (ids go round the 8 XCDs) and share it in its L2
   constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;            // output row-blocks per workgroup
   const int NT = (a.NB + NBT - 1) / NBT, MT = (a.rows + TM - 1) / TM;
-  const int per = (NT * MT + 7) >> 3, v = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
-  if (((int)blockIdx.x >> 3) >= per || v >= NT * MT) return;
+  int id = blockIdx.x, count = NT * MT, piece = blockIdx.y, pieces = a.splits;
+  const bool behind = EPI != EPI_PART && a.tail > 0 && id >= a.whole;   // a piece of one of the last tiles
+  if (EPI != EPI_PART && a.tail > 0) {
+    count = behind ? a.tail * a.tail_splits : a.whole;
+    id -= behind ? a.whole : 0;
+  }
+  const int per = (count + 7) >> 3;
+  int v = (id & 7) * per + (id >> 3);
+  if ((id >> 3) >= per || v >= count) return;
+  if (behind) {
+    pieces = a.tail_splits;
+    piece = v / a.tail;
+    v = a.whole + v % a.tail;
+  }
   const int nb_t = v / MT * NBT, row_t = (v % MT) * TM;
   // this workgroup's piece of K, in stages of 32
   int NS = (a.K + 95) / 96 * 3, lo = 0;                     // in threes
-  if (EPI == EPI_PART) {
+  if (EPI == EPI_PART || behind) {
     const int np = NS / 3;
-    lo = np * (int)blockIdx.y / a.splits * 3;
-    NS = np * ((int)blockIdx.y + 1) / a.splits * 3 - lo;
+    lo = np * piece / pieces * 3;
+    NS = np * (piece + 1) / pieces * 3 - lo;
   }
   const int K = min(a.K, (lo + NS) * 32) - lo * 32;
 
@@ -693,37 +736,58 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
               if (!(tot[i][jj][e] - tot[i][jj][e] == 0.f)) tot[i][jj][e] = s[i][e];
     }
   }
-  constexpr int STEP = EPI == EPI_SWIGLU ? 2 : 1;
+  if (EPI != EPI_PART && pieces > 1) {
+    f32x4 *out = a.tail_part + (((size_t)piece * a.tail + v - a.whole) * 4 + w) * (2 * J * 64) + lane;
 #pragma unroll
-  for (int i = 0; i < 2; i += STEP) {
-    const int nb = EPI == EPI_SWIGLU ? nb_t + w : nb_t + w * 2 + i;
-    if (nb >= a.NB) continue;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int row = row_t + j * 16 + m;
-      const bool row_ok = row < a.rows;
-      if (EPI == EPI_SWIGLU) {
-        const int n = nb * 16 + 4 * g;
-        const f32x4 s = tot[0][j], u = tot[1][j];
-        if (row_ok && n < a.N)
-          planes_store4(a.Xp_out + (size_t)(row >> 4) * kPlanePieces, m, n,
-                        f32x4{silu_dev(s[0]) * u[0], silu_dev(s[1]) * u[1], silu_dev(s[2]) * u[2], silu_dev(s[3]) * u[3]}, kts);
-        continue;
-      }
-      const EpiPre pre = f32_epi_prefetch<EPI>(a, nb, g, row, row_ok);
-      f32_epi<EPI>(a, tot[i][j], tot[i][j], nb, g, m, row, row_ok, 1.f, pre);
-    }
+      for (int j = 0; j < J; ++j) out[(i * J + j) * 64] = tot[i][j];
+    return;
   }
+  f32_dense_epilogue<EPI, J>(a, tot, nb_t, row_t, w, g, m);
+}
+
+// Adds the pieces of a tile whose K was split and runs the GEMM's epilogue on it.
+template <int EPI, int J>
+__global__ __launch_bounds__(256) void f32_tail_kernel(const F32Args a) {
+  constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, MT = (a.rows + 16 * J - 1) / (16 * J), v = a.whole + (int)blockIdx.x;
+  const f32x4 *in = a.tail_part + ((size_t)blockIdx.x * 4 + w) * (2 * J * 64) + lane;
+  const size_t stride = (size_t)a.tail * 4 * (2 * J * 64);
+  f32x4 tot[2][J];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < J; ++j) tot[i][j] = in[(i * J + j) * 64];
+  for (int s = 1; s < a.tail_splits; ++s)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < J; ++j) tot[i][j] += in[s * stride + (i * J + j) * 64];
+  f32_dense_epilogue<EPI, J>(a, tot, v / MT * NBT, (v % MT) * 16 * J, w, lane >> 4, lane & 15);
 }
 
 template <int EPI, int J>
-static void launch_f32_dense_tile(const F32Args &a, hipStream_t s) {
+static void launch_f32_dense_tile(F32Args a, hipStream_t s, size_t max_part) {
   constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;
   const int tiles = (a.NB + NBT - 1) / NBT * ((a.rows + 16 * J - 1) / (16 * J));
-  const dim3 grid((tiles + 7) / 8 * 8, a.splits);
+  // 512 workgroups are resident, two per compute unit (a lone one is no faster).  Where at most half as many are left behind
+  // the last full round, K of those is dealt to as many as there is room for, 16 stages each at least.  7B widths, 333
+  // rows: QKV (512 + 160 tiles, 3 pieces) 238 -> 204 + 7 us, gate/up (1024 + 180, 2 pieces) 382 -> 360 + 6.
+  const int left = tiles % 512, room = left ? 512 / left : 0, longest = (a.K + 31) / 32 / 16, S = room < longest ? room : longest;
+  a.whole = tiles;
+  if (EPI != EPI_PART && left > 0 && S > 1 && (size_t)left * S * 2048 * J <= max_part) {
+    a.whole = tiles - left;
+    a.tail = left;
+    a.tail_splits = S < 8 ? S : 8;
+  }
+  const dim3 grid((a.whole + 7) / 8 * 8 + (a.tail * a.tail_splits + 7) / 8 * 8, a.splits);
   // the joins of a chain cost vector instructions; of a long sum half as many keep the error below that of scalar sums
   if (a.K >= 4096) gemm_f32_dense_kernel<EPI, J, true><<<grid, 256, 0, s>>>(a);
   else gemm_f32_dense_kernel<EPI, J, false><<<grid, 256, 0, s>>>(a);
+  if constexpr (EPI != EPI_PART) {
+    if (a.tail > 0) f32_tail_kernel<EPI, J><<<a.tail, 256, 0, s>>>(a);
+  }
 }
 
 // Rows of a tile and (EPI_PART) pieces of K: the least of tiles per compute unit times rows of a tile over pieces.  A
@@ -743,10 +807,10 @@ static int launch_f32_dense_cfg(F32Args a, hipStream_t s, size_t max_part = 0) {
       const double c = (double)((tiles + 255) / 256 * J) / S * per_row[J] * (tiles <= 256 ? 1.25 : 1.0) * (1.0 + 0.03 * S);
       if (c < cost) { cost = c; best = J; a.splits = S; }
     }
-  if (best == 4) launch_f32_dense_tile<EPI, 4>(a, s);
-  else if (best == 3) launch_f32_dense_tile<EPI, 3>(a, s);
-  else if (best == 2) launch_f32_dense_tile<EPI, 2>(a, s);
-  else launch_f32_dense_tile<EPI, 1>(a, s);
+  if (best == 4) launch_f32_dense_tile<EPI, 4>(a, s, max_part);
+  else if (best == 3) launch_f32_dense_tile<EPI, 3>(a, s, max_part);
+  else if (best == 2) launch_f32_dense_tile<EPI, 2>(a, s, max_part);
+  else launch_f32_dense_tile<EPI, 1>(a, s, max_part);
   return a.splits;
 }
 
@@ -812,10 +876,11 @@ static F32Args f32_dense_args(const GemmLaunch &L, int RB) {
   return a;
 }
 
-void launch_gemm_f32_dense(const GemmLaunch &L, int RB, hipStream_t s) {
-  const F32Args a = f32_dense_args(L, RB);
-  if (L.epi == EPI_QKV) launch_f32_dense_cfg<EPI_QKV>(a, s);
-  else launch_f32_dense_cfg<EPI_SWIGLU>(a, s);
+void launch_gemm_f32_dense(const GemmLaunch &L, int RB, float *part, size_t max_part, hipStream_t s) {
+  F32Args a = f32_dense_args(L, RB);
+  a.tail_part = (f32x4 *)part;
+  if (L.epi == EPI_QKV) launch_f32_dense_cfg<EPI_QKV>(a, s, max_part);
+  else launch_f32_dense_cfg<EPI_SWIGLU>(a, s, max_part);
 }
 
 void launch_gemm_f32_resid_norm(const GemmLaunch &L, int RB, float *part, size_t max_part, const float *base, size_t base_ld, float *x,
