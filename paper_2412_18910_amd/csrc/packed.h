@@ -49,6 +49,21 @@ __device__ __forceinline__ void packed_store4(u32x4 *Xp, int m, int k0, float a,
   *pl = u32x2{l0, l1};
 }
 
+// Eight of them (k0 % 8 == 0), prompt pass.
+__device__ __forceinline__ void packed_store8(u32x4 *Xp, int m, int k0, const float (&x)[8], size_t kts) {
+  u32x4 h, l;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t hi, lo;
+    split2(x[2 * i], x[2 * i + 1], hi, lo);
+    h[i] = hi;
+    l[i] = lo;
+  }
+  u32x4 *p = Xp + (size_t)(k0 >> 5) * kts + ((k0 & 31) >> 3) * 16 + m;
+  p[0] = h;
+  p[64] = l;
+}
+
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
