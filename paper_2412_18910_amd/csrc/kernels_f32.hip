@@ -510,8 +510,9 @@ __device__ __forceinline__ void f32_dense_epilogue(const F32Args &a, const f32x4
 // weight row-blocks and all J activation row-blocks.  Stages of 32 k go straight into LDS, weights three stages ahead,
 // activations one.  While a stage is multiplied the weights of the next one are split, vector instructions between the
 // matrix instructions: an MFMA of 16 cycles leaves room for two.  7B widths, 333 rows, against the float32 instruction:
-// gate/up 649 -> 382 us, QKV 408 -> 238, o / down 247 -> 146 on average; activations split here too (44 vector instructions
-// more a stage) 478 / 295 / 182.  What is left of the matrix rate (40 %): 3.7 vector instructions an MFMA at J = 3,
+// gate/up 649 -> 360 + 6 us (the last tiles in pieces of K; 382 whole), QKV 408 -> 204 + 7 (238), o / down 247 -> 139 on
+// average; whole tiles with the activations split here too (44 vector instructions more a stage) 478 / 295.  What is left
+// of the matrix rate (40 %): 3.7 vector instructions an MFMA at J = 3,
 // latencies that two waves a SIMD do not cover, clocks of 2.05 GHz.
 template <int EPI, int J, bool LONG>
 __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a) {
@@ -791,7 +792,7 @@ static void launch_f32_dense_tile(F32Args a, hipStream_t s, size_t max_part) {
 }
 
 // Rows of a tile and (EPI_PART) pieces of K: the least of tiles per compute unit times rows of a tile over pieces.  A
-// narrow tile splits its weights for fewer products (7B widths, 333 rows: gate/up 472, 387, 411, 416 us with J = 2, 3, 4,
+// narrow tile splits its weights for fewer products (7B widths, 333 rows, last tiles whole: gate/up 472, 387, 411, 416 us with J = 2, 3, 4,
 // 5, QKV 302, 246, 256, 223, o / down 180, 146, 132, 142 on average), a lone workgroup per compute unit has nothing to cover its barriers with, and each piece costs a pass over the
 // partial sums.
 template <int EPI>
