@@ -327,6 +327,14 @@ void release_dense(ae_ctx *c) {
   c->ppart_floats = 0;
 }
 
+// float32: floats of the buffer for pieces of K that a chunk of `rows` rows brings along.  A chunk uses no more of it where an
+// earlier prompt left a larger one: else its sums would be cut elsewhere.  (More room is no gain: at 1024 x 2816, 128 rows,
+// gate/up's last tiles in pieces, which 512 x 128 x 64 floats allow, take 426 us for 4 layers instead of 416.)
+size_t f32_part_floats(const ae_config &g, int rows) {
+  const size_t cap = (size_t)(rows + 127) / 128 * 128;
+  return (cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048) * g.d_model;
+}
+
 // Chunk buffers for `cap` rows (a multiple of 128): float residual stream and queries, the
 // inputs of the five GEMMs; bf16: RMSNorm partial sums and 1/rms, zero-filled so that the
 // padding rows of a packed chunk are finite (float32: so that what lies behind the end of K is zero).  Nothing is held where they do not fit; bf16 prompts
@@ -347,9 +355,9 @@ int ensure_dense(ae_ctx *c, int n) {
   const size_t dmax = dq > d ? dq : d;
   // sums over pieces of K.  float32: up to 8 pieces for short prompts; bf16: 768 tiles of 128 x 128, no more than
   // 16 pieces of the widest output
-  const size_t part_rows = cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048;
+  const size_t rows_floats = f32_part_floats(g, want);
   const size_t widest = 2 * f > dq + 2 * dkv ? 2 * f : dq + 2 * dkv, most = (size_t)768 * 128 * 128;
-  const size_t part_floats = !c->fast ? part_rows * d : 16 * cap * widest < most ? 16 * cap * widest : most;
+  const size_t part_floats = !c->fast ? rows_floats : 16 * cap * widest < most ? 16 * cap * widest : most;
   struct Buf { void **p; size_t bytes; bool clear = true; };
   const int w = want;
   const std::vector<Buf> bufs = !c->fast ? std::vector<Buf>{
@@ -446,11 +454,6 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
   ids.ids = c->hist + p0;
   launch_embed_f32(c->tok_emb, ids, rows, d, nullptr, c->px, nullptr, nullptr, s);
   launch_norm_cat_f32(c->px, rows, d, c->layers[0].attn_norm, g.rms_eps, nullptr, nullptr, c->pxa, RB, s);
-  // no more pieces than a buffer of this chunk's own size has room for: sums do not depend on earlier prompts
-  auto part_room = [&](int nrows) {
-    const size_t room = (size_t)(nrows > 2048 ? nrows : 2048) * d;
-    return c->ppart_floats < room ? c->ppart_floats : room;
-  };
   auto qkv_pass = [&](int li, int nrows, bool with_q) {   // projections, rotary embedding, cache append
     GemmLaunch qkv;
     qkv.W = &c->layers[li].f_qkv; qkv.Xp = c->pxa; qkv.rows = nrows; qkv.epi = EPI_QKV;
@@ -458,12 +461,12 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
     qkv.seg_N[0] = with_q ? dq : 0; qkv.seg_N[1] = dkv; qkv.seg_N[2] = dkv;
     qkv.rope_tab = c->rope_tab; qkv.Kc = kv_layer_ptr(c, li); qkv.Vc = (char *)kv_layer_ptr(c, li) + c->kv_v_offset;
     qkv.pos0 = p0; qkv.n_ctx = kv_capacity(g); qkv.hd = g.head_dim;
-    launch_gemm_f32_dense(qkv, RB, c->ppart, part_room(nrows), s);
+    launch_gemm_f32_dense(qkv, RB, c->ppart, f32_part_floats(g, nrows), s);
   };
   auto project = [&](const Mat *W, const void *X, int nrows, const float *base, size_t base_ld, float *x, const float *gain) {
     GemmLaunch L;
     L.W = W; L.Xp = X; L.rows = nrows; L.eps = g.rms_eps;
-    launch_gemm_f32_resid_norm(L, RB, c->ppart, part_room(nrows), base, base_ld, x, gain, gain ? c->pxa : nullptr, s);
+    launch_gemm_f32_resid_norm(L, RB, c->ppart, f32_part_floats(g, nrows), base, base_ld, x, gain, gain ? c->pxa : nullptr, s);
   };
   for (int l = 0; l < g.n_layers; ++l) {
     const LayerW &w = c->layers[l];
@@ -472,7 +475,7 @@ void dense_chunk_f32(ae_ctx *c, int p0, int rows, int drows) {
     project(&w.wo, c->pxatt, rows, c->px, d, c->px, w.ffn_norm);
     GemmLaunch gu;
     gu.W = &w.f_gu; gu.Xp = c->pxa; gu.rows = rows; gu.epi = EPI_SWIGLU; gu.Xp_out = c->pxh; gu.ldxo = f;
-    launch_gemm_f32_dense(gu, RB, c->ppart, part_room(rows), s);
+    launch_gemm_f32_dense(gu, RB, c->ppart, f32_part_floats(g, rows), s);
     project(&w.w_down, c->pxh, rows, c->px, d, c->px, l + 1 < g.n_layers ? c->layers[l + 1].attn_norm : nullptr);
   }
   if (drows > 0) {
