@@ -1186,11 +1186,16 @@ static int copy_out(ae_ctx *c, const float *src, size_t n, float *dst, const flo
     return launch_export_row(row, n, c->h_rows_dev + half * c->row_floats,
                              (uint32_t *)(c->h_rows_dev + 2 * c->row_floats) + half * pieces, ++c->seq, c->stream);
   };
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;   // a stream that is being captured answers nothing
-  const bool here = src == c->ahead_row && hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-  const bool on = rows > 0 && c->last_row && src == c->last_row + n && src + n < first + (size_t)rows * n;
-  c->last_row = c->ahead_row = nullptr;
+  bool here = src == c->ahead_row;
+  bool on = rows > 0 && c->last_row && src == c->last_row + n && src + n < first + (size_t)rows * n;
+  if (here || on) {   // a stream that is being captured answers nothing and sends nothing
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool live = hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    here = here && live;
+    on = on && live;
+  }
   uint32_t seq = c->ahead_seq;
+  forget_rows(c);
   c->row_half ^= 1;
   const int half = c->row_half;
   if (!here) {
@@ -1206,7 +1211,10 @@ static int copy_out(ae_ctx *c, const float *src, size_t n, float *dst, const flo
   for (size_t i = 0; i < n; i += 1024) *(volatile float *)(dst + i) = *(volatile float *)(dst + i);
   for (size_t p = 0; p * kExportPiece < n; ++p) {
     int rc = wait_flag(c, flags + p, seq);
-    if (rc) return rc;
+    if (rc) {
+      forget_rows(c);
+      return rc;
+    }
     const size_t at = p * kExportPiece;
     memcpy(dst + at, from + at, (n - at < kExportPiece ? n - at : kExportPiece) * sizeof(float));
   }

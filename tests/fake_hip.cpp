@@ -25,6 +25,7 @@ long g_fail_launch = -1;     // launches until one fails
 size_t g_fail_alloc = 0;     // device allocations of this size and more fail (0: none)
 bool g_go_on = true;         // answer of the exit rule
 bool g_mute = false;         // no kernel answers
+bool g_capture = false;      // streams are being captured: launches are recorded for later, waiting is an error
 int g_syncs = 0;             // stream synchronisations
 struct { dim3 grid, block; size_t shm; hipStream_t s; } g_call;
 
@@ -54,6 +55,7 @@ void fake_fail_alloc(size_t bytes) { g_fail_alloc = bytes; }
 void fake_set_error(int e) { g_last = (hipError_t)e; }
 int fake_last_error() { return (int)g_last; }
 void fake_mute(int mute) { g_mute = mute != 0; }
+void fake_capture(int on) { g_capture = on != 0; }
 int fake_syncs() { return g_syncs; }
 void fake_set_device(int d) { g_device = d; }
 int fake_device() { return g_device; }
@@ -84,7 +86,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
   if (g_fail_launch >= 0 && g_fail_launch-- == 0) return note(hipErrorLaunchOutOfResources);
   const std::string &name = g_names[f];
   g_launches.push_back(Launch{name, grid.x, grid.y, block.x});
-  if (g_mute) return hipSuccess;
+  if (g_mute || g_capture) return hipSuccess;
   if (is(name, "export_row_kernel")) {
     memcpy(arg<float *>(args, 2), arg<const float *>(args, 0), arg<size_t>(args, 1) * sizeof(float));
     for (unsigned p = 0; p < grid.x; ++p) arg<uint32_t *>(args, 3)[p] = arg<uint32_t>(args, 4);
@@ -141,8 +143,14 @@ hipError_t hipGetDevice(int *d) { *d = g_device; return hipSuccess; }
 hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { ++g_syncs; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
+  *s = g_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) {
+  ++g_syncs;
+  return g_capture ? note(hipErrorStreamCaptureUnsupported) : hipSuccess;
+}
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = (hipEvent_t)calloc(1, 8); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e) { free((void *)e); return hipSuccess; }

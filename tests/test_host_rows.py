@@ -3,7 +3,7 @@ they are returned in."""
 import numpy as np
 import pytest
 
-from paper_2412_18910_amd.binding import AE_OK, _RowMemory
+from paper_2412_18910_amd.binding import AE_EHIP, AE_OK, _RowMemory
 from paper_2412_18910_amd.config import BF16, FP32, Config
 
 from .fake_runtime import Ctx
@@ -38,6 +38,25 @@ def test_a_row_ahead_is_dropped_by_whatever_writes_rows(ctx):
         assert [n(lambda: ctx.logits(i)) for i in (0, 1)] == [1, 2]
         assert other() == AE_OK
         assert n(lambda: ctx.logits(2)) == 1
+
+
+@pytest.mark.parametrize("before", [0, 1, 2])   # rows fetched in order before the capture: none sent ahead, one that would be, one that is
+def test_a_fetch_under_capture_is_refused_and_leaves_nothing_behind(ctx, before):
+    assert ctx.verify(5) == AE_OK
+    assert [ctx.logits(i) for i in range(before)] == [AE_OK] * before
+    ctx.lib.fake_capture(1)
+    assert ctx.logits(before) == AE_EHIP
+    ctx.lib.fake_capture(0)
+    ctx.lib.fake_set_error(0)   # of the wait that was refused
+    assert [ctx.logits(i) for i in (before + 1, before + 2, before, 0)] == [AE_OK] * 4
+
+
+def test_a_row_that_could_not_be_sent_ahead_is_sent_when_it_is_fetched(ctx):
+    n = ctx.count
+    assert ctx.verify(4) == AE_OK and ctx.logits(0) == AE_OK
+    ctx.lib.fake_fail_launch(1)
+    assert ctx.logits(1) == AE_OK and ctx.lib.fake_last_error() == 0
+    assert [n(lambda: ctx.logits(i)) for i in (2, 3)] == [2, 0] and ctx.accept() == AE_OK
 
 
 def test_rows_are_reused_only_when_nobody_has_them():
