@@ -6,8 +6,6 @@ does not need a GPU; creating an Engine does, and raises if the library is missi
 """
 import ctypes as C
 import os
-import sys
-import threading
 
 import numpy as np
 
@@ -145,27 +143,6 @@ def _f32(a):
     return np.ascontiguousarray(a, dtype=np.float32)
 
 
-class _RowMemory:
-    """Memory for the rows an engine returns, used again once nobody refers to a row any more: fresh pages cost 4 of the 37 us
-    that a row of 128256 floats takes.  At most KEEP rows of each length are kept; they go with the engine."""
-
-    KEEP = 32
-
-    def __init__(self):
-        self.lock, self.kept = threading.Lock(), {}
-
-    def take(self, n):
-        with self.lock:   # a row is free while the list and `row` (and the call's argument) are all that refers to it
-            rows = self.kept.setdefault(n, [])
-            for row in rows:
-                if sys.getrefcount(row) == 3:
-                    return row[:]
-            row = np.zeros(n, np.float32)
-            if len(rows) < self.KEEP:
-                rows.append(row)
-            return row[:]
-
-
 _LAYER_KEYS = [n for n, _ in AeLayerW._fields_]
 
 
@@ -202,7 +179,6 @@ class Engine:
         w.ldlp_w_out, w.ldlp_b_out = ptr(weights["ldlp_w_out"], torch.float32), ptr(weights["ldlp_b_out"], torch.float32)
         self._w = w
         self.stream = stream
-        self._rows = _RowMemory()
         h = C.c_void_p()
         rc = self.lib.ae_init(C.byref(self.c), C.byref(w), stream.cuda_stream if stream is not None else None, C.byref(h))
         if rc != AE_OK:
@@ -291,7 +267,7 @@ class Engine:
         return self.lib.ae_pending(self.h)
 
     def _get(self, fn, what, n, *args):
-        out = self._rows.take(n)
+        out = np.empty(n, np.float32)   # all of it is written, or the call raises
         self._chk(fn(self.h, *args, _p(out, C.c_float)), what)
         return out
 

@@ -1,9 +1,8 @@
 """Rows on their way to the host: which fetches launch what (host code over a recorded HIP runtime, no GPU), and the memory
 they are returned in."""
-import numpy as np
 import pytest
 
-from paper_2412_18910_amd.binding import AE_EHIP, AE_OK, _RowMemory
+from paper_2412_18910_amd.binding import AE_EHIP, AE_OK, AdaEagleError, Engine
 from paper_2412_18910_amd.config import BF16, FP32, Config
 
 from .fake_runtime import Ctx
@@ -59,23 +58,15 @@ def test_a_row_that_could_not_be_sent_ahead_is_sent_when_it_is_fetched(ctx):
     assert [n(lambda: ctx.logits(i)) for i in (2, 3)] == [2, 0] and ctx.accept() == AE_OK
 
 
-def test_rows_are_reused_only_when_nobody_has_them():
-    mem = _RowMemory()
-    a = mem.take(100)
-    a[:] = 1.0
-    part = mem.take(100)[10:20]
-    part[:] = 2.0
-    b = mem.take(100)
-    b[:] = 3.0
-    assert np.all(a == 1.0) and np.all(part == 2.0)
-    where = b.ctypes.data
-    del b
-    c = mem.take(100)
-    assert c.ctypes.data == where and np.all(a == 1.0) and np.all(part == 2.0)
-    a.shape = (10, 10)      # a row is the caller's own array
-    a.flags.writeable = False
-    del a
-    d = mem.take(100)
-    assert d.shape == (100,) and d.flags.writeable
-    many = [mem.take(64) for _ in range(2 * mem.KEEP)]
-    assert len({m.ctypes.data for m in many}) == len(many) and len(mem.kept[64]) == mem.KEEP
+def test_rows_are_the_callers_own(ctx):
+    eng = Engine.__new__(Engine)   # (an engine's weights are on a GPU)
+    eng.lib, eng.cfg, eng.h = ctx.lib, ctx.cfg, ctx.h
+    try:
+        assert ctx.verify(4) == AE_OK
+        rows = [eng.logits(i % 4) for i in range(100)] + [eng.feature(0), eng.kv_row(0, 0, 0)]
+        assert all(r.flags.owndata and r.flags.writeable for r in rows) and len({r.ctypes.data for r in rows}) == len(rows)
+        rows[0].resize(2 * len(rows[0]), refcheck=False)
+        with pytest.raises(AdaEagleError):
+            eng.logits(99)
+    finally:
+        eng.h = None
