@@ -409,13 +409,17 @@ void launch_gemm_f32(const GemmLaunch &L, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ prompt GEMM
-// Products of float32 numbers on the bf16 matrix instruction.  x = hi + mid + lo in bf16 (round to nearest even; the
-// remainders are exact) holds all 24 bits; of the nine products the three smallest (2^-26 of the whole) are left out.  The
-// instruction takes 6 x 16 cycles for what v_mfma_f32_16x16x4_f32 takes 256 for, and rounds once for several products
-// where that rounds each.  Activations come split ("planes", written by the kernels before), weights are split on the way.
+// Products of float32 numbers on the bf16 matrix instruction.  2^24 x = hi + mid + lo in bf16 (round to nearest even; the
+// remainders are exact) holds all 24 bits of x: without the factor the last part of what lies below 2^-110 would fall under
+// bf16's smallest number.  Of the nine products the three smallest are left out: up to 2^-24.2 of the whole, 2^-27.4 in the
+// root mean square, of either sign.  The instruction takes 6 x 16 cycles for what v_mfma_f32_16x16x4_f32 takes 256 for, and rounds once
+// for several products where that rounds each.  Activations come split ("planes", written by the kernels before), weights are
+// split on the way.
 //
 // Planes: Xp[kt][rb][hi, mid, lo][slot = row * 4 + k octet] of 16 bytes, the packed form of packed.h with three parts; what
-// lies behind the end of K in the last k-tile is zero.  hi + mid + lo is x for every x, Inf and NaN included.
+// lies behind the end of K in the last k-tile is zero.  A number that has no such parts (2^103 and more, Inf, NaN) is kept as it
+// is in mid and lo, its hi is a NaN: sums that meet one come out not finite and are made again in float32.
+constexpr float kSplitScale = 0x1p24f, kSumScale = 0x1p-48f;
 __device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
   bf16x2 h;
   h[0] = (__bf16)x0; h[1] = (__bf16)x1;
@@ -423,40 +427,38 @@ __device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
   asm("" : "+v"(p));   // (else every half is converted a second time where its value is needed)
   return p;
 }
+// x0, x1: the numbers times 2^24
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t (&p)[3]) {
   p[0] = pack_bf16(x0, x1);
   const float r0 = x0 - __uint_as_float(p[0] << 16), r1 = x1 - __uint_as_float(p[0] & 0xffff0000u);
   p[1] = pack_bf16(r0, r1);
   p[2] = pack_bf16(r0 - __uint_as_float(p[1] << 16), r1 - __uint_as_float(p[1] & 0xffff0000u));
 }
+constexpr uint32_t kAsItIs = 0x7fffu;   // hi of a number without parts
 constexpr int kPlanePieces = 192;   // 16-byte pieces of a row-block and k-tile
 
-// Four consecutive k (k0 % 4 == 0) of row m of the row-block whose first tile is at xp; kts: pieces from k-tile to k-tile
-__device__ __forceinline__ void planes_store4(u32x4 *xp, int m, int k0, f32x4 x, size_t kts) {
+// Products a * b at four consecutive k (k0 % 4 == 0) of row m of the row-block whose first tile is at xp; kts: pieces from k-tile
+// to k-tile.  The parts are those of the product itself, not of the float32 number that it rounds to.
+__device__ __forceinline__ void planes_store4(u32x4 *xp, int m, int k0, f32x4 a, f32x4 b, size_t kts) {
   uint32_t p[2][3];
-  split3(x[0], x[1], p[0]);
-  split3(x[2], x[3], p[1]);
-  // what rounds up to Inf is cut off instead, Inf and NaN stand alone
-  constexpr float kBf16Max = 3.3895313892515355e38f;
-  const float big = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])));
-  if (!(big < kBf16Max) || x[0] != x[0] || x[1] != x[1] || x[2] != x[2] || x[3] != x[3]) {
+  bool odd = false;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float a0 = a[2 * h], a1 = a[2 * h + 1], b0 = b[2 * h] * kSplitScale, b1 = b[2 * h + 1] * kSplitScale;
+    const float x0 = a0 * b0, x1 = a1 * b1;
+    p[h][0] = pack_bf16(x0, x1);
+    const float r0 = fmaf(a0, b0, -__uint_as_float(p[h][0] << 16)), r1 = fmaf(a1, b1, -__uint_as_float(p[h][0] & 0xffff0000u));
+    p[h][1] = pack_bf16(r0, r1);
+    p[h][2] = pack_bf16(r0 - __uint_as_float(p[h][1] << 16), r1 - __uint_as_float(p[h][1] & 0xffff0000u));
+    odd |= !(fabsf(x0) < 0x1p127f) | !(fabsf(x1) < 0x1p127f);
+  }
+  if (odd) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const bool finite = x[e] - x[e] == 0.f;
-      const float h = fminf(fmaxf(x[e], -kBf16Max), kBf16Max);
-      uint32_t q[3] = {(__float_as_uint(x[e]) >> 16) | (x[e] != x[e] ? 0x40u : 0u), 0u, 0u};
-      if (finite) split3(h, 0.f, q);
-      if (finite && h != x[e]) {   // h is one bf16 number; the remainder has 16 bits
-        uint32_t r[3];
-        split3(x[e] - h, 0.f, r);
-        q[1] = r[0];
-        q[2] = r[1];
-      }
+      if (fabsf(a[e] * (b[e] * kSplitScale)) < 0x1p127f) continue;
+      const uint32_t u = __float_as_uint(a[e] * b[e]), q[3] = {kAsItIs, u >> 16, u & 0xffffu};
 #pragma unroll
-      for (int n = 0; n < 3; ++n) {
-        const uint32_t v = q[n] & 0xffffu;
-        p[e >> 1][n] = e & 1 ? (p[e >> 1][n] & 0xffffu) | v << 16 : (p[e >> 1][n] & 0xffff0000u) | v;
-      }
+      for (int n = 0; n < 3; ++n) p[e >> 1][n] = e & 1 ? (p[e >> 1][n] & 0xffffu) | q[n] << 16 : (p[e >> 1][n] & 0xffff0000u) | q[n];
     }
   }
   const int g = (k0 & 31) >> 3, half = (k0 & 7) >> 2;
@@ -471,10 +473,11 @@ __device__ __forceinline__ f32x4 planes_load4(const u32x4 *xp, int m, int k0, si
   f32x4 x;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    float f[3];
+    uint32_t q[3];
 #pragma unroll
-    for (int n = 0; n < 3; ++n) f[n] = __uint_as_float(e & 1 ? v[n][e >> 1] & 0xffff0000u : v[n][e >> 1] << 16);
-    x[e] = f[0] + (f[1] + f[2]);
+    for (int n = 0; n < 3; ++n) q[n] = e & 1 ? v[n][e >> 1] >> 16 : v[n][e >> 1] & 0xffffu;
+    x[e] = q[0] == kAsItIs ? __uint_as_float(q[1] << 16 | q[2])
+                           : (__uint_as_float(q[0] << 16) + (__uint_as_float(q[1] << 16) + __uint_as_float(q[2] << 16))) * (1.f / kSplitScale);
   }
   return x;
 }
@@ -496,8 +499,7 @@ __device__ __forceinline__ void f32_dense_epilogue(const F32Args &a, const f32x4
         const f32x4 s = tot[0][j], u = tot[1][j];
         if (row_ok && n < a.N)
           planes_store4(a.Xp_out + (size_t)(row >> 4) * kPlanePieces, m, n,
-                        f32x4{silu_dev(s[0]) * u[0], silu_dev(s[1]) * u[1], silu_dev(s[2]) * u[2], silu_dev(s[3]) * u[3]},
-                        (size_t)a.RB * kPlanePieces);
+                        f32x4{silu_dev(s[0]), silu_dev(s[1]), silu_dev(s[2]), silu_dev(s[3])}, u, (size_t)a.RB * kPlanePieces);
         continue;
       }
       const EpiPre pre = f32_epi_prefetch<EPI>(a, nb, g, row, row_ok);
@@ -622,7 +624,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
     for (int i = 0; i < 2; ++i) {
       uint32_t p[4][3];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) split3(raw[i][e >> 1][e % 2 * 2], raw[i][e >> 1][e % 2 * 2 + 1], p[e]);
+      for (int e = 0; e < 4; ++e) split3(raw[i][e >> 1][e % 2 * 2] * kSplitScale, raw[i][e >> 1][e % 2 * 2 + 1] * kSplitScale, p[e]);
 #pragma unroll
       for (int n = 0; n < 3; ++n) {
         f[i][n] = u32x4{p[0][n], p[1][n], p[2][n], p[3][n]};
@@ -703,11 +705,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
   for (int j = 0; j < J; ++j)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      tot[i][j] += acc[i][j] + sml[i][j];
+      tot[i][j] = (tot[i][j] + (acc[i][j] + sml[i][j])) * kSumScale;
       const f32x4 d = tot[i][j] - tot[i][j];
       odd |= row_t + j * 16 + m < a.rows && !((d[0] + d[1]) + (d[2] + d[3]) == 0.f);
     }
-  if (__any(odd)) {   // Inf or NaN somewhere, or a weight that rounds to Inf in 16 bits: these sums again in float32
+  if (__any(odd)) {   // Inf or NaN somewhere, a number without parts, or a sum above 2^80: these again in float32
 #pragma unroll 1
     for (int j = 0; j < J; ++j) {
       const u32x4 *xp = xbase + min(j, rbs - 1) * kPlanePieces;
@@ -825,7 +827,7 @@ __device__ __forceinline__ void norm_row_planes(const float *x, float ss, int d,
   const float rn = 1.0f / sqrtf(((red[0] + red[1]) + (red[2] + red[3])) / (float)d + eps);
   for (int k = threadIdx.x * 4; k < d; k += 1024) {
     const f32x4 v = *reinterpret_cast<const f32x4 *>(x + k), gn = *reinterpret_cast<const f32x4 *>(gain + k);
-    planes_store4(xp, m, k, f32x4{(v[0] * rn) * gn[0], (v[1] * rn) * gn[1], (v[2] * rn) * gn[2], (v[3] * rn) * gn[3]}, kts);
+    planes_store4(xp, m, k, v * rn, gn, kts);
   }
 }
 
@@ -858,7 +860,8 @@ __global__ __launch_bounds__(256) void norm_cat_f32_kernel(const float *x, int d
   norm_row_planes(x + r * d, ss, d, gain, eps, xp, r & 15, kts);
   if (!emb) return;
   const float *e = emb + (size_t)next_ids[r] * d;
-  for (int k = threadIdx.x * 4; k < d; k += 1024) planes_store4(xp, r & 15, d + k, *reinterpret_cast<const f32x4 *>(e + k), kts);
+  const f32x4 one = f32x4{1.f, 1.f, 1.f, 1.f};
+  for (int k = threadIdx.x * 4; k < d; k += 1024) planes_store4(xp, r & 15, d + k, *reinterpret_cast<const f32x4 *>(e + k), one, kts);
 }
 
 void launch_norm_cat_f32(const float *x, int rows, int d, const float *gain, float eps, const void *emb, const int32_t *next_ids,
@@ -1157,7 +1160,7 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const float *q, i
         f32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (T[4 * t + e][i] + O[4 * t + e][i]) / ltot;
-        planes_store4(xp, row & 15, head * HD + (4 * g + i) * VT + 4 * t, o, kts);
+        planes_store4(xp, row & 15, head * HD + (4 * g + i) * VT + 4 * t, o, f32x4{1.f, 1.f, 1.f, 1.f}, kts);
       }
   }
 }

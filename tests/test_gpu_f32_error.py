@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("k", [1024, 2048, 4096, 8192])   # 8 waves in the decode GEMM; both chain lengths of the prompt GEMM
-def test_sums_lose_no_more_than_scalar_sums(k):
+@pytest.mark.parametrize("sign", ["both", "one"])   # of one sign: a rounding that leans one way would add up
+def test_sums_lose_no_more_than_scalar_sums(k, sign):
     """V rows of the first layer (normalised embedding times wv), by the prompt pass and by a verification block.
 
     A wave of scalar code sums K products as 64 chains of K / 64 and a butterfly of 6 levels: K / 128 + 6 roundings at
@@ -21,6 +22,9 @@ def test_sums_lose_no_more_than_scalar_sums(k):
     (uniform error, mantissas log-uniform), 0.5 leaves a sixth.  One chain per accumulator costs K / 64 and more."""
     cfg = Config(1, k, 4, 4, 64, 64, 64, dtype=FP32, k_max=7, n_ctx_max=128, ldlp_hidden=64)
     w = synth.make_weights(cfg, 91)
+    if sign == "one":
+        w["tok_emb"].abs_()
+        w["layers"][0]["wv"].abs_()
     eng = Engine(cfg, to_device(w))
     ids = synth.token_ids(60, cfg.vocab, 92)
     block = synth.token_ids(8, cfg.vocab, 93)
