@@ -32,6 +32,12 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Loads are waited for by counting those behind them: the compiler may not change their order here.
+__device__ __forceinline__ void keep_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 struct F32Args {
   const float *W[3];    // row-major sources: q, k, v (EPI_QKV), gate, up (EPI_SWIGLU), or one
   int seg_nb[3];        // EPI_QKV: exclusive end of each source in row-blocks
@@ -293,7 +299,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
 #pragma unroll
     for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(wv[i][0]), "+v"(wv[i][1]));   // read before the slot is filled again
     issue_w(c + NW, half, slot);
-    __builtin_amdgcn_sched_barrier(0);
+    keep_order();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int n = half * 2 + j;
@@ -309,11 +315,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(const F32Args a) {
     }
     __builtin_amdgcn_sched_barrier(0);
     issue_x(c + NW, half, x);
+    keep_order();
   };
   issue_w(w, 0, r0);
+  keep_order();
   issue_x(w, 0, xb[0]);
+  keep_order();
   issue_w(w, 1, r1);
+  keep_order();
   issue_x(w, 1, xb[1]);
+  keep_order();
 
   // 1/rms of every row from the producer's partial sums of x^2, summed by wave 0 in a fixed order
   __shared__ float rinv_s[16];
@@ -644,8 +655,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
   // the activations of stage st+1; a2nd: weights of stage st+2; far: room for those of stage st+3.
   auto stage = [&](int st, int u, const u32x4 *xs, u32x4 *x1st, const u32x4 *a2nd, u32x4 *far) {
     issue_x(st + 1, x1st);
+    keep_order();
     issue_a(st + 3, far);
-    __builtin_amdgcn_sched_barrier(0);
+    keep_order();
     const u32x4 *sb = xs + lane;
     const u32x4 (&f)[2][3] = fa[u & 1];
 #pragma unroll
@@ -685,6 +697,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
   issue_a(0, a0);
   issue_a(1, a1);
   issue_x(0, x0);
+  keep_order();
   issue_a(2, a2);
   gate();
   read_raw(a0);
