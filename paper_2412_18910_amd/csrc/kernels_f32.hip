@@ -529,7 +529,7 @@ __device__ __forceinline__ void f32_dense_epilogue(const F32Args &a, const f32x4
 // latencies that two waves a SIMD do not cover, clocks of 2.05 GHz.
 template <int EPI, int J, bool LONG>
 __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a) {
-  constexpr int TM = 16 * J, CH = LONG && J < 4 ? 6 : 3;    // CH: stages in a chain of products (J = 4: registers)
+  constexpr int TM = 16 * J, CH = LONG ? 6 : 3;             // CH: stages in a chain of products
   constexpr int NX = (3 * J + 3) / 4;                       // activation tiles of 1 KB that a wave loads per stage
   // Activations of two stages [row-block][hi, mid, lo][lane], weights of three as they are [wave][row-block][slot]: arrays
   // of their own, so that the compiler can tell a read of one from a load into another.
@@ -799,7 +799,8 @@ static void launch_f32_dense_tile(F32Args a, hipStream_t s, size_t max_part) {
   }
   const dim3 grid((a.whole + 7) / 8 * 8 + (a.tail * a.tail_splits + 7) / 8 * 8, a.splits);
   // the joins of a chain cost vector instructions; of a long sum half as many keep the error below that of scalar sums
-  if (a.K >= 4096) gemm_f32_dense_kernel<EPI, J, true><<<grid, 256, 0, s>>>(a);
+  // (J = 4: its registers do not hold longer chains)
+  if (J < 4 && a.K >= 4096) gemm_f32_dense_kernel<EPI, J, (J < 4)><<<grid, 256, 0, s>>>(a);
   else gemm_f32_dense_kernel<EPI, J, false><<<grid, 256, 0, s>>>(a);
   if constexpr (EPI != EPI_PART) {
     if (a.tail > 0) f32_tail_kernel<EPI, J><<<a.tail, 256, 0, s>>>(a);

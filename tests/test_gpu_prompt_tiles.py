@@ -50,9 +50,9 @@ CASES = {
     "f32-1001": Case(F_SHORT, 1001, (("PART", 3, 0), ("QKV", 4, 0), ("SWIGLU", 3, 0)), oracle=False),
     "f32-long-21": Case(F_LONG, 21, (("PART", 2, 1), ("QKV", 1, 1), ("SWIGLU", 1, 1))),
     "f32-long-61": Case(F_LONG, 61, (("PART", 2, 1), ("QKV", 1, 1), ("SWIGLU", 2, 1))),
-    "f32-long-403": Case(F_LONG, 403, (("PART", 3, 0), ("PART", 3, 1), ("QKV", 2, 1), ("SWIGLU", 4, 1)), oracle=False),
-    "f32-long-601": Case(F_LONG, 601, (("PART", 4, 0), ("PART", 4, 1), ("QKV", 3, 1), ("SWIGLU", 2, 1)), oracle=False),
-    "f32-long-901": Case(F_LONG, 901, (("PART", 3, 1), ("QKV", 4, 1), ("SWIGLU", 3, 1)), oracle=False),
+    "f32-long-403": Case(F_LONG, 403, (("PART", 3, 0), ("PART", 3, 1), ("QKV", 2, 1), ("SWIGLU", 4, 0)), oracle=False),
+    "f32-long-601": Case(F_LONG, 601, (("PART", 4, 0), ("QKV", 3, 1), ("SWIGLU", 2, 1)), oracle=False),
+    "f32-long-901": Case(F_LONG, 901, (("PART", 3, 1), ("QKV", 4, 0), ("SWIGLU", 3, 1)), oracle=False),
     "bf16-ffn-777": Case(B_FFN, 777, (("SWIGLU", 4, 4),)),
     "bf16-ffn-1950": Case(B_FFN, 1950, (("SWIGLU", 8, 4),)),
     "bf16-wide-1500": Case(B_WIDE, 1500, (("RESID", 4, 4), ("STORE", 4, 4))),

@@ -36,6 +36,6 @@ def test_the_cases_reach_every_kernel():
     f32, bf16 = set(), set()
     for c in CASES.values():
         (bf16 if c.cfg.dtype == BF16 else f32).update(c.reaches)
-    assert f32 == {(e, j, long) for e in ("QKV", "SWIGLU", "PART") for j in (1, 2, 3, 4) for long in (0, 1)}
+    assert f32 == {(e, j, long) for e in ("QKV", "SWIGLU", "PART") for j in (1, 2, 3, 4) for long in (0, 1) if (j, long) != (4, 1)}
     assert bf16 == {(e, rows, 4) for e in ("QKV", "SWIGLU", "RESID", "STORE") for rows in (4, 8)} | \
         {("PART", rows, w) for rows in (4, 8) for w in (2, 3)}
