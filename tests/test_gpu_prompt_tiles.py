@@ -34,33 +34,48 @@ class Case:
         return self.cfg.with_(n_ctx_max=self.n + 16)
 
 
-# float32: (epilogue, 16-row blocks of a tile, chains of 32); widths leave tails in K and half row-blocks
+# float32: (epilogue, 16-row blocks of a tile, long chains), ("TAIL-" epilogue, 16-row blocks of a tile, 1: behind whole tiles)
+# where the last tiles are made in pieces of K; widths leave tails in K and half row-blocks
 F_SHORT, F_LONG = _cfg(FP32, 1032, 16, 8, 128, 4104), _cfg(FP32, 4104, 16, 8, 128, 4104)
-F_MID = _cfg(FP32, 1032, 12, 6, 64, 2056)
-# bf16, whole K: (epilogue, row-blocks of a tile, weight row-blocks of a wave); the widths of the QKV cases end in half a tile
+F_MID, F_2K, F_MHA = _cfg(FP32, 1032, 12, 6, 64, 2056), _cfg(FP32, 2056, 16, 8, 128, 4104), _cfg(FP32, 1032, 32, 32, 128, 4104)
+F_WIDE = _cfg(FP32, 4104, 32, 8, 128, 1032)
+# bf16, whole K: (epilogue, row-blocks of a tile, weight row-blocks of a wave, waves); the widths of QKV (120 and 264 row-blocks)
+# and of B_ODD (272) end within a tile of 16, those of B_ODD within one of 32
 B_FFN, B_WIDE, B_QKV = _cfg(BF16, 256, 4, 2, 64, 4096), _cfg(BF16, 4096, 4, 4, 64, 256), _cfg(BF16, 256, 20, 5, 64, 512)
+B_QKV2, B_ODD = _cfg(BF16, 256, 44, 11, 64, 4352), _cfg(BF16, 4352, 4, 4, 64, 256)
 # bf16, K in pieces
 B_SPLIT = _cfg(BF16, 1024, 4, 2, 64, 11008)
 CASES = {
-    "f32-61": Case(F_SHORT, 61, (("PART", 1, 0), ("QKV", 1, 0), ("SWIGLU", 2, 0), ("PART", 1, 1))),
-    "f32-101": Case(F_MID, 101, (("PART", 1, 0), ("QKV", 1, 0), ("SWIGLU", 1, 0))),
-    "f32-131": Case(F_SHORT, 131, (("QKV", 2, 0), ("SWIGLU", 3, 0))),
+    "f32-61": Case(F_SHORT, 61, (("PART", 1, 0), ("QKV", 1, 0), ("SWIGLU", 2, 0), ("PART", 1, 1), ("TAIL-QKV", 1, 0))),
+    "f32-101": Case(F_MID, 101, (("PART", 1, 0), ("QKV", 1, 0), ("SWIGLU", 1, 0), ("TAIL-SWIGLU", 1, 0))),
+    "f32-131": Case(F_SHORT, 131, (("QKV", 2, 0), ("SWIGLU", 3, 0), ("TAIL-QKV", 2, 0))),
+    "f32-163": Case(F_SHORT, 163, (("TAIL-SWIGLU", 1, 1),)),
     "f32-301": Case(F_SHORT, 301, (("PART", 2, 0), ("PART", 2, 1), ("QKV", 3, 0))),
     "f32-403": Case(F_SHORT, 403, (("QKV", 2, 0), ("SWIGLU", 4, 0)), oracle=False),
     "f32-1001": Case(F_SHORT, 1001, (("PART", 3, 0), ("QKV", 4, 0), ("SWIGLU", 3, 0)), oracle=False),
+    "f32-mha-101": Case(F_MHA, 101, (("TAIL-QKV", 1, 1),)),
+    "f32-mha-249": Case(F_MHA, 249, (("TAIL-QKV", 2, 1),), oracle=False),
+    "f32-mha-333": Case(F_MHA, 333, (("TAIL-QKV", 3, 1),), oracle=False),
+    "f32-2k-131": Case(F_2K, 131, (("TAIL-SWIGLU", 3, 0),), oracle=False),
+    "f32-2k-703": Case(F_2K, 703, (("TAIL-SWIGLU", 4, 1),), oracle=False),
+    "f32-wide-901": Case(F_WIDE, 901, (("TAIL-QKV", 4, 1),), oracle=False),
     "f32-long-21": Case(F_LONG, 21, (("PART", 2, 1), ("QKV", 1, 1), ("SWIGLU", 1, 1))),
-    "f32-long-61": Case(F_LONG, 61, (("PART", 2, 1), ("QKV", 1, 1), ("SWIGLU", 2, 1))),
+    "f32-long-61": Case(F_LONG, 61, (("PART", 2, 1), ("QKV", 1, 1), ("SWIGLU", 2, 1), ("TAIL-SWIGLU", 2, 0))),
     "f32-long-403": Case(F_LONG, 403, (("PART", 3, 0), ("PART", 3, 1), ("QKV", 2, 1), ("SWIGLU", 4, 0)), oracle=False),
-    "f32-long-601": Case(F_LONG, 601, (("PART", 4, 0), ("QKV", 3, 1), ("SWIGLU", 2, 1)), oracle=False),
-    "f32-long-901": Case(F_LONG, 901, (("PART", 3, 1), ("QKV", 4, 0), ("SWIGLU", 3, 1)), oracle=False),
-    "bf16-ffn-777": Case(B_FFN, 777, (("SWIGLU", 4, 4),)),
-    "bf16-ffn-1950": Case(B_FFN, 1950, (("SWIGLU", 8, 4),)),
-    "bf16-wide-1500": Case(B_WIDE, 1500, (("RESID", 4, 4), ("STORE", 4, 4))),
-    "bf16-wide-2501": Case(B_WIDE, 2501, (("RESID", 8, 4), ("STORE", 8, 4)), oracle=False, chunk=8192),
-    "bf16-qkv-3100": Case(B_QKV, 3100, (("QKV", 4, 4),), oracle=False, chunk=8192),
-    "bf16-qkv-8100": Case(B_QKV, 8100, (("QKV", 8, 4), ("SWIGLU", 4, 4)), oracle=False, chunk=8192),
-    "bf16-split-50": Case(B_SPLIT, 50, (("PART", 4, 2), ("PART", 4, 3))),
-    "bf16-split-101": Case(B_SPLIT, 101, (("PART", 8, 2), ("PART", 8, 3))),
+    "f32-long-601": Case(F_LONG, 601, (("PART", 4, 0), ("QKV", 3, 1), ("SWIGLU", 2, 1), ("TAIL-QKV", 3, 0), ("TAIL-SWIGLU", 2, 1)),
+                         oracle=False),
+    "f32-long-901": Case(F_LONG, 901, (("PART", 3, 1), ("QKV", 4, 0), ("SWIGLU", 3, 1), ("TAIL-SWIGLU", 3, 1)), oracle=False),
+    "bf16-ffn-777": Case(B_FFN, 777, (("SWIGLU", 4, 4, 8),)),
+    "bf16-ffn-1950": Case(B_FFN, 1950, (("SWIGLU", 8, 4, 4),)),
+    "bf16-ffn-2301": Case(B_FFN, 2301, (("SWIGLU", 4, 4, 4),), oracle=False, chunk=8192),
+    "bf16-wide-1500": Case(B_WIDE, 1500, (("RESID", 4, 4, 4), ("STORE", 4, 4, 4))),
+    "bf16-wide-2501": Case(B_WIDE, 2501, (("RESID", 8, 4, 4), ("STORE", 8, 4, 4)), oracle=False, chunk=8192),
+    "bf16-odd-1500": Case(B_ODD, 1500, (("RESID", 4, 4, 8), ("STORE", 4, 4, 8)), oracle=False),
+    "bf16-qkv-1901": Case(B_QKV2, 1901, (("QKV", 4, 4, 4),), oracle=False),
+    "bf16-qkv-3100": Case(B_QKV, 3100, (("QKV", 4, 4, 8),), oracle=False, chunk=8192),
+    "bf16-qkv-8100": Case(B_QKV, 8100, (("QKV", 8, 4, 4), ("SWIGLU", 4, 4, 8)), oracle=False, chunk=8192),
+    "bf16-split-50": Case(B_SPLIT, 50, (("PART", 4, 2, 8), ("PART", 4, 3, 8))),
+    "bf16-split-101": Case(B_SPLIT, 101, (("PART", 8, 2, 8), ("PART", 8, 3, 8))),
 }
 
 
