@@ -335,19 +335,12 @@ size_t f32_part_floats(const ae_config &g, int rows) {
   return (cap > 2048 ? cap : 8 * cap < 2048 ? 8 * cap : 2048) * g.d_model;
 }
 
-// Chunk buffers for `cap` rows (a multiple of 128): float residual stream and queries, the
+// Chunk buffers for `want` rows (a multiple of 128): float residual stream and queries, the
 // inputs of the five GEMMs; bf16: RMSNorm partial sums and 1/rms, zero-filled so that the
-// padding rows of a packed chunk are finite (float32: so that what lies behind the end of K is zero).  Nothing is held where they do not fit; bf16 prompts
-// do without room for pieces of K (no GEMM is split then).
-int ensure_dense(ae_ctx *c, int n) {
+// padding rows of a packed chunk are finite (float32: so that what lies behind the end of K is zero).  Nothing is held where
+// they do not fit; bf16 prompts do without room for pieces of K (no GEMM is split then).
+int alloc_dense(ae_ctx *c, int want) {
   const ae_config &g = c->cfg;
-  int want = ((n < c->dense_chunk ? n : c->dense_chunk) + 127) / 128 * 128;
-  if (!c->fast) {   // offsets into a plane buffer have 32 bits
-    const int widest = g.d_ffn > 2 * g.d_model ? g.d_ffn : 2 * g.d_model, dq = g.n_heads * g.head_dim;
-    const size_t fits = 0xffff0000u / planes_bytes(128, widest > dq ? widest : dq) * 128;
-    if ((size_t)want > fits && fits) want = (int)fits;
-  }
-  if (want <= c->dense_cap) return AE_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   release_dense(c);
   const OnDevice here(c->device);   // float32 prompts never depended on the thread's device
@@ -387,6 +380,23 @@ int ensure_dense(ae_ctx *c, int n) {
   }
   c->dense_cap = want;
   return AE_OK;
+}
+
+// Buffers for a prompt of n tokens, or for the longest chunk of it
+int ensure_dense(ae_ctx *c, int n) {
+  const ae_config &g = c->cfg;
+  int want = ((n < c->dense_chunk ? n : c->dense_chunk) + 127) / 128 * 128;
+  if (!c->fast) {   // offsets into a plane buffer have 32 bits
+    const int widest = g.d_ffn > 2 * g.d_model ? g.d_ffn : 2 * g.d_model, dq = g.n_heads * g.head_dim;
+    const size_t fits = 0xffff0000u / planes_bytes(128, widest > dq ? widest : dq) * 128;
+    if ((size_t)want > fits && fits) want = (int)fits;
+  }
+  if (want <= c->dense_cap) return AE_OK;
+  int rc = alloc_dense(c, want);
+  // three bf16 parts take half as much again as a float: where they do not fit, a chunk of two thirds takes what floats would
+  const int less = want * 2 / 3 / 128 * 128;
+  if (rc == AE_ENOMEM && !c->fast && less > 0) rc = alloc_dense(c, less);
+  return rc;
 }
 
 // Target layers over chunk rows [p0, p0+rows) and the draft head's K/V rows for the first

@@ -71,6 +71,20 @@ def test_float32_goes_back_to_blocks_and_holds_no_memory(make, limit):
     assert c.prefill(300) == AE_OK and "attn_prefill_f32_kernel" in names(c)
 
 
+@pytest.mark.parametrize("n", [700, 1100, 2048])
+def test_float32_planes_that_do_not_fit_take_smaller_chunks(make, n):
+    cfg = TINY.with_(n_ctx_max=2400)
+    c = make(cfg)
+    # room for a float an activation (K in whole k-tiles of 32), not for three parts
+    c.lib.fake_fail_alloc((n + 127) // 128 * 128 * ((cfg.d_ffn + 31) // 32 * 32) * 4 + 1)
+    for _ in range(2):
+        c.lib.fake_clear()
+        assert c.prefill(n) == AE_OK and c.lib.fake_last_error() == 0
+        k = names(c)
+        assert "attn_prefill_f32_kernel" in k and "attn_f32_kernel" not in k
+        assert k.count("embed_f32_kernel") == 2
+
+
 def test_a_failed_larger_prompt_leaves_the_shorter_ones_working(make):
     for cfg in (MID, TINY.with_(n_ctx_max=2400)):
         c = make(cfg)
