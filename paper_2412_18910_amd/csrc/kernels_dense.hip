@@ -240,12 +240,15 @@ __global__ __launch_bounds__(256) void dense_finish_kernel(const GemmArgs a, int
 
 // Row of a workgroup of the kernels that pack a row each.  Neighbouring rows share lines of a packed tile, so they go to
 // one XCD (workgroups are handed out round-robin to the eight), whose L2 puts the lines together: the 16 rows of a row-block,
-// or four, which share 64 bytes, where the row-blocks are too few for all of the chip.  1100 rows, in row order: sum 28.8 us,
-// draft input 44.6, embedding 28.4; so 19.7, 28.1, 18.6.
+// or four, which share 64 bytes, where the row-blocks are too few for all of the chip.  Tiles in lane order, 7B widths,
+// microseconds in row order -> so (row-major tiles, which these kernels alone would want): sum of K pieces, 100 rows 8.9 -> 7.9
+// (7.6), 333 13.3 -> 11.1 (10.0), 1100 27.0 -> 19.2 (18.0); draft input, 333 rows 17.3 -> 12.8 (10.0), 1100 44.3 -> 28.2 (25.5),
+// 2048 78.7 -> 51.4 (45.5); embedding, 1100 rows 23.1 -> 17.2 (18.2), 2048 40.0 -> 24.8 (29.0).  What lane order costs the
+// first two the GEMMs gain several times over (a layer of 2048 rows 24 us).
 constexpr int packed_row_groups(int rows) { return rows > 512 ? (rows + 127) / 128 * 128 : (rows + 31) / 32 * 32; }
 __device__ __forceinline__ int packed_row() {
   const int b = blockIdx.x, sh = gridDim.x > 512 ? 4 : 2;   // rows beside each other: 16 or 4
-  return ((b >> (3 + sh)) * 8 + (b & 7) << sh) + ((b >> 3) & ((1 << sh) - 1));
+  return (((b >> (3 + sh)) * 8 + (b & 7)) << sh) + ((b >> 3) & ((1 << sh) - 1));
 }
 
 // Adds the pieces of a row to its residual (x, updated in place) or to the bias, leaves row * gain packed for the next
