@@ -1187,9 +1187,10 @@ int32_t ae_pending(const ae_ctx *c) { return c && c->have_pending ? c->pending :
 // device is at work.
 // rows: rows of n floats from `first` on that belong together.  A caller that has fetched the row before this one of them
 // will fetch the one behind it too: that one sets out with this one, so that the launch and the link (5 + 14 us of
-// 128256 floats) run beside the host's copy.  Whatever may write rows forgets it (forget_rows).  Nine rows behind a
-// verification of 8 layers of 8B-GQA, the whole pass 1420 -> 1297 us; eleven of 32000 floats 1497 -> 1428; nine of 4096 334 -> 307.
-// A row that comes for nothing (somebody reads two rows and no more) costs the stream its export.
+// 128256 floats) run beside the host's copy.  Whatever may write rows forgets it (forget_rows).  Whole passes, without -> so: nine rows
+// behind a verification of 8 layers of 8B-GQA 1406 -> 1305 us; eleven of 32000 floats 1429 -> 1365; nine of 4096 behind the smallest
+// model's step 312 -> 286.  A row that comes for nothing costs the stream its export: two of the nine read and then the next
+// block 1124 -> 1126.
 static int copy_out(ae_ctx *c, const float *src, size_t n, float *dst, const float *first = nullptr, int rows = 0) {
   const size_t pieces = c->row_floats / kExportPiece;
   auto send = [&](const float *row, int half) {

@@ -19,7 +19,7 @@
 // of K then K / (2 c n).  The sums that a wave of scalar code makes (64 lanes, each a chain of K / 64 products, and a
 // butterfly) cost K / 128 + 6 of these, and neither GEMM may cost more: the decode GEMM cuts at 16 products (8 where K
 // is below 1024) and adds wave results as a tree.  The prompt GEMM's instruction adds 32 products with fewer roundings;
-// its chains of three instructions join one total.
+// its chains of three instructions (six where K is 4096 and more and the tile leaves the registers) join one total.
 // The flash attention adds its accumulators to a second set every 256 keys.
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
@@ -523,10 +523,10 @@ __device__ __forceinline__ void f32_dense_epilogue(const F32Args &a, const f32x4
 // weight row-blocks and all J activation row-blocks.  Stages of 32 k go straight into LDS, weights three stages ahead,
 // activations one.  While a stage is multiplied the weights of the next one are split, vector instructions between the
 // matrix instructions: an MFMA of 16 cycles leaves room for two.  7B widths, 333 rows, against the float32 instruction:
-// gate/up 649 -> 360 + 6 us (the last tiles in pieces of K; 382 whole), QKV 408 -> 204 + 7 (238), o / down 247 -> 139 on
-// average; whole tiles with the activations split here too (44 vector instructions more a stage) 478 / 295.  What is left
-// of the matrix rate (40 %): 3.7 vector instructions an MFMA at J = 3,
-// latencies that two waves a SIMD do not cover, clocks of 2.05 GHz.
+// gate/up 649 -> 356 + 5 us (the last tiles in pieces of K), QKV 408 -> 203 + 6, o / down 247 -> 140 on average; the factor of
+// the split takes 16 of 118 vector instructions a stage (J = 3) and 6, 4 and 3 us of these.  With the activations split here too
+// (44 vector instructions more a stage; whole tiles, without the factor: 382 and 238 us) 478 / 295.  What is left of the matrix rate
+// (40 %): 3.3 vector instructions an MFMA at J = 3, latencies that two waves a SIMD do not cover, clocks of 2.05 GHz.
 template <int EPI, int J, bool LONG>
 __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a) {
   constexpr int TM = 16 * J, CH = LONG ? 6 : 3;             // CH: stages in a chain of products
