@@ -1,12 +1,13 @@
 """Float32 models on the GPU against the oracle at the sizes where the kernels change shape (needs an MI355X)."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2412_18910_amd import synth
 from paper_2412_18910_amd.binding import Engine
 from paper_2412_18910_amd.config import FP32, Config
 
-from .gpu_helpers import make_pair, top2_margin
+from .gpu_helpers import make_pair, to_device, top2_margin
 
 pytestmark = pytest.mark.gpu
 
@@ -109,3 +110,34 @@ def test_sampled_draft_and_ddd_statistic_with_an_odd_vocabulary():
                 float(l[t] / 0.7 - np.log(np.sum(np.exp(l.astype(np.float64) / 0.7))))
                 for l, t in ((eng.draft_logits(i), d_g[i]) for i in range(c.k_max)))) < 1e-3
         eng.close()
+
+
+def test_weights_that_begin_at_any_float():
+    """Matrices are contiguous, but may begin anywhere in a larger tensor: the same bits from every alignment."""
+    cfg = Config(2, 264, 4, 2, 64, 520, 515, dtype=FP32, k_max=4, n_ctx_max=128, ldlp_hidden=64)
+    w = synth.make_weights(cfg, 71)
+    ids, block = synth.token_ids(70, cfg.vocab, 72), synth.token_ids(5, cfg.vocab, 73)
+
+    def moved(t, by):
+        if t is None or t.dim() < 2:
+            return t
+        store = torch.empty(t.numel() + by, dtype=t.dtype, device="cuda")
+        store[by:].copy_(t.reshape(-1))
+        return store[by:].view(t.shape)
+
+    def run(by):
+        dev = {k: moved(v, by) if torch.is_tensor(v) else v for k, v in to_device(w).items()}
+        dev["layers"] = [{k: moved(v, by) for k, v in lw.items()} for lw in dev["layers"]]
+        dev["draft_layer"] = {k: moved(v, by) for k, v in dev["draft_layer"].items()}
+        eng = Engine(cfg, dev)
+        eng.prefill(ids)
+        out = [eng.logits(0)]
+        d = eng.draft(4)
+        eng.verify(block)
+        out += [eng.logits(i) for i in range(5)] + [eng.draft_logits(i) for i in range(4)] + [d]
+        eng.close()
+        return out
+
+    want = run(0)
+    for by in (1, 2, 3):
+        assert all(np.array_equal(a, b) for a, b in zip(want, run(by)))
