@@ -5,14 +5,13 @@
 // live in the packed bf16 hi/lo form of the decode step, extended to many row-blocks
 // (Xp[kt][rb][h][64], see packed.h); weights are the same k-major MFMA tiles the decode
 // GEMMs stream.  Kernels:
-//  * gemm_dense_kernel: workgroup tile = 256 weight rows x 128 (or 64) activation rows.  Each
-//    of the 4 waves owns 4 weight row-blocks (A operands: buffer loads straight from the tiled
-//    matrix into registers, one coalesced 1 KB burst per tile, three k-tiles ahead) and all 8 (4)
-//    activation row-blocks, which go straight into an LDS ring of four k-tiles (64 KB).
-//    64 MFMAs per wave and k-tile against 16 LDS reads, which are issued
-//    one step ahead of the MFMAs that use them; two workgroups per CU (<= 256 registers) so
-//    that two waves feed every matrix pipe; tiles are handed out XCD-aware; epilogues are
-//    those of the decode GEMM.
+//  * gemm_dense_kernel: a workgroup of 4 or 8 waves makes a tile of 128 to 512 weight rows x 32 to 128
+//    activation rows (dense_plan).  Each wave owns 2 to 4 weight row-blocks (A operands: buffer loads straight
+//    from the tiled matrix into registers, one coalesced 1 KB burst per tile, three k-tiles ahead) and
+//    multiplies them with all activation row-blocks, which go straight into an LDS ring of four k-tiles
+//    (64 KB for 128 rows).  At 4 x 8 row-blocks, 64 MFMAs per wave and k-tile against 16 LDS reads, which are
+//    issued one step ahead of the MFMAs that use them; two waves feed every matrix pipe (<= 256 registers);
+//    tiles are handed out XCD-aware; epilogues are those of the decode GEMM.
 //  * attn_prefill_kernel: causal flash attention straight off the tiled KV cache; a wave owns
 //    16 or 32 (row, head) pairs of one KV head and walks the visible keys 32 at a time with an
 //    online softmax in the log2 domain; no partials, no merge, packed output.
@@ -25,10 +24,9 @@ namespace ae {
 
 constexpr int EPI_PART = 4;   // raw float32 sums over a piece of K -> a.part[piece][row][N]
 
-// DM = activation row-blocks per workgroup: 8 (128 rows), or 4 when the wide tile would leave
-// compute units without two resident workgroups.  DN = weight row-blocks per wave, NW = waves: 4 x 4, 4 x 8 for
-// 512 weight rows, or 2 x 8 (half the accumulators, twice the waves) where K is split over workgroups (gridDim.y pieces,
-// EPI_PART).
+// DM = activation row-blocks per workgroup, DN = weight row-blocks per wave, NW = waves; EPI_PART: K is split over workgroups
+// (gridDim.y pieces).  The waves lie along the weights alone: with two groups of waves along the rows (half the LDS
+// reads, each weight tile loaded twice) 100 rows of 7B gate/up took 52 us instead of 46, the vector cache being what is short.
 template <int EPI, bool NORM, int DM, int DN, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a) {
   // ring of four k-tiles of B, [DM][2][64] pieces each: arrays of their own, so that the compiler can tell a read of
@@ -70,7 +68,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)a.Xp, 0, a.xp_bytes, 0x00020000);
   const unsigned wl = lane * 16;                                         // per-lane byte offset
   const unsigned kstride_b = a.NBtot * 1024u, kts_b = a.RB * 2048u;      // bytes per k-tile
-  unsigned wq = nbw * 1024u, xq = (rb0 * 128u + w * 64u) * 16u;           // first k-tile (uniform)
+  unsigned wq = nbw * 1024u, xq = rb0 * 2048u;           // first k-tile (uniform)
   int NK = a.KT;   // k-tiles, a multiple of 4
   if (EPI == EPI_PART) {   // a piece of K in units of 4 k-tiles
     const int u0 = a.KT / 4 * (int)blockIdx.y / (int)gridDim.y, u1 = a.KT / 4 * ((int)blockIdx.y + 1) / (int)gridDim.y;
@@ -89,14 +87,16 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
   // without passing registers.  (Through registers only one stage fitted beside the 128 accumulators; waits on
   // loads one stage old and the LDS writes kept the matrix pipes at 60 % of a 7B gate/up GEMM over 2048 rows.)
   // 7B widths, 2048 rows: gate/up 597 -> 548 us, QKV 346 -> 319, o/down 225 -> 213 on average.
-  constexpr int XI = DM * 2 / NW, VM = XI + DN;   // B tiles per wave, loads per wave and k-tile
+  constexpr int XI = (DM * 2 + NW - 1) / NW, VM = XI + DN;   // B tiles per wave, loads per wave and k-tile
   u32x4 w0[DN], w1[DN], w2[DN], w3[DN];
   auto put = [&](u32x4 *slot, u32x4 (&wr)[DN], int kt) {   // k-tiles behind the last repeat it (ignored)
     const unsigned k = min(kt, NK - 1);
 #pragma unroll
-    for (int i = 0; i < XI; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(slot + (w + NW * i) * 64), 16, wl,
-                                               xq + k * kts_b + i * (NW * 1024), 0, 0);
+    for (int i = 0; i < XI; ++i) {   // the same number for every wave: one too many loads the last tile again
+      const int t = DM * 2 % NW ? min(w + NW * i, DM * 2 - 1) : w + NW * i;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(slot + t * 64), 16, wl,
+                                               xq + k * kts_b + t * 1024, 0, 0);
+    }
 #pragma unroll
     for (int i = 0; i < DN; ++i) wr[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, wl + i * 1024, wq + k * kstride_b, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -163,13 +163,14 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
 #pragma unroll
     for (int j = 0; j < DM; ++j) {
       const int rb = rb0 + j, row = rb * 16 + m;
+      if (rb * 16 >= a.rows) break;   // wave-uniform: behind the rows, and where DM does not divide them behind the buffers
       const bool row_ok = row < a.rows;
       if (EPI == EPI_PART) {
         if (row_ok)
           *reinterpret_cast<f32x4 *>(a.part + (((size_t)blockIdx.y * a.rows + row) * a.NBtot + nb) * 16 + 4 * g) = acc[i][j];
         continue;
       }
-      const float rinv = NORM ? a.rinv[row] : 1.f;
+      const float rinv = NORM && row_ok ? a.rinv[row] : 1.f;
       epi_tile<EPI, true>(a, acc[i][j], acc[i + STEP - 1][j], nb, g, m, rb, row_ok, rinv, kts);
     }
   }
@@ -181,39 +182,103 @@ static void launch_dense_tile(const GemmArgs &a, int splits, hipStream_t s) {
   gemm_dense_kernel<EPI, NORM, DM, DN, NW><<<dim3((tiles + 7) / 8 * 8, splits), NW * 64, 0, s>>>(a);
 }
 
-// A GEMM whose tiles of 256 weight rows x 64 rows number less than 384 would leave compute units idle (256, two
-// workgroups each).  It runs in workgroups of 8 waves, at most one per compute unit, that take 256 or 384 weight rows
-// (DN = 2, 3) and a piece of K, and a pass that adds the pieces.  7B widths, 100 rows: o/down 155 -> 27 + 8 us, QKV
-// 90 -> 35 + 10, gate/up 92 -> 54 + 9.  The line: a prompt of 256 rows over 4 layers (gate/up 344 tiles) takes 1297 us
-// split and 1320 whole, one of 320 rows (430 tiles) 1670 split and 1557 whole.  splits == 0: the GEMM is not one of
-// those, or there is no room for the pieces.
-struct DenseSplit {
-  int splits = 0, dn = 2;
+// How a GEMM is laid out on the chip: waves (4 or 8) and weight row-blocks of each (dn), activation row-blocks of a workgroup
+// (dm, exact: a prompt of 100 rows multiplies 7, not 8), pieces of K (0: whole K, and the epilogue in the same kernel).
+struct DensePlan {
+  int nw = 8, dn = 2, dm = 8, splits = 0;
 };
-static DenseSplit dense_splits(const GemmArgs &a, size_t part_floats) {
-  DenseSplit best;
-  if ((long)((a.NBtot + 15) / 16) * ((a.rows + 63) / 64) >= 384) return best;
-  const long mt = a.rows > 64 ? (a.rows + 127) / 128 : 1;
-  double cost = 1e30;
-  for (int dn = 2; dn <= 3; ++dn) {
-    if (a.NBtot < 8 * dn) break;
-    const long tiles = (a.NBtot + 8 * dn - 1) / (8 * dn) * mt;
-    for (int S = 1; S <= 16 && S <= a.KT / 8; ++S) {   // a piece: two passes of the k-loop at least
-      if ((size_t)S * a.rows * a.NBtot * 16 > part_floats) break;
-      const double c = (double)((tiles * S + 255) / 256) * dn / S + 0.005 * S;   // rounds x work of a piece, its pass
-      if (c < cost) { cost = c; best.splits = S; best.dn = dn; }
+
+// Microseconds that a plan takes, fitted to 9600 launches (7B, 13B and 8B-GQA widths, 20 to 4096 rows; the plan it picks is
+// 1-2 % off the best of all measured ones on average).  Workgroups go round-robin to the 8 XCDs of 32 compute units.  A
+// k-tile of a workgroup costs what is largest of its products (5 ns for 16 x 16 x 32, hi and lo), what it takes through the
+// vector cache (16 ns a KB: 64 GB/s a compute unit, by lines in flight) and the weights' share of HBM.  Pieces are
+// written at 3.8 TB/s when all workgroups end at once, and a pass adds them; whole K pays for its epilogue, and for
+// o and down for the launch that sums x^2.  One workgroup of four waves alone on a compute unit is 12 % slower at the
+// products; of those that run for several rounds 4 x 4 tiles (two workgroups a unit) are ahead for gate/up (7B, 2048 rows: 528 us, 8 x 2 537, 8 x 4
+// 526; 4096 rows 988, 1011), 8 x 2 for the rest (QKV, 2048 rows: 297, 4 x 4 301; o and down together 395, 435).
+static double dense_cost(const GemmArgs &a, int epi, const DensePlan &p) {
+  const int n = p.nw * p.dn, S = p.splits > 0 ? p.splits : 1;
+  const long tiles = (long)((a.NBtot + n - 1) / n) * ((a.rows + p.dm * 16 - 1) / (p.dm * 16));
+  const long rounds = ((tiles + 7) / 8 * S + 31) / 32;
+  double e = 1.0 + 0.02 * (8 - p.dm);
+  if (p.nw == 4 && rounds == 1) e *= 1.116;
+  else if (p.nw == 8 && rounds > 1) e *= p.dn == 4 ? 1.04 : epi == EPI_SWIGLU ? 1.02 : 1.0;
+  const double active = (double)tiles * S / rounds, products = n * p.dm * 4.98 * e, cache = (n + 2 * p.dm) * 15.84,
+               memory = n * 0.128 * (active < 256 ? active : 256);   // 8 TB/s: ramps are in the constant
+  double k = products > cache ? products : cache;
+  if (memory > k) k = memory;
+  const double out = (double)a.rows * a.NBtot * 64;   // bytes of one float32 result
+  const double t = 6.9 + rounds * (a.KT / (double)S) * k * 1e-3;
+  if (p.splits > 0) return t + S * out / 3.8e6 + 5.4 + (S + 1) * out / 6.6e6;
+  return t + out * (epi == EPI_QKV ? 1 : epi == EPI_SWIGLU ? 0.5 : 3) / 10.9e6 + (epi == EPI_QKV || epi == EPI_SWIGLU ? 0 : 5.5);
+}
+
+// Plans by the number of tiles, for what dense_cost has not been measured on: K below 3072, a last chunk of one row-block, and whole K of the draft head's
+// input projection (once a prompt: 200 us of 2048 rows of 7B either way).  Less than 384 tiles of 256 weight rows x 64 rows
+// would leave compute units idle (256, two workgroups each): pieces of K.  Else 128-row tiles, or 64-row ones (0.55 of
+// their time) where these fill rounds of 512 workgroups better; one round of them in workgroups of eight waves, which
+// take the activations through the vector cache once instead of twice.
+static DensePlan plan_by_tiles(const GemmArgs &a, size_t part_floats) {
+  DensePlan best;
+  const long nt = (a.NBtot + 15) / 16, t8 = nt * ((a.rows + 127) / 128), t4 = nt * ((a.rows + 63) / 64);
+  if (t4 < 384) {
+    const long mt = a.rows > 64 ? (a.rows + 127) / 128 : 1;
+    double cost = 1e30;
+    for (int dn = 2; dn <= 3; ++dn) {
+      if (a.NBtot < 8 * dn) break;
+      const long tiles = (a.NBtot + 8 * dn - 1) / (8 * dn) * mt;
+      for (int S = 1; S <= 16 && S <= a.KT / 8; ++S) {   // a piece: two passes of the k-loop at least
+        if ((size_t)S * a.rows * a.NBtot * 16 > part_floats) break;
+        const double c = (double)((tiles * S + 255) / 256) * dn / S + 0.005 * S;   // rounds x work of a piece, its pass
+        if (c < cost) { cost = c; best = DensePlan{8, dn, a.rows > 64 ? 8 : 4, S}; }
+      }
     }
+    if (best.splits) return best;
   }
+  const double c8 = (double)((t8 + 511) / 512), c4 = 0.55 * (double)((t4 + 511) / 512);
+  const long t48 = (nt + 1) / 2 * ((a.rows + 63) / 64);
+  if (c4 < c8 && t4 <= 512 && t48 > 192 && t48 <= 256) return DensePlan{8, 4, 4, 0};
+  return DensePlan{4, 4, c4 < c8 ? 4 : 8, 0};
+}
+
+// Short prompts: few tiles, all of the weights to read.  K is cut so that all compute units read, but in as few pieces as that
+// takes: writing and adding them was a third of a 7B layer of 100 rows (gate/up 4 pieces of 384 weight rows 46 + 9 us, now 2 of 192
+// 46 + 6; QKV 8 of 384 31 + 10, now 4 of 192 29 + 7; o and down 16 of 256 24 + 8, now 8 of 128 20 + 6).  Long prompts: whole K, the
+// rows in tiles that fill their last round.
+static DensePlan dense_plan(const GemmArgs &a, int epi, size_t part_floats) {
+  const DensePlan by_tiles = plan_by_tiles(a, part_floats);
+  if (a.KT < 96 || a.rows <= 16 || (epi == EPI_STORE && by_tiles.splits == 0)) return by_tiles;
+  static constexpr int kSplit[4][2] = {{4, 2}, {4, 3}, {8, 2}, {8, 3}}, kWhole[3][2] = {{8, 2}, {8, 4}, {4, 4}};   // waves, dn
+  DensePlan best = by_tiles;
+  double cost = 1e30;
+  auto consider = [&](const DensePlan &p) {
+    if (a.NBtot < p.nw * p.dn) return;
+    const double c = dense_cost(a, epi, p);
+    if (c < cost) { cost = c; best = p; }
+  };
+  for (int i = 0; i < (epi == EPI_STORE ? 0 : epi == EPI_SWIGLU ? 3 : 1); ++i)   // gate/up alone gains by the other two
+    for (int dm = 4; dm <= 8; ++dm) consider(DensePlan{kWhole[i][0], kWhole[i][1], dm, 0});
+  const int rbs = (a.rows + 15) / 16, mt = (rbs + 7) / 8;
+  for (auto &w : kSplit)
+    for (int S = 1; S <= 16 && (size_t)S * a.rows * a.NBtot * 16 <= part_floats; ++S)
+      consider(DensePlan{w[0], w[1], (rbs + mt - 1) / mt, S});
   return best;
 }
 
-static void launch_dense_part(const GemmArgs &a, DenseSplit sp, hipStream_t s) {
-  if (sp.dn == 2) {
-    if (a.rows > 64) launch_dense_tile<EPI_PART, false, 8, 2, 8>(a, sp.splits, s);
-    else launch_dense_tile<EPI_PART, false, 4, 2, 8>(a, sp.splits, s);
-  } else {
-    if (a.rows > 64) launch_dense_tile<EPI_PART, false, 8, 3, 8>(a, sp.splits, s);
-    else launch_dense_tile<EPI_PART, false, 4, 3, 8>(a, sp.splits, s);
+template <int DM>
+static void launch_dense_part(const GemmArgs &a, const DensePlan &p, hipStream_t s) {
+  if (p.nw == 4 && p.dn == 2) launch_dense_tile<EPI_PART, false, DM, 2, 4>(a, p.splits, s);
+  else if (p.nw == 4) launch_dense_tile<EPI_PART, false, DM, 3, 4>(a, p.splits, s);
+  else if (p.dn == 2) launch_dense_tile<EPI_PART, false, DM, 2, 8>(a, p.splits, s);
+  else launch_dense_tile<EPI_PART, false, DM, 3, 8>(a, p.splits, s);
+}
+
+template <int EPI, bool NORM, int DM>
+static void launch_dense_whole(const GemmArgs &a, const DensePlan &p, hipStream_t s) {
+  if (p.nw == 8 && p.dn == 2) launch_dense_tile<EPI, NORM, DM, 2, 8>(a, 1, s);
+  else if constexpr (EPI == EPI_SWIGLU || DM == 4 || DM == 8) {   // else plan_by_tiles alone
+    if (p.nw == 4) launch_dense_tile<EPI, NORM, DM, 4, 4>(a, 1, s);
+    else if constexpr (EPI == EPI_SWIGLU || DM == 4) launch_dense_tile<EPI, NORM, DM, 4, 8>(a, 1, s);
   }
 }
 
@@ -293,21 +358,20 @@ __global__ __launch_bounds__(1024) void dense_sum_rows_kernel(const GemmArgs a, 
 }
 
 template <int EPI, bool NORM>
-static void launch_dense_cfg(const GemmArgs &a, hipStream_t s) {
-  // 256 compute units x 2 resident workgroups: estimate both tilings in rounds of 512
-  // workgroups; a 64-row tile costs about 0.55 of a 128-row one.
-  const long nt = (a.NBtot + 15) / 16;
-  const long t8 = nt * ((a.rows + 127) / 128), t4 = nt * ((a.rows + 63) / 64);
-  const double c8 = (double)((t8 + 511) / 512), c4 = 0.55 * (double)((t4 + 511) / 512);
-  // Where the 64-row tiles are one round of two workgroups a compute unit, one workgroup of eight waves does the work of the
-  // two and takes its activations through the vector cache once (a compute unit gets some 50 GB/s through it, which is what
-  // these tiles ask for): 7B o / down over 2048 rows 207.5 -> 199.3 us on average.  QKV, three rounds: 307 -> 327.
-  // (1601 rows, 208 workgroups of eight waves, 10.02 -> 9.87 ms for 8 layers; 1100 rows, 144 of them, 7.23 -> 7.47.)
-  const long t48 = (nt + 1) / 2 * ((a.rows + 63) / 64);
-  if (c4 < c8 && t4 <= 512 && t48 > 192 && t48 <= 256)
-    launch_dense_tile<EPI, NORM, 4, 4, 8>(a, 1, s);
-  else if (c4 < c8) launch_dense_tile<EPI, NORM, 4, 4, 4>(a, 1, s);
-  else launch_dense_tile<EPI, NORM, 8, 4, 4>(a, 1, s);
+static void launch_dense_cfg(const GemmArgs &a, const DensePlan &p, hipStream_t s) {
+  if constexpr (EPI == EPI_STORE) {   // plan_by_tiles
+    if (p.nw == 8) launch_dense_tile<EPI, NORM, 4, 4, 8>(a, 1, s);
+    else if (p.dm == 4) launch_dense_tile<EPI, NORM, 4, 4, 4>(a, 1, s);
+    else launch_dense_tile<EPI, NORM, 8, 4, 4>(a, 1, s);
+  } else {
+    switch (p.dm) {
+      case 4: launch_dense_whole<EPI, NORM, 4>(a, p, s); break;
+      case 5: launch_dense_whole<EPI, NORM, 5>(a, p, s); break;
+      case 6: launch_dense_whole<EPI, NORM, 6>(a, p, s); break;
+      case 7: launch_dense_whole<EPI, NORM, 7>(a, p, s); break;
+      default: launch_dense_whole<EPI, NORM, 8>(a, p, s); break;
+    }
+  }
 }
 
 bool launch_gemm_dense(const GemmLaunch &L, int RB, const float *rinv, hipStream_t s, float *part, size_t part_floats,
@@ -332,20 +396,28 @@ bool launch_gemm_dense(const GemmLaunch &L, int RB, const float *rinv, hipStream
   a.rope_tab = L.rope_tab; a.Kc = (uint16_t *)L.Kc; a.Vc = (uint16_t *)L.Vc;
   a.pos0 = L.pos0; a.n_ctx = L.n_ctx; a.hd = L.hd;
   a.part = part;
-  const DenseSplit sp = dense_splits(a, part_floats);
-  const int S = sp.splits;
+  const DensePlan p = dense_plan(a, L.epi, part_floats);
+  const int S = p.splits;
   if (S > 0) {
-    launch_dense_part(a, sp, s);
+    switch (p.dm) {
+      case 2: launch_dense_part<2>(a, p, s); break;
+      case 3: launch_dense_part<3>(a, p, s); break;
+      case 4: launch_dense_part<4>(a, p, s); break;
+      case 5: launch_dense_part<5>(a, p, s); break;
+      case 6: launch_dense_part<6>(a, p, s); break;
+      case 7: launch_dense_part<7>(a, p, s); break;
+      default: launch_dense_part<8>(a, p, s); break;
+    }
     const int rb = (a.rows + 15) / 16;
     if (L.epi == EPI_QKV) dense_finish_kernel<EPI_QKV><<<(a.NBtot * rb + 3) / 4, 256, 0, s>>>(a, S);
     else if (L.epi == EPI_SWIGLU) dense_finish_kernel<EPI_SWIGLU><<<(a.NBtot / 2 * rb + 3) / 4, 256, 0, s>>>(a, S);
     else dense_sum_rows_kernel<<<packed_row_groups(a.rows), 1024, 0, s>>>(a, S, rinv_out, L.eps);
     return true;
   }
-  if (L.epi == EPI_QKV) launch_dense_cfg<EPI_QKV, true>(a, s);
-  else if (L.epi == EPI_SWIGLU) launch_dense_cfg<EPI_SWIGLU, true>(a, s);
-  else if (L.epi == EPI_RESID) launch_dense_cfg<EPI_RESID, false>(a, s);
-  else launch_dense_cfg<EPI_STORE, false>(a, s);
+  if (L.epi == EPI_QKV) launch_dense_cfg<EPI_QKV, true>(a, p, s);
+  else if (L.epi == EPI_SWIGLU) launch_dense_cfg<EPI_SWIGLU, true>(a, p, s);
+  else if (L.epi == EPI_RESID) launch_dense_cfg<EPI_RESID, false>(a, p, s);
+  else launch_dense_cfg<EPI_STORE, false>(a, p, s);
   return false;
 }
 
