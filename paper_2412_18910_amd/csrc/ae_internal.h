@@ -148,7 +148,7 @@ struct ae_ctx {
   // dense prompt pass: chunk buffers, allocated at the first long prompt (pxa normalised rows, pxh FFN rows, pxcat draft head
   // input, pxatt attention output, packed or float32 planes; pxf and the partial sums are bf16 only)
   int prefill_mode = 0;            // AE_PREFILL_AUTO / _BLOCKS / _DENSE
-  int dense_chunk = 2048;          // rows per dense pass (multiple of 128)
+  int dense_chunk = 0;             // rows per dense pass (multiple of 128); 0: as ensure_dense has it
   int dense_cap = 0;               // rows the buffers below hold
   std::vector<void *> dense_owned;
   float *px = nullptr, *pq = nullptr, *prinv = nullptr, *pssq_a = nullptr, *pssq_f = nullptr;
