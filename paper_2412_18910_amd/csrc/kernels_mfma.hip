@@ -217,6 +217,14 @@ static void launch_shape(const GemmArgs &a, hipStream_t s) {
     else if (a.NBtot >= 512) launch_cfg<EPI, NORM, 4, 4, 4>(a, s);
     else launch_cfg<EPI, NORM, 2, 4, 4>(a, s);
   } else {
+    // LM heads of large vocabularies: 16 row-blocks a workgroup and one k-tile a wave in flight (one workgroup a compute unit, 16 KB
+    // reads) where their rounds are no longer than those of 8 row-blocks.  8B-GQA (8016 row-blocks, 1.05 GB) 180 -> 168 us;
+    // 8B widths, one row and a layer, us with 8 -> 16: 2500 row-blocks 191 -> 180, 4096 225 -> 218, 6272 292 -> 282; where the
+    // rounds are longer 2000 158 -> 167, 5120 254 -> 266, 9496 363 -> 379, 12504 452 -> 469.
+    if constexpr (EPI == EPI_STORE) {
+      const auto rounds = [&](int n) { return ((a.NBtot + n - 1) / n + g_num_cus - 1) / g_num_cus; };
+      if (a.NBtot >= 1536 && 2 * rounds(16) <= rounds(8)) return launch_cfg<EPI, NORM, 16, 8, 1>(a, s);
+    }
     if (a.NBtot >= 1536) launch_cfg<EPI, NORM, 8, 8, 2>(a, s);
     else if (a.NBtot >= 640) launch_cfg<EPI, NORM, 4, 8, 2>(a, s);
     // 8B-GQA QKV (384 row-blocks): (2,8,4) 12.6 us against (2,4,8) 15.6, (2,8,2) 13.5, (2,16,2) 13.0, (1,4,4) 15.2
