@@ -19,7 +19,7 @@
 // of K then K / (2 c n).  The sums that a wave of scalar code makes (64 lanes, each a chain of K / 64 products, and a
 // butterfly) cost K / 128 + 6 of these, and neither GEMM may cost more: the decode GEMM cuts at 16 products (8 where K
 // is below 1024) and adds wave results as a tree.  The prompt GEMM's instruction adds 32 products with fewer roundings;
-// its chains of three instructions (six where K is 4096 and more and the tile leaves the registers) join one total.
+// its chains of three instructions (six where K is 4096 and more) join one total.
 // The flash attention adds its accumulators to a second set every 256 keys.
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
@@ -653,7 +653,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
   u32x4 fa[2][2][3];   // split weights of stages st and st+1
   // Stage st: products with the activations xs, beside them the splitting of the weights of stage st+1 (in raw).  x1st: room for
   // the activations of stage st+1; a2nd: weights of stage st+2; far: room for those of stage st+3.
-  auto stage = [&](int st, int u, const u32x4 *xs, u32x4 *x1st, const u32x4 *a2nd, u32x4 *far) {
+  auto stage = [&](int st, int u, const u32x4 *xs, u32x4 *x1st, const u32x4 *a2nd, u32x4 *far) __attribute__((always_inline)) {
     issue_x(st + 1, x1st);
     keep_order();
     issue_a(st + 3, far);
@@ -703,14 +703,32 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a)
   read_raw(a0);
   split(fa[0]);
   read_raw(a1);
-  for (int st = 0; st < NS; st += 6) {
+  auto first3 = [&](int st) __attribute__((always_inline)) {
     stage(st, 0, x0, x1, a2, a0);
     stage(st + 1, 1, x1, x0, a0, a1);
     stage(st + 2, 2, x0, x1, a1, a2);
-    if (st + 3 >= NS) break;
+  };
+  auto second3 = [&](int st) __attribute__((always_inline)) {
     stage(st + 3, 3, x1, x0, a2, a0);
     stage(st + 4, 4, x0, x1, a0, a1);
     stage(st + 5, 5, x1, x0, a1, a2);
+  };
+  // Sixes, then three where they are left (of three stages alone those behind the last one multiply zeros).  A way out in the
+  // middle of the loop costs 40 registers of copies, which long chains at J = 4 do not have.
+  int st = 0;
+  if constexpr (J == 1) {
+    for (; st < NS; st += 6) {
+      first3(st);
+      if (st + 3 >= NS) break;
+      second3(st);
+    }
+  } else {
+    do {
+      first3(st);
+      second3(st);
+      st += 6;
+    } while (st + 6 <= NS);
+    if (st < NS) first3(st);
   }
   __builtin_amdgcn_s_waitcnt(0xf70);   // vmcnt(0): no load into LDS outlives the loop
   bool odd = false;
@@ -783,45 +801,81 @@ __global__ __launch_bounds__(256) void f32_tail_kernel(const F32Args a) {
   f32_dense_epilogue<EPI, J>(a, tot, v / MT * NBT, (v % MT) * 16 * J, w, lane >> 4, lane & 15);
 }
 
+// Tiles behind the last full round of 512 workgroups (two per compute unit), and the pieces that K of each is dealt to where
+// that fills the round: at most half as many tiles as it has places, 16 stages a piece at least, room for the pieces in max_part.  7B widths, 333
+// rows: QKV (512 + 160 tiles, 3 pieces) 238 -> 204 + 7 us, gate/up (1024 + 180, 2 pieces) 382 -> 360 + 6.
+struct F32Tail {
+  int tiles = 0, pieces = 1;
+};
+static F32Tail f32_tail(long tiles, int K, int J, size_t max_part) {
+  F32Tail t;
+  const int left = (int)(tiles % 512), room = left ? 512 / left : 0, longest = (K + 31) / 32 / 16, S = room < longest ? room : longest;
+  if (left > 0 && S > 1 && (size_t)left * S * 2048 * J <= max_part) {
+    t.tiles = left;
+    t.pieces = S < 8 ? S : 8;
+  }
+  return t;
+}
+
+// Widths that end with a tile.
+template <int EPI>
+static bool f32_whole(const F32Args &a) { return a.N % (EPI == EPI_SWIGLU ? 64 : 128) == 0 && a.K % 32 == 0; }
+
 template <int EPI, int J>
 static void launch_f32_dense_tile(F32Args a, hipStream_t s, size_t max_part) {
   constexpr int NBT = EPI == EPI_SWIGLU ? 4 : 8;
   const int tiles = (a.NB + NBT - 1) / NBT * ((a.rows + 16 * J - 1) / (16 * J));
-  // 512 workgroups are resident, two per compute unit (a lone one is no faster).  Where at most half as many are left behind
-  // the last full round, K of those is dealt to as many as there is room for, 16 stages each at least.  7B widths, 333
-  // rows: QKV (512 + 160 tiles, 3 pieces) 238 -> 204 + 7 us, gate/up (1024 + 180, 2 pieces) 382 -> 360 + 6.
-  const int left = tiles % 512, room = left ? 512 / left : 0, longest = (a.K + 31) / 32 / 16, S = room < longest ? room : longest;
-  a.whole = tiles;
-  if (EPI != EPI_PART && left > 0 && S > 1 && (size_t)left * S * 2048 * J <= max_part) {
-    a.whole = tiles - left;
-    a.tail = left;
-    a.tail_splits = S < 8 ? S : 8;
-  }
+  const F32Tail t = EPI == EPI_PART ? F32Tail() : f32_tail(tiles, a.K, J, max_part);
+  a.whole = tiles - t.tiles;
+  a.tail = t.tiles;
+  a.tail_splits = t.tiles ? t.pieces : 0;
   const dim3 grid((a.whole + 7) / 8 * 8 + (a.tail * a.tail_splits + 7) / 8 * 8, a.splits);
-  // the joins of a chain cost vector instructions; of a long sum half as many keep the error below that of scalar sums
-  // (J = 4: its registers do not hold longer chains)
-  if (J < 4 && a.K >= 4096) gemm_f32_dense_kernel<EPI, J, (J < 4)><<<grid, 256, 0, s>>>(a);
+  // the joins of a chain cost vector instructions and, of a long sum, roundings: half as many there (a 7B gate/up sum 21 instead of
+  // 43; at J = 4 of whole widths alone, 500 rows 1.25e-6 -> 1.20e-6 off float64)
+  if (a.K >= 4096 && (J < 4 || f32_whole<EPI>(a))) gemm_f32_dense_kernel<EPI, J, true><<<grid, 256, 0, s>>>(a);
   else gemm_f32_dense_kernel<EPI, J, false><<<grid, 256, 0, s>>>(a);
   if constexpr (EPI != EPI_PART) {
     if (a.tail > 0) f32_tail_kernel<EPI, J><<<a.tail, 256, 0, s>>>(a);
   }
 }
 
-// Rows of a tile and (EPI_PART) pieces of K: the least of tiles per compute unit times rows of a tile over pieces.  A
-// narrow tile splits its weights for fewer products (7B widths, 333 rows, last tiles whole: gate/up 472, 387, 411, 416 us with J = 2, 3, 4,
-// 5, QKV 302, 246, 256, 223, o / down 180, 146, 132, 142 on average), a lone workgroup per compute unit has nothing to cover its barriers with, and each piece costs a pass over the
-// partial sums.
+// Microseconds of a GEMM in tiles of 16 * J rows and S pieces of K (EPI_PART).  A round of 512 workgroups takes 84, 118, 136 or 160 us
+// for K = 4096 with J = 1 .. 4 (narrow tiles split their weights for fewer products), one of at most 256, alone on their
+// compute units, 0.65 of that; tiles behind the last full round are cut (f32_tail) or a round of their own; a piece of K is
+// written and added.  Within 10 % of what 7B widths take over 100 to 600 rows, and the order of J = 1 .. 4 is the measured one:
+// gate/up, 128 rows 252, 181, 157, 154 us, 400 rows 733, 498, 423, 404; QKV, 333 rows 200 with 3 and 4; o / down, 100 rows
+// in 4 pieces 44 / 94 with 2 and 39 / 78 with 4.
+static double f32_dense_cost(bool part, long NT, const F32Args &a, int J, int S, size_t max_part) {
+  static constexpr double kRound[5] = {0, 84, 118, 136, 160};
+  const long tiles = NT * ((a.rows + 16 * J - 1) / (16 * J));
+  const double c = kRound[J] * a.K / 4096;
+  const auto rounds = [](long w) { return (double)(w / 512) + (w % 512 == 0 ? 0.0 : w % 512 <= 256 ? 0.65 : 1.0); };
+  if (part) return rounds(tiles * S) * c / S + 0.9 * S + (double)S * a.rows * a.N * 4 / 5e6;
+  const F32Tail t = f32_tail(tiles, a.K, J, max_part);
+  return rounds(tiles - t.tiles) * c + (t.tiles ? rounds((long)t.tiles * t.pieces) * c / t.pieces + 5 : 0);
+}
+
+// The same by tiles per compute unit times rows of a tile over pieces, for widths that end within a tile: what these take has
+// not been measured.
+static double f32_tile_count(long NT, const F32Args &a, int J, int S) {
+  static constexpr double kPerRow[5] = {0, 1.4, 1.1, 1.0, 1.0};
+  const long tiles = NT * ((a.rows + 16 * J - 1) / (16 * J)) * S;
+  return (double)((tiles + 255) / 256 * J) / S * kPerRow[J] * (tiles <= 256 ? 1.25 : 1.0) * (1.0 + 0.03 * S);
+}
+
+// Rows of a tile and (EPI_PART) pieces of K, by f32_dense_cost.  (By f32_tile_count, which takes narrow tiles to be dearer by 10
+// to 40 % and a round to have 256 places, 7B, 2 layers: 64 rows 984 us, 100 1255, 128 1297, 200 1691, 333 2206, 400 3019, 600 3848;
+// so 841, 1074, 1102, 1556, 2155, 2499, 3487.)
 template <int EPI>
 static int launch_f32_dense_cfg(F32Args a, hipStream_t s, size_t max_part = 0) {   // returns the pieces of K
   const long NT = EPI == EPI_SWIGLU ? (a.NB + 3) / 4 : (a.NB + 7) / 8;
-  const double per_row[5] = {0, 1.4, 1.1, 1.0, 1.0};
+  const bool whole = f32_whole<EPI>(a);
   int best = 4;
   double cost = 1e30;
   for (int J = 4; J >= 1; --J)
     for (int S = 1; S <= (EPI == EPI_PART ? 8 : 1); ++S) {
       if (S > 1 && (a.K < S * 256 || (size_t)S * a.rows * a.N > max_part)) break;
-      const long tiles = NT * ((a.rows + 16 * J - 1) / (16 * J)) * S;
-      const double c = (double)((tiles + 255) / 256 * J) / S * per_row[J] * (tiles <= 256 ? 1.25 : 1.0) * (1.0 + 0.03 * S);
+      const double c = whole ? f32_dense_cost(EPI == EPI_PART, NT, a, J, S, max_part) : f32_tile_count(NT, a, J, S);
       if (c < cost) { cost = c; best = J; a.splits = S; }
     }
   if (best == 4) launch_f32_dense_tile<EPI, 4>(a, s, max_part);
