@@ -23,6 +23,7 @@
 // exact zeros and every reduction has a fixed order, so a row's result does not depend on
 // the number of rows in the block.
 #include "ae_internal.h"
+#include "attn_merge.h"
 #include "packed.h"
 
 namespace ae {
@@ -30,22 +31,24 @@ namespace ae {
 #define split2a split2
 
 // KPW = keys per wave (32 or 64); a workgroup covers kMfmaAttnChunk = 4 * KPW keys.  Where one workgroup holds
-// the whole context (gridDim.y == 1: up to 256 slots) it writes the input of the output projection itself, bit for
+// the whole context (gridDim.y == 1: up to 256 slots, with NG = 2 groups of waves 512) it writes the input of the output projection itself, bit for
 // bit what the merge of a single partial gives; the merge launch (4.5 us of the 85 us of a 7B layer) falls away.
-template <int HD, int KPW, bool GATED>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
+template <int HD, int KPW, int NG, bool GATED>
+__global__ __launch_bounds__(256 * NG) void attn_mfma_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
                                                         const u32x4 *Kc, const u32x4 *Vc, float *part, u32x4 *Xp_out,
                                                         float scale_log2e, const int32_t *gate) {
   constexpr int DT = HD / 32, VT = HD / 16, KT = KPW / 16, VB = KPW / 32;
   extern __shared__ u32x4 smem[];
   if constexpr (GATED) AE_GATE(gate);
-  const int kh = blockIdx.x, chunk = blockIdx.y, n_chunks = gridDim.y;
+  // a group of four waves takes a chunk
+  const int tid = threadIdx.x & 255, gi = NG > 1 ? threadIdx.x >> 8 : 0, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
+  const int kh = blockIdx.x, chunk = NG > 1 ? gi : blockIdx.y, n_chunks = gridDim.y;
   const int G = H / Hkv, R = rows * G, MT = (R + 15) / 16;
   u32x4 *Qs = smem;                                           // [MT][DT][2][64]
-  float *red = reinterpret_cast<float *>(smem + MT * DT * 128); // [4][16][HD]
+  float *red = reinterpret_cast<float *>(smem + MT * DT * 128) + gi * (4 * 16 * HD + 128); // [4][16][HD] of every group
   float *wm = red + 4 * 16 * HD;                              // [4][16]
   float *wl = wm + 64;                                        // [4][16]
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
+  ChunkMerge<HD, NG> &mrg = *reinterpret_cast<ChunkMerge<HD, NG> *>(reinterpret_cast<float *>(smem + MT * DT * 128) + NG * (4 * 16 * HD + 128));
   const int kbase = chunk * (4 * KPW) + w * KPW;
   const bool active = kbase < pos0 + rows;   // does this wave own any visible key?
 
@@ -65,7 +68,7 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float *q, int rows
   }
 
   // queries -> bf16 hi/lo B-operand tiles in LDS, pre-scaled into the log2 domain
-  for (int idx = tid; idx < MT * DT * 64; idx += 256) {
+  for (int idx = threadIdx.x; idx < MT * DT * 64; idx += 256 * NG) {
     const int l = idx & 63, dt = (idx >> 6) % DT, mt = idx / (DT * 64);
     const int row = mt * 16 + (l & 15), gg = l >> 4;
     u32x4 hi = {0, 0, 0, 0}, lo = {0, 0, 0, 0};
@@ -170,7 +173,11 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float *q, int rows
 #pragma unroll
           for (int ww = 0; ww < 4; ++ww) o[i] = fmaf(wgt[ww], red[((size_t)ww * 16 + m2) * HD + seg * (HD / 16) + i], o[i]);
         }
-        if (n_chunks == 1) {
+        if (NG > 1) {
+#pragma unroll
+          for (int i = 0; i < HD / 16; ++i) mrg.o[gi][m2][seg * (HD / 16) + i] = o[i];
+          if (seg == 0) { mrg.mx[gi][m2] = ms; mrg.l[gi][m2] = l; }
+        } else if (n_chunks == 1) {
 #pragma unroll
           for (int i = 0; i < HD / 16; i += 4)
             packed_store4(Xp_out, row2 / G, (kh * G + row2 % G) * HD + seg * (HD / 16) + i, o[i] / l, o[i + 1] / l, o[i + 2] / l,
@@ -184,6 +191,13 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float *q, int rows
       }
     }
     __syncthreads();
+    if constexpr (NG > 1) {   // (the next tile writes mrg behind its own barrier)
+      const int m2 = threadIdx.x / (HD / 4), k0 = threadIdx.x % (HD / 4) * 4, row2 = mt * 16 + m2;
+      if (m2 < 16 && row2 < R) {
+        const float4 o = mrg.merged(m2, k0);
+        packed_store4(Xp_out, row2 / G, (kh * G + row2 % G) * HD + k0, o.x, o.y, o.z, o.w);
+      }
+    }
   }
 }
 
@@ -267,44 +281,54 @@ void launch_attention_merge(const float *part, int rows, int n_chunks, const ae_
   }
 }
 
-size_t attn_mfma_smem_bytes(int MT, int HD) {
-  return (size_t)MT * (HD / 32) * 128 * 16 + (size_t)4 * 16 * HD * 4 + 128 * 4;
+size_t attn_mfma_smem_bytes(int MT, int HD, int NG) {   // queries, what the waves leave, NG > 1: what the groups leave
+  return (size_t)MT * (HD / 32) * 128 * 16 + NG * ((size_t)4 * 16 * HD * 4 + 128 * 4) + (NG > 1 ? NG * (16 * HD + 32) * 4 : 0);
 }
 
 // The widest block (4 query tiles: 16 rows x group size 4) needs more dynamic LDS than the
 // default limit; raised once per context set-up instead of before every launch.
 void attention_mfma_setup() {
-  const int sm128 = (int)attn_mfma_smem_bytes(4, 128), sm64 = (int)attn_mfma_smem_bytes(4, 64);
   constexpr int KPW = kMfmaKeysPerWave;
-  const auto raise = [](const void *f, int bytes) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
-  raise((const void *)attn_mfma_kernel<128, KPW, false>, sm128);
-  raise((const void *)attn_mfma_kernel<128, KPW, true>, sm128);
-  raise((const void *)attn_mfma_kernel<64, KPW, false>, sm64);
-  raise((const void *)attn_mfma_kernel<64, KPW, true>, sm64);
+  const auto raise = [](const void *f, int HD, int NG) {
+    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_mfma_smem_bytes(4, HD, NG));
+  };
+  raise((const void *)attn_mfma_kernel<128, KPW, 1, false>, 128, 1);
+  raise((const void *)attn_mfma_kernel<128, KPW, 1, true>, 128, 1);
+  raise((const void *)attn_mfma_kernel<128, KPW, 2, false>, 128, 2);
+  raise((const void *)attn_mfma_kernel<128, KPW, 2, true>, 128, 2);
+  raise((const void *)attn_mfma_kernel<64, KPW, 1, false>, 64, 1);
+  raise((const void *)attn_mfma_kernel<64, KPW, 1, true>, 64, 1);
+  raise((const void *)attn_mfma_kernel<64, KPW, 2, false>, 64, 2);
+  raise((const void *)attn_mfma_kernel<64, KPW, 2, true>, 64, 2);
 }
 
 template <int HD, bool GATED>
 static void launch_attention_cfg(const float *q, int rows, int pos0, const ae_config &c, const u32x4 *Kc, const u32x4 *Vc,
-                                 size_t sm, float *part, void *Xp_out, hipStream_t s, const int32_t *gate) {
-  const int n_chunks = (pos0 + rows + kMfmaAttnChunk - 1) / kMfmaAttnChunk;
-  const dim3 grid(c.n_kv_heads, n_chunks);
+                                 float *part, void *Xp_out, hipStream_t s, const int32_t *gate) {
+  const int n_chunks = (pos0 + rows + kMfmaAttnChunk - 1) / kMfmaAttnChunk, MT = (rows * (c.n_heads / c.n_kv_heads) + 15) / 16;
+  // Two chunks in one workgroup spare the merge, where one tile of 16 (row, head) pairs makes all rows: six layers behind 300 slots, us, 7B
+  // 5 rows 646 -> 637, 8B-GQA 1 row 808 -> 794; behind 490 slots 648 -> 647 (a compute unit then takes 256 KB, as long as the
+  // launch); three tiles (8B-GQA, 9 rows) 1036 -> 1038.
+  const bool two = n_chunks == 2 && MT == 1;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
-  attn_mfma_kernel<HD, kMfmaKeysPerWave, GATED><<<grid, 256, sm, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c),
-                                                                      Kc, Vc, part, (u32x4 *)Xp_out, scale_log2e, gate);
-  if (n_chunks > 1) launch_attention_merge(part, rows, n_chunks, c, Xp_out, false, s, gate);
+  const auto launch = [&](auto *kernel, int ng) {
+    kernel<<<dim3(c.n_kv_heads, ng > 1 ? 1 : n_chunks), 256 * ng, attn_mfma_smem_bytes(MT, HD, ng), s>>>(
+        q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, part, (u32x4 *)Xp_out, scale_log2e, gate);
+  };
+  if (two) launch(attn_mfma_kernel<HD, kMfmaKeysPerWave, 2, GATED>, 2);
+  else launch(attn_mfma_kernel<HD, kMfmaKeysPerWave, 1, GATED>, 1);
+  if (n_chunks > 1 && !two) launch_attention_merge(part, rows, n_chunks, c, Xp_out, false, s, gate);
 }
 
 void launch_attention_mfma(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
                            float *part, void *Xp_out, hipStream_t s, const int32_t *gate) {
-  const int G = c.n_heads / c.n_kv_heads, R = rows * G, MT = (R + 15) / 16;
-  const size_t sm = attn_mfma_smem_bytes(MT, c.head_dim);
   const u32x4 *Kc = (const u32x4 *)kv_layer, *Vc = (const u32x4 *)((const char *)kv_layer + v_off);
   if (c.head_dim == 128) {
-    if (gate) launch_attention_cfg<128, true>(q, rows, pos0, c, Kc, Vc, sm, part, Xp_out, s, gate);
-    else launch_attention_cfg<128, false>(q, rows, pos0, c, Kc, Vc, sm, part, Xp_out, s, gate);
+    if (gate) launch_attention_cfg<128, true>(q, rows, pos0, c, Kc, Vc, part, Xp_out, s, gate);
+    else launch_attention_cfg<128, false>(q, rows, pos0, c, Kc, Vc, part, Xp_out, s, gate);
   } else {
-    if (gate) launch_attention_cfg<64, true>(q, rows, pos0, c, Kc, Vc, sm, part, Xp_out, s, gate);
-    else launch_attention_cfg<64, false>(q, rows, pos0, c, Kc, Vc, sm, part, Xp_out, s, gate);
+    if (gate) launch_attention_cfg<64, true>(q, rows, pos0, c, Kc, Vc, part, Xp_out, s, gate);
+    else launch_attention_cfg<64, false>(q, rows, pos0, c, Kc, Vc, part, Xp_out, s, gate);
   }
 }
 

@@ -22,6 +22,7 @@
 // its chains of three instructions (six where K is 4096 and more) join one total.
 // The flash attention adds its accumulators to a second set every 256 keys.
 #include "ae_internal.h"
+#include "attn_merge.h"
 #include "gemm_epilogue.h"
 #include "packed.h"
 #include "step_inputs.h"
@@ -981,17 +982,21 @@ __device__ __forceinline__ void clear_dead_rows(f32x4 (&v)[4][N], int live) {
     for (int i = 0; i < N; ++i) v[j][i] = j < live ? v[j][i] : f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-template <int HD, bool GATED>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
+template <int HD, int NG, bool GATED>
+__global__ __launch_bounds__(256 * NG) void attn_f32_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
                                                        const float *Kc, const float *Vc, float *part, float *out,
                                                        float scale_log2e, const int32_t *gate) {
   constexpr int C = HD / 32, VT = HD / 16;
-  __shared__ float red[4][16][HD];
-  __shared__ float wm[4][16], wl[4][16];
+  __shared__ float reds[NG][4][16][HD];
+  __shared__ float wms[NG][4][16], wls[NG][4][16];
+  __shared__ ChunkMerge<HD, NG> mrg;
   if constexpr (GATED) AE_GATE(gate);
-  const int kh = blockIdx.x, chunk = blockIdx.y, n_chunks = gridDim.y;
+  // a group of four waves takes a chunk
+  const int tid = threadIdx.x & 255, gi = NG > 1 ? threadIdx.x >> 8 : 0, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
+  const int kh = blockIdx.x, chunk = NG > 1 ? gi : blockIdx.y, n_chunks = gridDim.y;
   const int G = H / Hkv, R = rows * G, MT = (R + 15) / 16;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15;
+  float (&red)[4][16][HD] = reds[gi];
+  float (&wm)[4][16] = wms[gi], (&wl)[4][16] = wls[gi];
   const int kbase = chunk * kF32AttnKeys + w * 16;
   const bool active = kbase < pos0 + rows;   // does this wave own any visible key?
 
@@ -1075,9 +1080,9 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows,
           l = fmaf(wgt[ww], wl[ww][m2], l);
         }
         // one workgroup holds the whole context: the result itself, as the merge of a single partial gives it
-        const bool whole = n_chunks == 1;
-        float *dst = whole ? out + ((size_t)(r2 / G) * H + kh * G + r2 % G) * HD
-                           : part + (((size_t)kh * n_chunks + chunk) * R + r2) * (HD + 2);
+        const bool whole = NG == 1 && n_chunks == 1;
+        float *res = out + ((size_t)(r2 / G) * H + kh * G + r2 % G) * HD;
+        float *dst = NG > 1 ? mrg.o[gi][m2] : whole ? res : part + (((size_t)kh * n_chunks + chunk) * R + r2) * (HD + 2);
 #pragma unroll
         for (int i = 0; i < HD / 16; ++i) {
           float o = 0.f;
@@ -1085,10 +1090,18 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *q, int rows,
           for (int ww = 0; ww < 4; ++ww) o = fmaf(wgt[ww], red[ww][m2][seg * (HD / 16) + i], o);
           dst[seg * (HD / 16) + i] = whole ? o / l : o;
         }
-        if (seg == 0 && !whole) { dst[HD] = ms; dst[HD + 1] = l; }
+        if (seg == 0 && NG > 1) { mrg.mx[gi][m2] = ms; mrg.l[gi][m2] = l; }
+        else if (seg == 0 && !whole) { dst[HD] = ms; dst[HD + 1] = l; }
       }
     }
     __syncthreads();
+    if constexpr (NG > 1) {   // (the next tile writes mrg behind its own barrier)
+      const int m2 = threadIdx.x / (HD / 4), k0 = threadIdx.x % (HD / 4) * 4, r2 = mt * 16 + m2;
+      if (m2 < 16 && r2 < R) {
+        const float4 o = mrg.merged(m2, k0);
+        *reinterpret_cast<float4 *>(out + ((size_t)(r2 / G) * H + kh * G + r2 % G) * HD + k0) = o;
+      }
+    }
   }
 }
 
@@ -1096,9 +1109,17 @@ template <int HD, bool GATED>
 static void launch_attention_f32_cfg(const float *q, int rows, int pos0, const ae_config &c, const float *Kc, const float *Vc,
                                      float *part, float *out, hipStream_t s, const int32_t *gate) {
   const int n_chunks = (pos0 + rows + kF32AttnKeys - 1) / kF32AttnKeys;
-  attn_f32_kernel<HD, GATED><<<dim3(c.n_kv_heads, n_chunks), 256, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc,
-                                                                          Vc, part, out, 1.4426950408889634f / sqrtf((float)HD), gate);
-  if (n_chunks > 1) launch_attention_merge(part, rows, n_chunks, c, out, true, s, gate);
+  // Two chunks in one workgroup spare the merge (the smallest model's verification of 5 rows behind 100 slots 105 -> 96 us).  Three and four give nothing
+  // (103 -> 101 us, as contexts that they do not concern), nor do heads of 128 elements (431.8 us both): what a
+  // compute unit then reads takes as long as the launch.
+  const bool two = HD == 64 && n_chunks == 2;
+  const auto launch = [&](auto *kernel, int ng) {
+    kernel<<<dim3(c.n_kv_heads, ng > 1 ? 1 : n_chunks), 256 * ng, 0, s>>>(q, rows, pos0, c.n_heads, c.n_kv_heads, kv_capacity(c), Kc, Vc, part, out,
+                                                                          1.4426950408889634f / sqrtf((float)HD), gate);
+  };
+  if (two) launch(attn_f32_kernel<HD, HD == 64 ? 2 : 1, GATED>, 2);
+  else launch(attn_f32_kernel<HD, 1, GATED>, 1);
+  if (n_chunks > 1 && !two) launch_attention_merge(part, rows, n_chunks, c, out, true, s, gate);
 }
 
 void launch_attention_f32(const float *q, int rows, int pos0, const ae_config &c, const void *kv_layer, size_t v_off,
