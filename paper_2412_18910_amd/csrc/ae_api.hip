@@ -239,8 +239,7 @@ void draft_lm_head(ae_ctx *c, int row, int i, int k, bool flag_decision) {
   if (greedy) {
     launch_argmax_finish(c->amax_val, c->amax_idx, NB, 1, c->st, i, s, c->gate, cat, ddd);   // argmax + override
   } else {
-    launch_sample_draft(dl, g.vocab, g.temperature, c->st, i, c->prob, s, c->gate);
-    launch_pick_draft_packed(c->st, i, s, c->gate, cat, ddd);
+    launch_sample_draft(dl, g.vocab, g.temperature, c->st, i, c->prob, s, c->gate, cat, ddd);
   }
 }
 
@@ -1058,8 +1057,7 @@ int ae_accept(ae_ctx *c, const double *u, int *n_accepted, int32_t *bonus) {
     if (rows > 1 && !c->have_draft) return fail(c, AE_ESTATE, "ae_accept: rejection sampling needs the draft's own logits");
     for (int i = 0; i < rows; ++i)
       if (!(u[i] >= 0.0 && u[i] < 1.0)) return fail(c, AE_EINVAL, "ae_accept: u outside [0,1)");
-    launch_set_u_accept(c->st, u, rows, c->stream);
-    launch_accept_sample(c->logits, c->dlogits, g.vocab, rows - 1, c->k_on_device, g.temperature, c->st, c->hist, n,
+    launch_accept_sample(c->logits, c->dlogits, g.vocab, rows - 1, c->k_on_device, g.temperature, c->st, c->hist, n, u,
                          c->prob, c->stream);
   }
   // Alg. 1 predicts the next draft length right after the verification

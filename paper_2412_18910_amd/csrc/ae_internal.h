@@ -214,7 +214,6 @@ struct GreedyAccept {
 
 // ---- dtype-independent kernels (kernels_generic.hip); all launches are asynchronous on `s` ----
 void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, float *out, hipStream_t s);
-void launch_set_u_accept(DevState *st, const double *u, int rows, hipStream_t s);
 // k_on_device: the draft length is st->draft_len (the block is padded to `rows` rows)
 void launch_accept_greedy(DevState *st, int32_t *hist, int kv_len, int rows, bool k_on_device, hipStream_t s);
 // z0 = W_in [e ; f] + b_in (Eq. 3 input layer), e and f read in place; st_nacc != nullptr: slot and
@@ -256,13 +255,11 @@ hipError_t launch_kv_export(const void *kv_layer, size_t v_off, const ae_config 
 size_t attn_part_floats(const ae_config &c);
 
 // ---- T > 0 sampling (kernels_sample.hip) ----
-size_t sample_scratch_doubles(int V);   // size of the scratch both launches below take
-void launch_sample_draft(const float *logits, int V, float T, DevState *st, int i, double *scratch, hipStream_t s,
-                         const int32_t *gate = nullptr);
+size_t sample_scratch_doubles(int V);   // size of the scratch that sampling and acceptance take
 // k = draft tokens the block holds room for (rows - 1); k_on_device: only the first
-// st->draft_len of them were drafted (padded block of the device-gated DDD chain)
+// st->draft_len of them were drafted (padded block of the device-gated DDD chain); u: k + 1 uniforms
 void launch_accept_sample(const float *tl, const float *dl, int V, int k, bool k_on_device, float T, DevState *st,
-                          int32_t *hist, int kv_len, double *prob, hipStream_t s);
+                          int32_t *hist, int kv_len, const double *u, double *prob, hipStream_t s);
 
 // ---- bf16 decode GEMMs (kernels_mfma.hip) ----
 // Row-block nb of a row-major [N,K] matrix -> row-block nb_off + nb*nb_stride of a fused
@@ -321,7 +318,9 @@ struct DddFinish {
 void launch_argmax_finish(const float *val, const int32_t *idx, int NB, int rows, DevState *st, int pick_i, hipStream_t s,
                           const int32_t *gate = nullptr, DraftCat cat = DraftCat(), DddFinish ddd = DddFinish(),
                           const NormRows &norm = NormRows());
-void launch_pick_draft_packed(DevState *st, int i, hipStream_t s, const int32_t *gate, DraftCat cat, DddFinish ddd);
+// temperature > 0: draft token i by inverse CDF, and what launch_argmax_finish does with a greedy one
+void launch_sample_draft(const float *logits, int V, float T, DevState *st, int i, double *scratch, hipStream_t s,
+                         const int32_t *gate, DraftCat cat, DddFinish ddd);
 void launch_embed_packed(const void *emb, const BlockIds &ids, int rows, int d, const float *gain, float *x,
                          void *Xp, float *ssq, hipStream_t s);
 void launch_pack_rows(const float *src, int ld, int rows, int K, const float *gain, void *Xp, hipStream_t s);

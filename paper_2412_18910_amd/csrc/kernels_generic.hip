@@ -48,19 +48,6 @@ void launch_rmsnorm(const float *x, const float *g, int rows, int d, float eps, 
 }
 
 // ------------------------------------------------------------------ tiny control kernels
-// Small host values reach the device state as kernel arguments: the launch carries them, so no
-// staging buffer has to outlive the call and no copy engine is involved.
-struct HostUniforms { double v[kMaxRows]; };
-
-__global__ void set_u_accept_kernel(DevState *st, HostUniforms u, int rows) {
-  if ((int)threadIdx.x < rows) st->u_accept[threadIdx.x] = u.v[threadIdx.x];
-}
-void launch_set_u_accept(DevState *st, const double *u, int rows, hipStream_t s) {
-  HostUniforms h;
-  for (int i = 0; i < kMaxRows; ++i) h.v[i] = i < rows ? u[i] : 0.0;
-  set_u_accept_kernel<<<1, 64, 0, s>>>(st, h, rows);
-}
-
 // Greedy acceptance (longest draft prefix equal to the target argmax, then the target's
 // own token) and the token-history side of the rollback, where no LDLP follows (one wave).
 __global__ void accept_greedy_kernel(DevState *st, int32_t *hist, int kv_len, int rows, int k_on_device) {

@@ -28,6 +28,7 @@
 #include "ae_internal.h"
 #include "gemm_epilogue.h"
 #include "packed.h"
+#include "pick_token.h"
 #include "step_inputs.h"
 
 namespace ae {
@@ -272,57 +273,6 @@ void launch_gemm_mfma(const GemmLaunch &L, hipStream_t s) {
   }
 }
 
-// Embedding of token t -> row cat.row, k = d .. 2d - 1 (the second half of the draft head's input
-// [feature ; embedding of the next token]); all threads of the workgroup.
-__device__ __forceinline__ void write_embedding(const DraftCat &cat, int32_t t) {
-  const int d = cat.d;
-  if (cat.f32) {
-    const float *e = (const float *)cat.emb + (size_t)t * d;
-    float *o = (float *)cat.Xp + (size_t)cat.row * 2 * d + d;
-    for (int k0 = threadIdx.x * 4; k0 < d; k0 += blockDim.x * 4)
-      *reinterpret_cast<float4 *>(o + k0) = *reinterpret_cast<const float4 *>(e + k0);
-    return;
-  }
-  const uint16_t *e = (const uint16_t *)cat.emb + (size_t)t * d;
-  for (int k0 = threadIdx.x * 4; k0 < d; k0 += blockDim.x * 4) {
-    const uint2 raw = *reinterpret_cast<const uint2 *>(e + k0);
-    packed_store4((u32x4 *)cat.Xp, cat.row, d + k0, __uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
-                  __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xffff0000u));
-  }
-}
-
-// AdaEAGLE-DDD bookkeeping behind draft token i = tok (Sec. 3.4, 4.2) from the LM-head epilogue's
-// row-block statistics of row 0; all 256 threads call.  Fixed-shape reductions.
-__device__ void ddd_finish(const DddFinish &d, int32_t tok, int i, DevState *st) {
-  __shared__ float red_s[4];
-  const int t = threadIdx.x;
-  float mx = -INFINITY;
-  for (int p = t; p < d.NB; p += 256) mx = fmaxf(mx, d.val[p]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  if ((t & 63) == 0) red_s[t >> 6] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(red_s[0], red_s[1]), fmaxf(red_s[2], red_s[3]));
-  __syncthreads();
-  float se = 0.f;
-  for (int p = t; p < d.NB; p += 256) se += d.lse_sum[p] * expf((d.val[p] - mx) * d.inv_t);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, 64);
-  if ((t & 63) == 0) red_s[t >> 6] = se;
-  __syncthreads();
-  if (t == 0) {
-    se = (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
-    const float lp = (d.logits[tok] - mx) * d.inv_t - logf(se);
-    const float cum = (i == 0 ? 0.f : st->cum_logp) + lp;
-    st->draft_lp[i] = lp;
-    st->cum_logp = cum;
-    st->draft_len = i + 1;
-    const bool stop = i + 1 >= d.k && !(cum >= d.theta);
-    if (stop) st->draft_live = 0;
-    if (d.flag) __hip_atomic_store(d.flag, d.seq << 1 | (stop ? 0u : 1u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-}
-
 // Final argmax over the LM head's row-block partials (lowest token id wins ties), one
 // workgroup per row.  pick_i >= 0 (draft head, one row): also applies the caller's override
 // table, records draft token pick_i and, when cat.Xp is set, writes that token's embedding into
@@ -387,22 +337,6 @@ __global__ __launch_bounds__(256) void argmax_finish_kernel(const float *val, co
 void launch_argmax_finish(const float *val, const int32_t *idx, int NB, int rows, DevState *st, int pick_i, hipStream_t s,
                           const int32_t *gate, DraftCat cat, DddFinish ddd, const NormRows &norm) {
   argmax_finish_kernel<<<rows + norm.rows, 256, 0, s>>>(val, idx, NB, st, pick_i, gate, cat, ddd, rows, norm);
-}
-
-// temperature > 0: the sampled token (st->argmax[0]) with the override table applied becomes draft
-// token i; its embedding goes into the draft head's packed input row like above
-__global__ __launch_bounds__(256) void pick_draft_packed_kernel(DevState *st, int i, const int32_t *gate, DraftCat cat,
-                                                                DddFinish ddd) {
-  AE_GATE(gate);
-  int32_t t = st->argmax[0];
-  if (st->override_ids[i] >= 0) t = st->override_ids[i];
-  if (threadIdx.x == 0) st->draft_ids[i] = t;
-  write_embedding(cat, t);
-  if (ddd.lse_sum) ddd_finish(ddd, t, i, st);
-}
-
-void launch_pick_draft_packed(DevState *st, int i, hipStream_t s, const int32_t *gate, DraftCat cat, DddFinish ddd) {
-  pick_draft_packed_kernel<<<1, 256, 0, s>>>(st, i, gate, cat, ddd);
 }
 
 // ------------------------------------------------------------------ packed-form producers

@@ -14,6 +14,7 @@
 //   the final one-workgroup kernel scans the owning segment (one token per thread).
 // All reductions have a fixed shape, so a draw does not depend on launch geometry.
 #include "ae_internal.h"
+#include "pick_token.h"
 
 namespace ae {
 
@@ -71,7 +72,8 @@ __device__ __forceinline__ void block_scan_inclusive(double v, double *out, doub
   if (lane == 63) wsum[w] = v;
   __syncthreads();
   double off = 0.0;
-  for (int i = 0; i < w; ++i) off += wsum[i];
+#pragma unroll
+  for (int i = 0; i < kSeg / 64; ++i) off += i < w ? wsum[i] : 0.0;   // (all loads at once; adding a zero changes nothing)
   out[threadIdx.x] = off + v;
   __syncthreads();
 }
@@ -168,20 +170,37 @@ __device__ int inverse_cdf_final(double segv, int S, const float *trow, const fl
 }
 
 // ------------------------------------------------------------------ draft sampling
-// Draft token i ~ softmax(logits / T) by inverse CDF with st->u_draft[i]; result in st->argmax[0].
-// Segment totals of p follow from the segment statistics, no second pass over the logits.
+// Draft token i ~ softmax(logits / T) by inverse CDF with st->u_draft[i], left in st->argmax[0]; with the override table
+// applied it becomes draft token i, its embedding goes into the draft head's input row, and the exit rule is evaluated.
+// Segment totals of p follow from the segment statistics, no second pass over the logits.  One workgroup, latency alone: each
+// exponential of a segment is taken once, by the segment's thread, and summed in the order of combine_row_wave; with a
+// second exponential, a second read and the token fixed by a launch of its own a token of 128256 took 15.3 + 4.7 us and the gap
+// between, now 16.6.
 __global__ __launch_bounds__(kSeg) void sample_draft_final_kernel(const float *logits, int V, int S, double T,
                                                                   const double *segstats, DevState *st, int i,
-                                                                  const int32_t *gate) {
+                                                                  const int32_t *gate, DraftCat cat, DddFinish ddd) {
   __shared__ double sh[kSeg + kSeg / 64];
   AE_GATE(gate);
-  double mx, sum;
-  combine_row_wave(segstats, S, 0, T, mx, sum);   // every wave computes the same pair
   const int t = threadIdx.x;
-  // segment totals of p follow from the segment statistics
-  const double segv = t < S ? segstats[(size_t)t * 2 + 1] * exp((segstats[(size_t)t * 2] - mx) / T) / sum : 0.0;
-  const int tok = inverse_cdf_final(segv, S, logits, nullptr, V, 0, T, mx, sum, 0.0, 1.0, st->u_draft[i], sh, nullptr);
-  if (t == 0) st->argmax[0] = tok;
+  const double ms = t < S ? segstats[(size_t)t * 2] : -INFINITY, ss = t < S ? segstats[(size_t)t * 2 + 1] : 0.0;
+  const double u = st->u_draft[i];
+  const int32_t over = st->override_ids[i];
+  const double mx = block_max<kSeg>(ms, sh);
+  const double e = t < S ? ss * exp((ms - mx) / T) : 0.0;
+  sh[t] = e;
+  __syncthreads();
+  double sum = 0.0;
+  for (int sg = t & 63; sg < S; sg += 64) sum += sh[sg];
+  sum = wave_sum_d(sum);   // every wave computes the same
+  __syncthreads();
+  const int tok = inverse_cdf_final(e / sum, S, logits, nullptr, V, 0, T, mx, sum, 0.0, 1.0, u, sh, nullptr);
+  const int32_t pick = over >= 0 ? over : tok;
+  if (t == 0) {
+    st->argmax[0] = tok;
+    st->draft_ids[i] = pick;
+  }
+  write_embedding(cat, pick);
+  if (ddd.lse_sum) ddd_finish(ddd, pick, i, st);
 }
 
 // scratch layout (doubles): segstats [rows][S][2] | rowstats [rows][2] | segtot [S]
@@ -191,11 +210,11 @@ size_t sample_scratch_doubles(int V) {
 }
 
 void launch_sample_draft(const float *logits, int V, float T, DevState *st, int i, double *scratch, hipStream_t s,
-                         const int32_t *gate) {
+                         const int32_t *gate, DraftCat cat, DddFinish ddd) {
   const int S = (V + kSeg - 1) / kSeg;
   double *segstats = scratch;
   seg_stats_kernel<<<dim3(S, 1), kSegThreads, 0, s>>>(logits, nullptr, V, 1, (double)T, segstats, gate);
-  sample_draft_final_kernel<<<1, kSeg, 0, s>>>(logits, V, S, (double)T, segstats, st, i, gate);
+  sample_draft_final_kernel<<<1, kSeg, 0, s>>>(logits, V, S, (double)T, segstats, st, i, gate, cat, ddd);
 }
 
 // ------------------------------------------------------------------ acceptance + rollback bookkeeping
@@ -205,13 +224,15 @@ __device__ __forceinline__ int drafted(const DevState *st, int kp, int k_on_devi
   return k_on_device ? min(st->draft_len, kp) : kp;
 }
 
-// Combines the row statistics, runs the accept tests (thread 0, in order) and records the
-// outcome: st->n_acc, and the (max, sum) pairs of target row n_acc and, on a rejection, of
+// Takes over the caller's uniforms (kernel arguments), combines the row statistics, runs the accept tests (thread 0, in order) and
+// records the outcome: st->n_acc, and the (max, sum) pairs of target row n_acc and, on a rejection, of
 // draft row n_acc in rowstats[0..3].
+struct HostUniforms { double v[kMaxRows]; };
 __global__ __launch_bounds__(kSeg) void accept_decide_kernel(const float *tl, const float *dl, int V, int S, int kp,
                                                              int k_on_device, double T, const double *segstats,
-                                                             double *rowstats, DevState *st) {
+                                                             double *rowstats, DevState *st, HostUniforms u) {
   __shared__ double rs[2 * kMaxRows][2];
+  if ((int)threadIdx.x <= kp) st->u_accept[threadIdx.x] = u.v[threadIdx.x];
   const int k = drafted(st, kp, k_on_device);
   const int wave = threadIdx.x >> 6;
   for (int row = wave; row < 2 * kp + 1; row += kSeg / 64) {   // one wave per row
@@ -229,7 +250,7 @@ __global__ __launch_bounds__(kSeg) void accept_decide_kernel(const float *tl, co
       const double ph = exp(((double)dl[(size_t)acc * V + t] - rs[kp + 1 + acc][0]) / T) / rs[kp + 1 + acc][1];
       double ratio = ph > 0.0 ? p / ph : 1.0;
       if (ratio > 1.0) ratio = 1.0;
-      if (!(st->u_accept[acc] < ratio)) break;
+      if (!(u.v[acc] < ratio)) break;
     }
     st->n_acc = acc;
     rowstats[0] = rs[acc][0]; rowstats[1] = rs[acc][1];
@@ -285,14 +306,16 @@ __global__ __launch_bounds__(kSeg) void accept_final_kernel(const float *tl, con
 }
 
 void launch_accept_sample(const float *tl, const float *dl, int V, int k, bool k_on_device, float T, DevState *st,
-                          int32_t *hist, int kv_len, double *scratch, hipStream_t s) {
+                          int32_t *hist, int kv_len, const double *u, double *scratch, hipStream_t s) {
+  HostUniforms h;
+  for (int i = 0; i < kMaxRows; ++i) h.v[i] = i <= k ? u[i] : 0.0;
   const int kd = k_on_device ? 1 : 0;
   const int S = (V + kSeg - 1) / kSeg;
   double *segstats = scratch;
   double *rowstats = scratch + (size_t)2 * kMaxRows * S * 2;
   double *segtot = rowstats + 2 * kMaxRows * 2;
   seg_stats_kernel<<<dim3(S, 2 * k + 1), kSegThreads, 0, s>>>(tl, dl, V, k + 1, (double)T, segstats, nullptr);
-  accept_decide_kernel<<<1, kSeg, 0, s>>>(tl, dl, V, S, k, kd, (double)T, segstats, rowstats, st);
+  accept_decide_kernel<<<1, kSeg, 0, s>>>(tl, dl, V, S, k, kd, (double)T, segstats, rowstats, st, h);
   seg_total_kernel<<<S, kSegThreads, 0, s>>>(tl, dl, V, k, kd, (double)T, rowstats, st, segtot);
   accept_final_kernel<<<1, kSeg, 0, s>>>(tl, dl, V, S, k, kd, (double)T, segstats, rowstats, segtot, st, hist, kv_len);
 }
