@@ -200,7 +200,11 @@ __global__ __launch_bounds__(kSeg) void sample_draft_final_kernel(const float *l
     st->draft_ids[i] = pick;
   }
   write_embedding(cat, pick);
-  if (ddd.lse_sum) ddd_finish(ddd, pick, i, st);
+  if (ddd.lse_sum) {
+    DddPartial part;
+    part.logit = ddd.logits[pick];
+    ddd_finish(ddd, i, st, part);
+  }
 }
 
 // scratch layout (doubles): segstats [rows][S][2] | rowstats [rows][2] | segtot [S]

@@ -24,28 +24,36 @@ __device__ __forceinline__ void write_embedding(const DraftCat &cat, int32_t t) 
   }
 }
 
-// AdaEAGLE-DDD bookkeeping behind draft token i = tok (Sec. 3.4, 4.2) from the LM-head epilogue's
+// What a kernel knows already when it calls ddd_finish: the token's logit; held: the maximum over the row-blocks and this thread's
+// share of the sum of exponentials (row-blocks threadIdx.x + 256 * j).
+struct DddPartial {
+  bool held = false;
+  float logit = 0.f, mx = -INFINITY, se = 0.f;
+};
+
+// AdaEAGLE-DDD bookkeeping behind draft token i (Sec. 3.4, 4.2) from the LM-head epilogue's
 // row-block statistics of row 0; all threads of the workgroup call, 256 of them work.  Fixed-shape reductions.
-__device__ inline void ddd_finish(const DddFinish &d, int32_t tok, int i, DevState *st) {
+__device__ inline void ddd_finish(const DddFinish &d, int i, DevState *st, const DddPartial &part) {
   __shared__ float red_s[4];
   const int t = threadIdx.x;
-  float mx = -INFINITY;
-  for (int p = t; t < 256 && p < d.NB; p += 256) mx = fmaxf(mx, d.val[p]);
+  float mx = part.mx, se = part.se;
+  if (!part.held) {
+    for (int p = t; t < 256 && p < d.NB; p += 256) mx = fmaxf(mx, d.val[p]);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  if ((t & 63) == 0 && t < 256) red_s[t >> 6] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(red_s[0], red_s[1]), fmaxf(red_s[2], red_s[3]));
-  __syncthreads();
-  float se = 0.f;
-  for (int p = t; t < 256 && p < d.NB; p += 256) se += d.lse_sum[p] * expf((d.val[p] - mx) * d.inv_t);
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if ((t & 63) == 0 && t < 256) red_s[t >> 6] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red_s[0], red_s[1]), fmaxf(red_s[2], red_s[3]));
+    __syncthreads();
+    for (int p = t; t < 256 && p < d.NB; p += 256) se += d.lse_sum[p] * expf((d.val[p] - mx) * d.inv_t);
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, 64);
   if ((t & 63) == 0 && t < 256) red_s[t >> 6] = se;
   __syncthreads();
   if (t == 0) {
     se = (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]);
-    const float lp = (d.logits[tok] - mx) * d.inv_t - logf(se);
+    const float lp = (part.logit - mx) * d.inv_t - logf(se);
     const float cum = (i == 0 ? 0.f : st->cum_logp) + lp;
     st->draft_lp[i] = lp;
     st->cum_logp = cum;
