@@ -30,6 +30,11 @@ namespace ae {
 
 #define split2a split2
 
+// Floats between the rows that the waves leave in LDS: 16 lanes write 16 rows at a time, which without it lie on the same banks.  us
+// without -> with it and with pieces of a row side by side: 7B, 1 row, 1024 slots 7.6 -> 7.0; 13B, 11 rows, 4096 slots 18.9 ->
+// 18.1; 8B-GQA, 9 rows (3 tiles), 8001 slots 15.8 -> 13.8.
+constexpr int kRedPad = 4;
+
 // KPW = keys per wave (32 or 64); a workgroup covers kMfmaAttnChunk = 4 * KPW keys.  Where one workgroup holds
 // the whole context (gridDim.y == 1: up to 256 slots, with NG = 2 groups of waves 512) it writes the input of the output projection itself, bit for
 // bit what the merge of a single partial gives; the merge launch (4.5 us of the 85 us of a 7B layer) falls away.
@@ -37,7 +42,7 @@ template <int HD, int KPW, int NG, bool GATED>
 __global__ __launch_bounds__(256 * NG) void attn_mfma_kernel(const float *q, int rows, int pos0, int H, int Hkv, int n_ctx,
                                                         const u32x4 *Kc, const u32x4 *Vc, float *part, u32x4 *Xp_out,
                                                         float scale_log2e, const int32_t *gate) {
-  constexpr int DT = HD / 32, VT = HD / 16, KT = KPW / 16, VB = KPW / 32;
+  constexpr int DT = HD / 32, VT = HD / 16, KT = KPW / 16, VB = KPW / 32, RS = HD + kRedPad;
   extern __shared__ u32x4 smem[];
   if constexpr (GATED) AE_GATE(gate);
   // a group of four waves takes a chunk
@@ -45,10 +50,10 @@ __global__ __launch_bounds__(256 * NG) void attn_mfma_kernel(const float *q, int
   const int kh = blockIdx.x, chunk = NG > 1 ? gi : blockIdx.y, n_chunks = gridDim.y;
   const int G = H / Hkv, R = rows * G, MT = (R + 15) / 16;
   u32x4 *Qs = smem;                                           // [MT][DT][2][64]
-  float *red = reinterpret_cast<float *>(smem + MT * DT * 128) + gi * (4 * 16 * HD + 128); // [4][16][HD] of every group
-  float *wm = red + 4 * 16 * HD;                              // [4][16]
+  float *red = reinterpret_cast<float *>(smem + MT * DT * 128) + gi * (4 * 16 * RS + 128); // [4][16][RS] of every group
+  float *wm = red + 4 * 16 * RS;                              // [4][16]
   float *wl = wm + 64;                                        // [4][16]
-  ChunkMerge<HD, NG> &mrg = *reinterpret_cast<ChunkMerge<HD, NG> *>(reinterpret_cast<float *>(smem + MT * DT * 128) + NG * (4 * 16 * HD + 128));
+  ChunkMerge<HD, NG> &mrg = *reinterpret_cast<ChunkMerge<HD, NG> *>(reinterpret_cast<float *>(smem + MT * DT * 128) + NG * (4 * 16 * RS + 128));
   const int kbase = chunk * (4 * KPW) + w * KPW;
   const bool active = kbase < pos0 + rows;   // does this wave own any visible key?
 
@@ -152,7 +157,7 @@ __global__ __launch_bounds__(256 * NG) void attn_mfma_kernel(const float *q, int
     // combine the four waves (fixed order) with the usual max-rescaling
 #pragma unroll
     for (int dt = 0; dt < VT; ++dt)
-      *reinterpret_cast<f32x4 *>(red + ((size_t)w * 16 + m) * HD + dt * 16 + 4 * g) = O[dt];
+      *reinterpret_cast<f32x4 *>(red + ((size_t)w * 16 + m) * RS + dt * 16 + 4 * g) = O[dt];
     if (g == 0) { wm[w * 16 + m] = mx; wl[w * 16 + m] = lsum; }
     __syncthreads();
     {
@@ -166,27 +171,33 @@ __global__ __launch_bounds__(256 * NG) void attn_mfma_kernel(const float *q, int
           wgt[ww] = mw > -INFINITY ? __builtin_amdgcn_exp2f(mw - ms) : 0.f;
           l = fmaf(wgt[ww], wl[ww * 16 + m2], l);
         }
-        float o[HD / 16];
+        f32x4 o[HD / 64];   // elements i * 64 + seg * 4 .. + 3: 16 lanes side by side
 #pragma unroll
-        for (int i = 0; i < HD / 16; ++i) {
-          o[i] = 0.f;
+        for (int i = 0; i < HD / 64; ++i) {
+          o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int ww = 0; ww < 4; ++ww) o[i] = fmaf(wgt[ww], red[((size_t)ww * 16 + m2) * HD + seg * (HD / 16) + i], o[i]);
+          for (int ww = 0; ww < 4; ++ww) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(red + ((size_t)ww * 16 + m2) * RS + i * 64 + seg * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[i][e] = fmaf(wgt[ww], v[e], o[i][e]);
+          }
         }
         if (NG > 1) {
 #pragma unroll
-          for (int i = 0; i < HD / 16; ++i) mrg.o[gi][m2][seg * (HD / 16) + i] = o[i];
+          for (int i = 0; i < HD / 64; ++i) *reinterpret_cast<f32x4 *>(&mrg.o[gi][m2][i * 64 + seg * 4]) = o[i];
           if (seg == 0) { mrg.mx[gi][m2] = ms; mrg.l[gi][m2] = l; }
         } else if (n_chunks == 1) {
 #pragma unroll
-          for (int i = 0; i < HD / 16; i += 4)
-            packed_store4(Xp_out, row2 / G, (kh * G + row2 % G) * HD + seg * (HD / 16) + i, o[i] / l, o[i + 1] / l, o[i + 2] / l,
-                          o[i + 3] / l);
+          for (int i = 0; i < HD / 64; ++i)
+            packed_store4(Xp_out, row2 / G, (kh * G + row2 % G) * HD + i * 64 + seg * 4, o[i][0] / l, o[i][1] / l, o[i][2] / l, o[i][3] / l);
         } else {
-          float *dst = part + (((size_t)kh * n_chunks + chunk) * R + row2) * (HD + 2);
+          float *dst = part + (((size_t)kh * n_chunks + chunk) * R + row2) * (HD + 2);   // (8-byte aligned)
 #pragma unroll
-          for (int i = 0; i < HD / 16; ++i) dst[seg * (HD / 16) + i] = o[i];
-          if (seg == 0) { dst[HD] = ms; dst[HD + 1] = l; }
+          for (int i = 0; i < HD / 64; ++i) {
+            *reinterpret_cast<float2 *>(dst + i * 64 + seg * 4) = make_float2(o[i][0], o[i][1]);
+            *reinterpret_cast<float2 *>(dst + i * 64 + seg * 4 + 2) = make_float2(o[i][2], o[i][3]);
+          }
+          if (seg == 0) *reinterpret_cast<float2 *>(dst + HD) = make_float2(ms, l);
         }
       }
     }
@@ -282,7 +293,7 @@ void launch_attention_merge(const float *part, int rows, int n_chunks, const ae_
 }
 
 size_t attn_mfma_smem_bytes(int MT, int HD, int NG) {   // queries, what the waves leave, NG > 1: what the groups leave
-  return (size_t)MT * (HD / 32) * 128 * 16 + NG * ((size_t)4 * 16 * HD * 4 + 128 * 4) + (NG > 1 ? NG * (16 * HD + 32) * 4 : 0);
+  return (size_t)MT * (HD / 32) * 128 * 16 + NG * ((size_t)4 * 16 * (HD + kRedPad) * 4 + 128 * 4) + (NG > 1 ? NG * (16 * HD + 32) * 4 : 0);
 }
 
 // The widest block (4 query tiles: 16 rows x group size 4) needs more dynamic LDS than the
