@@ -17,6 +17,7 @@
 //    online softmax in the log2 domain; no partials, no merge, packed output.
 //  * embedding, 1/rms finalisation and the draft head's [feature ; embedding] input.
 #include "ae_internal.h"
+#include "dense_tile.h"
 #include "gemm_epilogue.h"
 #include "packed.h"
 
@@ -61,8 +62,9 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
   const int nbw = min(tn * (NW * DN), a.NBtot - NW * DN) + w * DN;
   const size_t kts = (size_t)a.RB * 128;
   // Operands come through buffer loads: resource descriptor and per-k-tile byte offset in
-  // scalar registers, one fixed per-lane offset register each (out-of-range reads return 0).
-  // The DM row-blocks of one k-tile are 2*DM tiles of 64 contiguous pieces; a wave loads tiles w + NW*i straight
+  // scalar registers, one fixed per-lane offset register each.  All reads are in range: the descriptors' sizes
+  // do not cover a position that is in the scalar offset.
+  // The DM row-blocks of one k-tile are 2*DM tiles of 64 contiguous pieces; a wave loads its own (dense_slot) straight
   // into LDS in lane order, so its accesses are conflict-free.
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)a.W, 0, a.w_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)a.Xp, 0, a.xp_bytes, 0x00020000);
@@ -92,10 +94,10 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_dense_kernel(const GemmArgs a
   auto put = [&](u32x4 *slot, u32x4 (&wr)[DN], int kt) {   // k-tiles behind the last repeat it (ignored)
     const unsigned k = min(kt, NK - 1);
 #pragma unroll
-    for (int i = 0; i < XI; ++i) {   // the same number for every wave: one too many loads the last tile again
-      const int t = DM * 2 % NW ? min(w + NW * i, DM * 2 - 1) : w + NW * i;
+    for (int i = 0; i < XI; ++i) {
+      const int t = dense_slot(w, i, NW, DM);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(slot + t * 64), 16, wl,
-                                               xq + k * kts_b + t * 1024, 0, 0);
+                                               xq + k * kts_b + dense_source(t, rb0, a.RB) * 1024, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < DN; ++i) wr[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, wl + i * 1024, wq + k * kstride_b, 0);

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "ae_internal.h"
+#include "dense_tile.h"
 
 namespace {
 
@@ -66,6 +67,10 @@ size_t fake_live_bytes() {
   for (auto &a : g_live) t += a.second;
   return t;
 }
+
+// ---- device code that host code can follow
+int fake_dense_slot(int w, int i, int nw, int dm) { return ae::dense_slot(w, i, nw, dm); }
+int fake_dense_source(int slot, int rb0, int RB) { return ae::dense_source(slot, rb0, RB); }
 
 // ---- registration and launches
 void **__hipRegisterFatBinary(const void *) { static void *m; return &m; }
