@@ -117,8 +117,9 @@ int ae_prefill(ae_ctx *ctx, const int32_t *prompt_ids, int n);
 /* How ae_prefill runs.  mode: AE_PREFILL_AUTO (default, rule above), AE_PREFILL_BLOCKS
  * (always the 16-row decode kernels) or AE_PREFILL_DENSE (always the dense pass;
  * AE_EUNSUPPORTED for fp32 weights).  chunk_rows: rows per dense pass, a multiple of 128
- * in [128, 8192], or 0 to keep the current value (default 4096 for bf16, 2048 where that does
- * not fit in memory or for fp32). */
+ * in [128, 8192], or 0 to keep the current value (default 4096 for bf16, 2048 for fp32 or where
+ * the memory for 4096 cannot be had: later prompts of the context then keep to 2048 until this
+ * function is called). */
 enum { AE_PREFILL_AUTO = 0, AE_PREFILL_BLOCKS = 1, AE_PREFILL_DENSE = 2 };
 int ae_set_prefill_mode(ae_ctx *ctx, int mode, int chunk_rows);
 

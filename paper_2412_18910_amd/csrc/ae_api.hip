@@ -318,9 +318,13 @@ struct OnDevice {
   }
 };
 
+void free_all(std::vector<void *> &owned) {
+  for (void *p : owned) hipFree(p);
+  owned.clear();
+}
+
 void release_dense(ae_ctx *c) {
-  for (void *p : c->dense_owned) hipFree(p);
-  c->dense_owned.clear();
+  free_all(c->dense_owned);
   c->dense_cap = 0;
   c->ppart = nullptr;
   c->ppart_floats = 0;
@@ -336,12 +340,12 @@ size_t f32_part_floats(const ae_config &g, int rows) {
 
 // Chunk buffers for `want` rows (a multiple of 128): float residual stream and queries, the
 // inputs of the five GEMMs; bf16: RMSNorm partial sums and 1/rms, zero-filled so that the
-// padding rows of a packed chunk are finite (float32: so that what lies behind the end of K is zero).  Nothing is held where
-// they do not fit; bf16 prompts do without room for pieces of K (no GEMM is split then).
-int alloc_dense(ae_ctx *c, int want) {
+// padding rows of a packed chunk are finite (float32: so that what lies behind the end of K is zero).  Where they do not fit nothing is
+// held, or with keep what was there; pieces: so it is too where room for pieces of K alone is missing (without it no bf16 GEMM is split).
+int alloc_dense(ae_ctx *c, int want, bool keep, bool pieces) {
   const ae_config &g = c->cfg;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  release_dense(c);
+  if (!keep) release_dense(c);
   const OnDevice here(c->device);   // float32 prompts never depended on the thread's device
   const size_t cap = want, d = g.d_model, dq = (size_t)g.n_heads * g.head_dim, dkv = (size_t)g.n_kv_heads * g.head_dim, f = g.d_ffn;
   const size_t dmax = dq > d ? dq : d;
@@ -360,6 +364,7 @@ int alloc_dense(ae_ctx *c, int want) {
       {(void **)&c->pssq_a, cap * d * 4 / 16 * 1 + cap * 4}, {(void **)&c->pssq_f, cap * d * 4 / 16 + cap * 4},
       {&c->pxa, cap * d * 4},              {&c->pxf, cap * d * 4},            {&c->pxatt, cap * dq * 4},
       {&c->pxh, cap * f * 4},              {&c->pxcat, cap * 2 * d * 4}, {(void **)&c->ppart, part_floats * 4}};
+  std::vector<void *> owned;
   for (auto &b : bufs) {
     void *q = nullptr;
     const size_t bytes = (b.bytes + 255) / 256 * 256;
@@ -367,16 +372,20 @@ int alloc_dense(ae_ctx *c, int want) {
     const bool part = b.p == (void **)&c->ppart;
     if (e != hipSuccess) {
       (void)hipGetLastError();
-      if (c->fast && part) break;   // the last buffer
+      if (part && !pieces) break;   // the last buffer
       (void)hipStreamSynchronize(c->stream);   // the buffers before this one are being cleared
-      release_dense(c);
+      free_all(owned);
       return fail(c, AE_ENOMEM, std::string("dense prefill buffers: ") + hipGetErrorString(e));
     }
-    c->dense_owned.push_back(q);
-    *b.p = q;
-    if (part) c->ppart_floats = part_floats;
-    else if (b.clear) launch_fill_zero(q, bytes, c->stream);
+    owned.push_back(q);
+    if (!part && b.clear) launch_fill_zero(q, bytes, c->stream);
   }
+  release_dense(c);
+  for (size_t i = 0; i < owned.size(); ++i) {
+    *bufs[i].p = owned[i];
+    if (bufs[i].p == (void **)&c->ppart) c->ppart_floats = part_floats;
+  }
+  c->dense_owned = std::move(owned);
   c->dense_cap = want;
   return AE_OK;
 }
@@ -385,19 +394,27 @@ int alloc_dense(ae_ctx *c, int want) {
 // GEMMs' last rounds weigh half as much, and o and down have work for two workgroups of 128 rows a compute unit.  4 layers, ms
 // with chunks of 2048 -> 4096 (8192): 8B-GQA 4096 tokens 13.0 -> 12.3 (12.4), 7777 26.6 -> 25.4 (25.1), 7B 3000 9.50 -> 9.02 (8.99),
 // 13B 4000 19.4 -> 18.1 (18.1); 8192 would hold twice the memory.
+// What could not be had once is not asked for again until the caller sets the mode: a prompt's sums then do not depend on the free memory of
+// the moment, and buffers that will do (2048 rows and more) are given up only for larger ones that are there.
 int ensure_dense(ae_ctx *c, int n) {
   const ae_config &g = c->cfg;
   const int chunk = c->dense_chunk ? c->dense_chunk : c->fast ? 4096 : 2048;
   int want = ((n < chunk ? n : chunk) + 127) / 128 * 128;
+  if (c->dense_limit && want > c->dense_limit) want = c->dense_limit;
   // offsets into a chunk buffer have 32 bits (float32), their sizes 31 (bf16)
   const int fd = g.d_ffn > 2 * g.d_model ? g.d_ffn : 2 * g.d_model, dq = g.n_heads * g.head_dim, widest = fd > dq ? fd : dq;
   const size_t fits = (c->fast ? 0x7fffffffu / ((size_t)widest * 512) : 0xffff0000u / planes_bytes(128, widest)) * 128;
   if ((size_t)want > fits && fits) want = (int)fits;
   if (want <= c->dense_cap) return AE_OK;
-  int rc = alloc_dense(c, want);
   // three bf16 parts take half as much again as a float: where they do not fit, a chunk of two thirds takes what floats would
   const int less = !c->fast ? want * 2 / 3 / 128 * 128 : !c->dense_chunk && want > 2048 ? 2048 : 0;
-  if (rc == AE_ENOMEM && less > 0) rc = alloc_dense(c, less);
+  const bool keep = c->fast && less > 0 && c->dense_cap >= less;
+  int rc = alloc_dense(c, want, keep, !c->fast || less > 0);
+  if (rc == AE_ENOMEM && less > 0) {
+    if (keep) rc = AE_OK;
+    else rc = alloc_dense(c, less, false, !c->fast);
+    if (rc == AE_OK) c->dense_limit = c->dense_cap;
+  }
   return rc;
 }
 
@@ -825,6 +842,7 @@ int ae_set_prefill_mode(ae_ctx *c, int mode, int chunk_rows) {
   if (mode == AE_PREFILL_DENSE && !dense_ok(c))
     return fail(c, AE_EUNSUPPORTED, "the dense prompt pass needs bf16 weights and d_model >= 256");
   c->prefill_mode = mode;
+  c->dense_limit = 0;
   if (chunk_rows && chunk_rows != c->dense_chunk) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     release_dense(c);

@@ -149,6 +149,7 @@ struct ae_ctx {
   // input, pxatt attention output, packed or float32 planes; pxf and the partial sums are bf16 only)
   int prefill_mode = 0;            // AE_PREFILL_AUTO / _BLOCKS / _DENSE
   int dense_chunk = 0;             // rows per dense pass (multiple of 128); 0: as ensure_dense has it
+  int dense_limit = 0;             // 0, or what a chunk is held to because more could not be had
   int dense_cap = 0;               // rows the buffers below hold
   std::vector<void *> dense_owned;
   float *px = nullptr, *pq = nullptr, *prinv = nullptr, *pssq_a = nullptr, *pssq_f = nullptr;

@@ -24,6 +24,7 @@ int g_device = 0, g_malloc_device = -1;   // current one, that of the last devic
 hipError_t g_last = hipSuccess;
 long g_fail_launch = -1;     // launches until one fails
 size_t g_fail_alloc = 0;     // device allocations of this size and more fail (0: none)
+size_t g_room = 0;           // device memory that there is (0: no end of it)
 bool g_go_on = true;         // answer of the exit rule
 bool g_mute = false;         // no kernel answers
 bool g_capture = false;      // streams are being captured: launches are recorded for later, waiting is an error
@@ -53,6 +54,7 @@ void fake_grid(int i, unsigned *gx, unsigned *gy, unsigned *threads) {
 void fake_clear() { g_launches.clear(); }
 void fake_fail_launch(long after) { g_fail_launch = after; }
 void fake_fail_alloc(size_t bytes) { g_fail_alloc = bytes; }
+void fake_room(size_t bytes) { g_room = bytes; }
 void fake_set_error(int e) { g_last = (hipError_t)e; }
 int fake_last_error() { return (int)g_last; }
 void fake_mute(int mute) { g_mute = mute != 0; }
@@ -115,7 +117,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
 
 // ---- memory
 hipError_t hipMalloc(void **p, size_t n) {
-  if (g_fail_alloc && n >= g_fail_alloc) return note(hipErrorOutOfMemory);
+  if ((g_fail_alloc && n >= g_fail_alloc) || (g_room && fake_live_bytes() + n > g_room)) return note(hipErrorOutOfMemory);
   *p = calloc(1, n);
   g_live[*p] = n;
   g_malloc_device = g_device;

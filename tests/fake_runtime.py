@@ -32,6 +32,7 @@ def load():
         _lib.fake_name.restype = C.c_char_p
         _lib.fake_live_bytes.restype = C.c_size_t
         _lib.fake_fail_alloc.argtypes = [C.c_size_t]
+        _lib.fake_room.argtypes = [C.c_size_t]
         _lib.fake_fail_launch.argtypes = [C.c_long]
     return _lib
 
