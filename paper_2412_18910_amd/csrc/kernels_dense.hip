@@ -275,13 +275,14 @@ static void launch_dense_part(const GemmArgs &a, const DensePlan &p, hipStream_t
   else launch_dense_tile<EPI_PART, false, DM, 3, 8>(a, p.splits, s);
 }
 
+// Every plan ends in a launch, one without an instance of its own in the narrowest tile: 16 weight row-blocks, which all matrices have.
 template <int EPI, bool NORM, int DM>
 static void launch_dense_whole(const GemmArgs &a, const DensePlan &p, hipStream_t s) {
-  if (p.nw == 8 && p.dn == 2) launch_dense_tile<EPI, NORM, DM, 2, 8>(a, 1, s);
-  else if constexpr (EPI == EPI_SWIGLU || DM == 4 || DM == 8) {   // else plan_by_tiles alone
-    if (p.nw == 4) launch_dense_tile<EPI, NORM, DM, 4, 4>(a, 1, s);
-    else if constexpr (EPI == EPI_SWIGLU || DM == 4) launch_dense_tile<EPI, NORM, DM, 4, 8>(a, 1, s);
-  }
+  if constexpr (EPI == EPI_SWIGLU || DM == 4 || DM == 8)   // else plan_by_tiles alone
+    if (p.nw == 4) return launch_dense_tile<EPI, NORM, DM, 4, 4>(a, 1, s);
+  if constexpr (EPI == EPI_SWIGLU || DM == 4)
+    if (p.nw == 8 && p.dn == 4) return launch_dense_tile<EPI, NORM, DM, 4, 8>(a, 1, s);
+  launch_dense_tile<EPI, NORM, DM, 2, 8>(a, 1, s);
 }
 
 // Adds the pieces of one 16x16 tile (EPI_SWIGLU: of a gate and an up tile) per wave and runs the GEMM's epilogue on it.
