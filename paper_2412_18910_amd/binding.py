@@ -6,6 +6,7 @@ does not need a GPU; creating an Engine does, and raises if the library is missi
 """
 import ctypes as C
 import os
+import types
 
 import numpy as np
 
@@ -81,24 +82,24 @@ def load_library(path=LIB_PATH):
         "ae_init": (I, [C.POINTER(AeConfig), C.POINTER(AeWeights), P, C.POINTER(P)]),
         "ae_free": (None, [P]),
         "ae_last_error": (C.c_char_p, [P]),
-        "ae_prefill": (I, [P, P, I]),
-        "ae_kv_import": (I, [P, I, P, P, I]),
-        "ae_kv_import_static": (I, [P, I, P, P, I]),
-        "ae_ldlp_loss": (I, [P, P, P, I, C.c_double, f64p]),
-        "ae_set_state": (I, [P, I, C.c_int32, C.c_int32, P]),
+        "ae_prefill": (I, [P, i32p, I]),
+        "ae_kv_import": (I, [P, I, f32p, f32p, I]),
+        "ae_kv_import_static": (I, [P, I, f32p, f32p, I]),
+        "ae_ldlp_loss": (I, [P, f32p, i32p, I, C.c_double, f64p]),
+        "ae_set_state": (I, [P, I, C.c_int32, C.c_int32, f32p]),
         "ae_ldlp": (I, [P, C.POINTER(I), f32p]),
-        "ae_draft": (I, [P, I, P, P, P]),
-        "ae_verify": (I, [P, P, I]),
-        "ae_accept": (I, [P, P, C.POINTER(I), i32p]),
+        "ae_draft": (I, [P, I, i32p, f64p, i32p]),
+        "ae_verify": (I, [P, i32p, I]),
+        "ae_accept": (I, [P, f64p, C.POINTER(I), i32p]),
         "ae_step": (I, [P, C.POINTER(AeStepIO)]),
         "ae_kv_len": (I, [P]),
         "ae_last_draft_len": (I, [P]),
         "ae_get_draft_logprob": (I, [P, f32p]),
         "ae_pending": (C.c_int32, [P]),
-        "ae_get_logits": (I, [P, I, P]),
-        "ae_get_feature": (I, [P, I, P]),
-        "ae_get_draft_logits": (I, [P, I, P]),
-        "ae_get_kv_row": (I, [P, I, I, I, P]),
+        "ae_get_logits": (I, [P, I, f32p]),
+        "ae_get_feature": (I, [P, I, f32p]),
+        "ae_get_draft_logits": (I, [P, I, f32p]),
+        "ae_get_kv_row": (I, [P, I, I, I, f32p]),
         "ae_set_profiling": (I, [P, I]),
         "ae_get_phase_times": (I, [P, C.POINTER(AePhaseTimes)]),
         "ae_set_kernel_timing": (I, [P, I]),
@@ -112,6 +113,13 @@ def load_library(path=LIB_PATH):
     for name, (res, args) in sig.items():
         fn = getattr(lib, name)
         fn.restype, fn.argtypes = res, args
+    # The same functions for Engine, which has made its arrays of the right type itself: an address passes as it is (a typed pointer
+    # object costs 3 us more).  The functions above refuse pointers of another type.
+    lib.by_address = types.SimpleNamespace()
+    for name, (res, args) in sig.items():
+        fn = lib[name]
+        fn.restype, fn.argtypes = res, [P if t in (i32p, f32p, f64p) else t for t in args]
+        setattr(lib.by_address, name, fn)
     _lib = lib
     return lib
 
@@ -128,7 +136,7 @@ def probe_read_stream(bytes_per_launch, launches=64, repeats=5, stream=None):
 
 
 def _p(a):
-    """Address of an array that the caller keeps for as long as it is used (a typed pointer object costs 3 us more)."""
+    """Address of an array that the caller keeps for as long as it is used."""
     return None if a is None else a.ctypes.data
 
 
@@ -200,20 +208,19 @@ class Engine:
 
     def prefill(self, ids):
         ids = _i32(ids)
-        self._chk(self.lib.ae_prefill(self.h, _p(ids), len(ids)), "ae_prefill")
+        self._chk(self.lib.by_address.ae_prefill(self.h, _p(ids), len(ids)), "ae_prefill")
 
     def kv_import(self, layer, k, v):
         k, v = _f32(k), _f32(v)
-        self._chk(self.lib.ae_kv_import(self.h, layer, _p(k), _p(v), k.shape[0]), "ae_kv_import")
+        self._chk(self.lib.by_address.ae_kv_import(self.h, layer, _p(k), _p(v), k.shape[0]), "ae_kv_import")
 
     def kv_import_static(self, layer, k, v):
         k, v = _f32(k), _f32(v)
-        self._chk(self.lib.ae_kv_import_static(self.h, layer, _p(k), _p(v), k.shape[0]),
-                  "ae_kv_import_static")
+        self._chk(self.lib.by_address.ae_kv_import_static(self.h, layer, _p(k), _p(v), k.shape[0]), "ae_kv_import_static")
 
     def set_state(self, kv_len, last_tok, pending, feat):
         feat = _f32(feat)
-        self._chk(self.lib.ae_set_state(self.h, kv_len, last_tok, pending, _p(feat)), "ae_set_state")
+        self._chk(self.lib.by_address.ae_set_state(self.h, kv_len, last_tok, pending, _p(feat)), "ae_set_state")
 
     def ldlp(self):
         k, y = C.c_int(), C.c_float()
@@ -223,15 +230,14 @@ class Engine:
     def ldlp_loss(self, pred, truth, lam):
         pred, truth = _f32(pred), _i32(truth)
         out = C.c_double()
-        self._chk(self.lib.ae_ldlp_loss(self.h, _p(pred), _p(truth), len(pred), float(lam),
-                                        C.byref(out)), "ae_ldlp_loss")
+        self._chk(self.lib.by_address.ae_ldlp_loss(self.h, _p(pred), _p(truth), len(pred), float(lam), C.byref(out)),
+                  "ae_ldlp_loss")
         return out.value
 
     def draft(self, k, override_ids=None, u_draft=None, want_ids=True):
         out = np.zeros(self.cfg.k_max + 1, np.int32)
         ov, ud = _i32(override_ids), _f64(u_draft)
-        self._chk(self.lib.ae_draft(self.h, k, _p(ov), _p(ud),
-                                    _p(out) if want_ids else None), "ae_draft")
+        self._chk(self.lib.by_address.ae_draft(self.h, k, _p(ov), _p(ud), _p(out) if want_ids else None), "ae_draft")
         return out[:self.lib.ae_last_draft_len(self.h)]
 
     @property
@@ -243,12 +249,12 @@ class Engine:
     def verify(self, block_ids=None, n_rows=None):
         b = _i32(block_ids)
         n = len(b) if b is not None else n_rows
-        self._chk(self.lib.ae_verify(self.h, _p(b), n), "ae_verify")
+        self._chk(self.lib.by_address.ae_verify(self.h, _p(b), n), "ae_verify")
 
     def accept(self, u=None):
         u = _f64(u)
         na, bonus = C.c_int(), C.c_int32()
-        self._chk(self.lib.ae_accept(self.h, _p(u), C.byref(na), C.byref(bonus)), "ae_accept")
+        self._chk(self.lib.by_address.ae_accept(self.h, _p(u), C.byref(na), C.byref(bonus)), "ae_accept")
         return na.value, bonus.value
 
     def step(self, k_force=-1, override_ids=None, u_draft=None, u_accept=None):
@@ -277,16 +283,16 @@ class Engine:
         return out
 
     def logits(self, row):
-        return self._get(self.lib.ae_get_logits, "ae_get_logits", self.cfg.vocab, row)
+        return self._get(self.lib.by_address.ae_get_logits, "ae_get_logits", self.cfg.vocab, row)
 
     def feature(self, row):
-        return self._get(self.lib.ae_get_feature, "ae_get_feature", self.cfg.d_model, row)
+        return self._get(self.lib.by_address.ae_get_feature, "ae_get_feature", self.cfg.d_model, row)
 
     def draft_logits(self, i):
-        return self._get(self.lib.ae_get_draft_logits, "ae_get_draft_logits", self.cfg.vocab, i)
+        return self._get(self.lib.by_address.ae_get_draft_logits, "ae_get_draft_logits", self.cfg.vocab, i)
 
     def kv_row(self, layer, which, slot):
-        return self._get(self.lib.ae_get_kv_row, "ae_get_kv_row", self.cfg.d_kv, layer, which, slot)
+        return self._get(self.lib.by_address.ae_get_kv_row, "ae_get_kv_row", self.cfg.d_kv, layer, which, slot)
 
     def set_profiling(self, on=True):
         self._chk(self.lib.ae_set_profiling(self.h, int(on)), "ae_set_profiling")

@@ -53,6 +53,14 @@ def test_init_rejects_bad_arguments_without_a_gpu(lib):
     assert lib.ae_version().startswith(b"adaeagle")
 
 
+@pytest.mark.parametrize("name,args", [("ae_prefill", (None, C.c_float, 1)), ("ae_verify", (None, C.c_double, 1)),
+                                       ("ae_accept", (None, C.c_float, C.c_int, C.c_int32)), ("ae_get_logits", (None, 0, C.c_int32)),
+                                       ("ae_get_kv_row", (None, 0, 0, 0, C.c_double)), ("ae_prefill", (None, "text", 1))])
+def test_arrays_of_another_type_are_refused(lib, name, args):
+    with pytest.raises(C.ArgumentError):
+        getattr(lib, name)(*[(a * 4)() if isinstance(a, type) else a for a in args])
+
+
 def test_engine_fails_loudly_when_library_is_missing(tmp_path):
     saved = binding._lib
     binding._lib = None
