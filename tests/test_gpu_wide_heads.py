@@ -24,8 +24,18 @@ def test_logits_argmax_and_draft_probability(d, heads, vocab, rows):
     eng.verify(block)
     got = np.stack([eng.logits(i) for i in range(rows)])
     assert np.max(np.abs(got - np.stack([orc.logits(i) for i in range(rows)]))) <= TOL
-    eng.accept(), orc.accept()
-    assert eng.pending == int(np.argmax(got[0])) or rows > 1   # (of a row alone, the argmax over all workgroups)
+    accepted, bonus = eng.accept()
+    assert bonus == eng.pending == int(np.argmax(got[accepted]))
+    # a block whose drafts are the argmaxes of the rows before them: each row's own argmax, over all workgroups, is asked for
+    eng.prefill(ids)
+    block = block[:1]
+    while len(block) < rows:
+        eng.verify(block)
+        block = np.append(block, np.argmax(eng.logits(len(block) - 1))).astype(np.int32)
+    eng.verify(block)
+    got = np.stack([eng.logits(i) for i in range(rows)])
+    assert eng.accept() == (rows - 1, int(np.argmax(got[-1])))
+    assert np.array_equal(block[1:], got[:-1].argmax(1))
     eng.prefill(ids)
     draft = eng.draft(3)
     logits = np.stack([eng.draft_logits(i) for i in range(len(draft))]).astype(np.float64)
