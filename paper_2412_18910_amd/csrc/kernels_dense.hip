@@ -190,8 +190,9 @@ struct DensePlan {
   int nw = 8, dn = 2, dm = 8, splits = 0;
 };
 
-// Microseconds that a plan takes, fitted to 9600 launches (7B, 13B and 8B-GQA widths, 20 to 4096 rows; the plan it picks is
-// 1-2 % off the best of all measured ones on average).  Workgroups go round-robin to the 8 XCDs of 32 compute units.  A
+// Microseconds that a plan takes, fitted to 9600 launches (7B, 13B and 8B-GQA widths, 20 to 4096 rows).  Measured again (4876 plans, 216
+// GEMMs): the plan it picks is 2.3, 1.1 and 1.1 % off the best of all on average, its microseconds are 0.78 to 1.21 of the
+// measured ones.  Workgroups go round-robin to the 8 XCDs of 32 compute units.  A
 // k-tile of a workgroup costs what is largest of its products (5 ns for 16 x 16 x 32, hi and lo), what it takes through the
 // vector cache (16 ns a KB: 64 GB/s a compute unit, by lines in flight) and the weights' share of HBM.  Pieces are
 // written at 3.8 TB/s when all workgroups end at once, and a pass adds them; whole K pays for its epilogue, and for
@@ -215,8 +216,9 @@ static double dense_cost(const GemmArgs &a, int epi, const DensePlan &p) {
   return t + out * (epi == EPI_QKV ? 1 : epi == EPI_SWIGLU ? 0.5 : 3) / 10.9e6 + (epi == EPI_QKV || epi == EPI_SWIGLU ? 0 : 5.5);
 }
 
-// Plans by the number of tiles, for what dense_cost has not been measured on: K below 3072, a last chunk of one row-block, and whole K of the draft head's
-// input projection (once a prompt: 200 us of 2048 rows of 7B either way).  Less than 384 tiles of 256 weight rows x 64 rows
+// Plans by the number of tiles, the older rule, for what dense_cost was not fitted to: K below 3072, a last chunk of one row-block, and whole K
+// of the draft head's input projection (once a prompt: 200 us of 2048 rows of 7B either way).  At K below 3072 it is the slower one: 2048 x 5632
+// 18 % off the best plan on average, dense_cost 1.7; 1024 x 2816 28 %, 2.5 (20 to 4096 rows): the line could lie lower.  Less than 384 tiles of 256 weight rows x 64 rows
 // would leave compute units idle (256, two workgroups each): pieces of K.  Else 128-row tiles, or 64-row ones (0.55 of
 // their time) where these fill rounds of 512 workgroups better; one round of them in workgroups of eight waves, which
 // take the activations through the vector cache once instead of twice.

@@ -19,7 +19,8 @@
 // of K then K / (2 c n).  The sums that a wave of scalar code makes (64 lanes, each a chain of K / 64 products, and a
 // butterfly) cost K / 128 + 6 of these, and neither GEMM may cost more: the decode GEMM cuts at 16 products (8 where K
 // is below 1024) and adds wave results as a tree.  The prompt GEMM's instruction adds 32 products with fewer roundings;
-// its chains of three instructions (six where K is 4096 and more) join one total.
+// its chains of three instructions (six where K is 4096 and more, but not in 64-row tiles of widths that end within a tile) join one
+// total.
 // The flash attention adds its accumulators to a second set every 256 keys.
 #include "ae_internal.h"
 #include "attn_merge.h"
@@ -523,11 +524,12 @@ __device__ __forceinline__ void f32_dense_epilogue(const F32Args &a, const f32x4
 // Workgroup tile: 128 weight rows (gate/up: 64 of each) x 16*J activation rows; each of the 4 waves owns two
 // weight row-blocks and all J activation row-blocks.  Stages of 32 k go straight into LDS, weights three stages ahead,
 // activations one.  While a stage is multiplied the weights of the next one are split, vector instructions between the
-// matrix instructions: an MFMA of 16 cycles leaves room for two.  7B widths, 333 rows, against the float32 instruction:
-// gate/up 649 -> 356 + 5 us (the last tiles in pieces of K), QKV 408 -> 203 + 6, o / down 247 -> 140 on average; the factor of
-// the split takes 16 of 118 vector instructions a stage (J = 3) and 6, 4 and 3 us of these.  With the activations split here too
-// (44 vector instructions more a stage; whole tiles, without the factor: 382 and 238 us) 478 / 295.  What is left of the matrix rate
-// (40 %): 3.3 vector instructions an MFMA at J = 3, latencies that two waves a SIMD do not cover, clocks of 2.05 GHz.
+// matrix instructions: an MFMA of 16 cycles leaves room for two.  7B widths, 333 rows, against the float32 instruction, in
+// tiles of 48 rows: gate/up 649 -> 356 + 5 us (the last tiles in pieces of K), QKV 408 -> 203 + 6, o / down 247 -> 140 on average; the
+// factor of the split takes 16 of 118 vector instructions a stage (J = 3) and 6, 4 and 3 us of these.  With the activations split here
+// too (44 vector instructions more a stage; whole tiles, without the factor: 382 and 238 us) 478 / 295.  What is left of the matrix rate
+// (40 %): 3.3 vector instructions an MFMA at J = 3, latencies that two waves a SIMD do not cover, clocks of 2.05 GHz.  Such a prompt
+// now takes tiles of 64 rows (one layer, 48 -> 64 rows in one process: gate/up 348 + 5 -> 330 + 9, QKV 193 + 6 -> 188 + 10).
 template <int EPI, int J, bool LONG>
 __global__ __launch_bounds__(256, 2) void gemm_f32_dense_kernel(const F32Args a) {
   constexpr int TM = 16 * J, CH = LONG ? 6 : 3;             // CH: stages in a chain of products
@@ -804,7 +806,8 @@ __global__ __launch_bounds__(256) void f32_tail_kernel(const F32Args a) {
 
 // Tiles behind the last full round of 512 workgroups (two per compute unit), and the pieces that K of each is dealt to where
 // that fills the round: at most half as many tiles as it has places, 16 stages a piece at least, room for the pieces in max_part.  7B widths, 333
-// rows: QKV (512 + 160 tiles, 3 pieces) 238 -> 204 + 7 us, gate/up (1024 + 180, 2 pieces) 382 -> 360 + 6.
+// rows in tiles of 48: QKV (512 + 160 tiles, 3 pieces) 238 -> 204 + 7 us, gate/up (1024 + 180, 2 pieces) 382 -> 360 + 6.  In the 64-row
+// tiles that such a prompt takes, 64 and 8 tiles are cut into eight pieces each.
 struct F32Tail {
   int tiles = 0, pieces = 1;
 };
@@ -843,9 +846,10 @@ static void launch_f32_dense_tile(F32Args a, hipStream_t s, size_t max_part) {
 // Microseconds of a GEMM in tiles of 16 * J rows and S pieces of K (EPI_PART).  A round of 512 workgroups takes 84, 118, 136 or 160 us
 // for K = 4096 with J = 1 .. 4 (narrow tiles split their weights for fewer products), one of at most 256, alone on their
 // compute units, 0.65 of that; tiles behind the last full round are cut (f32_tail) or a round of their own; a piece of K is
-// written and added.  Within 10 % of what 7B widths take over 100 to 600 rows, and the order of J = 1 .. 4 is the measured one:
-// gate/up, 128 rows 252, 181, 157, 154 us, 400 rows 733, 498, 423, 404; QKV, 333 rows 200 with 3 and 4; o / down, 100 rows
-// in 4 pieces 44 / 94 with 2 and 39 / 78 with 4.
+// written and added.  Meant for the order of plans, not for their times (0.6 of the measured ones at 20 rows of 7B, 0.85 to 1.03 from 160
+// on): what it picks is 0.6, 0.6, 1.0 and 2.1 % off the best of all plans on average (7B, 13B, 2048 x 5632, 1024 x 2816; 20 to 2048 rows).  The
+// pass behind cut tiles is charged 5 us; it takes 4 to 6 with J <= 2, 5 to 8 with 3, 6 to 10 with 4, which charged to them changes
+// nothing of that (0.6, 0.6, 0.8, 2.0 %).
 static double f32_dense_cost(bool part, long NT, const F32Args &a, int J, int S, size_t max_part) {
   static constexpr double kRound[5] = {0, 84, 118, 136, 160};
   const long tiles = NT * ((a.rows + 16 * J - 1) / (16 * J));
@@ -856,8 +860,10 @@ static double f32_dense_cost(bool part, long NT, const F32Args &a, int J, int S,
   return rounds(tiles - t.tiles) * c + (t.tiles ? rounds((long)t.tiles * t.pieces) * c / t.pieces + 5 : 0);
 }
 
-// The same by tiles per compute unit times rows of a tile over pieces, for widths that end within a tile: what these take has
-// not been measured.
+// The same by tiles per compute unit times rows of a tile over pieces, the older rule, for widths that end within a tile.  It is 14, 14, 7
+// and 11 % off the best plan there (4104 x 11016, 2056 x 5640, 1032 x 2824, 5128 x 13832; 20 to 2048 rows), mostly by tiles of too few rows up
+// to 500 rows; f32_dense_cost would be 4, 7, 2 and 4 % off (pieces of 33 or 41 tiles do not fill the 8 XCDs alike, which it does
+// not count).  The tests of the tile shapes hold these widths to this rule, which reaches all shapes within 1000 rows.
 static double f32_tile_count(long NT, const F32Args &a, int J, int S) {
   static constexpr double kPerRow[5] = {0, 1.4, 1.1, 1.0, 1.0};
   const long tiles = NT * ((a.rows + 16 * J - 1) / (16 * J)) * S;

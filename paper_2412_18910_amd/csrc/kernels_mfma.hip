@@ -231,7 +231,8 @@ static void launch_shape(const GemmArgs &a, hipStream_t s) {
     // 8B-GQA QKV (384 row-blocks): (2,8,4) 12.6 us against (2,4,8) 15.6, (2,8,2) 13.5, (2,16,2) 13.0, (1,4,4) 15.2
     else if (a.NBtot >= 384) launch_cfg<EPI, NORM, 2, 8, 4>(a, s);
     // more row-blocks than compute units (13B o / down, 320): two per workgroup and 16 waves, 21.1 us
-    // for the pair's average against 26.9 with (1,4,4), 24.1 (2,8,4), 22.2 (2,16,4), 28.7 (1,16,2)
+    // for the pair's average against 26.9 with (1,4,4), 24.1 (2,8,4), 22.2 (2,16,4), 28.7 (1,16,2) over a loop of that time
+    // (19.4 over one now, most of whose passes have a row; 25.8 at 11 rows, whose activations are as many bytes as the weights)
     else if (a.NBtot > g_num_cus) launch_cfg<EPI, NORM, 2, 16, 2>(a, s);
     // at most one row-block per compute unit (7B o / down, 256): (1,4,8) 14.1, (1,8,4) 13.0, (1,16,1) 13.3,
     // (1,2,8) 13.0, (2,16,2) 16.3 us against 12.7
