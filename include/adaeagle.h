@@ -118,8 +118,8 @@ int ae_prefill(ae_ctx *ctx, const int32_t *prompt_ids, int n);
  * (always the 16-row decode kernels) or AE_PREFILL_DENSE (always the dense pass;
  * AE_EUNSUPPORTED for fp32 weights).  chunk_rows: rows per dense pass, a multiple of 128
  * in [128, 8192], or 0 to keep the current value (default 4096 for bf16, 2048 for fp32 or where
- * the memory for 4096 cannot be had: later prompts of the context then keep to 2048 until this
- * function is called). */
+ * the memory for 4096 cannot be had).  A smaller size that was taken for want of memory (fp32:
+ * two thirds) holds for the context's later prompts until this function is called. */
 enum { AE_PREFILL_AUTO = 0, AE_PREFILL_BLOCKS = 1, AE_PREFILL_DENSE = 2 };
 int ae_set_prefill_mode(ae_ctx *ctx, int mode, int chunk_rows);
 
